@@ -312,23 +312,32 @@ static mpk_status run_passes(PassInput& in, const mpk_compile_options& opt, Host
   }
   g.aot_off[W] = (uint32_t)g.aot.size();
 
-  // Wide events whose producers all have a fixed worker (AOT) count arrivals per worker group.
+  // Events whose producers all have a fixed worker (AOT) count arrivals per worker group.
   g.n_hier_events = 0;
   {
-    std::vector<std::vector<uint32_t>> sub(g.events.size(), std::vector<uint32_t>(8, 0));
+    std::vector<std::vector<uint32_t>> sub(g.events.size(), std::vector<uint32_t>(kShards, 0));
     std::vector<uint8_t> has_jit_producer(g.events.size(), 0);
     for (uint32_t i = 0; i < n_tasks; ++i) {
       int32_t e = g.tasks[i].trig_event;
       if (g.tasks[i].jit) has_jit_producer[e] = 1;
-      else sub[e][(uint32_t)g.tasks[i].worker & 7u]++;
+      else sub[e][(uint32_t)g.tasks[i].worker % kShards]++;
     }
+    auto n_sharded = [&](uint32_t least) {
+      size_t n = 0;
+      for (size_t e = 0; e < g.events.size(); ++e) n += g.events[e].required >= least && !has_jit_producer[e];
+      return n;
+    };
+    auto fits = [&](uint32_t least) {
+      return scratch_layout(g.events.size(), n_sharded(least), g.n_group_counters, g.arena_floats).end <= MPK_STATIC_SCRATCH_BYTES;
+    };
+    const uint32_t least = !fits(kHierMinRequired) && fits(kHierMinRequiredTight) ? kHierMinRequiredTight : kHierMinRequired;
     for (size_t e = 0; e < g.events.size(); ++e) {
       EventDesc& ev = g.events[e];
-      if (ev.required < kHierMinRequired || has_jit_producer[e]) continue;
+      if (ev.required < least || has_jit_producer[e]) continue;
       ev.flags |= EV_HIER;
       ev.hier_slot = g.n_hier_events++;
       ev.n_groups = 0;
-      for (int k = 0; k < 8; ++k) {
+      for (uint32_t k = 0; k < kShards; ++k) {
         ev.sub_required[k] = sub[e][k];
         ev.n_groups += sub[e][k] ? 1u : 0u;
       }

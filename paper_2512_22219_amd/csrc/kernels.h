@@ -2983,16 +2983,16 @@ __device__ __forceinline__ bool run_task(const TaskDesc& t, const StepArgs& a, f
 // ------------------------------------------------------------------------------ runtime
 
 // Has event e been activated for this step?  The whole wavefront calls it; the answer is uniform.
-// Simple events: one counter, compared with epoch * required by lane 0.  Sharded events (wide,
-// all producers ahead-of-time): one counter per producer group (worker index mod 8), each on its
-// own 256-byte line; lanes 0..7 read one group's counter each -- a single load instruction -- and
-// compare it with epoch * (that group's producers).  An arrival is then ONE atomic add that nobody
-// waits for, and 256 producers spread over 8 lines.
+// Simple events: one counter, compared with epoch * required by lane 0.  Sharded events (all
+// producers ahead-of-time): one counter per producer group (worker index mod kShards), each on its
+// own 256-byte line; lanes 0 .. kShards-1 read one group's counter each -- a single load instruction
+// -- and compare it with epoch * (that group's producers).  An arrival is then ONE atomic add that
+// nobody waits for, and the producers spread over kShards lines (see kHierMinRequired).
 __device__ __forceinline__ bool event_reached(const StepArgs& a, int32_t e, int lane) {
   const MPK_CONST EventDesc& ev = *(const MPK_CONST EventDesc*)(a.events + e);
   bool ok = true;
   if (ev.flags & EV_HIER) {
-    if (lane < 8) {
+    if (lane < (int)kShards) {
       const uint32_t need = a.epoch * ((const MPK_CONST EventDesc*)(a.events + e))->sub_required[lane];
       const uint32_t v = ld_relaxed(a.hier + (size_t)ev.hier_slot * kHierWordsPerEvent + (1 + lane) * kHierStrideWords);
       ok = (int32_t)(v - need) >= 0;
@@ -3045,7 +3045,7 @@ __device__ __forceinline__ void notify_event(const StepArgs& a, int32_t e) {
   bool activated = false;
   if (flags & EV_HIER) {
     uint32_t* blk = a.hier + (size_t)ev.hier_slot * kHierWordsPerEvent;
-    const uint32_t grp = blockIdx.x & 7u;
+    const uint32_t grp = blockIdx.x % kShards;
     if ((flags & EV_JIT) && a.n_sched) {
       // a scheduler has to be told by the arrival that completes the event: the last arrival of a
       // producer group adds to the top counter, the last of those hands the event over
@@ -3237,14 +3237,14 @@ __device__ __noinline__ bool run_other_task(typename TaskArgs<NB, MOE>::type arg
 __device__ __forceinline__ bool event_active(const StepArgs& a, int32_t e) {
   const MPK_CONST EventDesc& ev = *(const MPK_CONST EventDesc*)(a.events + e);
   if (ev.required == 0) return true;
-  if (ev.flags & EV_HIER) {   // (one lane: the eight group counters one after the other, all in flight together)
+  if (ev.flags & EV_HIER) {   // (one lane: the group counters one after the other, all in flight together)
     const uint32_t* blk = a.hier + (size_t)ev.hier_slot * kHierWordsPerEvent;
-    uint32_t v[8];
+    uint32_t v[kShards];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = ld_relaxed(blk + (1 + k) * kHierStrideWords);
+    for (uint32_t k = 0; k < kShards; ++k) v[k] = ld_relaxed(blk + (1 + k) * kHierStrideWords);
     bool ok = true;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) ok = ok && (int32_t)(v[k] - a.epoch * ev.sub_required[k]) >= 0;
+    for (uint32_t k = 0; k < kShards; ++k) ok = ok && (int32_t)(v[k] - a.epoch * ev.sub_required[k]) >= 0;
     return ok;
   }
   return (int32_t)(ld_relaxed(a.counters + e) - a.epoch * ev.required) >= 0;
@@ -3416,7 +3416,7 @@ __device__ __noinline__ void serve_skip_steps(StepArgs a_in, uint32_t q0, uint32
     const int32_t e = ((const MPK_CONST TaskDesc*)(a.tasks + ld_u32c(a.g->aot + qi)))->trig_event;
     if (e < 0) continue;
     const MPK_CONST EventDesc& ev = *(const MPK_CONST EventDesc*)(a.events + e);
-    uint32_t* cnt = (ev.flags & EV_HIER) ? a.hier + (size_t)ev.hier_slot * kHierWordsPerEvent + (1u + (blockIdx.x & 7u)) * kHierStrideWords
+    uint32_t* cnt = (ev.flags & EV_HIER) ? a.hier + (size_t)ev.hier_slot * kHierWordsPerEvent + (1u + blockIdx.x % kShards) * kHierStrideWords
                                          : a.counters + e;
     __hip_atomic_fetch_add(as_global(cnt), steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }

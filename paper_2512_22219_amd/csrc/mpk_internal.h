@@ -79,23 +79,47 @@ struct alignas(16) TaskDesc {
 };
 static_assert(sizeof(TaskDesc) == 128, "TaskDesc must stay 128 bytes");
 
+constexpr uint32_t kShards = 16;   // producer groups of a sharded event, see below
 struct EventDesc {   // paper Section 4.1 "tGraph linearization" / Fig. 4(f)
   uint32_t required, first, last;
   uint32_t flags;       // bit 0: launches JIT tasks; bit 1: hierarchical arrival (see EV_HIER)
   uint32_t hier_slot;   // index into the hierarchical counter blocks
-  uint32_t n_groups;    // worker groups (worker index mod 8) that hold at least one producer
-  uint32_t sub_required[8];   // producers per worker group
+  uint32_t n_groups;    // worker groups (worker index mod kShards) that hold at least one producer
+  uint32_t sub_required[kShards];   // producers per worker group
   uint32_t pad[2];
 };
-static_assert(sizeof(EventDesc) == 64, "EventDesc is 64 bytes");
+static_assert(sizeof(EventDesc) == 96, "EventDesc is 96 bytes");
 constexpr uint32_t EV_JIT = 1, EV_HIER = 2;
-// A sharded ("hierarchical") event owns 9 words in use, each on its own 256-byte line: 8 producer-
-// group counters (worker index mod 8) that arrivals add to and pollers read all at once (one load
-// instruction, a lane per counter), and a top counter used only when a scheduler has to learn which
-// arrival was the last.  256 same-address atomics plus 256 pollers on one line cost about 4 us per
-// hop on this GPU; sharded, an arrival is one atomic add that nobody waits for.
-constexpr uint32_t kHierStrideWords = 64, kHierWordsPerEvent = 17 * kHierStrideWords;
-constexpr uint32_t kHierMinRequired = 48;
+// A sharded ("hierarchical") event owns 17 words in use, each on its own 256-byte line: kShards
+// producer-group counters (worker index mod kShards) that arrivals add to and pollers read all at
+// once (one load instruction, a lane per counter), and a top counter used only when a scheduler has
+// to learn which arrival was the last.
+// What bounds an unsharded event is that atomics on one address are performed one after the other,
+// about 90 ns each, with the polls of everybody who waits for a counter on the same line between
+// them: a 32-producer event reached its consumers 3 us after the last arrival, a 256-producer one 4.
+// Sharded, every event of an all-ahead-of-time graph is seen 0.8 .. 1 us after the last arrival.
+// Sharding only the events of 48 and more producers left the narrow ones (QKV projection to the
+// attention tasks of a KV head, the operators of small models) at 3 us.  Step times, that rule
+// against all events sharded: tiny model 77.0 -> 61.7 us, 8B shape at batch 1 3001 -> 2886 us, at
+// batch 8 (8 layers) 1209 -> 1186 us.  8 and 16 groups measured the same to 0.3 %.
+// The counter blocks are part of the scratch memory of a step: a graph that only fits the static
+// scratch array (mpk_decode_step_static) with its narrow events unsharded keeps them unsharded.
+constexpr uint32_t kHierStrideWords = 64, kHierWordsPerEvent = (1 + kShards) * kHierStrideWords;
+constexpr uint32_t kHierMinRequired = 1, kHierMinRequiredTight = 48;
+// Bytes of the pieces of a step's scratch memory, each rounded up to 256, in this order.
+struct ScratchLayout {
+  size_t hier, grp, arena, end;   // (event counters at 0)
+};
+inline ScratchLayout scratch_layout(size_t n_events, size_t n_hier, size_t n_group_counters, size_t arena_floats) {
+  auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
+  auto at_least = [](size_t v, size_t m) { return v > m ? v : m; };
+  ScratchLayout L;
+  L.hier = up256(n_events * sizeof(uint32_t));
+  L.grp = L.hier + up256(at_least(n_hier, 1) * kHierWordsPerEvent * sizeof(uint32_t));
+  L.arena = L.grp + up256(at_least(n_group_counters, 1) * sizeof(uint32_t));
+  L.end = L.arena + up256(at_least(arena_floats, 64) * sizeof(float));
+  return L;
+}
 
 // ---------------------------------------------------------------- serving state (device)
 // What the start-event task of a serving graph keeps in device memory (paper Section 6.1: "the

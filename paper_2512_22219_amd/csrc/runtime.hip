@@ -410,12 +410,9 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     g->step_flags = (g->d_trace ? kTraceBit : 0u) | ((o.debug_flags & MPK_DEBUG_JITTER) ? kJitterBit : 0u) |
                     (o.no_preload ? kNoPreloadBit : 0u);
     // ---- the same graph over the static scratch array (mpk_decode_step_static)
-    auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const ScratchLayout lay = scratch_layout(h.events.size(), h.n_hier_events, h.n_group_counters, h.arena_floats);
     g->st_counters = 0;
-    g->st_hier = up256(h.events.size() * sizeof(uint32_t));
-    g->st_grp = g->st_hier + up256((size_t)std::max(h.n_hier_events, 1u) * kHierWordsPerEvent * sizeof(uint32_t));
-    g->st_arena = g->st_grp + up256(std::max<size_t>(h.n_group_counters, 1) * sizeof(uint32_t));
-    g->st_need = g->st_arena + up256(arena_bytes);
+    g->st_hier = lay.hier; g->st_grp = lay.grp; g->st_arena = lay.arena; g->st_need = lay.end;
     g->static_refusal = nullptr;
     if (g->n_sched) g->static_refusal = "graph was compiled with scheduler workgroups";
     else if (h.opt.greedy_loop) g->static_refusal = "graph was compiled with greedy_loop";
@@ -491,7 +488,9 @@ static mpk_status launch_steps(mpk_graph* g, uint32_t n_steps, const int32_t* to
     a.counters = (uint32_t*)(g->static_base + g->st_counters);
     a.hier = (uint32_t*)(g->static_base + g->st_hier);
     arena = (float*)(g->static_base + g->st_arena);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, s, (uint32_t*)g->static_base, g->st_arena / sizeof(uint32_t), 0u);
+    const size_t words = g->st_arena / sizeof(uint32_t);   // (a few words a thread: the sharded counters of a deep model are megabytes)
+    hipLaunchKernelGGL(fill_u32_kernel, dim3((uint32_t)std::min<size_t>(1024, std::max<size_t>(64, words / 1024))), dim3(256), 0, s,
+                       (uint32_t*)g->static_base, words, 0u);
     HIP_TRY(hipGetLastError());
   }
   if (h.opt.debug_flags & MPK_DEBUG_POISON) {
