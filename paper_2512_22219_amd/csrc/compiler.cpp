@@ -1023,8 +1023,10 @@ static void build_descs(const mpk_model_config& c, const mpk_kv_ptrs* kv, HostGr
   }
 }
 
-static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_t C) {
-  size_t need = 0;
+// vector_need: bytes with the vector linear body (batch up to 4; 0 above), which decides what shapes
+// are accepted at batch 3 and 4 although the matrix-core body, which needs less, runs them.
+static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_t C, size_t* vector_need) {
+  size_t need = 0, need_vec = 0;
   const uint32_t grp = c.n_q_heads / c.n_kv_heads;
   const uint32_t nb = c.batch <= 2 ? c.batch : (c.batch <= 4 ? 4u : 8u);   // body template sizes
   // linear tasks: staged input rows | per-row results | residual slice | partial sums of squares
@@ -1041,12 +1043,14 @@ static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_
     uint32_t nu = op.cols / op.unit;
     res_rows = std::max(res_rows, col_tile_max_units(op) * op.unit);
   }
+  if (c.batch >= kMfmaMinBatch) res_rows = std::min(res_rows, kMfmaJobRows);   // (a job's)
   g.lin_res_rows_max = res_rows;
   for (auto& op : g.ops) {
-    size_t f = 0;
+    size_t f = 0, fv = 0;
     if (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) {
-      if (c.batch <= 4) {
-        f = (size_t)nb * ((op.K + 4095u) / 4096u * 4096u) + 2 * (size_t)rows_max * nb + 8 * nb;
+      if (c.batch <= 4) fv = (size_t)nb * ((op.K + 4095u) / 4096u * 4096u) + 2 * (size_t)rows_max * nb + 8 * nb;
+      if (c.batch < kMfmaMinBatch) {
+        f = fv;
       } else {
         // matrix-core body: the staged fp32 input, one chunk (reused for the per-wavefront
         // partial tiles) | residual slice | sums of squares | 1/rms per row
@@ -1065,8 +1069,10 @@ static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_
     if (op.kind == MPK_OP_ATTN_PARTIAL && g.opt.kv_page_size)   // paged cache: + the chunk's page numbers
       f += c.max_seq / g.opt.kv_page_size;
     need = std::max(need, f);
+    need_vec = std::max(need_vec, std::max(f, fv));
   }
   size_t bytes = (need + kLdsReduceFloats + kLdsCtrlFloats) * sizeof(float);   // + the control words
+  *vector_need = c.batch <= 4 ? (need_vec + kLdsReduceFloats + kLdsCtrlFloats) * sizeof(float) : 0;
   return (uint32_t)std::max<size_t>(bytes, kMinLdsBytes);
 }
 
@@ -1296,7 +1302,7 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
     // task has a fixed cost: event wait, query staging, the merge of its partial result).
     // Measured: C2 (8 pairs, 1088 positions) is fastest with 8 chunks, C3 (64 pairs) with 4.
     const uint32_t pairs = cfg.batch * cfg.n_kv_heads;
-    C = (opt.n_workers + pairs - 1) / pairs;
+    C = std::max(1u, opt.n_workers / pairs);
     C = std::min(C, std::max(1u, cfg.max_seq / 128u));
     C = std::max(1u, std::min(C, 64u));
   }
@@ -1323,7 +1329,8 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
   if (st != MPK_OK) return st;
   g.stats.n_pair_deps += g.stats.n_pairs_removed;
   build_descs(cfg, kv, g);
-  g.lds_bytes = lds_requirement(cfg, g, C);
+  size_t vector_lds = 0;
+  g.lds_bytes = lds_requirement(cfg, g, C, &vector_lds);
   if (sp.page_ready) {   // (second pass: the tile sizes already account for the pages)
     const std::vector<uint16_t> plan = page_plan(cfg, opt, g);
     bool any = false;
@@ -1337,8 +1344,8 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
       g.lds_bytes = 160 * 1024;
     }
   }
-  if (cfg.batch > 4 && g.lin_rows_max > 512) { set_error("a linear task would own %u weight rows; the batch >= 5 body handles at most 512: raise tiles_linear / tiles_lm_head", g.lin_rows_max); return MPK_ERR_UNSUPPORTED; }
-  if (g.lds_bytes > 160 * 1024 && !opt.host_only) { set_error("task bodies need %u bytes of LDS (> 160 KB): batch x input length too large", g.lds_bytes); return MPK_ERR_UNSUPPORTED; }
+  if (cfg.batch > 4 && g.lin_rows_max > kMfmaJobRows) { set_error("a linear task would own %u weight rows; the batch >= 5 body handles at most 512: raise tiles_linear / tiles_lm_head", g.lin_rows_max); return MPK_ERR_UNSUPPORTED; }
+  if (std::max<size_t>(g.lds_bytes, vector_lds) > 160 * 1024 && !opt.host_only) { set_error("task bodies need %zu bytes of LDS (> 160 KB): batch x input length too large", std::max<size_t>(g.lds_bytes, vector_lds)); return MPK_ERR_UNSUPPORTED; }
   // statistics
   g.stats.struct_size = sizeof(mpk_stats);
   g.stats.n_ops = (uint32_t)g.ops.size();

@@ -49,6 +49,8 @@ struct GraphConst {
   const uint32_t* op_list;   // per-operator launch: task indices grouped by operator
   uint32_t* err;             // [0] error code, [1] abort flag, [2..3] detail
   const double* inv_freq;    // RoPE frequencies theta^(-2i/d), i < head_dim / 2
+  uint32_t attn_shape;       // attn_shape_index of the model and its cache
+  float* rope_tab;           // [batch][head_dim / 2] (cos, sin) of this step's rotation angles, written by the embedding tasks
   uint32_t* grp_counters;    // arrival counters per (layer, sequence, KV head), monotonic
   uint64_t* trace;           // optional [n_tasks][kTraceSlots] timestamps (100 MHz), or null
   uint64_t timeout_ticks;
@@ -82,6 +84,12 @@ struct GraphConst {
   int32_t serve_event;         // event the serving task triggers, -1 = none
 };
 
+// Which instance of the attention task runs: head_dim 64 / 128, 1 / 2 / 4 / 8 query heads per KV head,
+// contiguous or paged cache.
+constexpr uint32_t attn_shape_index(uint32_t d, uint32_t grp, uint32_t paged) {
+  return ((d == 128u ? 4u : 0u) + (grp == 8u ? 3u : grp == 4u ? 2u : grp == 2u ? 1u : 0u)) * 2u + paged;
+}
+
 // Per-step kernel arguments, passed by value.  Every device function taking it is force-inlined:
 // a real call with a reference to it would make the compiler copy the struct to private memory.
 // Tables that no kernel ever writes (the graph record, task and event descriptors, queues) are
@@ -114,6 +122,7 @@ struct StepArgs {
 static_assert(sizeof(StepArgs) == 80, "StepArgs grew: check the single-step launch time");
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // A struct passed by value to a real (non-inlined) function travels through private memory and
 // arrives in vector registers: to the compiler every field is then a per-lane value, so the
@@ -288,6 +297,9 @@ __device__ __forceinline__ float2 ld_act2(const float* p) {   // p 8-byte aligne
   uint64_t u = __hip_atomic_load(as_global((const uint64_t*)p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
 }
+__device__ __forceinline__ void st_act2(float* p, float x, float y) {   // p 8-byte aligned
+  __hip_atomic_store(as_global((uint64_t*)p), ((uint64_t)__float_as_uint(y) << 32) | __float_as_uint(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p) {
   return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -323,17 +335,43 @@ __device__ __forceinline__ void report(const StepArgs& a, uint32_t code, uint32_
 }
 
 // ------------------------------------------------------------------------------ task bodies
-// T0: x[b] = E[token[b]] widened to fp32.
+// cos and sin of position * inv_freq[i]: the angle is formed and reduced to [-pi, pi] in double.
+__device__ __forceinline__ void rope_cs(const StepArgs& a, int32_t pos, uint32_t i, float* c, float* s) {
+  double ang = (double)pos * as_global(a.g->inv_freq)[i];
+  const double two_pi = 6.283185307179586476925286766559;
+  ang -= two_pi * rint(ang / two_pi);
+  double sd, cd;
+  sincos(ang, &sd, &cd);
+  *c = (float)cd;
+  *s = (float)sd;
+}
+
+// T0: x[b] = E[token[b]] widened to fp32.  Eight elements a thread: the row is one round trip (an
+// element at a time, loads and coherent stores took turns: 7 us for 4096 inputs, now 2).
+// The task also leaves the step's rotation angles of its sequences in the rope table: they depend
+// on the position alone, and every attention task of every layer that worked them out for itself (in
+// double precision) spent 1 to 3 us on them ahead of its event.
 __device__ __forceinline__ void body_embed(const TaskDesc& t, const StepArgs& a) {
   for (uint32_t b = t.b0; b < t.b1; ++b) {
     int32_t tok = (int32_t)ld_relaxed((const uint32_t*)a.token_ids + b);   // may come from the previous step's sampling task
+    const int32_t pos = (a.flags & kServeBit) ? (int32_t)ld_relaxed((const uint32_t*)a.positions + b) : a.positions[b] + (int32_t)a.step;
     if (tok < 0 || (uint32_t)tok >= a.g->vocab) {
       if (threadIdx.x == 0) report(a, DE_BAD_TOKEN, b, (uint32_t)tok);
       tok = 0;
     }
     const uint16_t* row = (const uint16_t*)t.w + (size_t)tok * t.K;
     float* out = t.out + (size_t)b * t.ld_out;
-    for (uint32_t i = threadIdx.x; i < t.K; i += kThreads) st_act(out + i, bf16_to_f32(as_global(row)[i]));
+    for (uint32_t i = 8u * threadIdx.x; i < t.K; i += 8u * kThreads) {   // (the host checks that K is a multiple of 8)
+      const u32x4 w = *as_global((const u32x4*)(row + i));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) st_act2(out + i + 2 * k, bf16_lo(w[k]), bf16_hi(w[k]));
+    }
+    const uint32_t half = a.g->head_dim / 2u, i = kThreads - 1u - threadIdx.x;   // (threads without a share of a short row)
+    if (i < half) {
+      float cs, sn;
+      rope_cs(a, pos, i, &cs, &sn);
+      st_act2(a.g->rope_tab + 2u * ((size_t)b * half + i), cs, sn);
+    }
   }
 }
 
@@ -354,7 +392,12 @@ __device__ __forceinline__ void body_rmsnorm(const TaskDesc& t, float* lds) {
   }
 }
 
+struct EventProbe {   // a look at an event whose loads may still be in flight
+  uint32_t seen = 0, need = 1;
+};
+__device__ __forceinline__ EventProbe probe_event(const StepArgs& a, int32_t e, int lane);
 __device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag);
+__device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag, const EventProbe& probe);
 
 // ------------------------------------------------------------------------------ linear tasks
 // T2/T6/T9/T11/T14: y[b][c] = sum_j W[c][j] x[b][j] for output columns [c0, c1), all batch rows
@@ -960,6 +1003,20 @@ __device__ __forceinline__ u32x4 select4(bool c, const u32x4& x, const u32x4& y)
   return u32x4{c ? x.x : y.x, c ? x.y : y.y, c ? x.z : y.z, c ? x.w : y.w};
 }
 
+// A pair of loads of 8 rows x 128 bytes (lane l: row l % 8 of rows 0..7 / 8..15, 16-byte block l / 8)
+// -> the two matrix operands of the pair (lane = row + 16 x input group), in place; the derivation
+// is in mfma_job_packed.
+__device__ __forceinline__ void pair_to_operands(u32x4& l0, u32x4& l1) {
+  auto ror8 = [](uint32_t old, uint32_t src, auto bank) {   // lanes of `bank`: src of the lane 8 further in its row of 16
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)src, 0x128, 0xF, decltype(bank)::value, false);
+  };
+  const u32x4 a = l0, b = l1;
+  l0 = u32x4{ror8(a.x, b.x, std::integral_constant<int, 0xC>{}), ror8(a.y, b.y, std::integral_constant<int, 0xC>{}),
+             ror8(a.z, b.z, std::integral_constant<int, 0xC>{}), ror8(a.w, b.w, std::integral_constant<int, 0xC>{})};
+  l1 = u32x4{ror8(b.x, a.x, std::integral_constant<int, 0x3>{}), ror8(b.y, a.y, std::integral_constant<int, 0x3>{}),
+             ror8(b.z, a.z, std::integral_constant<int, 0x3>{}), ror8(b.w, a.w, std::integral_constant<int, 0x3>{})};
+}
+
 // One job: out[r][b] partial tiles = W rows x staged input rows, left in LDS.
 //   wbase, row_off(rt) : weight rows start at wbase (uniform) + row_off(rt) bytes, row_off = this
 //                  lane's row of 16-row tile rt (32 bits: a scalar base and one vector offset per
@@ -1018,17 +1075,6 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   auto ld_frag = [&](uint32_t ro, uint32_t k, bool real) {
     const uint32_t off = real ? ro + 2u * min(k + lk, K - 8u) : 0u;   // not real: every lane the matrix' first 16 bytes
     return __builtin_nontemporal_load((const MPK_GLOBAL u32x4*)((const MPK_GLOBAL char*)wbase + off));
-  };
-  // the pair as loaded -> the two operands (in place)
-  auto to_operands = [&](u32x4& l0, u32x4& l1) {
-    auto ror8 = [](uint32_t old, uint32_t src, auto bank) {   // lanes of `bank`: src of the lane 8 further in its row of 16
-      return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)src, 0x128, 0xF, decltype(bank)::value, false);
-    };
-    const u32x4 a = l0, b = l1;
-    l0 = u32x4{ror8(a.x, b.x, std::integral_constant<int, 0xC>{}), ror8(a.y, b.y, std::integral_constant<int, 0xC>{}),
-               ror8(a.z, b.z, std::integral_constant<int, 0xC>{}), ror8(a.w, b.w, std::integral_constant<int, 0xC>{})};
-    l1 = u32x4{ror8(b.x, a.x, std::integral_constant<int, 0x3>{}), ror8(b.y, a.y, std::integral_constant<int, 0x3>{}),
-               ror8(b.z, a.z, std::integral_constant<int, 0x3>{}), ror8(b.w, a.w, std::integral_constant<int, 0x3>{})};
   };
   // the wavefront's run of k-groups in chunk c; a chunk takes an even number of round slots
   // (>= 2), so that even slots always use fragment buffer A and odd ones B
@@ -1143,7 +1189,7 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
     const uint32_t kg0 = run_lo(c) + i * kgpr, hi = run_hi(c);
     if (kg0 < hi) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) to_operands(buf[FR * q], buf[FR * q + 1]);
+      for (int q = 0; q < 4; ++q) pair_to_operands(buf[FR * q], buf[FR * q + 1]);
       static_for<0, (int)FR>([&](auto Uc) {
         constexpr uint32_t U = (uint32_t)decltype(Uc)::value;
         u32x4 p0, p1, p2;   // operands of the first, second, third multiply
@@ -1252,7 +1298,8 @@ __device__ __forceinline__ float mfma_dot(const float* part, const MfmaGeom& G, 
 }
 
 // LDS of a linear task (from the task area): job buffers (mfma_x_floats) | res [residual columns][16] f32
-// | ssq [8][16] f32 | 1/rms [16] f32.
+// | ssq [8][16] f32 | 1/rms [16] f32.  A job takes up to 512 weight rows; a task of more (batch 3 and 4
+// with few, user-given tiles) is worked off in several, the input staged again for each.
 template <bool MEGA, class Svc = NoJit>
 __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
                                                      uint32_t* s_flag, const Svc& svc = Svc{}) {
@@ -1261,70 +1308,73 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
   const uint32_t K = t.K, nb = t.b1 - t.b0, ncols = t.c1 - t.c0;
   const uint32_t gateup = (t.flags & TF_GATEUP) ? 1u : 0u;
   const uint32_t R = ncols << gateup;            // weight rows of the task ("ring rows")
-  const MfmaGeom G = mfma_geom(K, nb, (R + 15u) / 16u, wave);
   float* part = lds;
-  float* res_lds = lds + mfma_x_floats(nb);                    // [residual columns][16]
+  float* res_lds = lds + mfma_x_floats(nb);                    // [residual columns of a job][16]
   float* ssq = res_lds + (size_t)a.g->lin_res_rows_max * 16;   // [8][16]
-  const uint16_t* W = (const uint16_t*)t.w;
-  const uint32_t frow = lane & 15u, fk = (uint32_t)(lane >> 4) * 8u;   // fragment row / input offset
   // split-K task (TF_SPLITK): rows [row0, row0 + ncols) of the matrix, inputs of ONE part; the
   // weight pointer is already advanced to the part, rows are ldw apart
   const bool splitk = t.flags & TF_SPLITK;
   const uint32_t parts = splitk ? (t.p3 & 0xFFu) : 1u, my_part = splitk ? (t.p3 >> 8) : 0u;
   const uint32_t Hs = t.ld_out / parts;              // columns of the real output
   const uint32_t row0 = t.c0 - my_part * Hs, ldw = splitk ? t.p1 : K;
-  auto row_off = [&](uint32_t rt, uint32_t row) {       // row: this lane's row of the 16-row tile
-    const uint32_t r = min(rt * 16u + row, R - 1u);    // rows past the end repeat the last one
-    const uint32_t wrow = gateup ? (row0 + (r >> 1) + ((r & 1u) ? t.p0 : 0u)) : row0 + r;
-    return wrow * ldw * 2u;   // bytes; the host checks that a weight matrix stays below 4 GB
-  };
+  const uint16_t* W = (const uint16_t*)t.w + (size_t)row0 * ldw;   // the task's first row (gate/up: of the gate rows)
   auto src_row = [&](uint32_t b) { return t.in + (size_t)(t.b0 + b) * t.ld_in; };
   const bool pro_norm = t.flags & TF_PRO_NORM;
-  auto wait_fn = [&]() -> uint32_t {
-    if (wait_ev >= 0) {
-      const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc);
+  for (uint32_t r0 = 0; r0 < R; r0 += kMfmaJobRows) {
+    const uint32_t Rj = min(R - r0, kMfmaJobRows), cj = r0 >> gateup, nj = Rj >> gateup;   // the job's rows, columns
+    const MfmaGeom G = mfma_geom(K, nb, (Rj + 15u) / 16u, wave);
+    auto row_off = [&](uint32_t rt, uint32_t row) {       // row: this lane's row of the 16-row tile
+      const uint32_t r = r0 + min(rt * 16u + row, Rj - 1u);    // rows past the end repeat the last one
+      const uint32_t wrow = gateup ? ((r >> 1) + ((r & 1u) ? t.p0 : 0u)) : r;
+      return wrow * ldw * 2u;   // bytes from the task's first row; the host checks that they stay below 4 GB
+    };
+    auto wait_fn = [&]() -> uint32_t {
+      if (wait_ev >= 0 && r0 == 0) {
+        const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc);
+        if (w != kLinDone) return w;
+      }
+      // the residual slice of this tile goes out first (tile-local, small): its round trip overlaps the staging
+      if ((t.flags & TF_EPI_RESID) && !splitk) {
+        for (uint32_t i = threadIdx.x; i < nb * nj; i += kThreads) {
+          uint32_t bb = i / nj, cc = i % nj;
+          res_lds[cc * 16 + bb] = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cj + cc);
+        }
+      }
+      return kLinDone;
+    };
+    {
+      const uint32_t w = mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, wait_fn);
       if (w != kLinDone) return w;
     }
-    // the residual slice of this tile goes out first (tile-local, small): its round trip overlaps the staging
-    if ((t.flags & TF_EPI_RESID) && !splitk) {
-      for (uint32_t i = threadIdx.x; i < nb * ncols; i += kThreads) {
-        uint32_t bb = i / ncols, cc = i % ncols;
-        res_lds[cc * 16 + bb] = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc);
-      }
-    }
-    return kLinDone;
-  };
-  {
-    const uint32_t w = mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, wait_fn);
-    if (w != kLinDone) return w;
-  }
-  trace_mark(a, t, 3);
-  // ---- all wavefronts: add the K slices in order, epilogue, outputs; then the notification
-  float* inv_lds = ssq + 8 * 16;   // [16] 1/rms of each batch row
-  if (pro_norm) {
-    if (threadIdx.x < 16) {
-      float ss = 0.f;
+    trace_mark(a, t, 3);
+    // ---- all wavefronts: add the K slices in order, epilogue, outputs; then the notification
+    float* inv_lds = ssq + 8 * 16;   // [16] 1/rms of each batch row
+    if (pro_norm) {
+      if (threadIdx.x < 16) {
+        float ss = 0.f;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) ss += ssq[w * 16 + threadIdx.x];
-      inv_lds[threadIdx.x] = 1.0f / sqrtf(ss / (float)K + t.f0);
-    }
-    lds_barrier();
-  }
-  {
-    float* outp = (t.flags & TF_OUT_LOGITS) ? a.logits : t.out;
-    for (uint32_t i = threadIdx.x; i < ncols * nb; i += kThreads) {
-      const uint32_t cc = i / nb, bb = i % nb;
-      const float inv = pro_norm ? inv_lds[bb] : 1.0f;
-      float v;
-      if (gateup) {
-        const float gte = mfma_dot(part, G, 2 * cc, bb) * inv, up = mfma_dot(part, G, 2 * cc + 1, bb) * inv;
-        v = gte / (1.0f + expf(-gte)) * up;
-      } else {
-        v = mfma_dot(part, G, cc, bb) * inv;
+        for (int w = 0; w < 8; ++w) ss += ssq[w * 16 + threadIdx.x];
+        inv_lds[threadIdx.x] = 1.0f / sqrtf(ss / (float)K + t.f0);
       }
-      if ((t.flags & TF_EPI_RESID) && !splitk) v = res_lds[cc * 16 + bb] + v;
-      st_act(outp + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc, v);   // split-K: the partial sums of this part
+      lds_barrier();
     }
+    {
+      float* outp = (t.flags & TF_OUT_LOGITS) ? a.logits : t.out;
+      for (uint32_t i = threadIdx.x; i < nj * nb; i += kThreads) {
+        const uint32_t cc = i / nb, bb = i % nb;
+        const float inv = pro_norm ? inv_lds[bb] : 1.0f;
+        float v;
+        if (gateup) {
+          const float gte = mfma_dot(part, G, 2 * cc, bb) * inv, up = mfma_dot(part, G, 2 * cc + 1, bb) * inv;
+          v = gte / (1.0f + expf(-gte)) * up;
+        } else {
+          v = mfma_dot(part, G, cc, bb) * inv;
+        }
+        if ((t.flags & TF_EPI_RESID) && !splitk) v = res_lds[cc * 16 + bb] + v;
+        st_act(outp + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cj + cc, v);   // split-K: the partial sums of this part
+      }
+    }
+    if (r0 + kMfmaJobRows < R) lds_barrier();   // the next job reuses the buffers
   }
   if (MEGA || splitk) {
     // every wavefront's coherent stores complete before anyone is told
@@ -1640,17 +1690,6 @@ __device__ __forceinline__ void body_moe_combine(const TaskDesc& t, const StepAr
   }
 }
 
-// cos and sin of position * inv_freq[i]: the angle is formed and reduced to [-pi, pi] in double.
-__device__ __forceinline__ void rope_cs(const StepArgs& a, int32_t pos, uint32_t i, float* c, float* s) {
-  double ang = (double)pos * as_global(a.g->inv_freq)[i];
-  const double two_pi = 6.283185307179586476925286766559;
-  ang -= two_pi * rint(ang / two_pi);
-  double sd, cd;
-  sincos(ang, &sd, &cd);
-  *c = (float)cd;
-  *s = (float)sd;
-}
-
 // Sum over an aligned group of N adjacent lanes (N a power of two <= 64); every lane gets it.
 template <int N>
 __device__ __forceinline__ float lane_group_sum(float v) {
@@ -1716,52 +1755,6 @@ __device__ __forceinline__ void body_rope(const TaskDesc& t, const StepArgs& a) 
   }
 }
 
-// Sum over the LPP (8 or 16) adjacent lanes that share one cache position, with DPP lane
-// permutations (register-to-register, no LDS round trip); every lane gets the sum.
-template <int LPP>
-__device__ __forceinline__ float group_sum(float v) {
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));   // lane ^ 1
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));   // lane ^ 2
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));  // mirror in 8
-  if (LPP == 16)
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));  // mirror in 16
-  return v;
-}
-
-// Rounds of cache rows the running-softmax attention body keeps in registers (requested ahead of
-// their use), by the kernel's batch class nb (0: the generic kernels) and query heads per KV head.
-// Batch 1: chunks are a few rounds long and the task is a chain of latencies -- as many rounds as
-// the running state of the heads leaves registers for, so that a whole chunk is requested before
-// the event.  Matrix-core batch classes: chunks are tens of rounds long and all 256 workers stream
-// at once; three rounds in flight per wavefront measured fastest (8B shape at batch 8: 5.29 ms per
-// step against 5.30 / 5.36 / 5.36 / 5.52 with 2 / 4 / 6 / 8; the mixture-of-experts shape at batch
-// 16: 15.0 against 15.5 / 15.4 with 2 / 4) -- what is in flight beyond that only lengthens the
-// queue in front of everybody's next request.
-constexpr int attn_depth(int nb, int grp) { return nb >= 5 ? 3 : (grp <= 4 ? 8 : 4); }
-constexpr bool attn_streams(int nb) { return nb >= 5; }
-
-__device__ __forceinline__ void unpack8(const u32x4& w, float (&f)[8]) {   // 8 bf16 -> fp32
-  f[0] = bf16_lo(w.x); f[1] = bf16_hi(w.x); f[2] = bf16_lo(w.y); f[3] = bf16_hi(w.y);
-  f[4] = bf16_lo(w.z); f[5] = bf16_hi(w.z); f[6] = bf16_lo(w.w); f[7] = bf16_hi(w.w);
-}
-
-// 16 bytes of a cache row of an earlier step.  Contiguous cache: a plain streaming load (the row's
-// lines were never read in this launch before they were written, see the attention body).  Paged
-// cache: a page that one request gave back may be handed to another within the same launch, so a
-// compute unit may still hold lines of the page's previous life -- in a launch that runs several
-// steps every row is read with agent-scope loads, which do not hit such lines; a launch of one
-// step cannot see a page change owners (the serving task runs before any row is read), so there
-// the streaming load is as good as on the contiguous cache.
-template <bool PAGED>
-__device__ __forceinline__ u32x4 ld_cache_row(const StepArgs& a, const uint16_t* p) {
-  if constexpr (PAGED) {
-    if (a.flags & kOneStepBit) return ld_stream16(p);
-    return ld_row16_coherent(p);
-  } else {
-    return ld_stream16(p);
-  }
-}
-
 // Position of sequence b in this step.  positions[] is the host's and stays as written for the
 // whole launch (tasks add the step number) -- except in a serving launch, where the serving task
 // rewrites it at the start of every step: then it holds the step's own positions and is read with
@@ -1772,348 +1765,11 @@ __device__ __forceinline__ int32_t step_position(const StepArgs& a, uint32_t b) 
   return a.positions[b] + (int32_t)a.step;
 }
 
-// T4, short chunks: the same task when a chunk never exceeds kAttnRounds rounds (8 x 32 = 256 cache
-// positions at head_dim 128): all of its K and V rows are requested before the event wait and
-// stay in registers, scores are formed once, one chunk-wide maximum, one exp per score.  Fewer
-// instructions than the running-softmax body below; the decoder at batch 1 spends its attention
-// phase on latency, not bandwidth, so that is what counts there.
-// Layout of the work: D/8 adjacent lanes share one position (16 bytes of the row each), a
-// wavefront covers 64/(D/8) positions per round, the 8 wavefronts of the workgroup take rounds
-// of 8 x that many positions; kAttnRounds rounds fit in registers and the compiler picks the chunk
-// count so that a chunk never exceeds them.
-// Cache rows of earlier steps are immutable during a step, so the task requests its K and V rows
-// BEFORE it waits for its dependent event; only the query (and the row appended this step)
-// arrive later.  Scores, probabilities and the running sums stay in registers.
-constexpr int kAttnRounds = 8;
-
-template <int D, int GRP, bool PAGED = false>
-__device__ __forceinline__ bool body_attn_partial_regs(const TaskDesc& t, const StepArgs& a, float* lds,
-                                                  int32_t wait_ev, uint32_t* s_flag) {
-  constexpr uint32_t d = D, grp = GRP, LPP = D / 8, PPW = 64 / LPP, NW = kThreads / 64;
-  constexpr uint32_t stride = NW * PPW, per = grp * (d + 2);
-  constexpr uint32_t WS = d + 4;   // row of one partial in LDS: output, max, sum; 16-byte aligned rows
-  const uint32_t nq = a.g->n_q, nkv = a.g->n_kv, C = t.p1;
-  const uint32_t b = t.b0, u = t.c0 / per, g = u / C, c = u % C;
-  // (paged cache: positions and page table are this step's once the serving task has run -- see
-  // the running-softmax body below)
-  if (PAGED && wait_ev >= 0 && a.g->serve_event >= 0 && !wait_event(a, a.g->serve_event, s_flag)) return false;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float* qs = lds;                       // [grp][d]
-  float* wpart = qs + grp * d;           // [NW * PPW][grp][WS]: partial output and sum per position slot
-  uint32_t* flag = (uint32_t*)(wpart + stride * grp * WS);    // then [16..) the maxima exchange
-  float* outp = t.out + (size_t)b * t.ld_out + t.c0;
-  const int32_t pos = step_position<PAGED>(a, b);    // written by the host before the launch (or by the serving task)
-  const bool bad_pos = pos < 0 || (uint32_t)pos >= a.g->max_seq;
-  const uint32_t len = bad_pos ? 0u : (uint32_t)pos + 1;
-  const uint32_t t0 = (uint32_t)((uint64_t)c * len / C), t1 = (uint32_t)((uint64_t)(c + 1) * len / C);
-  const uint32_t n = t1 - t0;
-  const uint16_t* Kb = (const uint16_t*)t.aux0 + (PAGED ? (size_t)0 : (((size_t)b * nkv + g) * a.g->max_seq + t0) * d);
-  const uint16_t* Vb = (const uint16_t*)t.aux1 + (PAGED ? (size_t)0 : (((size_t)b * nkv + g) * a.g->max_seq + t0) * d);
-  // paged: the chunk's page numbers, staged in LDS (behind the maxima exchange)
-  const uint32_t pshift = PAGED ? a.g->page_shift : 0u;
-  const uint32_t pg0 = t0 >> pshift;
-  uint32_t* pgs = flag + 48;
-  bool bad_page = false;
-  if constexpr (PAGED) {
-    const uint32_t* ptab = (const uint32_t*)a.g->page_table + (size_t)b * (a.g->max_seq >> pshift);
-    const uint32_t npg = n ? ((t1 - 1u) >> pshift) - pg0 + 1u : 0u;
-    for (uint32_t i = threadIdx.x; i < npg; i += kThreads) {
-      uint32_t pg = ld_relaxed(ptab + pg0 + i);
-      if (pg >= a.g->kv_pages) { bad_page = true; pg = 0; }
-      pgs[i] = pg;
-    }
-    __syncthreads();
-    if (bad_page) report(a, DE_BAD_PAGE, b, t0);   // (its rows come from page 0 instead: wrong, but in bounds)
-  }
-  auto row_off = [&](uint32_t i) -> size_t {   // element offset of row i of the chunk from Kb / Vb
-    if constexpr (PAGED) {
-      const uint32_t r = t0 + i;
-      return ((((size_t)pgs[(r >> pshift) - pg0] * nkv + g) << pshift) + (r & ((1u << pshift) - 1u))) * d;
-    } else {
-      return (size_t)i * d;
-    }
-  };
-  const uint32_t sub = lane % LPP, slot = lane / LPP;
-  const uint32_t i_first = wave * PPW + slot;
-  const uint32_t n_rounds = (n + stride - 1) / stride;
-  // ---- pre-load: K and V rows of earlier steps
-  u32x4 kreg[kAttnRounds], vreg[kAttnRounds];
-  auto load_rows = [&]() {
-#pragma unroll
-    for (int r = 0; r < kAttnRounds; ++r) {
-      const uint32_t i = i_first + r * stride;
-      kreg[r] = u32x4{0, 0, 0, 0};
-      vreg[r] = u32x4{0, 0, 0, 0};
-      if (i < n && t0 + i != (uint32_t)pos) {
-        const size_t off = row_off(i);
-        kreg[r] = ld_cache_row<PAGED>(a, Kb + off + sub * 8);
-        vreg[r] = ld_cache_row<PAGED>(a, Vb + off + sub * 8);
-      }
-    }
-  };
-  const bool preload = !(a.flags & kNoPreloadBit);
-  if (preload) {
-    load_rows();
-    asm volatile("; cache rows requested" ::: "memory");
-  }
-  // the rotation angles depend on the position alone: worked out (in double precision) before the
-  // event, off the critical path from the QKV projection to the O projection.  A thread's first
-  // query element, and the two key pairs of the threads that append the new row.
-  float pre_cs = 1.f, pre_sn = 0.f, pre_c0 = 1.f, pre_s0 = 0.f, pre_c1 = 1.f, pre_s1 = 0.f;
-  if (t.flags & TF_ROPE_FUSED) {
-    if (threadIdx.x < grp * (d / 2)) rope_cs(a, pos, threadIdx.x % (d / 2), &pre_cs, &pre_sn);
-    const uint32_t ik = kThreads - 1 - threadIdx.x;
-    if (c == C - 1 && ik < d / 4) {
-      rope_cs(a, pos, 2 * ik, &pre_c0, &pre_s0);
-      rope_cs(a, pos, 2 * ik + 1, &pre_c1, &pre_s1);
-    }
-  }
-  if (wait_ev >= 0 && !wait_event(a, wait_ev, s_flag)) return false;
-  trace_mark(a, t, 1);
-  if (!preload) {
-    load_rows();
-    asm volatile("; cache rows requested after the event" ::: "memory");
-  }
-  if (bad_pos || n_rounds > (uint32_t)kAttnRounds) {
-    if (threadIdx.x == 0) report(a, DE_BAD_POSITION, b, (uint32_t)pos);
-    for (uint32_t i = threadIdx.x; i < per; i += kThreads) st_act(outp + i, ((i % (d + 2)) == d) ? -INFINITY : 0.f);
-    return true;
-  }
-  const float* qsrc = t.in + (size_t)b * t.ld_in + (size_t)g * grp * d;
-  if (t.flags & TF_ROPE_FUSED) {
-    // the input is the raw QKV projection: rotate the group's query heads here; the task of the
-    // last chunk also rotates this step's key, and appends key and value to the cache
-    constexpr uint32_t half = d / 2;
-    const bool qk_norm = t.flags & TF_QK_NORM;
-    for (uint32_t i = threadIdx.x; i < grp * half; i += kThreads) {
-      uint32_t j = i / half, e = i % half;
-      float u0 = ld_act(qsrc + j * d + e), u1 = ld_act(qsrc + j * d + e + half), cs, sn;
-      if (qk_norm) {   // RMSNorm over the head: its `half` threads are one aligned group of lanes
-        const float inv = 1.0f / sqrtf(lane_group_sum<(int)half>(u0 * u0 + u1 * u1) / (float)d + t.f0);
-        const uint16_t* gq = (const uint16_t*)t.w;
-        u0 *= inv * bf16_to_f32(as_global(gq)[e]);
-        u1 *= inv * bf16_to_f32(as_global(gq)[e + half]);
-      }
-      if (i < kThreads) { cs = pre_cs; sn = pre_sn; }
-      else rope_cs(a, pos, e, &cs, &sn);
-      qs[j * d + e] = u0 * cs - u1 * sn;
-      qs[j * d + e + half] = u1 * cs + u0 * sn;
-    }
-    if (c == C - 1) {
-      const float* ksrc = t.in + (size_t)b * t.ld_in + (size_t)(nq + g) * d;
-      const float* vsrc = t.in + (size_t)b * t.ld_in + (size_t)(nq + nkv + g) * d;
-      uint16_t *krow, *vrow;
-      if constexpr (PAGED) {
-        const size_t off = row_off((uint32_t)pos - t0);
-        krow = const_cast<uint16_t*>(Kb) + off;
-        vrow = const_cast<uint16_t*>(Vb) + off;
-      } else {
-        krow = (uint16_t*)t.aux0 + (((size_t)b * nkv + g) * a.g->max_seq + (uint32_t)pos) * d;
-        vrow = (uint16_t*)t.aux1 + (((size_t)b * nkv + g) * a.g->max_seq + (uint32_t)pos) * d;
-      }
-      // threads from the top of the workgroup, so that they do not also rotate query pairs
-      for (uint32_t i = kThreads - 1 - threadIdx.x; i < half / 2 + half; i += kThreads) {
-        if (i < half / 2) {   // two adjacent rotation pairs of the key
-          uint32_t e = 2 * i;
-          float2 lo = ld_act2(ksrc + e), hi = ld_act2(ksrc + e + half);
-          if (qk_norm) {   // the key's half/2 threads: one aligned group of lanes at the top of the workgroup
-            const float ss = lane_group_sum<(int)(half / 2)>(lo.x * lo.x + lo.y * lo.y + hi.x * hi.x + hi.y * hi.y);
-            const float inv = 1.0f / sqrtf(ss / (float)d + t.f0);
-            const uint16_t* gk = (const uint16_t*)t.w2;
-            const uint32_t g0 = *as_global((const uint32_t*)(gk + e)), g1 = *as_global((const uint32_t*)(gk + e + half));
-            lo.x *= inv * bf16_lo(g0); lo.y *= inv * bf16_hi(g0);
-            hi.x *= inv * bf16_lo(g1); hi.y *= inv * bf16_hi(g1);
-          }
-          const float c0 = pre_c0, s0 = pre_s0, c1 = pre_c1, s1 = pre_s1;   // (i < half / 2 <= kThreads: the first pass)
-          float r0 = lo.x * c0 - hi.x * s0, r1 = lo.y * c1 - hi.y * s1;
-          float r2 = hi.x * c0 + lo.x * s0, r3 = hi.y * c1 + lo.y * s1;
-          st_act_u32((uint32_t*)(krow + e), (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16));
-          st_act_u32((uint32_t*)(krow + e + half), (uint32_t)f32_to_bf16(r2) | ((uint32_t)f32_to_bf16(r3) << 16));
-        } else {              // two adjacent value elements
-          uint32_t e = 2 * (i - half / 2);
-          float2 v2 = ld_act2(vsrc + e);
-          st_act_u32((uint32_t*)(vrow + e), (uint32_t)f32_to_bf16(v2.x) | ((uint32_t)f32_to_bf16(v2.y) << 16));
-        }
-      }
-      // the appended row is read back below with coherent loads: the stores must have completed
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
-  } else {
-    for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) qs[i] = ld_act(qsrc + i);
-  }
-  __syncthreads();
-  trace_mark(a, t, 2);
-  // The row appended during this step is read with coherent loads (it was written after the
-  // pre-load, by this or another workgroup); it can only be the last position of the last chunk.
-  if (c == C - 1) {
-    const uint32_t i_new = n - 1;
-#pragma unroll
-    for (int r = 0; r < kAttnRounds; ++r) {
-      if (i_first + r * stride == i_new) {
-        const size_t off = row_off(i_new);
-        kreg[r] = ld_row16_coherent(Kb + off + sub * 8);
-        vreg[r] = ld_row16_coherent(Vb + off + sub * 8);
-      }
-    }
-  }
-  // ---- per block of HB heads (bounds the register footprint): scores, softmax statistics and
-  // P.V, all in registers; sreg[r][j] belongs to position i_first + r * stride, head jb + j
-  constexpr int HB = GRP < 4 ? GRP : 4;
-  const float inv_sqrt_d = 1.0f / sqrtf((float)d);
-  // The body is bound by vector instructions, not by memory (two wavefronts per SIMD, about a
-  // thousand instructions each for a full chunk): rounds the chunk does not reach are skipped.
-  // The count is the same in every lane (it comes from positions[b]); say so to the compiler.
-  const uint32_t n_rounds_u = __builtin_amdgcn_readfirstlane(n_rounds);
-  float* mxch = wpart + stride * grp * WS + 16;   // [NW][HB] maxima exchange
-  // scores are kept times log2(e): the probabilities are then one v_exp_f32 each
-  const float score_scale = inv_sqrt_d * 1.44269504088896341f;
-  float m_all[GRP];
-#pragma unroll 1
-  for (int jb = 0; jb < GRP; jb += HB) {
-    float q[HB][8];
-#pragma unroll
-    for (int j = 0; j < HB; ++j) {
-      const float4* qp = (const float4*)(qs + (jb + j) * d + sub * 8);
-      float4 q0 = qp[0], q1 = qp[1];
-      q[j][0] = q0.x; q[j][1] = q0.y; q[j][2] = q0.z; q[j][3] = q0.w;
-      q[j][4] = q1.x; q[j][5] = q1.y; q[j][6] = q1.z; q[j][7] = q1.w;
-    }
-    float sreg[kAttnRounds][HB];
-    float mloc[HB];
-#pragma unroll
-    for (int j = 0; j < HB; ++j) mloc[j] = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < kAttnRounds; ++r) {
-      if ((uint32_t)r >= n_rounds_u) continue;   // (uniform) rounds past the chunk: nothing to do
-      const bool valid = i_first + r * stride < n;
-      const u32x4 kv = kreg[r];
-      const float k8[8] = {bf16_lo(kv.x), bf16_hi(kv.x), bf16_lo(kv.y), bf16_hi(kv.y),
-                           bf16_lo(kv.z), bf16_hi(kv.z), bf16_lo(kv.w), bf16_hi(kv.w)};
-#pragma unroll
-      for (int j = 0; j < HB; ++j) {
-        float sv = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sv = fmaf(k8[e], q[j][e], sv);
-        sv = group_sum<LPP>(sv) * score_scale;
-        sreg[r][j] = valid ? sv : -INFINITY;
-        mloc[j] = fmaxf(mloc[j], sreg[r][j]);
-      }
-    }
-    // chunk maximum per head: across position slots, then across wavefronts
-#pragma unroll
-    for (int j = 0; j < HB; ++j) {
-#pragma unroll
-      for (uint32_t off = LPP; off < 64; off <<= 1) mloc[j] = fmaxf(mloc[j], __shfl_xor(mloc[j], off, 64));
-      if (lane == 0) mxch[wave * HB + j] = mloc[j];
-    }
-    __syncthreads();
-    float m[HB];
-#pragma unroll
-    for (int j = 0; j < HB; ++j) {
-      float v = mxch[j];
-#pragma unroll
-      for (uint32_t w = 1; w < NW; ++w) v = fmaxf(v, mxch[w * HB + j]);
-      m[j] = v;
-      m_all[jb + j] = v * 0.693147180559945309f;   // the partial's maximum is stored in natural units
-    }
-    // ---- probabilities and P.V
-    float acc[HB][8], lsum[HB];
-#pragma unroll
-    for (int j = 0; j < HB; ++j) {
-      lsum[j] = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[j][e] = 0.f;
-    }
-#pragma unroll
-    for (int r = 0; r < kAttnRounds; ++r) {
-      if ((uint32_t)r >= n_rounds_u) continue;
-      const u32x4 vv = vreg[r];
-      const float v8[8] = {bf16_lo(vv.x), bf16_hi(vv.x), bf16_lo(vv.y), bf16_hi(vv.y),
-                           bf16_lo(vv.z), bf16_hi(vv.z), bf16_lo(vv.w), bf16_hi(vv.w)};
-#pragma unroll
-      for (int j = 0; j < HB; ++j) {
-        const float p = (sreg[r][j] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(sreg[r][j] - m[j]);
-        lsum[j] += p;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[j][e] = fmaf(p, v8[e], acc[j][e]);
-      }
-    }
-    // every position slot's partial goes to LDS as it is (two 16-byte stores per head); the
-    // slots are added up below, by the threads that write the result.  (Adding them with lane
-    // shuffles first cost 4 instructions per value here, where instructions are what is scarce.)
-#pragma unroll
-    for (int j = 0; j < HB; ++j) {
-      float4* wp = (float4*)(wpart + ((size_t)(wave * PPW + slot) * grp + jb + j) * WS + sub * 8);
-      wp[0] = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
-      wp[1] = make_float4(acc[j][4], acc[j][5], acc[j][6], acc[j][7]);
-      // every lane of a position group holds the same p: one of them stores the sum
-      if (sub == 0) wpart[((size_t)(wave * PPW + slot) * grp + jb + j) * WS + d + 1] = lsum[j];
-    }
-    __syncthreads();   // also protects mxch before the next block
-  }
-  trace_mark(a, t, 10);
-  for (uint32_t i = threadIdx.x; i < grp * (d + 2); i += kThreads) {
-    const uint32_t j = i / (d + 2), dim = i % (d + 2);
-    float sv;
-    if (dim == d) {
-      sv = m_all[0];
-#pragma unroll
-      for (int jj = 1; jj < GRP; ++jj) sv = (j == (uint32_t)jj) ? m_all[jj] : sv;
-    } else {
-      sv = 0.f;
-#pragma unroll
-      for (uint32_t w = 0; w < stride; ++w) sv += wpart[((size_t)w * grp + j) * WS + dim];
-    }
-    st_act(outp + i, sv);
-  }
-  trace_mark(a, t, 11);
-  if (t.flags & TF_ATTN_MERGE) {
-    // Arrival counter of (layer, sequence, KV head): the chunk task that arrives last sees all C
-    // partials complete and merges them (log-sum-exp, one pass with running maximum) into the
-    // attention output.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t* cnt = a.g->grp_counters + t.p2 + b * nkv + g;
-      uint32_t old = __hip_atomic_fetch_add(as_global(cnt), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      *flag = ((old + 1u) % C == 0u) ? 1u : 0u;   // every step adds exactly C
-    }
-    __syncthreads();
-    if (*flag) {
-      const float* part = t.out + (size_t)b * t.ld_out + (size_t)g * C * per;
-      float* o = const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d;
-      for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) {
-        uint32_t j = i / d, dim = i % d;
-        float M = -INFINITY, L = 0.f, acc_o = 0.f;
-        for (uint32_t c0 = 0; c0 < C; c0 += 8) {   // 24 coherent loads in flight: one round trip for 8 chunks
-          float mm[8], ll[8], oo[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            if (c0 + k < C) {
-              const float* pp = part + ((size_t)(c0 + k) * grp + j) * (d + 2);
-              mm[k] = ld_act(pp + d);
-              ll[k] = ld_act(pp + d + 1);
-              oo[k] = ld_act(pp + dim);
-            } else {
-              mm[k] = -INFINITY; ll[k] = 0.f; oo[k] = 0.f;
-            }
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            float Mn = fmaxf(M, mm[k]);
-            if (Mn == -INFINITY) continue;   // empty chunks only so far
-            float sc_old = expf(M - Mn), sc_new = expf(mm[k] - Mn);
-            L = L * sc_old + ll[k] * sc_new;
-            acc_o = acc_o * sc_old + oo[k] * sc_new;
-            M = Mn;
-          }
-        }
-        st_act(o + i, acc_o / L);
-      }
-    }
-  }
-  return true;
+// First row of chunk c of C of a sequence of len rows.  (A 64-bit division is a hundred instructions;
+// up to kSmallSeq positions the product of a length and a task count (at most 16 x 64) fits 32 bits.)
+constexpr uint32_t kSmallSeq = 1u << 21;
+__device__ __forceinline__ uint32_t chunk_begin(const StepArgs& a, uint32_t c, uint32_t len, uint32_t C) {
+  return a.g->max_seq <= kSmallSeq ? c * len / C : (uint32_t)((uint64_t)c * len / C);
 }
 
 // TF_ATTN_BALANCE: the batch x C chunk tasks of a KV head, numbered v = row x C + chunk, are dealt
@@ -2132,28 +1788,31 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
     const int32_t pos = step_position<PAGED>(a, li);
     w = (pos >= 0 && (uint32_t)pos < a.g->max_seq) ? (uint32_t)pos + 1u : 1u;   // (a bad position is reported by its tasks)
   }
-  auto row_sum = [&](uint32_t x) {   // over the 16 lanes of the row, in every lane
-#pragma unroll
-    for (uint32_t off = 1; off < 16; off <<= 1) x += (uint32_t)__shfl_xor((int)x, off, 16);
-    return x;
+  // within a row of 16 lanes by DPP moves (a lane shuffle is an LDS round trip, and the loop below is a
+  // chain of them: at batch 16 the deal took 2.5 us ahead of the first row request)
+  auto dpp = [](uint32_t x, auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xF, 0xF, true); };
+  auto row_all = [&](uint32_t x, auto op) {   // op over the 16 lanes of the row, in every lane
+    x = op(x, dpp(x, std::integral_constant<int, 0xB1>{}));    // lane ^ 1
+    x = op(x, dpp(x, std::integral_constant<int, 0x4E>{}));    // lane ^ 2
+    x = op(x, dpp(x, std::integral_constant<int, 0x141>{}));   // mirror in 8
+    return op(x, dpp(x, std::integral_constant<int, 0x140>{}));   // mirror in 16
   };
-  const uint32_t total = row_sum(w);
-  uint32_t cnt = li < B ? 1u + (uint32_t)((uint64_t)(B * C - B) * w / total) : 0u;
-  const uint32_t left = B * C - row_sum(cnt);   // uniform, < B
+  auto add = [](uint32_t x, uint32_t y) { return x + y; };
+  const uint32_t total = row_all(w, add);
+  uint32_t cnt = 0;
+  if (li < B) cnt = 1u + (a.g->max_seq <= kSmallSeq ? (B * C - B) * w / total : (uint32_t)((uint64_t)(B * C - B) * w / total));
+  const uint32_t left = B * C - row_all(cnt, add);   // uniform, < B
   for (uint32_t r = 0; r < left; ++r) {
-    const float len = li < B ? (float)w / (float)cnt : -1.f;   // current chunk length of the sequence
-    float mx = len;
-#pragma unroll
-    for (uint32_t off = 1; off < 16; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 16));
+    const float len = li < B ? (float)w / (float)cnt : 0.f;   // current chunk length of the sequence (at least 1 / cnt)
+    const float mx = __uint_as_float(row_all(__float_as_uint(len), [](uint32_t x, uint32_t y) { return max(x, y); }));   // (no negative lengths)
     const uint32_t who = (uint32_t)__ballot(len == mx) & 0xFFFFu;   // (the wavefront's first 16 lanes)
     if (li == (uint32_t)__builtin_ctz(who)) ++cnt;
   }
   uint32_t end = cnt;   // inclusive prefix sum: first task after the sequence
-#pragma unroll
-  for (uint32_t off = 1; off < 16; off <<= 1) {
-    const uint32_t o = (uint32_t)__shfl_up((int)end, off, 16);
-    if (li >= off) end += o;
-  }
+  end += dpp(end, std::integral_constant<int, 0x111>{});   // row_shr 1, 2, 4, 8 (nothing comes in from the left)
+  end += dpp(end, std::integral_constant<int, 0x112>{});
+  end += dpp(end, std::integral_constant<int, 0x114>{});
+  end += dpp(end, std::integral_constant<int, 0x118>{});
   const uint32_t start = end - cnt;
   const uint32_t mask = (uint32_t)__ballot(li < B && start <= v) & 0xFFFFu;
   const uint32_t bsel = 31u - (uint32_t)__builtin_clz(mask);                  // start of sequence 0 is 0 <= v
@@ -2163,18 +1822,108 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
   *chunk = v - *first;
 }
 
+// ------------------------------------------------------------------------------ attention on the matrix cores
 // T4: split-KV decode attention for one (sequence, KV head, chunk).  Chunk c of C covers cache
 // rows [c*len/C, (c+1)*len/C) with len = position + 1, so the last chunk holds the new row.
-// Output per query head of the group: sum_t exp(s_t - m) V_t (D floats), m, l = sum_t exp(s_t - m).
-// Layout of the work: D/8 adjacent lanes share one position (16 bytes of the row each), a
-// wavefront covers 64/(D/8) positions per round, the wavefronts of the workgroup take rounds of
-// (wavefronts x that many) positions.  Every lane group keeps a running maximum, sum and output
-// per query head (online softmax), so a chunk may be of any length and no barrier is needed until
-// the end, where the lane groups of a wavefront are combined with lane shuffles and the
-// wavefronts through LDS.
+// Output per query head of the group, with the scores s times log2(e): sum_t 2^(s_t - m) V_t (D
+// floats), m, l = sum_t 2^(s_t - m).
+//
+// Work: a wavefront takes blocks of 32 cache rows (wavefront w: blocks w, w + 8, ...), independent
+// of the others until the partial results meet in LDS.  Per block
+//   scores  S[32 rows][16 columns] = K[32][D] x Q[D][16]       two 16-row tiles, D / 32 multiplies each
+//   p       = 2^(S - m), fp32, lane = (column, 4 rows of each tile)
+//   output  O[16 rows][D] += P[16][32] x V[32][D]               D / 16 multiplies
+// with v_mfma_f32_16x16x32_bf16.  Cache rows are bf16 as stored; queries and probabilities are
+// fp32 and enter as the exact sum of three bf16 terms (split_hi_mid_lo), so every product is exact
+// and the only rounding is the fp32 accumulation, as in vector arithmetic.  The 16 columns (rows of
+// P) hold the terms side by side: up to 4 query heads per KV head hi | mid | lo | 0 in four groups of
+// four (fewer heads repeat), one multiply; 8 heads hi | mid in two groups of eight and a second
+// multiply with lo | 0 into the same accumulators.  Adding the column groups (one or two DPP row
+// rotations) leaves every lane with the whole score of its head.
+//
+// Why: on the vector ALUs a row costs about 135 instructions per wavefront and 4 rows (16 lanes a
+// row, scores reduced over lanes, one exp per head and 16 lanes), 9 us of arithmetic alone for the
+// 660-row chunks of the 8B shape at batch 8; here 32 rows cost 16 (8 heads: 32) multiplies and
+// about 150 vector instructions, and the task streams.
+//
+// Operand layouts come without a shuffle through LDS:
+//   K (A operand, lane = row + 16 x input group): loaded as 8 rows x 128 bytes per instruction and put
+//     into operand order by one DPP move per register, see mfma_job_packed
+//   P (A operand, lane = (head, term) + 16 x row group): the lane that holds the scores of tile rows
+//     4 j .. 4 j + 3 of both tiles holds exactly 8 of the 32 inputs of the multiply; V follows that order
+//   V (B operand, lane = column + 16 x row group): a lane loads its 8 rows at D / 16 consecutive
+//     elements (whole rows per instruction) and transposes the 8 x (D / 16) block in its registers
+//     (v_perm_b32); tile t then covers output elements (D / 16) column + t
+//
+// K and V rows of a block are requested ahead: the first block's before the task's event, the next
+// K as soon as K has been multiplied, the next V likewise -- 8 to 16 KB in flight per wavefront
+// (D = 128).  The requests of a round carry no branch (rows past the chunk repeat its last row), the
+// loop's last round is peeled and requests nothing.
+//
+// The running maximum m is only raised when a score exceeds it by more than 2^16 (lazy rescaling:
+// sums and outputs are relative to m, so any m within the fp32 range gives the same digits).
+//
+// The row appended this step is not in the cache when rows are requested: the task of the last
+// chunk has it in registers (fused RoPE), keeps the stored (bf16) values in LDS and adds it as a
+// partial result of its own: m = its score, l = 1, output = the value row.
+constexpr float kLazyMax = 16.f;   // in powers of two
+
+template <int N>
+__device__ __forceinline__ float row_ror(float v) {   // value of the lane N further in its row of 16
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, true));
+}
+
+// Partial results of a task's sequence -> attention output, by the chunk task that arrives last:
+// log-sum-exp over the C partials ([grp][d + 2]: output, max, sum each).  They are in the slots of C
+// consecutive chunk tasks: rows of Cs slots, ld floats apart, from slot `slot` of the row at `row` on.
+// A thread owns two adjacent output elements; all loads of up to 16 partials are in flight together
+// (the loads are what this costs: 3.3 us for 16 partials when they went out 8 at a time, 2 dwords
+// a partial, with an exp chain between).
+template <int D, int GRP>
+__device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row, uint32_t slot, uint32_t Cs, uint32_t ld, float* o) {
+  constexpr uint32_t per = GRP * (D + 2);
+  constexpr int kAtOnce = 16;
+  for (uint32_t i = threadIdx.x; i < (uint32_t)(GRP * D / 2); i += kThreads) {
+    const uint32_t j = i / (D / 2), e = 2u * (i % (D / 2));
+    float M = -INFINITY, L = 0.f, ax = 0.f, ay = 0.f;
+    const float* part = row + (size_t)slot * per;
+    uint32_t sl = slot;
+    for (uint32_t c0 = 0; c0 < C; c0 += kAtOnce) {
+      float2 ml[kAtOnce], ov[kAtOnce];
+#pragma unroll
+      for (int k = 0; k < kAtOnce; ++k) {
+        ml[k] = make_float2(-INFINITY, 0.f);
+        ov[k] = make_float2(0.f, 0.f);
+        if (c0 + k < C) {
+          const float* pp = part + j * (D + 2);
+          ml[k] = ld_act2(pp + D);
+          ov[k] = ld_act2(pp + e);
+          part += per;
+          if (++sl == Cs) { sl = 0; part += ld - (size_t)Cs * per; }
+        }
+      }
+      float Mn = M;
+#pragma unroll
+      for (int k = 0; k < kAtOnce; ++k) Mn = fmaxf(Mn, ml[k].x);
+      if (Mn == -INFINITY) continue;   // empty chunks only so far
+      const float s0 = __builtin_amdgcn_exp2f(M - Mn);
+      L *= s0; ax *= s0; ay *= s0;
+#pragma unroll
+      for (int k = 0; k < kAtOnce; ++k) {
+        const float w = __builtin_amdgcn_exp2f(ml[k].x - Mn);   // 2^(-inf) = 0: empty
+        L = fmaf(w, ml[k].y, L);
+        ax = fmaf(w, ov[k].x, ax);
+        ay = fmaf(w, ov[k].y, ay);
+      }
+      M = Mn;
+    }
+    st_act2(o + 2u * i, ax / L, ay / L);
+  }
+}
+
 // Cache rows of earlier steps are immutable during a step, so the task requests its first
-// kAttnPre rounds of K and V rows BEFORE it waits for its dependent event; only the query (and the
-// row appended this step) arrive later.  Later rounds are requested a batch at a time.
+// blocks of K and V rows BEFORE it waits for its dependent event; only the query (and the row
+// appended this step) arrive later.
 // These early reads are plain non-temporal loads.  In a multi-token launch they include the row
 // another workgroup appended in the PREVIOUS step of the same launch; that is safe because (1) the
 // row was written with coherent stores that completed before its task notified, and this worker
@@ -2189,41 +1938,51 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
 // only once the serving task has run, so the task first waits for that task's event -- activated
 // at the very start of the step, long before the task's own event -- and only then deals the chunk
 // tasks, looks up its pages and requests its rows.  Table entries are read with coherent loads
-// (one per row and lane group; the lookups of a batch of rounds travel together).  An entry
+// (one per page of the chunk, all in flight together).  An entry
 // outside the pool is reported and replaced by page 0: no address ever leaves the pool.
-template <int D, int GRP, bool PAGED = false, int NB = 0>
-__device__ __forceinline__ bool body_attn_partial(const TaskDesc& t, const StepArgs& a, float* lds,
-                                                  int32_t wait_ev, uint32_t* s_flag) {
-  constexpr uint32_t d = D, grp = GRP, LPP = D / 8, PPW = 64 / LPP, NW = kThreads / 64;
-  constexpr uint32_t stride = NW * PPW, per = grp * (d + 2);
+template <int D, int GRP, bool PAGED>
+__device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev, uint32_t* s_flag) {
+  constexpr uint32_t d = D, grp = GRP, NW = kThreads / 64, per = grp * (d + 2);
+  constexpr bool TWO = GRP == 8;                       // the lo terms take a second multiply
+  constexpr uint32_t HG = TWO ? 8u : 4u;               // columns per term group
+  constexpr uint32_t NTERM = TWO ? 2u : 3u;            // partial outputs per wavefront and head
+  constexpr int KG = D / 64, NT = D / 16;              // 64-input groups of a score, output tiles
+  constexpr uint32_t BLK = 32, WS = d + 4;
+  using VVec = std::conditional_t<D == 128, u32x4, u32x2>;   // D / 16 elements of a value row
+  constexpr int VW = D / 32;                                 // ... in words
   const uint32_t nq = a.g->n_q, nkv = a.g->n_kv, Cs = t.p1;
   const uint32_t bs = t.b0, u = t.c0 / per, g = u / Cs;   // the task's own row: where its partial result goes
   if (PAGED && wait_ev >= 0 && a.g->serve_event >= 0 && !wait_event(a, a.g->serve_event, s_flag)) return false;
   // sequence, chunk and chunk count the task works on, first task of that sequence
   uint32_t b = bs, c = u % Cs, C = Cs, v0 = bs * Cs;
   if (t.flags & TF_ATTN_BALANCE) attn_deal<PAGED>(a, Cs, bs * Cs + c, &b, &c, &C, &v0);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float* qs = lds;                       // [grp][d]
-  float* wpart = qs + grp * d;           // [NW][grp][d + 2]: partial output, max, sum per wavefront
-  uint32_t* flag = (uint32_t*)(wpart + NW * grp * (d + 2));
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* qs = lds;                                   // [grp][d], times log2(e) / sqrt(d)
+  float* wpart = qs + grp * d;                       // [NW][NTERM][grp][WS]: partial outputs
+  float* ml = wpart + NW * NTERM * grp * WS;         // [NW][grp][2]: running maximum and sum
+  float* knew = ml + NW * grp * 2;                   // [d], [d]: the appended rows as stored; [8] their scores
+  float* vnew = knew + d;
+  float* snew = vnew + d;
+  uint32_t* flag = (uint32_t*)(snew + 8);
+  uint32_t* pgs = flag + 16;                         // paged: the chunk's page numbers
   float* outp = t.out + (size_t)bs * t.ld_out + t.c0;
   const int32_t pos = step_position<PAGED>(a, b);    // written by the host before the launch (or by the serving task)
   const bool bad_pos = pos < 0 || (uint32_t)pos >= a.g->max_seq;
   const uint32_t len = bad_pos ? 0u : (uint32_t)pos + 1;
-  const uint32_t t0 = (uint32_t)((uint64_t)c * len / C), t1 = (uint32_t)((uint64_t)(c + 1) * len / C);
-  const uint32_t n = t1 - t0;
+  const uint32_t t0 = chunk_begin(a, c, len, C), t1 = chunk_begin(a, c + 1u, len, C);
+  const bool has_new = !bad_pos && c == C - 1;       // the chunk ends with the row appended this step
+  const uint32_t n_old = __builtin_amdgcn_readfirstlane(t1 - t0 - (has_new ? 1u : 0u));   // rows of earlier steps
+  const uint32_t nblk = (n_old + BLK - 1u) / BLK;
   // contiguous cache: the chunk's first row; paged: the layer's pools
   const uint16_t* Kb = (const uint16_t*)t.aux0 + (PAGED ? (size_t)0 : (((size_t)b * nkv + g) * a.g->max_seq + t0) * d);
   const uint16_t* Vb = (const uint16_t*)t.aux1 + (PAGED ? (size_t)0 : (((size_t)b * nkv + g) * a.g->max_seq + t0) * d);
-  // paged: the page numbers of the chunk's rows go to LDS first (one coherent load per page, all in
-  // flight together), so that a row's address costs an LDS read, not a trip to memory
   const uint32_t pshift = PAGED ? a.g->page_shift : 0u;
   const uint32_t pg0 = t0 >> pshift;
-  uint32_t* pgs = flag + 16;
   bool bad_page = false;
-  if constexpr (PAGED) {
+  if constexpr (PAGED) {   // one coherent load per page, all in flight together: a row's address is then an LDS read
     const uint32_t* ptab = (const uint32_t*)a.g->page_table + (size_t)b * (a.g->max_seq >> pshift);
-    const uint32_t npg = n ? ((t1 - 1u) >> pshift) - pg0 + 1u : 0u;
+    const uint32_t npg = t1 > t0 ? ((t1 - 1u) >> pshift) - pg0 + 1u : 0u;
     for (uint32_t i = threadIdx.x; i < npg; i += kThreads) {
       uint32_t pg = ld_relaxed(ptab + pg0 + i);
       if (pg >= a.g->kv_pages) { bad_page = true; pg = 0; }
@@ -2232,7 +1991,7 @@ __device__ __forceinline__ bool body_attn_partial(const TaskDesc& t, const StepA
     __syncthreads();
   }
   // element offset of row i of the chunk (row t0 + i of the sequence) from Kb / Vb
-  auto row_off = [&](uint32_t i) -> size_t {
+  auto row_off = [&](uint32_t i) {
     if constexpr (PAGED) {
       const uint32_t r = t0 + i;
       return ((((size_t)pgs[(r >> pshift) - pg0] * nkv + g) << pshift) + (r & ((1u << pshift) - 1u))) * d;
@@ -2240,81 +1999,59 @@ __device__ __forceinline__ bool body_attn_partial(const TaskDesc& t, const StepA
       return (size_t)i * d;
     }
   };
-  const uint32_t sub = lane % LPP, slot = lane / LPP;
-  const uint32_t i_first = wave * PPW + slot;
-  const uint32_t n_rounds = (n + stride - 1) / stride;
-  constexpr int kAttnPre = attn_depth(NB, GRP);   // rounds held in registers at a time
-  constexpr bool STREAM = attn_streams(NB);         // which of the two request schedules below
-  // the row appended this step, if in this chunk: it is written after the early reads (by this or
-  // another workgroup), so it is never among them and is fetched with coherent loads when its turn
-  // comes (STREAM: after all the rounds)
-  const uint32_t i_new = (!bad_pos && c == C - 1) ? n - 1 : 0xFFFFFFFFu;
-  // ---- STREAM: K and V rows of round `rnd` into register pair r.  Always two loads, no branch around
-  // them: the compiler counts the loads in flight statically, and a load that may or may not have
-  // been issued makes every later wait a wait for everything.  A position the chunk does not have
-  // (or the appended row) reads the chunk's last row of an earlier step again -- this compute
-  // unit's own line, already on its way or cached -- and nobody uses the result; a chunk with no
-  // such row reads 16 bytes of the task array (immutable).
-  u32x4 kreg[kAttnPre], vreg[kAttnPre];
-  const uint16_t* nothing = (const uint16_t*)a.tasks;
-  const uint32_t n_old = n - (i_new != 0xFFFFFFFFu ? 1u : 0u);   // rows of earlier steps in the chunk
-  // (`coherent`: which kind of load a paged cache needs in this launch, see ld_cache_row -- a
-  // compile-time choice here, made once per task by the callers: a branch around the load would
-  // spoil the count just the same)
-  auto request_round = [&](auto coherent, int r, uint32_t rnd) {
-    const uint32_t i = min(i_first + rnd * stride, n_old - 1u);
-    const bool ok = n_old != 0u;
-    const size_t off = ok ? row_off(i) + sub * 8 : (size_t)0;
-    const uint16_t *kp = ok ? Kb + off : nothing, *vp = ok ? Vb + off : nothing;
-    kreg[r] = decltype(coherent)::value ? ld_row16_coherent(kp) : ld_stream16(kp);
-    vreg[r] = decltype(coherent)::value ? ld_row16_coherent(vp) : ld_stream16(vp);
-  };
-  const bool coherent_rows = PAGED && !(a.flags & kOneStepBit);
-  // ---- pre-load: the first rounds (never the row appended this step)
-  auto load_rows = [&]() {
-    if constexpr (STREAM) {
-      if (coherent_rows) {
+  const uint32_t col = lane & 15u, jg = (uint32_t)lane >> 4;   // column / row of an operand, its input group
+  u32x4 kreg[2][KG][2];   // [tile][64-input group][rows 0..7 / 8..15]
+  VVec vreg[8];           // [row slot]
+  // `coherent`: a paged cache in a launch of several steps is read with agent-scope loads (a page may
+  // have changed owners within the launch) -- a compile-time choice, made once per task by the callers
+  auto request_k = [&](auto coherent, uint32_t blk) {
 #pragma unroll
-        for (int r = 0; r < kAttnPre; ++r) request_round(std::true_type{}, r, (uint32_t)r);
-      } else {
+    for (int T = 0; T < 2; ++T)
 #pragma unroll
-        for (int r = 0; r < kAttnPre; ++r) request_round(std::false_type{}, r, (uint32_t)r);
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t i = min(blk * BLK + 16u * T + 8u * h + (lane & 7u), n_old - 1u);
+        const uint16_t* p = Kb + row_off(i) + 8u * ((uint32_t)lane >> 3);
+#pragma unroll
+        for (int q = 0; q < KG; ++q) kreg[T][q][h] = decltype(coherent)::value ? ld_row16_coherent(p + 64 * q) : ld_stream16(p + 64 * q);
       }
-    } else {
+  };
+  auto request_v = [&](auto coherent, uint32_t blk) {
 #pragma unroll
-      for (int r = 0; r < kAttnPre; ++r) {
-        const uint32_t i = i_first + r * stride;
-        kreg[r] = u32x4{0, 0, 0, 0};
-        vreg[r] = u32x4{0, 0, 0, 0};
-        if (i < n && i != i_new) {
-          const size_t off = row_off(i);
-          kreg[r] = ld_cache_row<PAGED>(a, Kb + off + sub * 8);
-          vreg[r] = ld_cache_row<PAGED>(a, Vb + off + sub * 8);
+    for (int s = 0; s < 8; ++s) {
+      const uint32_t i = min(blk * BLK + 16u * (s >> 2) + 4u * jg + (s & 3), n_old - 1u);
+      const uint16_t* p = Vb + row_off(i) + (uint32_t)NT * col;
+      if constexpr (D == 128) {
+        vreg[s] = decltype(coherent)::value ? ld_row16_coherent(p) : ld_stream16(p);
+      } else {
+        if (decltype(coherent)::value) {
+          const uint64_t w = __hip_atomic_load(as_global((const uint64_t*)p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          vreg[s] = u32x2{(uint32_t)w, (uint32_t)(w >> 32)};
+        } else {
+          vreg[s] = __builtin_nontemporal_load(as_global((const u32x2*)p));
         }
       }
     }
   };
+  const bool coherent_rows = PAGED && !(a.flags & kOneStepBit);
+  const bool mine = wave < nblk;   // (uniform) this wavefront has blocks
+  auto first_rows = [&]() {
+    if (!mine) return;
+    if (coherent_rows) { request_k(std::true_type{}, wave); request_v(std::true_type{}, wave); }
+    else { request_k(std::false_type{}, wave); request_v(std::false_type{}, wave); }
+  };
   const bool preload = !(a.flags & kNoPreloadBit);
+  // A wavefront's loads complete in the order they were issued: a poll behind the row requests
+  // returns behind the rows.  So the first look at the event goes out ahead of them.
+  EventProbe probe{};
+  if (wait_ev >= 0 && wave == 0) probe = probe_event(a, wait_ev, lane);
   if (preload) {
-    load_rows();
+    first_rows();
     asm volatile("; cache rows requested" ::: "memory");
   }
-  // the rotation angles depend on the position alone: worked out (in double precision) before the
-  // event, off the critical path from the QKV projection to the O projection.  A thread's first
-  // query element, and the two key pairs of the threads that append the new row.
-  float pre_cs = 1.f, pre_sn = 0.f, pre_c0 = 1.f, pre_s0 = 0.f, pre_c1 = 1.f, pre_s1 = 0.f;
-  if (t.flags & TF_ROPE_FUSED) {
-    if (threadIdx.x < grp * (d / 2)) rope_cs(a, pos, threadIdx.x % (d / 2), &pre_cs, &pre_sn);
-    const uint32_t ik = kThreads - 1 - threadIdx.x;
-    if (c == C - 1 && ik < d / 4) {
-      rope_cs(a, pos, 2 * ik, &pre_c0, &pre_s0);
-      rope_cs(a, pos, 2 * ik + 1, &pre_c1, &pre_s1);
-    }
-  }
-  if (wait_ev >= 0 && !wait_event(a, wait_ev, s_flag)) return false;
+  if (wait_ev >= 0 && !wait_event(a, wait_ev, s_flag, probe)) return false;
   trace_mark(a, t, 1);
   if (!preload) {
-    load_rows();
+    first_rows();
     asm volatile("; cache rows requested after the event" ::: "memory");
   }
   if (bad_pos) {
@@ -2322,43 +2059,48 @@ __device__ __forceinline__ bool body_attn_partial(const TaskDesc& t, const StepA
     for (uint32_t i = threadIdx.x; i < per; i += kThreads) st_act(outp + i, ((i % (d + 2)) == d) ? -INFINITY : 0.f);
     return true;
   }
+  // scores are kept times log2(e), folded into the query: a probability is one v_exp_f32
+  const float q_scale = 1.44269504088896341f / sqrtf((float)d);
   const float* qsrc = t.in + (size_t)b * t.ld_in + (size_t)g * grp * d;
+  uint16_t *krow = nullptr, *vrow = nullptr;   // the appended row in the cache
+  if (has_new) {
+    if constexpr (PAGED) {
+      const size_t off = row_off((uint32_t)pos - t0);
+      krow = const_cast<uint16_t*>(Kb) + off;
+      vrow = const_cast<uint16_t*>(Vb) + off;
+    } else {
+      krow = (uint16_t*)t.aux0 + (((size_t)b * nkv + g) * a.g->max_seq + (uint32_t)pos) * d;
+      vrow = (uint16_t*)t.aux1 + (((size_t)b * nkv + g) * a.g->max_seq + (uint32_t)pos) * d;
+    }
+  }
   if (t.flags & TF_ROPE_FUSED) {
     // the input is the raw QKV projection: rotate the group's query heads here; the task of the
     // last chunk also rotates this step's key, and appends key and value to the cache
     constexpr uint32_t half = d / 2;
+    const float* angles = a.g->rope_tab + (size_t)b * d;   // of this step, from the embedding tasks
     const bool qk_norm = t.flags & TF_QK_NORM;
     for (uint32_t i = threadIdx.x; i < grp * half; i += kThreads) {
       uint32_t j = i / half, e = i % half;
-      float u0 = ld_act(qsrc + j * d + e), u1 = ld_act(qsrc + j * d + e + half), cs, sn;
+      float u0 = ld_act(qsrc + j * d + e), u1 = ld_act(qsrc + j * d + e + half);
+      const float2 r = ld_act2(angles + 2u * e);   // (cos, sin)
       if (qk_norm) {   // RMSNorm over the head: its `half` threads are one aligned group of lanes
         const float inv = 1.0f / sqrtf(lane_group_sum<(int)half>(u0 * u0 + u1 * u1) / (float)d + t.f0);
         const uint16_t* gq = (const uint16_t*)t.w;
         u0 *= inv * bf16_to_f32(as_global(gq)[e]);
         u1 *= inv * bf16_to_f32(as_global(gq)[e + half]);
       }
-      if (i < kThreads) { cs = pre_cs; sn = pre_sn; }
-      else rope_cs(a, pos, e, &cs, &sn);
-      qs[j * d + e] = u0 * cs - u1 * sn;
-      qs[j * d + e + half] = u1 * cs + u0 * sn;
+      qs[j * d + e] = (u0 * r.x - u1 * r.y) * q_scale;
+      qs[j * d + e + half] = (u1 * r.x + u0 * r.y) * q_scale;
     }
-    if (c == C - 1) {
+    if (has_new) {
       const float* ksrc = t.in + (size_t)b * t.ld_in + (size_t)(nq + g) * d;
       const float* vsrc = t.in + (size_t)b * t.ld_in + (size_t)(nq + nkv + g) * d;
-      uint16_t *krow, *vrow;
-      if constexpr (PAGED) {
-        const size_t off = row_off((uint32_t)pos - t0);
-        krow = const_cast<uint16_t*>(Kb) + off;
-        vrow = const_cast<uint16_t*>(Vb) + off;
-      } else {
-        krow = (uint16_t*)t.aux0 + (((size_t)b * nkv + g) * a.g->max_seq + (uint32_t)pos) * d;
-        vrow = (uint16_t*)t.aux1 + (((size_t)b * nkv + g) * a.g->max_seq + (uint32_t)pos) * d;
-      }
       // threads from the top of the workgroup, so that they do not also rotate query pairs
       for (uint32_t i = kThreads - 1 - threadIdx.x; i < half / 2 + half; i += kThreads) {
         if (i < half / 2) {   // two adjacent rotation pairs of the key
           uint32_t e = 2 * i;
           float2 lo = ld_act2(ksrc + e), hi = ld_act2(ksrc + e + half);
+          const float2 r0 = ld_act2(angles + 2u * e), r1 = ld_act2(angles + 2u * e + 2u);
           if (qk_norm) {   // the key's half/2 threads: one aligned group of lanes at the top of the workgroup
             const float ss = lane_group_sum<(int)(half / 2)>(lo.x * lo.x + lo.y * lo.y + hi.x * hi.x + hi.y * hi.y);
             const float inv = 1.0f / sqrtf(ss / (float)d + t.f0);
@@ -2367,179 +2109,211 @@ __device__ __forceinline__ bool body_attn_partial(const TaskDesc& t, const StepA
             lo.x *= inv * bf16_lo(g0); lo.y *= inv * bf16_hi(g0);
             hi.x *= inv * bf16_lo(g1); hi.y *= inv * bf16_hi(g1);
           }
-          const float c0 = pre_c0, s0 = pre_s0, c1 = pre_c1, s1 = pre_s1;   // (i < half / 2 <= kThreads: the first pass)
-          float r0 = lo.x * c0 - hi.x * s0, r1 = lo.y * c1 - hi.y * s1;
-          float r2 = hi.x * c0 + lo.x * s0, r3 = hi.y * c1 + lo.y * s1;
-          st_act_u32((uint32_t*)(krow + e), (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16));
-          st_act_u32((uint32_t*)(krow + e + half), (uint32_t)f32_to_bf16(r2) | ((uint32_t)f32_to_bf16(r3) << 16));
+          const uint32_t w0 = (uint32_t)f32_to_bf16(lo.x * r0.x - hi.x * r0.y) | ((uint32_t)f32_to_bf16(lo.y * r1.x - hi.y * r1.y) << 16);
+          const uint32_t w1 = (uint32_t)f32_to_bf16(hi.x * r0.x + lo.x * r0.y) | ((uint32_t)f32_to_bf16(hi.y * r1.x + lo.y * r1.y) << 16);
+          st_act_u32((uint32_t*)(krow + e), w0);
+          st_act_u32((uint32_t*)(krow + e + half), w1);
+          *(float2*)(knew + e) = make_float2(bf16_lo(w0), bf16_hi(w0));   // as stored
+          *(float2*)(knew + e + half) = make_float2(bf16_lo(w1), bf16_hi(w1));
         } else {              // two adjacent value elements
           uint32_t e = 2 * (i - half / 2);
-          float2 v2 = ld_act2(vsrc + e);
-          st_act_u32((uint32_t*)(vrow + e), (uint32_t)f32_to_bf16(v2.x) | ((uint32_t)f32_to_bf16(v2.y) << 16));
+          const float2 v2 = ld_act2(vsrc + e);
+          const uint32_t w = (uint32_t)f32_to_bf16(v2.x) | ((uint32_t)f32_to_bf16(v2.y) << 16);
+          st_act_u32((uint32_t*)(vrow + e), w);
+          *(float2*)(vnew + e) = make_float2(bf16_lo(w), bf16_hi(w));
         }
       }
-      // the appended row is read back below with coherent loads: the stores must have completed
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
   } else {
-    for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) qs[i] = ld_act(qsrc + i);
+    for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) qs[i] = ld_act(qsrc + i) * q_scale;
+    if (has_new && threadIdx.x < d) {   // appended by the RoPE operator's task: coherent loads, two elements a thread
+      const uint16_t* row = threadIdx.x < d / 2 ? krow : vrow;
+      const uint32_t e = 2u * (threadIdx.x % (d / 2)), w = ld_relaxed((const uint32_t*)(row + e));
+      *(float2*)((threadIdx.x < d / 2 ? knew : vnew) + e) = make_float2(bf16_lo(w), bf16_hi(w));
+    }
   }
   __syncthreads();
   trace_mark(a, t, 2);
-  // ---- running softmax per lane group and query head.  Scores and maxima are kept times
-  // log2(e), folded into the query, so that every probability and rescale is one v_exp_f32 (the
-  // body is bound by vector instructions at 4 and 8 query heads per KV head).
-  const float inv_sqrt_d = 1.44269504088896341f / sqrtf((float)d);
-  float q[GRP][8], m[GRP], l[GRP], acc[GRP][8];
+  if (has_new && wave < grp) {   // score of the appended row for head `wave`
+    float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < GRP; ++j) {
-    const float4* qp = (const float4*)(qs + j * d + sub * 8);
-    const float4 q0 = qp[0], q1 = qp[1];
-    q[j][0] = q0.x * inv_sqrt_d; q[j][1] = q0.y * inv_sqrt_d; q[j][2] = q0.z * inv_sqrt_d; q[j][3] = q0.w * inv_sqrt_d;
-    q[j][4] = q1.x * inv_sqrt_d; q[j][5] = q1.y * inv_sqrt_d; q[j][6] = q1.z * inv_sqrt_d; q[j][7] = q1.w * inv_sqrt_d;
-    m[j] = -INFINITY;
-    l[j] = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[j][e] = 0.f;
+    for (uint32_t e = lane; e < d; e += 64) s = fmaf(qs[wave * d + e], knew[e], s);
+    s = wave_sum_dpp(s);
+    if (lane == 0) snew[wave] = s;
   }
-  // one position per lane group: score, running maximum, probability, P.V
-  auto consume = [&](const float (&k8)[8], const float (&v8)[8], bool valid) {
+  if (mine) {
+    // ---- query operand: lane = column (term group, head) + 16 x input group, see above
+    const uint32_t tg = col / HG, hd = (col % HG) % grp;
+    u32x4 qop[KG][2], qlo[TWO ? KG : 1][2];   // (qlo: the second multiply of 8 heads)
 #pragma unroll
-    for (int j = 0; j < GRP; ++j) {
-      float sv = 0.f;
+    for (int q = 0; q < KG; ++q)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) sv = fmaf(k8[e], q[j][e], sv);
-      sv = group_sum<LPP>(sv);
-      if (valid) {
-        if (sv > m[j]) {   // a new maximum (rare after the first positions): rescale the running state
-          const float sc = __builtin_amdgcn_exp2f(m[j] - sv);   // 2^(-inf) = 0 on the first position
-          l[j] *= sc;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[j][e] *= sc;
-          m[j] = sv;
-        }
-        const float p = __builtin_amdgcn_exp2f(sv - m[j]);
-        l[j] += p;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[j][e] = fmaf(p, v8[e], acc[j][e]);
-      }
-    }
-  };
-  if constexpr (STREAM) {
-    // Long chunks, every worker streaming: kAttnPre rounds live in registers; a pair is requested
-    // again, kAttnPre rounds ahead, as soon as it has been used, so that all but one of them are
-    // in flight while one is multiplied.
-    auto rounds = [&](auto coherent) {
-      for (uint32_t r0 = 0; r0 < n_rounds; r0 += kAttnPre) {
-#pragma unroll
-        for (int r = 0; r < kAttnPre; ++r) {
-          const uint32_t i = i_first + (r0 + r) * stride;
-          float k8[8], v8[8];
-          unpack8(kreg[r], k8);
-          unpack8(vreg[r], v8);
-          request_round(coherent, r, r0 + r + kAttnPre);   // (behind the unpacking: the pair's registers are free)
-          consume(k8, v8, i < n && i != i_new);
+      for (int U = 0; U < 2; ++U) {
+        const float* src = qs + hd * d + 64 * q + 8u * (2u * jg + U);
+        u32x4 h, m, l;
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        split8(*(const float4*)src, *(const float4*)(src + 4), &h, &m, &l);
+        if constexpr (TWO) {
+          qop[q][U] = select4(tg == 0u, h, m);
+          qlo[q][U] = select4(tg == 0u, l, zero);
+        } else {
+          qop[q][U] = select4(tg == 0u, h, select4(tg == 1u, m, select4(tg == 2u, l, zero)));
         }
       }
-    };
-    if (coherent_rows) rounds(std::true_type{});
-    else rounds(std::false_type{});
-    if (i_new != 0xFFFFFFFFu) {   // (uniform) the appended row: the lane group its position falls to
-      const size_t off = row_off(i_new) + sub * 8;
-      float k8[8], v8[8];
-      unpack8(ld_row16_coherent(Kb + off), k8);
-      unpack8(ld_row16_coherent(Vb + off), v8);
-      consume(k8, v8, i_new % stride == i_first);
-    }
-  } else {
-    // Short chunks (a few rounds, most often all of them requested before the event): a batch of
-    // rounds lives in registers; its first half is requested again (for the next batch) as soon
-    // as it has been used, the second half at the end of the batch, and only when the chunk goes
-    // on -- a chunk that fits the registers issues no further request at all.
-    constexpr int kHalf = kAttnPre / 2;
-    auto request_next = [&](uint32_t r0, auto first_half) {
-      constexpr int lo = decltype(first_half)::value ? 0 : kHalf, hi = decltype(first_half)::value ? kHalf : kAttnPre;
-      if (r0 + kAttnPre < n_rounds) {
+    float m = -INFINITY, lsum = 0.f;   // of head hd (the same in every lane of the head; lsum: this lane's rows)
+    f32x4 O[NT];
 #pragma unroll
-        for (int r = lo; r < hi; ++r) {
-          const uint32_t i = i_first + (r0 + kAttnPre + r) * stride;
-          if (i < n && i != i_new) {
-            const size_t off = row_off(i);
-            kreg[r] = ld_cache_row<PAGED>(a, Kb + off + sub * 8);
-            vreg[r] = ld_cache_row<PAGED>(a, Vb + off + sub * 8);
+    for (int k = 0; k < NT; ++k) O[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto block = [&](auto coherent, auto more, uint32_t blk) {
+      // ---- scores
+      f32x4 S[2];
+#pragma unroll
+      for (int T = 0; T < 2; ++T) {
+        S[T] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < KG; ++q) {
+          pair_to_operands(kreg[T][q][0], kreg[T][q][1]);
+#pragma unroll
+          for (int U = 0; U < 2; ++U) {
+            const bf16x8 kv = __builtin_bit_cast(bf16x8, kreg[T][q][U]);
+            S[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qop[q][U]), S[T], 0, 0, 0);
+            if constexpr (TWO) S[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qlo[q][U]), S[T], 0, 0, 0);
           }
         }
       }
-    };
-    for (uint32_t r0 = 0; r0 < n_rounds; r0 += kAttnPre) {
+      if (decltype(more)::value) request_k(coherent, blk + NW);
+      float s[8];
 #pragma unroll
-      for (int r = 0; r < kAttnPre; ++r) {
-        if (r == kHalf) request_next(r0, std::true_type{});
-        const uint32_t i = i_first + (r0 + r) * stride;
-        if (i == i_new) {
-          // written after the pre-load, by this or another workgroup: coherent loads
-          const size_t off = row_off(i);
-          kreg[r] = ld_row16_coherent(Kb + off + sub * 8);
-          vreg[r] = ld_row16_coherent(Vb + off + sub * 8);
-        }
-        float k8[8], v8[8];
-        unpack8(kreg[r], k8);
-        unpack8(vreg[r], v8);
-        consume(k8, v8, i < n);
+      for (int k = 0; k < 8; ++k) {
+        float v = S[k >> 2][k & 3];
+        v += row_ror<8>(v);
+        if constexpr (!TWO) v += row_ror<4>(v);
+        s[k] = v;
       }
-      request_next(r0, std::false_type{});
+      if ((blk + 1u) * BLK > n_old) {   // (uniform) the chunk's last, partial block
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (blk * BLK + 16u * (k >> 2) + 4u * jg + (k & 3) >= n_old) s[k] = -INFINITY;
+      }
+      float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+      if (__any(mx > m + kLazyMax)) {   // a new maximum: the first block, and seldom after it
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float mn = fmaxf(m, mx);
+        const float sc = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - mn);   // 2^(-inf) = 0 on the first block
+        m = mn;
+        lsum *= sc;
+        // output row 4 jg + r belongs to head (4 jg + r) % HG: its factor sits in lane (head)
+        float so[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float f0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), r));
+          const float f1 = TWO ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), 4 + r)) : f0;
+          so[r] = (jg & 1u) ? f1 : f0;
+        }
+#pragma unroll
+        for (int k = 0; k < NT; ++k)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) O[k][r] *= so[r];
+      }
+      // ---- probabilities, as the A operand of the second product
+      float p[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        p[k] = __builtin_amdgcn_exp2f(s[k] - m);
+        lsum += p[k];
+      }
+      u32x4 ph, pm, pl, pop, plo;
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      split8(make_float4(p[0], p[1], p[2], p[3]), make_float4(p[4], p[5], p[6], p[7]), &ph, &pm, &pl);
+      if constexpr (TWO) {
+        pop = select4(tg == 0u, ph, pm);
+        plo = select4(tg == 0u, pl, zero);
+      } else {
+        pop = select4(tg == 0u, ph, select4(tg == 1u, pm, select4(tg == 2u, pl, zero)));
+      }
+      // ---- outputs: tile k = elements NT col + k of the value rows
+#pragma unroll
+      for (int w = 0; w < VW; ++w)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const uint32_t sel = hf ? 0x07060302u : 0x05040100u;   // upper / lower halves of two rows' words
+          u32x4 vo;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) vo[k] = __builtin_amdgcn_perm(vreg[2 * k + 1][w], vreg[2 * k][w], sel);
+          const bf16x8 vv = __builtin_bit_cast(bf16x8, vo);
+          O[2 * w + hf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pop), vv, O[2 * w + hf], 0, 0, 0);
+          if constexpr (TWO) O[2 * w + hf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, plo), vv, O[2 * w + hf], 0, 0, 0);
+        }
+      if (decltype(more)::value) request_v(coherent, blk + NW);
+    };
+    auto blocks = [&](auto coherent) {
+      uint32_t blk = wave;
+      for (; blk + NW < nblk; blk += NW) block(coherent, std::true_type{}, blk);
+      block(coherent, std::false_type{}, blk);
+    };
+    if (coherent_rows) blocks(std::true_type{});
+    else blocks(std::false_type{});
+    // ---- the wavefront's partial results to LDS
+    lsum += __shfl_xor(lsum, 16, 64);
+    lsum += __shfl_xor(lsum, 32, 64);
+    if ((uint32_t)lane < grp) {
+      ml[(wave * grp + lane) * 2] = m;
+      ml[(wave * grp + lane) * 2 + 1] = lsum;
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+      const uint32_t row = 4u * jg + r, term = row / HG, head = row % HG;
+      if (term < NTERM && head < grp) {
+        float* wp = wpart + (((size_t)wave * NTERM + term) * grp + head) * WS + (uint32_t)NT * col;
+#pragma unroll
+        for (int k = 0; k < NT; k += 4) *(float4*)(wp + k) = make_float4(O[k][r], O[k + 1][r], O[k + 2][r], O[k + 3][r]);
+      }
     }
   }
   if (PAGED && bad_page) report(a, DE_BAD_PAGE, b, t0);   // (the rows came from page 0 instead: wrong, but in bounds)
-  // ---- combine the lane groups of the wavefront, then the wavefronts
-#pragma unroll
-  for (int j = 0; j < GRP; ++j) {
-#pragma unroll
-    for (uint32_t off = LPP; off < 64; off <<= 1) {
-      const float mo = __shfl_xor(m[j], off, 64), lo2 = __shfl_xor(l[j], off, 64);
-      const float mn = fmaxf(m[j], mo);
-      const float s0 = (m[j] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[j] - mn), s1 = (mo == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mo - mn);
-      l[j] = l[j] * s0 + lo2 * s1;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[j][e] = acc[j][e] * s0 + __shfl_xor(acc[j][e], off, 64) * s1;
-      m[j] = mn;
-    }
-    if (slot == 0) {
-      float* wp = wpart + ((size_t)wave * grp + j) * (d + 2);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) wp[sub * 8 + e] = acc[j][e];
-      if (sub == 0) {
-        wp[d] = m[j] * 0.693147180559945309f;   // back to natural units for the merges
-        wp[d + 1] = l[j];
-      }
-    }
-  }
   __syncthreads();
   trace_mark(a, t, 10);
-  for (uint32_t i = threadIdx.x; i < grp * (d + 2); i += kThreads) {
-    const uint32_t j = i / (d + 2), dim = i % (d + 2);
-    float M = -INFINITY;
+  // ---- the wavefronts' results and the appended row -> the task's partial result, two elements a thread
+  const uint32_t nw = min(nblk, NW);
+  for (uint32_t i = threadIdx.x; i < grp * (d / 2 + 1); i += kThreads) {
+    const uint32_t j = i / (d / 2 + 1), e = 2u * (i % (d / 2 + 1));   // e == d: the maximum and the sum
+    float mw[NW], M = has_new ? snew[j] : -INFINITY;
 #pragma unroll
-    for (uint32_t w = 0; w < NW; ++w) M = fmaxf(M, wpart[((size_t)w * grp + j) * (d + 2) + d]);
-    float sv;
-    if (dim == d) {
-      sv = M;
+    for (uint32_t w = 0; w < NW; ++w) {
+      mw[w] = w < nw ? ml[(w * grp + j) * 2] : -INFINITY;
+      M = fmaxf(M, mw[w]);
+    }
+    float x = 0.f, y = 0.f;
+    const float wn = has_new ? __builtin_amdgcn_exp2f(snew[j] - M) : 0.f;
+    if (e == d) {
+      y = wn;
+#pragma unroll
+      for (uint32_t w = 0; w < NW; ++w)
+        if (w < nw) y = fmaf(ml[(w * grp + j) * 2 + 1], __builtin_amdgcn_exp2f(mw[w] - M), y);
+      x = M;   // (a power of two, like everything the merges do with it)
     } else {
-      sv = 0.f;
-      const uint32_t src = (dim == d + 1) ? d + 1 : dim;
+      if (has_new) { x = wn * vnew[e]; y = wn * vnew[e + 1]; }
 #pragma unroll
       for (uint32_t w = 0; w < NW; ++w) {
-        const float mw = wpart[((size_t)w * grp + j) * (d + 2) + d];
-        if (mw != -INFINITY) sv += wpart[((size_t)w * grp + j) * (d + 2) + src] * expf(mw - M);
+        if (w >= nw) continue;
+        const float f = __builtin_amdgcn_exp2f(mw[w] - M);
+        float ox = 0.f, oy = 0.f;
+#pragma unroll
+        for (uint32_t term = 0; term < NTERM; ++term) {
+          const float2 v = *(const float2*)(wpart + (((size_t)w * NTERM + term) * grp + j) * WS + e);
+          ox += v.x; oy += v.y;
+        }
+        x = fmaf(f, ox, x);
+        y = fmaf(f, oy, y);
       }
     }
-    st_act(outp + i, sv);
+    st_act2(outp + j * (d + 2) + e, x, y);
   }
   trace_mark(a, t, 11);
   if (t.flags & TF_ATTN_MERGE) {
     // Arrival counter of (layer, sequence, KV head): the chunk task that arrives last sees all C
-    // partials complete and merges them (log-sum-exp, one pass with running maximum) into the
-    // attention output.
+    // partials complete and merges them into the attention output.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -2558,39 +2332,7 @@ __device__ __forceinline__ bool body_attn_partial(const TaskDesc& t, const StepA
     __syncthreads();
     if (*flag) {
       // chunk k of the sequence is the partial result of task v0 + k, in that task's own slot
-      auto part_of = [&](uint32_t k) {
-        const uint32_t v = v0 + k;
-        return t.out + (size_t)(v / Cs) * t.ld_out + (size_t)(g * Cs + v % Cs) * per;
-      };
-      float* o = const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d;
-      for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) {
-        uint32_t j = i / d, dim = i % d;
-        float M = -INFINITY, L = 0.f, acc_o = 0.f;
-        for (uint32_t c0 = 0; c0 < C; c0 += 8) {   // 24 coherent loads in flight: one round trip for 8 chunks
-          float mm[8], ll[8], oo[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            if (c0 + k < C) {
-              const float* pp = part_of(c0 + k) + (size_t)j * (d + 2);
-              mm[k] = ld_act(pp + d);
-              ll[k] = ld_act(pp + d + 1);
-              oo[k] = ld_act(pp + dim);
-            } else {
-              mm[k] = -INFINITY; ll[k] = 0.f; oo[k] = 0.f;
-            }
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            float Mn = fmaxf(M, mm[k]);
-            if (Mn == -INFINITY) continue;   // empty chunks only so far
-            float sc_old = expf(M - Mn), sc_new = expf(mm[k] - Mn);
-            L = L * sc_old + ll[k] * sc_new;
-            acc_o = acc_o * sc_old + oo[k] * sc_new;
-            M = Mn;
-          }
-        }
-        st_act(o + i, acc_o / L);
-      }
+      attn_merge_partials<D, GRP>(C, t.out + (size_t)(v0 / Cs) * t.ld_out + (size_t)g * Cs * per, v0 % Cs, Cs, t.ld_out, const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d);
     }
   }
   return true;
@@ -2610,7 +2352,7 @@ __device__ __forceinline__ void body_attn_merge(const TaskDesc& t, const StepArg
       float L = 0.f, o = 0.f;
       for (uint32_t c = 0; c < C; ++c) {
         const float* p = part + ((size_t)(g * C + c) * grp + j) * (d + 2);
-        float wgt = expf(ld_act(p + d) - M);   // exp(-inf) = 0 for empty chunks
+        float wgt = __builtin_amdgcn_exp2f(ld_act(p + d) - M);   // maxima are powers of two; 2^(-inf) = 0 for empty chunks
         L = fmaf(wgt, ld_act(p + d + 1), L);
         o = fmaf(wgt, ld_act(p + dim), o);
       }
@@ -2903,67 +2645,21 @@ __device__ __forceinline__ void body_serve(const StepArgs& a) {
   }
 }
 
-// D, GRP, NB pin head_dim, query heads per KV head and the batch class at compile time (0 = decide
-// at run time): a kernel that carries a single attention and a single linear variant keeps its
-// register allocation free of spills, the fully generic kernel does not.
-// Batch class -> body instance (NB = 0: decided at run time).
+// NB, the batch class, pins the linear body of a kernel: a kernel that carries a single one keeps its
+// register allocation (nearly) free of spills, one that decides between them at run time does not.
+//   1: one row, vector body; 9: one row, large tasks: three weight buffers; 2: two rows, vector body;
+//   8: 3 .. 16 rows, matrix cores
 template <int NB, bool MEGA, class Svc = NoJit>
 __device__ __forceinline__ uint32_t run_linear(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
                                            uint32_t* s_flag, const Svc& svc = Svc{}, uint32_t next_ti = 0) {
-  if (NB == 8) return linear_task_mfma<MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);   // batch class 5..16: matrix cores
-  if (NB == 9) return linear_task<1, MEGA, Svc, true>(t, a, lds, wait_ev, s_flag, svc, next_ti);   // batch 1, large tasks: three buffers
-  if (NB != 0) return linear_task<(NB ? NB : 1), MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc, next_ti);
-  const uint32_t nb = t.b1 - t.b0;
-  if (nb == 1) return linear_task<1, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc, next_ti);
-  if (nb == 2) return linear_task<2, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);
-  if (nb <= 4) return linear_task<4, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);
-  return linear_task_mfma<MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);
+  if constexpr (NB == 8) return linear_task_mfma<MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);
+  else if constexpr (NB == 9) return linear_task<1, MEGA, Svc, true>(t, a, lds, wait_ev, s_flag, svc, next_ti);
+  else return linear_task<NB, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc, next_ti);
 }
 
-// Runs one task that is not a linear task.  wait_ev >= 0: the task must first wait for that event
-// (persistent kernel); attention tasks do so after requesting their first cache rows.
-template <int D, int GRP, int NB>
-__device__ __forceinline__ bool run_task(const TaskDesc& t, const StepArgs& a, float* lds,
-                                         int32_t wait_ev, uint32_t* s_flag) {
-  if (t.kind == TK_ATTN_PARTIAL) {
-    if (t.flags & TF_KV_PAGED) {   // paged cache: the same two bodies, rows reached through the page table
-      if (D != 0) {
-        constexpr uint32_t window = kAttnRounds * (kThreads / 64) * (64 / ((D ? D : 128) / 8));
-        if ((GRP ? GRP : 1) <= 4 && !(t.flags & TF_ATTN_BALANCE) && (a.g->max_seq + t.p1 - 1) / t.p1 <= window)
-          return body_attn_partial_regs<(D ? D : 128), (GRP ? GRP : 1), true>(t, a, lds, wait_ev, s_flag);
-        return body_attn_partial<(D ? D : 128), (GRP ? GRP : 1), true, NB>(t, a, lds, wait_ev, s_flag);
-      }
-      const uint32_t grp = a.g->n_q / a.g->n_kv;
-      if (a.g->head_dim == 128) {
-        if (grp == 8) return body_attn_partial<128, 8, true>(t, a, lds, wait_ev, s_flag);
-        if (grp == 4) return body_attn_partial<128, 4, true>(t, a, lds, wait_ev, s_flag);
-        if (grp == 2) return body_attn_partial<128, 2, true>(t, a, lds, wait_ev, s_flag);
-        return body_attn_partial<128, 1, true>(t, a, lds, wait_ev, s_flag);
-      }
-      if (grp == 8) return body_attn_partial<64, 8, true>(t, a, lds, wait_ev, s_flag);
-      if (grp == 4) return body_attn_partial<64, 4, true>(t, a, lds, wait_ev, s_flag);
-      if (grp == 2) return body_attn_partial<64, 2, true>(t, a, lds, wait_ev, s_flag);
-      return body_attn_partial<64, 1, true>(t, a, lds, wait_ev, s_flag);
-    }
-    if (D != 0) {
-      // chunks that always fit the register-resident body (wavefront-uniform: graph constants)
-      constexpr uint32_t window = kAttnRounds * (kThreads / 64) * (64 / ((D ? D : 128) / 8));
-      if ((GRP ? GRP : 1) <= 4 && !(t.flags & TF_ATTN_BALANCE) && (a.g->max_seq + t.p1 - 1) / t.p1 <= window)
-        return body_attn_partial_regs<(D ? D : 128), (GRP ? GRP : 1)>(t, a, lds, wait_ev, s_flag);
-      return body_attn_partial<(D ? D : 128), (GRP ? GRP : 1), false, NB>(t, a, lds, wait_ev, s_flag);
-    }
-    const uint32_t grp = a.g->n_q / a.g->n_kv;
-    if (a.g->head_dim == 128) {
-      if (grp == 8) return body_attn_partial<128, 8>(t, a, lds, wait_ev, s_flag);
-      if (grp == 4) return body_attn_partial<128, 4>(t, a, lds, wait_ev, s_flag);
-      if (grp == 2) return body_attn_partial<128, 2>(t, a, lds, wait_ev, s_flag);
-      return body_attn_partial<128, 1>(t, a, lds, wait_ev, s_flag);
-    }
-    if (grp == 8) return body_attn_partial<64, 8>(t, a, lds, wait_ev, s_flag);
-    if (grp == 4) return body_attn_partial<64, 4>(t, a, lds, wait_ev, s_flag);
-    if (grp == 2) return body_attn_partial<64, 2>(t, a, lds, wait_ev, s_flag);
-    return body_attn_partial<64, 1>(t, a, lds, wait_ev, s_flag);
-  }
+// Runs one task that is neither a linear nor an attention task.  wait_ev >= 0: the task must first
+// wait for that event (persistent kernel).
+__device__ __forceinline__ bool run_task(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev, uint32_t* s_flag) {
   if (wait_ev >= 0 && !wait_event(a, wait_ev, s_flag)) return false;
   trace_mark(a, t, 1);
   switch (t.kind) {
@@ -2988,19 +2684,26 @@ __device__ __forceinline__ bool run_task(const TaskDesc& t, const StepArgs& a, f
 // own 256-byte line; lanes 0 .. kShards-1 read one group's counter each -- a single load instruction
 // -- and compare it with epoch * (that group's producers).  An arrival is then ONE atomic add that
 // nobody waits for, and the producers spread over kShards lines (see kHierMinRequired).
-__device__ __forceinline__ bool event_reached(const StepArgs& a, int32_t e, int lane) {
+__device__ __forceinline__ EventProbe probe_event(const StepArgs& a, int32_t e, int lane) {
   const MPK_CONST EventDesc& ev = *(const MPK_CONST EventDesc*)(a.events + e);
-  bool ok = true;
+  EventProbe p;
+  p.seen = p.need = 0;   // lanes without a counter agree
   if (ev.flags & EV_HIER) {
     if (lane < (int)kShards) {
-      const uint32_t need = a.epoch * ((const MPK_CONST EventDesc*)(a.events + e))->sub_required[lane];
-      const uint32_t v = ld_relaxed(a.hier + (size_t)ev.hier_slot * kHierWordsPerEvent + (1 + lane) * kHierStrideWords);
-      ok = (int32_t)(v - need) >= 0;
+      p.need = a.epoch * ((const MPK_CONST EventDesc*)(a.events + e))->sub_required[lane];
+      p.seen = ld_relaxed(a.hier + (size_t)ev.hier_slot * kHierWordsPerEvent + (1 + lane) * kHierStrideWords);
     }
   } else if (lane == 0) {
-    ok = (int32_t)(ld_relaxed(a.counters + e) - a.epoch * ev.required) >= 0;
+    p.need = a.epoch * ev.required;
+    p.seen = ld_relaxed(a.counters + e);
   }
-  return __builtin_amdgcn_readfirstlane((int)(__ballot(ok) == ~0ull)) != 0;
+  return p;
+}
+__device__ __forceinline__ bool probe_reached(const EventProbe& p) {
+  return __builtin_amdgcn_readfirstlane((int)(__ballot((int32_t)(p.seen - p.need) >= 0) == ~0ull)) != 0;
+}
+__device__ __forceinline__ bool event_reached(const StepArgs& a, int32_t e, int lane) {
+  return probe_reached(probe_event(a, e, lane));
 }
 
 // The first wavefront polls until event e is activated; *s_flag = 1, or 0 when the step is being
@@ -3032,6 +2735,16 @@ __device__ __forceinline__ void poll_event_wave0(const StepArgs& a, int32_t e, u
 __device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag) {
   if (threadIdx.x < 64) poll_event_wave0(a, e, s_flag, (int)threadIdx.x);
   __syncthreads();   // later agent-scope loads cannot move above this barrier
+  return __builtin_amdgcn_readfirstlane(*s_flag) != 0;
+}
+
+// The same behind an earlier look at the event (taken by all lanes of the first wavefront).
+__device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag, const EventProbe& probe) {
+  if (threadIdx.x < 64) {
+    if (!probe_reached(probe)) poll_event_wave0(a, e, s_flag, (int)threadIdx.x);
+    else if (threadIdx.x == 0) *s_flag = 1;
+  }
+  __syncthreads();
   return __builtin_amdgcn_readfirstlane(*s_flag) != 0;
 }
 
@@ -3122,7 +2835,8 @@ __device__ __forceinline__ void signal_from_wave0(const StepArgs& a, const TaskD
 // The arguments are kept there for the task functions that are real calls: a struct passed by
 // value to such a function travels through private memory -- every one of the 512 lanes stores
 // and re-loads its own 80-byte copy, 10 MB per call over the chip and a memory round trip before
-// the task can start (measured on the MoE shape: 3.9 GB written per step, most of it this).
+// the task can start, and every call site gets a private copy of its own that crowds the weight
+// buffers out of the registers (vector body: 55 spilled registers by value, none this way).
 constexpr uint32_t kLdsArgsAt = 16;
 static_assert(kLdsArgsAt * 4 + sizeof(StepArgs) <= kLdsCtrlFloats * 4, "control words too small for the arguments");
 // Thread 0 leaves the arguments in LDS; the callers' next barrier publishes them.
@@ -3134,31 +2848,13 @@ __device__ __forceinline__ StepArgs published_args() {
   extern __shared__ __align__(16) float dyn_lds[];
   return uniform_args(*(const StepArgs*)(dyn_lds + kLdsArgsAt));
 }
-// How a real task function gets the arguments: from LDS (the batch-5..16 kernel, NB = 8, for dense models:
-// -1.5 % per step on the batch-8 shape) or by value (the batch-1 kernels, where the LDS form
-// measured 0 to +1.3 %, and the mixture-of-experts kernels: +5 % on the MoE shape, also with the
-// expert bodies inlined into the task function).
-struct ArgsInLds {};
-__device__ __forceinline__ StepArgs task_args(const ArgsInLds&) { return published_args(); }
-__device__ __forceinline__ StepArgs task_args(const StepArgs& a) { return uniform_args(a); }
-template <int NB, bool MOE>
-struct TaskArgs {
-  using type = std::conditional_t<(NB == 8 && !MOE), ArgsInLds, StepArgs>;
-  static __device__ __forceinline__ type make(const StepArgs& a) {
-    if constexpr (NB == 8 && !MOE) return ArgsInLds{};
-    else return a;
-  }
-};
 
 // Mixture-of-experts tasks: inlined into run_other_task of the MoE kernels.  (As a real function of
 // its own -- so that attention calls would not have to save the many callee-saved registers the
 // expert jobs use -- every MoE task paid two nested calls, each with its by-value argument copies
 // and register saves: measured 3 to 4 % slower per step on the MoE shape.)
 template <bool MEGA>
-__device__ __forceinline__ bool run_moe_task(StepArgs a_in, uint32_t task_index, bool skip_wait) {
-  const StepArgs a = uniform_args(a_in);
-  task_index = uniform_u32(task_index);
-  skip_wait = uniform_u32(skip_wait) != 0;
+__device__ __forceinline__ bool run_moe_task(const StepArgs& a, uint32_t task_index, bool skip_wait) {
   extern __shared__ __align__(16) float dyn_lds[];
   float* lds = dyn_lds + kLdsCtrlFloats;
   uint32_t* s_flag = (uint32_t*)dyn_lds;
@@ -3206,9 +2902,9 @@ __device__ __forceinline__ bool is_moe_kind(uint16_t kind) { return kind >= TK_M
 // hoisted to the top of the persistent loop, where they would crowd out the weight ring and
 // force spills of registers that have loads in flight.
 // Returns false when the step is being aborted.
-template <int D, int GRP, int NB, bool MEGA, bool MOE>
-__device__ __noinline__ bool run_other_task(typename TaskArgs<NB, MOE>::type args, uint32_t task_index, bool skip_wait) {
-  const StepArgs a = task_args(args);
+template <bool MEGA, bool MOE>
+__device__ __noinline__ bool run_other_task(uint32_t task_index, bool skip_wait) {
+  const StepArgs a = published_args();
   task_index = uniform_u32(task_index);
   skip_wait = uniform_u32(skip_wait) != 0;
   extern __shared__ __align__(16) float dyn_lds[];
@@ -3224,7 +2920,7 @@ __device__ __noinline__ bool run_other_task(typename TaskArgs<NB, MOE>::type arg
     trace_mark(a, t, 0);
     if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)task_index * kTraceSlots + 5] = blockIdx.x;
   }
-  if (!run_task<D, GRP, NB>(t, a, lds, wait_ev, s_flag)) return false;
+  if (!run_task(t, a, lds, wait_ev, s_flag)) return false;
   if (MEGA) {
     trace_mark(a, t, 3);
     if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
@@ -3232,6 +2928,59 @@ __device__ __noinline__ bool run_other_task(typename TaskArgs<NB, MOE>::type arg
     trace_mark(a, t, 4);
   }
   return true;
+}
+
+// An attention task, one real function per (head_dim, query heads per KV head, kind of cache): the
+// matrix-core body wants its own register allocation, and every batch class gets every shape this
+// way (with the shapes pinned per kernel, a model without a kernel set of its own ran on a fallback
+// that decided everything at run time and spilled 350 registers: head size 64 at batch 1, every
+// model at batch 2 to 4).  skip_wait: the event is known to be active; signal: notify the
+// triggering event (persistent kernel).
+template <int D, int GRP, bool PAGED>
+__device__ __noinline__ bool run_attn_task(uint32_t task_index, bool skip_wait, bool signal) {
+  const StepArgs a = published_args();
+  task_index = uniform_u32(task_index);
+  skip_wait = uniform_u32(skip_wait) != 0;
+  signal = uniform_u32(signal) != 0;
+  extern __shared__ __align__(16) float dyn_lds[];
+  float* lds = dyn_lds + kLdsCtrlFloats;
+  uint32_t* s_flag = (uint32_t*)dyn_lds;
+  const TaskDesc t = ld_task(a, task_index);
+  int32_t wait_ev = -1;
+  if (signal) {
+    debug_jitter(a, task_index);
+    wait_ev = (!skip_wait && t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
+    trace_mark(a, t, 0);
+    if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)task_index * kTraceSlots + 5] = blockIdx.x;
+  }
+  if (!body_attn_mfma<D, GRP, PAGED>(t, a, lds, wait_ev, s_flag)) return false;
+  if (signal) {
+    trace_mark(a, t, 3);
+    if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
+    else __syncthreads();
+    trace_mark(a, t, 4);
+  }
+  return true;
+}
+// Runs a task that is not a linear task.  (A callee's result comes back in a vector register: it is
+// made scalar again, or the whole task loop, and every descriptor load in it, turns into per-lane code.)
+template <bool MEGA, bool MOE>
+__device__ __forceinline__ bool call_task(const StepArgs& a, uint16_t kind, uint32_t task_index, bool skip_wait) {
+  bool ok;
+  if (kind != TK_ATTN_PARTIAL) {
+    ok = run_other_task<MEGA, MOE>(task_index, skip_wait);
+  } else {
+    switch (a.g->attn_shape) {   // see attn_shape_index
+#define MPK_ATTN_CASE(D, LG)                                                                                                   \
+      case attn_shape_index(D, 1u << LG, 0): ok = run_attn_task<D, (1 << LG), false>(task_index, skip_wait, MEGA); break; \
+      case attn_shape_index(D, 1u << LG, 1): ok = run_attn_task<D, (1 << LG), true>(task_index, skip_wait, MEGA); break;
+      MPK_ATTN_CASE(64, 0) MPK_ATTN_CASE(64, 1) MPK_ATTN_CASE(64, 2) MPK_ATTN_CASE(64, 3)
+      MPK_ATTN_CASE(128, 0) MPK_ATTN_CASE(128, 1) MPK_ATTN_CASE(128, 2) MPK_ATTN_CASE(128, 3)
+#undef MPK_ATTN_CASE
+      default: ok = false; break;   // (the host admits no other shape)
+    }
+  }
+  return __builtin_amdgcn_readfirstlane((int)ok) != 0;
 }
 
 __device__ __forceinline__ bool event_active(const StepArgs& a, int32_t e) {
@@ -3376,7 +3125,7 @@ __device__ __forceinline__ uint32_t pick_task(const StepArgs& a, uint32_t* ctrl,
 // Every task ahead-of-time: the worker walks its pre-enqueued list, each task waits for its own
 // event.  after_first_step: a task without producers (an embedding task) first waits for the
 // previous step's terminal event, i.e. for that step's sampling tasks.  Returns false on abort.
-template <int D, int GRP, int NB, bool MOE>
+template <int NB, bool MOE>
 __device__ __forceinline__ bool aot_pass(const StepArgs& a, uint32_t q0, uint32_t q1, float* lds, uint32_t* s_flag,
                                          bool after_first_step) {
   for (uint32_t qi = q0; qi < q1; ++qi) {
@@ -3396,9 +3145,7 @@ __device__ __forceinline__ bool aot_pass(const StepArgs& a, uint32_t q0, uint32_
       const uint32_t next_ti = qi + 1 < q1 ? ld_u32c(a.g->aot + qi + 1) : 0u;
       if (!run_linear<NB, true>(t, a, lds, wait_ev, s_flag, NoJit{}, next_ti)) return false;
     } else {
-      // the callee's result comes back in a vector register: make it scalar again, or the whole
-      // task loop (and every descriptor load in it) turns into per-lane code
-      if (!__builtin_amdgcn_readfirstlane((int)run_other_task<D, GRP, NB, true, MOE>(TaskArgs<NB, MOE>::make(a), ti, false))) return false;
+      if (!call_task<true, MOE>(a, t.kind, ti, false)) return false;
     }
   }
   return true;
@@ -3440,7 +3187,7 @@ __device__ __noinline__ bool serve_step_gate(StepArgs a_in, uint32_t q0, uint32_
 // Multi-token launch (graphs with the sampling operator, no schedulers): the task list is walked
 // n_steps times, the epoch -- hence every counter target -- growing by one each time.  A kernel of
 // its own: with the step loop in mpk_mega_kernel the single-step launch measured 2 to 4 % slower.
-template <int D, int GRP, int NB, bool MOE>
+template <int NB, bool MOE>
 __global__ void __launch_bounds__(kThreads) mpk_loop_kernel(StepArgs a) {
   extern __shared__ __align__(16) float dyn_lds[];
   float* lds = dyn_lds + kLdsCtrlFloats;
@@ -3461,33 +3208,28 @@ __global__ void __launch_bounds__(kThreads) mpk_loop_kernel(StepArgs a) {
       serve_skip_steps(a, q0, q1, n_steps - step);
       return;
     }
-    if (NB == 8 && !MOE) {
-      __syncthreads();   // (nobody is inside a task function any more)
-      publish_args(a);
-      __syncthreads();
-    }
-    if (!aot_pass<D, GRP, NB, MOE>(a, q0, q1, lds, s_flag, step > 0)) return;
+    __syncthreads();   // (nobody is inside a task function any more)
+    publish_args(a);
+    __syncthreads();
+    if (!aot_pass<NB, MOE>(a, q0, q1, lds, s_flag, step > 0)) return;
   }
 }
 
-// PATHS: 0 = the all-ahead-of-time walk and the hybrid launch in one kernel, chosen at run time;
-// 1 = ahead-of-time only; 2 = hybrid only.  Which is faster is a matter of register allocation and
-// code layout, measured per body: the vector linear body (batch <= 4) runs 0.8 % faster from the
-// combined kernel, the matrix-core body spills three times less in a kernel of its own.
+// HYBRID: the hybrid launch (scheduler workgroups); otherwise the all-ahead-of-time walk.  Two kernels:
+// one that holds both spills three to eight times as many registers (vector body 209 against 26), and
+// a reload from scratch memory waits for every weight load in flight.
 // RUN: the instance launched once per step for a run of several steps (vector linear bodies): it
 // can find that an earlier step of the run left the server drained.  A kernel of its own, so that
 // the single-step kernel stays exactly as it is (1.2 % slower with the check compiled in).
-template <int D, int GRP, int NB, bool MOE, int PATHS = 0, bool RUN = false>
+template <int NB, bool MOE, bool HYBRID, bool RUN = false>
 __global__ void __launch_bounds__(kThreads) mpk_mega_kernel(StepArgs a) {
   extern __shared__ __align__(16) float dyn_lds[];
   float* lds = dyn_lds + kLdsCtrlFloats;
   uint32_t* s_flag = (uint32_t*)dyn_lds;
   const uint32_t w = blockIdx.x;
-  if (NB == 8 && !MOE) {
-    publish_args(a);
-    __syncthreads();
-  }
-  if (PATHS != 1 && w >= a.g->n_workers) {
+  publish_args(a);
+  __syncthreads();
+  if (HYBRID && w >= a.g->n_workers) {
     // scheduler workgroup: 4 scheduler wavefronts (Section 5.1, Table 2), the rest leave
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t sc = (w - a.g->n_workers) * 4u + wave;
@@ -3495,86 +3237,83 @@ __global__ void __launch_bounds__(kThreads) mpk_mega_kernel(StepArgs a) {
     return;
   }
   const uint32_t q0 = ld_u32c(a.g->aot_off + w), q1 = ld_u32c(a.g->aot_off + w + 1);
-  if (PATHS == 1 || (PATHS == 0 && a.n_sched == 0)) {
+  if constexpr (!HYBRID) {
     // (a run of serving iterations issued as one launch per step: the launches behind the one
     // that found the server drained only settle their share of the event counters)
     if (RUN && __builtin_amdgcn_readfirstlane((int)serve_step_gate(a, q0, q1))) return;
-    aot_pass<D, GRP, NB, MOE>(a, q0, q1, lds, s_flag, false);
+    aot_pass<NB, MOE>(a, q0, q1, lds, s_flag, false);
     return;
   }
-  // hybrid launch
-  uint32_t jit_head = ld_relaxed(a.g->wq_head + w), ai = q0;
-  while (true) {
-    const uint32_t pick = pick_task(a, (uint32_t*)dyn_lds, &jit_head, &ai, q1);
-    if (pick == kPickExit || pick == kPickAbort) break;
-    const uint32_t ti = pick & 0x7FFFFFFFu;
-    const TaskDesc t = ld_task(a, ti);
-    if (t.kind == TK_LINEAR) {
-      debug_jitter(a, ti);
-      trace_mark(a, t, 0);
-      if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.pad * kTraceSlots + 5] = blockIdx.x;
-      const int32_t wait_ev = (t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
-      uint32_t r;
-      // started before its event is activated; a just-in-time task that arrives first pre-empts it
-      while ((r = run_linear<NB, true>(t, a, lds, wait_ev, s_flag, JitWatch{jit_head})) == kLinPreempted) {
-        const uint32_t tj = __builtin_amdgcn_readfirstlane(((uint32_t*)dyn_lds)[1]);
-        lds_barrier();   // everybody has read the control word
-        ++jit_head;
-        // (a just-in-time task may itself be a linear task -- an operator whose tiles read only part
-        // of a just-in-time operator's output is labelled just-in-time too, Section 5.2: its event
-        // has been activated, so it runs without waiting and without watching the queue)
-        const TaskDesc tjd = ld_task(a, tj);
-        if (tjd.kind == TK_LINEAR) {
-          debug_jitter(a, tj);
-          if (run_linear<NB, true>(tjd, a, lds, -1, s_flag) != kLinDone) { r = kLinAbort; break; }
-        } else if (!__builtin_amdgcn_readfirstlane((int)run_other_task<D, GRP, NB, true, MOE>(TaskArgs<NB, MOE>::make(a), tj, true))) { r = kLinAbort; break; }
+  if constexpr (HYBRID) {
+    uint32_t jit_head = ld_relaxed(a.g->wq_head + w), ai = q0;
+    while (true) {
+      const uint32_t pick = pick_task(a, (uint32_t*)dyn_lds, &jit_head, &ai, q1);
+      if (pick == kPickExit || pick == kPickAbort) break;
+      const uint32_t ti = pick & 0x7FFFFFFFu;
+      const TaskDesc t = ld_task(a, ti);
+      if (t.kind == TK_LINEAR) {
+        debug_jitter(a, ti);
+        trace_mark(a, t, 0);
+        if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.pad * kTraceSlots + 5] = blockIdx.x;
+        const int32_t wait_ev = (t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
+        uint32_t r;
+        // started before its event is activated; a just-in-time task that arrives first pre-empts it
+        while ((r = run_linear<NB, true>(t, a, lds, wait_ev, s_flag, JitWatch{jit_head})) == kLinPreempted) {
+          const uint32_t tj = __builtin_amdgcn_readfirstlane(((uint32_t*)dyn_lds)[1]);
+          lds_barrier();   // everybody has read the control word
+          ++jit_head;
+          // (a just-in-time task may itself be a linear task -- an operator whose tiles read only part
+          // of a just-in-time operator's output is labelled just-in-time too, Section 5.2: its event
+          // has been activated, so it runs without waiting and without watching the queue)
+          const TaskDesc tjd = ld_task(a, tj);
+          if (tjd.kind == TK_LINEAR) {
+            debug_jitter(a, tj);
+            if (run_linear<NB, true>(tjd, a, lds, -1, s_flag) != kLinDone) { r = kLinAbort; break; }
+          } else if (!call_task<true, MOE>(a, tjd.kind, tj, true)) { r = kLinAbort; break; }
+        }
+        if (r == kLinAbort) break;
+      } else {
+        if (!call_task<true, MOE>(a, t.kind, ti, true)) break;
       }
-      if (r == kLinAbort) break;
-    } else {
-      if (!__builtin_amdgcn_readfirstlane((int)run_other_task<D, GRP, NB, true, MOE>(TaskArgs<NB, MOE>::make(a), ti, true))) break;
     }
+    if (threadIdx.x == 0) __hip_atomic_store(as_global(a.g->wq_head + w), jit_head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (threadIdx.x == 0) __hip_atomic_store(as_global(a.g->wq_head + w), jit_head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Kernel-per-operator baseline: the same task bodies, one launch per operator, dependencies
 // enforced by stream order (what the paper's comparison systems do, Section 6.5).
-template <int D, int GRP, int NB, bool MOE>
+template <int NB, bool MOE>
 __global__ void __launch_bounds__(kThreads) mpk_op_kernel(StepArgs a, uint32_t first) {
   extern __shared__ __align__(16) float dyn_lds[];
   float* lds = dyn_lds + kLdsCtrlFloats;
-  if (NB == 8 && !MOE) {
-    publish_args(a);
-    __syncthreads();
-  }
+  publish_args(a);
+  __syncthreads();
   const uint32_t ti = ld_u32c(a.g->op_list + first + blockIdx.x);
   const TaskDesc t = ld_task(a, ti);
   if (t.kind == TK_LINEAR) {
     run_linear<NB, false>(t, a, lds, -1, nullptr);
   } else {
-    run_other_task<D, GRP, NB, false, MOE>(TaskArgs<NB, MOE>::make(a), ti, true);
+    call_task<false, MOE>(a, t.kind, ti, true);
   }
 }
 
 
-// One specialised set of kernels; {0, 0, 0} is the generic fallback.  D, GRP, NB pin head_dim, query
-// heads per KV head and the batch class (1: one row, GEMV; 9: one row, three weight buffers; 8: 5..16
-// rows, matrix cores); MOE adds the mixture-of-experts task kinds.
+// One set of kernels per batch class (see run_linear) and per presence of the mixture-of-experts task
+// kinds; every set takes every attention shape.
 struct KernelVariant {
-  int d, grp, nb;
+  int nb;
   bool moe;
   void (*mega)(StepArgs);     // all tasks ahead-of-time
   void (*op)(StepArgs, uint32_t);
   void (*loop)(StepArgs);
-  void (*hybrid)(StepArgs);   // with scheduler workgroups (may be the same kernel as `mega`)
-  void (*run_step)(StepArgs); // one step of a run of several, a launch per step (null: use `loop`)
+  void (*hybrid)(StepArgs);   // with scheduler workgroups
+  void (*run_step)(StepArgs); // one step of a run of several, a launch per step
 };
-// index, head_dim, group, batch class, mixture of experts
-#define MPK_VARIANT_LIST(X)                                                                   \
-  X(0, 64, 2, 1, false) X(1, 128, 4, 1, false) X(2, 128, 8, 1, false) X(3, 128, 8, 9, false)  \
-  X(4, 128, 4, 8, false) X(5, 128, 8, 8, true) X(6, 0, 0, 0, false) X(7, 0, 0, 0, true)
-constexpr int kNumVariants = 8;
-#define MPK_DECLARE_VARIANT(I, D, G, N, M) const KernelVariant* kernel_variant_##I();
+// index, batch class, mixture of experts
+#define MPK_VARIANT_LIST(X) \
+  X(0, 1, false) X(1, 9, false) X(2, 2, false) X(3, 8, false) X(4, 1, true) X(5, 2, true) X(6, 8, true)
+constexpr int kNumVariants = 7;
+#define MPK_DECLARE_VARIANT(I, N, M) const KernelVariant* kernel_variant_##I();
 MPK_VARIANT_LIST(MPK_DECLARE_VARIANT)
 #undef MPK_DECLARE_VARIANT
 

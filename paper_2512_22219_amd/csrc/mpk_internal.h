@@ -256,6 +256,9 @@ MPK_HOST_DEVICE inline void moe_task_share(uint32_t n_active, uint32_t tiles_per
 }
 constexpr uint32_t kMoeMaxExperts = 512, kMoeMaxPairs = 256, kMoeMaxTopK = 16;
 
+constexpr uint32_t kMfmaMinBatch = 3;   // linear operators of this many rows and more run on the matrix cores
+constexpr uint32_t kMfmaJobRows = 512;  // weight rows of one matrix-core job
+
 // Matrix-core jobs (batch 5..16 and expert jobs) stage the input in LDS as fp32, a chunk of this
 // many inputs at a time; one definition for the host's LDS requirement and the kernels' layout.
 constexpr uint32_t mfma_kchunk(uint32_t nb) { return nb <= 8u ? 4096u : 2048u; }
@@ -273,6 +276,8 @@ constexpr uint32_t moe_x_floats(uint32_t batch) {
   const uint32_t t16 = batch > 8u ? mfma_x_floats(batch < 16u ? batch : 16u) : 0u;
   return t8 > t16 ? t8 : t16;
 }
+
+constexpr uint32_t kRopeTabFloatsMax = 16 * 128;   // [batch][head_dim]: (cos, sin) of a step's rotation angles
 
 // LDS layout constants shared with the kernels
 constexpr uint32_t kThreads = 512;        // worker workgroup size (8 wavefronts, two per SIMD)

@@ -7,29 +7,25 @@
 
 namespace mpk {
 
-#define MPK_GET_VARIANT(I, D, G, N, M) kernel_variant_##I(),
+#define MPK_GET_VARIANT(I, N, M) kernel_variant_##I(),
 static const KernelVariant* variant_at(int i) {
   static const KernelVariant* const table[kNumVariants] = {MPK_VARIANT_LIST(MPK_GET_VARIANT)};
   return table[i];
 }
 #undef MPK_GET_VARIANT
 
-static const KernelVariant* pick_variant(uint32_t d, uint32_t grp, uint32_t batch, bool moe, bool large_tasks) {
-  const int n = kNumVariants;
-  for (int pass = (batch == 1 && large_tasks) ? 0 : 1; pass < 2; ++pass) {
-    const int nb = batch == 1 ? (pass == 0 ? 9 : 1) : (batch > 4 && batch <= 16 ? 8 : -1);
-    for (int i = 0; i < n; ++i) {
-      const KernelVariant* v = variant_at(i);
-      if (v->d == (int)d && v->grp == (int)grp && v->nb == nb && v->moe == moe) return v;
-    }
-  }
-  return variant_at(moe ? 7 : 6);   // the generic fallbacks: dense, mixture of experts
+// The kernel set of a batch size; null: none (the host admits no such batch).
+static const KernelVariant* pick_variant(uint32_t batch, bool moe, bool large_tasks) {
+  const int nb = batch == 1 ? (large_tasks && !moe ? 9 : 1) : batch < kMfmaMinBatch ? 2 : 8;
+  for (int i = 0; i < kNumVariants; ++i)
+    if (variant_at(i)->nb == nb && variant_at(i)->moe == moe) return variant_at(i);
+  return nullptr;
 }
 
 // Scratch memory of mpk_decode_step_static: part of the library image, one copy per GPU.  In host
 // code this name is only a handle for hipGetSymbolAddress; every use of the memory goes through the
-// device address that call returns (static_scratch_base below).
-static __device__ __align__(256) unsigned char scratch[MPK_STATIC_SCRATCH_BYTES];
+// device address that call returns (static_scratch_base below).  Behind it: the rope table.
+static __device__ __align__(256) unsigned char scratch[MPK_STATIC_SCRATCH_BYTES + kRopeTabFloatsMax * sizeof(float)];
 
 // Streaming-speed calibration (option xcd_balance): every workgroup reads its own contiguous slab
 // of `slab16` 16-byte words with the access pattern of the linear bodies and records how long it
@@ -293,12 +289,13 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
   // residency: dynamic LDS above half of a CU's 160 KB caps occupancy at one workgroup per CU
   // "large": 3 MB or more of weights per worker and layer (8B shape: 1.6 MB, 70B shape: 6.8 MB)
   const bool large_tasks = h.stats.weight_bytes / std::max(1u, cfg->n_layers) / std::max(1u, o.n_workers) >= (3u << 20);
-  g->kv = pick_variant(cfg->head_dim, cfg->n_q_heads / cfg->n_kv_heads, cfg->batch, cfg->n_experts != 0, large_tasks);
+  g->kv = pick_variant(cfg->batch, cfg->n_experts != 0, large_tasks);
+  if (!g->kv) { set_error("no kernel set for batch %u", cfg->batch); return fail(MPK_ERR_INTERNAL); }
   hipError_t e = reserve_lds((const void*)g->kv->mega, h.lds_bytes);
   if (e == hipSuccess) e = reserve_lds((const void*)g->kv->op, h.lds_bytes);
   if (e == hipSuccess) e = reserve_lds((const void*)g->kv->loop, h.lds_bytes);
   if (e == hipSuccess) e = reserve_lds((const void*)g->kv->hybrid, h.lds_bytes);
-  if (e == hipSuccess && g->kv->run_step) e = reserve_lds((const void*)g->kv->run_step, h.lds_bytes);
+  if (e == hipSuccess) e = reserve_lds((const void*)g->kv->run_step, h.lds_bytes);
   if (e != hipSuccess) { set_error("cannot reserve %u bytes of LDS: %s", h.lds_bytes, hipGetErrorString(e)); return fail(MPK_ERR_RESIDENCY); }
   int per_cu = 0;
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)g->kv->mega, kThreads, h.lds_bytes);
@@ -308,7 +305,8 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     return fail(MPK_ERR_RESIDENCY);
   }
   // activation arena + relocation of the descriptors
-  size_t arena_bytes = std::max<size_t>(h.arena_floats, 64) * sizeof(float);
+  const size_t rope_at = std::max<size_t>(h.arena_floats, 64);   // the rope table sits behind the activations
+  size_t arena_bytes = (rope_at + (size_t)cfg->batch * cfg->head_dim) * sizeof(float);
   e = hipMalloc((void**)&g->d_arena, arena_bytes);
   if (e != hipSuccess) { set_error("hipMalloc(%zu) for activations failed: %s", arena_bytes, hipGetErrorString(e)); return fail(MPK_ERR_OOM); }
   if (hipMemset(g->d_arena, 0, arena_bytes) != hipSuccess) { set_error("hipMemset failed"); return fail(MPK_ERR_HIP); }
@@ -390,7 +388,9 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     GraphConst c{};
     c.tasks = g->d_tasks; c.events = g->d_events; c.counters = g->d_counters; c.hier = g->d_hier;
     c.aot_off = g->d_aot_off; c.aot = g->d_aot; c.op_list = g->d_op_list; c.err = g->d_err;
-    c.inv_freq = g->d_inv_freq; c.grp_counters = g->d_grp; c.trace = g->d_trace;
+    c.inv_freq = g->d_inv_freq; c.rope_tab = g->d_arena + rope_at;
+    c.attn_shape = attn_shape_index(h.cfg.head_dim, h.cfg.n_q_heads / h.cfg.n_kv_heads, h.opt.kv_page_size ? 1u : 0u);
+    c.grp_counters = g->d_grp; c.trace = g->d_trace;
     c.timeout_ticks = g->timeout_ticks;
     c.n_workers = h.opt.n_workers;
     c.vocab = h.cfg.vocab; c.max_seq = h.cfg.max_seq; c.n_q = h.cfg.n_q_heads;
@@ -434,6 +434,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
       if ((st = upload(&g->d_tasks_static, ds)) != MPK_OK) return fail(st);
       GraphConst cs = c;
       cs.tasks = g->d_tasks_static;
+      cs.rope_tab = (float*)(g->static_base + MPK_STATIC_SCRATCH_BYTES);
       cs.counters = (uint32_t*)(g->static_base + g->st_counters);
       cs.hier = (uint32_t*)(g->static_base + g->st_hier);
       cs.grp_counters = (uint32_t*)(g->static_base + g->st_grp);
@@ -479,7 +480,7 @@ static mpk_status launch_steps(mpk_graph* g, uint32_t n_steps, const int32_t* to
   a.token_ids = token_ids; a.positions = positions; a.logits = logits_out;
   hipStream_t s = (hipStream_t)stream;
   float* arena = g->d_arena;
-  const size_t arena_words = std::max<size_t>(h.arena_floats, 64);
+  const size_t arena_words = std::max<size_t>(h.arena_floats, 64) + (static_scratch ? 0 : (size_t)h.cfg.batch * h.cfg.head_dim);   // (the rope table too)
   if (static_scratch) {
     // the step's working memory is the static array: counters start from zero every time (the
     // array is shared by all graphs on this GPU), so this is always "step one"
@@ -518,13 +519,12 @@ static mpk_status launch_steps(mpk_graph* g, uint32_t n_steps, const int32_t* to
     a.epoch = static_scratch ? 1u : g->epoch + 1;
     a.step = 0; a.n_steps = (uint16_t)n_steps;
     if (!static_scratch) g->epoch += n_steps;
-    // Several steps: one launch of the loop kernel -- or, where the kernel set has a single-step
-    // kernel for runs (every set compiled for a model shape), a launch of that kernel per step, back
-    // to back with no host synchronisation: inside the step loop the linear bodies come out slower
-    // (8B shape, batch 1: 3.12 against 3.01 ms per token; batch 8: 4.93 against 4.87), and the GPU
-    // front end overlaps back-to-back launches almost completely.  greedy_loop = 2 asks for the
-    // single launch regardless.
-    const bool by_step = n_steps > 1 && h.opt.greedy_loop != 2 && !g->n_sched && g->kv->run_step != nullptr;
+    // Several steps: a launch of the single-step kernel for runs per step, back to back with no host
+    // synchronisation -- inside the loop kernel's step loop the linear bodies come out slower (8B
+    // shape, batch 1: 3.12 against 3.01 ms per token; batch 8: 4.93 against 4.87), and the GPU front
+    // end overlaps back-to-back launches almost completely.  greedy_loop = 2 asks for the one launch
+    // of the loop kernel regardless.
+    const bool by_step = n_steps > 1 && h.opt.greedy_loop != 2 && !g->n_sched;
     if (by_step || n_steps == 1) a.flags |= kOneStepBit;
     if (by_step) {
       for (uint32_t i = 0; i < n_steps; ++i) {

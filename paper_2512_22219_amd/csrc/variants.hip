@@ -6,9 +6,9 @@
 namespace mpk {
 
 template <int I> struct VariantParams;
-#define MPK_PARAMS(I, D, G, N, M)                    \
+#define MPK_PARAMS(I, N, M)                          \
   template <> struct VariantParams<I> {              \
-    static constexpr int d = D, grp = G, nb = N;     \
+    static constexpr int nb = N;                     \
     static constexpr bool moe = M;                   \
   };
 MPK_VARIANT_LIST(MPK_PARAMS)
@@ -17,14 +17,9 @@ MPK_VARIANT_LIST(MPK_PARAMS)
 template <int I>
 static const KernelVariant* make_variant() {
   using P = VariantParams<I>;
-  constexpr bool split = P::nb == 8;   // matrix-core bodies: one kernel per launch path
-  // kernel sets compiled for a model shape: several steps are issued as a launch per step
-  void (*run_step)(StepArgs) = nullptr;
-  if constexpr (P::nb == 1 || P::nb == 9) run_step = mpk_mega_kernel<P::d, P::grp, P::nb, P::moe, 0, true>;
-  if constexpr (P::nb == 8) run_step = mpk_mega_kernel<P::d, P::grp, P::nb, P::moe, 1, true>;
-  static const KernelVariant v = {P::d, P::grp, P::nb, P::moe, mpk_mega_kernel<P::d, P::grp, P::nb, P::moe, split ? 1 : 0>,
-                                  mpk_op_kernel<P::d, P::grp, P::nb, P::moe>, mpk_loop_kernel<P::d, P::grp, P::nb, P::moe>,
-                                  mpk_mega_kernel<P::d, P::grp, P::nb, P::moe, split ? 2 : 0>, run_step};
+  static const KernelVariant v = {P::nb, P::moe, mpk_mega_kernel<P::nb, P::moe, false>, mpk_op_kernel<P::nb, P::moe>,
+                                  mpk_loop_kernel<P::nb, P::moe>, mpk_mega_kernel<P::nb, P::moe, true>,
+                                  mpk_mega_kernel<P::nb, P::moe, false, true>};
   return &v;
 }
 
@@ -51,9 +46,6 @@ MPK_DEFINE_VARIANT(5)
 #endif
 #if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 6
 MPK_DEFINE_VARIANT(6)
-#endif
-#if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 7
-MPK_DEFINE_VARIANT(7)
 #endif
 
 }  // namespace mpk
