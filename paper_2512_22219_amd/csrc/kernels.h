@@ -963,13 +963,13 @@ struct MfmaGeom {
   uint32_t K, nb, nrt;
   uint32_t Kc, nchunk;   // inputs per chunk, chunks
   uint32_t xstride;      // floats between staged rows
-  uint32_t rg, ks;       // row groups x K slices = 8
+  uint32_t rg, rgsh, ks;   // row groups (= 1 << rgsh) x K slices = 8
   uint32_t my_g, my_s;
   uint32_t nrtw;         // row tiles of this wavefront: 0 .. 4
   uint32_t kgpr;         // k-groups per round: 1, 2 or 4
 };
-__device__ __forceinline__ uint32_t mfma_group_tiles(uint32_t nrt, uint32_t rg, uint32_t g) {
-  return g < nrt ? min(4u, (nrt - g + rg - 1u) / rg) : 0u;
+__device__ __forceinline__ uint32_t mfma_group_tiles(uint32_t nrt, uint32_t rgsh, uint32_t g) {
+  return g < nrt ? min(4u, (nrt - g + (1u << rgsh) - 1u) >> rgsh) : 0u;
 }
 __device__ __forceinline__ MfmaGeom mfma_geom(uint32_t K, uint32_t nb, uint32_t nrt, uint32_t wave) {
   MfmaGeom G;
@@ -977,13 +977,13 @@ __device__ __forceinline__ MfmaGeom mfma_geom(uint32_t K, uint32_t nb, uint32_t 
   G.Kc = mfma_kchunk(nb);
   G.nchunk = (K + G.Kc - 1u) / G.Kc;
   G.xstride = G.Kc + kMfmaXPad;
-  uint32_t rg = 1;
-  while (4u * rg < nrt && rg < 8u) rg <<= 1;
+  const uint32_t rgsh = (nrt > 4u ? 1u : 0u) + (nrt > 8u ? 1u : 0u) + (nrt > 16u ? 1u : 0u), rg = 1u << rgsh;
   G.rg = rg;
-  G.ks = 8u / rg;
-  G.my_g = wave % rg;
-  G.my_s = wave / rg;
-  G.nrtw = mfma_group_tiles(nrt, rg, G.my_g);
+  G.rgsh = rgsh;
+  G.ks = 8u >> rgsh;
+  G.my_g = wave & (rg - 1u);
+  G.my_s = wave >> rgsh;
+  G.nrtw = mfma_group_tiles(nrt, rgsh, G.my_g);
   G.kgpr = G.nrtw >= 3u ? 1u : (G.nrtw == 2u ? 2u : 4u);
   return G;
 }
@@ -1283,22 +1283,38 @@ __device__ __forceinline__ uint32_t mfma_job(const StepArgs& a, const TaskDesc& 
 
 // Dot product of weight row r (16-row tile r / 16) with batch column bb from the partial tiles a
 // job left in LDS: the row tile's slot groups of slice 0, then those of slice 1, ... added in
-// that order.
+// that order.  Up to 32 partials, read eight at a time (one after the other they were a chain of LDS
+// round trips: 1.3 us of the 3 us between the last multiply and the notification).
 __device__ __forceinline__ float mfma_dot(const float* part, const MfmaGeom& G, uint32_t r, uint32_t bb) {
   const uint32_t rt = r >> 4, row = r & 15u;
-  const uint32_t g = rt % G.rg, j = rt / G.rg;
-  const uint32_t n = mfma_group_tiles(G.nrt, G.rg, g);   // row tiles of the wavefronts of group g
-  const uint32_t q0 = n >= 3u ? j : (n == 2u ? j : 0u), dq = n >= 3u ? 4u : (n == 2u ? 2u : 1u);
+  const uint32_t g = rt & (G.rg - 1u), j = rt >> G.rgsh;
+  const uint32_t n = mfma_group_tiles(G.nrt, G.rgsh, g);   // row tiles of the wavefronts of group g
+  const uint32_t psh = n >= 3u ? 0u : (n == 2u ? 1u : 2u);   // 1 << psh slot groups per slice, 4 >> psh apart
+  const uint32_t np = G.ks << psh;
+  const float* p0 = part + ((g * 4u + (n >= 2u ? j : 0u)) * 16u + row) * 16u + bb;
   float v = 0.f;
-  for (uint32_t s = 0; s < G.ks; ++s) {
-    const uint32_t w = s * G.rg + g;
-    for (uint32_t q = q0; q < 4u; q += dq) v += part[(((w * 4u + q) * 16u) + row) * 16u + bb];
+  for (uint32_t k0 = 0; k0 < np; k0 += 8u) {
+    float p[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8u; ++k) {
+      const uint32_t kk = k0 + k, s = kk >> psh, q = (kk & ((1u << psh) - 1u)) * (4u >> psh);
+      p[k] = kk < np ? p0[((s << G.rgsh) * 4u + q) * 256u] : 0.f;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 8u; ++k) v += p[k];   // (absent ones add zero)
   }
   return v;
 }
+// 1 / rms of staged row bb from the wavefronts' sums of squares (every thread for itself: eight reads in flight, no barrier)
+__device__ __forceinline__ float mfma_inv_rms(const float* ssq, uint32_t bb, uint32_t K, float eps) {
+  float ss = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) ss += ssq[w * 16 + bb];
+  return 1.0f / sqrtf(ss / (float)K + eps);
+}
 
 // LDS of a linear task (from the task area): job buffers (mfma_x_floats) | res [residual columns][16] f32
-// | ssq [8][16] f32 | 1/rms [16] f32.  A job takes up to 512 weight rows; a task of more (batch 3 and 4
+// | ssq [8][16] f32 | arrival flag.  A job takes up to 512 weight rows; a task of more (batch 3 and 4
 // with few, user-given tiles) is worked off in several, the input staged again for each.
 template <bool MEGA, class Svc = NoJit>
 __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
@@ -1348,21 +1364,13 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
     }
     trace_mark(a, t, 3);
     // ---- all wavefronts: add the K slices in order, epilogue, outputs; then the notification
-    float* inv_lds = ssq + 8 * 16;   // [16] 1/rms of each batch row
-    if (pro_norm) {
-      if (threadIdx.x < 16) {
-        float ss = 0.f;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) ss += ssq[w * 16 + threadIdx.x];
-        inv_lds[threadIdx.x] = 1.0f / sqrtf(ss / (float)K + t.f0);
-      }
-      lds_barrier();
-    }
     {
       float* outp = (t.flags & TF_OUT_LOGITS) ? a.logits : t.out;
-      for (uint32_t i = threadIdx.x; i < nj * nb; i += kThreads) {
-        const uint32_t cc = i / nb, bb = i % nb;
-        const float inv = pro_norm ? inv_lds[bb] : 1.0f;
+      const uint32_t sh = nb <= 4u ? 2u : (nb <= 8u ? 3u : 4u);   // batch columns padded to 4, 8 or 16 lanes: no division
+      for (uint32_t i = threadIdx.x; i < nj << sh; i += kThreads) {
+        const uint32_t cc = i >> sh, bb = i & ((1u << sh) - 1u);
+        if (bb >= nb) continue;
+        const float inv = pro_norm ? mfma_inv_rms(ssq, bb, K, t.f0) : 1.0f;
         float v;
         if (gateup) {
           const float gte = mfma_dot(part, G, 2 * cc, bb) * inv, up = mfma_dot(part, G, 2 * cc + 1, bb) * inv;
@@ -1609,15 +1617,11 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
   };
   if (mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, wait_fn) != kLinDone) return false;
   const uint32_t ncols = (ntile * 16u) >> gateup, col0 = (tile0 * 16u) >> gateup;
-  for (uint32_t i = threadIdx.x; i < ncols * ne; i += kThreads) {
-    const uint32_t cc = i / ne, bb = i % ne;
-    float inv = 1.0f;
-    if (pro_norm) {
-      float ss = 0.f;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) ss += ssq[w * 16 + bb];
-      inv = 1.0f / sqrtf(ss / (float)K + t.f0);
-    }
+  const uint32_t sh = ne <= 1u ? 0u : (ne <= 2u ? 1u : (ne <= 4u ? 2u : (ne <= 8u ? 3u : 4u)));
+  for (uint32_t i = threadIdx.x; i < ncols << sh; i += kThreads) {
+    const uint32_t cc = i >> sh, bb = i & ((1u << sh) - 1u);
+    if (bb >= ne) continue;
+    const float inv = pro_norm ? mfma_inv_rms(ssq, bb, K, t.f0) : 1.0f;
     float v;
     if (gateup) {
       const float gte = mfma_dot(part, G, 2 * cc, bb) * inv, up = mfma_dot(part, G, 2 * cc + 1, bb) * inv;
