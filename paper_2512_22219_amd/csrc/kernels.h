@@ -167,6 +167,16 @@ __device__ __forceinline__ u32x4 ld_stream16(const void* p) {
   return __builtin_nontemporal_load(as_global((const u32x4*)p));
 }
 
+// 16-byte non-temporal load at byte `off` of a run of memory that ends at byte `end`, with the hardware's
+// range check: lanes at or past the end touch no memory and get zeros, and end = 0 is a load that costs an
+// issue slot.  The pipelines below issue the same number of loads whatever there is left to fetch,
+// because the compiler counts the loads in flight at compile time: behind a branch around some of them it
+// waits for everything older.  (off + 16 must not wrap; p uniform.)
+__device__ __forceinline__ u32x4 ld_stream16_ranged(const void* p, uint32_t end, uint32_t off) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)end, 0x00020000);
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 2));   // 2: non-temporal
+}
+
 template <typename T>
 __device__ __forceinline__ T ld_const_record(const T* p) {   // sizeof(T) a multiple of 16
   union {
@@ -1071,10 +1081,12 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
     wq[q][1] = row_off(rt, 8u + lrow);
   }
   // load h of the k-group at input k of the rows at byte offsets ro: this lane's 8 inputs start at
-  // k + lk, or are the row's last 8 when that lies past its end (their staged inputs are zeros)
+  // k + lk, or are the row's last 8 when that lies past its end (their staged inputs are zeros).  Not
+  // real: past the range of the load (a matrix ends below it, its size being a multiple of 16 below 4 GB)
+  constexpr uint32_t kRange = 0xFFFFFFF0u;
+  const uint16_t* wb = uniform_ptr(wbase);
   auto ld_frag = [&](uint32_t ro, uint32_t k, bool real) {
-    const uint32_t off = real ? ro + 2u * min(k + lk, K - 8u) : 0u;   // not real: every lane the matrix' first 16 bytes
-    return __builtin_nontemporal_load((const MPK_GLOBAL u32x4*)((const MPK_GLOBAL char*)wbase + off));
+    return ld_stream16_ranged(wb, kRange, real ? ro + 2u * min(k + lk, K - 8u) : kRange);
   };
   // the wavefront's run of k-groups in chunk c; a chunk takes an even number of round slots
   // (>= 2), so that even slots always use fragment buffer A and odd ones B
@@ -1088,11 +1100,10 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   };
   // requests the 4 FR kilobytes of round slot (c, i) into buf; buf[FR Q + u] = load u of slot
   // group Q's k-group (rows 8 u .. 8 u + 7 of the tile, see above; two fragments after the
-  // exchange in step).  Always that many loads, no branch: the compiler counts the loads in flight statically, and a
-  // load that may or may not have been issued makes it wait for everything older than it could
-  // be -- in effect for the whole pipeline, every round.  For a slot group that does not exist
-  // (past the end of the run, or no row tile) all lanes read the matrix' first 16 bytes instead
-  // (one cached line; nobody uses the result).
+  // exchange in step).  Always that many loads, no branch (see ld_stream16_ranged).  A slot group that
+  // does not exist (past the end of the run, or no row tile) is a load past the range.  (All lanes of all
+  // wavefronts of an XCD used to read the matrix' first 16 bytes instead: up to 4096 requests for one
+  // line at the end of every task, ahead of its output stores.)
   auto request_round = [&](u32x4* buf, uint32_t c, uint32_t i) {
     const uint32_t cc = min(c, nchunk - 1u);
     const uint32_t kg0 = run_lo(cc) + i * kgpr, hi = c < nchunk ? run_hi(cc) : 0u;
