@@ -325,6 +325,16 @@ __device__ __forceinline__ u32x4 ld_row16_coherent(const uint16_t* p) {   // p 1
   return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
 }
 
+// Waits for this wavefront's own loads and stores (and LDS operations).  A builtin and not assembly text:
+// the compiler then knows that nothing is in flight any more.  Otherwise it takes the last loads of a
+// task for pending in the next one, and copies into LDS (flat accesses to it, which may complete out of
+// order) make it wait for everything in flight wherever it needs one load.
+__device__ __forceinline__ void drain_vmem() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+  asm volatile("" ::: "memory");
+}
+
 __device__ __forceinline__ float dot8(const u32x4& w, const float4& x0, const float4& x1, float acc) {
   acc = fmaf(bf16_lo(w.x), x0.x, acc);
   acc = fmaf(bf16_hi(w.x), x0.y, acc);
@@ -406,6 +416,7 @@ struct EventProbe {   // a look at an event whose loads may still be in flight
   uint32_t seen = 0, need = 1;
 };
 __device__ __forceinline__ EventProbe probe_event(const StepArgs& a, int32_t e, int lane);
+__device__ __forceinline__ bool probe_reached(const EventProbe& p);
 __device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag);
 __device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag, const EventProbe& probe);
 
@@ -608,13 +619,28 @@ struct JitWatch {
   static constexpr bool enabled = true;
   uint32_t jit_head;   // the worker's consumer ticket of its just-in-time queue
 };
+// The first look at an event, by the first wavefront and ahead of the task's weight requests: loads
+// complete in the order they were issued, so a poll behind the requests comes back behind the weights -- 3
+// to 5 us when every compute unit asks for its share at once, which is what happens after an operator's
+// last tasks.  The worker that finished last finds the event activated and stages its input behind
+// the weights at once instead of a round trip after them.
+template <class Svc>
+__device__ __forceinline__ EventProbe linear_probe(const StepArgs& a, int32_t wait_ev, uint32_t wave, int lane) {
+  EventProbe p;   // (not reached)
+  if (!Svc::enabled && wait_ev >= 0 && wave == 0) p = probe_event(a, wait_ev, lane);
+  return p;
+}
 // The wait of a linear task for its dependent event: kLinDone (activated), kLinAbort, kLinPreempted.
 template <class Svc>
 __device__ __forceinline__ uint32_t linear_wait(const StepArgs& a, int32_t wait_ev, uint32_t* s_flag, uint32_t wave, int lane,
-                                                const Svc& svc) {
+                                                const Svc& svc, const EventProbe& probe) {
   if (wave == 0) {
-    if constexpr (Svc::enabled) poll_event_or_jit_wave0(a, wait_ev, s_flag, lane, svc.jit_head);
-    else poll_event_wave0(a, wait_ev, s_flag, lane);
+    if constexpr (Svc::enabled) {
+      poll_event_or_jit_wave0(a, wait_ev, s_flag, lane, svc.jit_head);
+    } else {
+      if (!probe_reached(probe)) poll_event_wave0(a, wait_ev, s_flag, lane);
+      else if (lane == 0) *s_flag = 1;
+    }
   }
   lds_barrier();
   return __builtin_amdgcn_readfirstlane(*s_flag);   // (uniform; tell the compiler)
@@ -700,7 +726,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   }
   // ---- dependent event: wavefront 0 polls, the others wait at the barrier
   if (wait_ev >= 0) {
-    const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc);
+    const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc, EventProbe{});
     if (w != kLinDone) return w;   // aborted, or pre-empted by a just-in-time task: the requested weights are dropped
   }
   trace_mark(a, t, 1);
@@ -882,7 +908,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     }
     if (MEGA) {   // wait for exactly these stores
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      drain_vmem();
       trace_mark(a, t, 7);
     }
   }
@@ -1032,7 +1058,8 @@ __device__ __forceinline__ void pair_to_operands(u32x4& l0, u32x4& l1) {
 //                  lane's row of 16-row tile rt (32 bits: a scalar base and one vector offset per
 //                  load, no address pairs to keep); loads are clamped to the end of the row
 //   src_row(b)   : fp32 input row b (read with coherent loads), b < nb
-//   wait_fn()    : called after the first two rounds of weights have been requested (cross-task
+//   probe_fn()   : called before any request: the first look at the event, handed to wait_fn
+//   wait_fn(p)   : called after the first two rounds of weights have been requested (cross-task
 //                  pre-loading, Section 5.3: 16 KB per wavefront, 32 MB over the chip); returns
 //                  kLinDone to go on
 // LDS: x [nb][xstride] f32 at `lds`, reused at the end for the per-wavefront partial tiles
@@ -1043,10 +1070,10 @@ __device__ __forceinline__ void pair_to_operands(u32x4& l0, u32x4& l1) {
 // the mid term of the same rows (PACK 2: two multiplies per fragment, the lo term alone in the
 // second, on accumulators of its own); up to 4 staged rows take hi | mid | lo in columns 0..3 |
 // 4..7 | 8..11 (PACK 3: one multiply).  The column groups are added up once, at the end.
-template <int PACK, class RowOff, class SrcRow, class Wait>
+template <int PACK, class RowOff, class SrcRow, class Probe, class Wait>
 __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const TaskDesc& t, float* lds, float* ssq, const MfmaGeom& G,
                                                     const uint16_t* wbase, RowOff row_off, SrcRow src_row, bool pro_norm,
-                                                    const uint16_t* gain, Wait wait_fn) {
+                                                    const uint16_t* gain, Probe probe_fn, Wait wait_fn) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t K = G.K, nb = G.nb, nrt = G.nrt, Kc = G.Kc, nchunk = G.nchunk, xstride = G.xstride;
@@ -1104,14 +1131,14 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   // does not exist (past the end of the run, or no row tile) is a load past the range.  (All lanes of all
   // wavefronts of an XCD used to read the matrix' first 16 bytes instead: up to 4096 requests for one
   // line at the end of every task, ahead of its output stores.)
-  auto request_round = [&](u32x4* buf, uint32_t c, uint32_t i) {
+  auto request_round = [&](u32x4* buf, uint32_t c, uint32_t i, bool wanted = true) {
     const uint32_t cc = min(c, nchunk - 1u);
     const uint32_t kg0 = run_lo(cc) + i * kgpr, hi = c < nchunk ? run_hi(cc) : 0u;
     const uint32_t k0 = cc * Kc;
     static_for<0, 4>([&](auto Qc) {
       constexpr uint32_t Q = (uint32_t)decltype(Qc)::value;
       const uint32_t kg = kg0 + (Q >> sh);
-      const bool ok = kg < hi && (kgpr == 1u ? Q < nrtw : true);
+      const bool ok = wanted && kg < hi && (kgpr == 1u ? Q < nrtw : true);
 #pragma unroll
       for (int u = 0; u < (int)FR; ++u) buf[FR * Q + u] = ld_frag(wq[Q][u], k0 + kg * KG, ok);
     });
@@ -1122,8 +1149,11 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   uint16_t* gl = (uint16_t*)(xs + (size_t)nb * xstride);   // [Kc]
   auto request_gains = [&](uint32_t c) {
     const uint32_t k0 = c * Kc, klen = min(Kc, K - k0), col = 8u * threadIdx.x;
+    // (a buffer load: the compiler takes a global load into LDS for a flat access, whose order it does not
+    // know, and until it has landed waits for everything in flight instead of for the event's probe alone)
     if (pro_norm && col < klen)
-      __builtin_amdgcn_global_load_lds(as_global((const u32x4*)(gain + k0 + col)), (lds_ptr_t)(gl + wave * 512u), 16, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(uniform_ptr(gain)), 0, (int)(2u * K), 0x00020000),
+                                               (lds_ptr_t)(gl + wave * 512u), 16, (int)(2u * (k0 + col)), 0, 0, 0);
     // between the end of the row and the end of its last k-group the staged inputs are zeros, and
     // so must the gains be: whatever an earlier workgroup left there may read as NaN, and
     // 0 x NaN is NaN
@@ -1135,15 +1165,14 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   // Both rounds (16 KB per wavefront) are requested before the event.  A wavefront sees its loads
   // complete in the order it issued them, so whatever is requested now stands between the event
   // and the staged input: more than this measured slower.
+  const auto probe = probe_fn();
   request_gains(0u);
-  if (preload) {
-    request_round(wA, 0u, 0u);
-    asm volatile("; first round requested" ::: "memory");
-    request_round(wB, 0u, 1u);
-    asm volatile("; second round requested" ::: "memory");
-  }
+  request_round(wA, 0u, 0u, preload);   // (not wanted: loads past the range, see ld_stream16_ranged)
+  asm volatile("; first round requested" ::: "memory");
+  request_round(wB, 0u, 1u, preload);
+  asm volatile("; second round requested" ::: "memory");
   {
-    const uint32_t w = wait_fn();
+    const uint32_t w = wait_fn(probe);
     if (w != kLinDone) return w;   // aborted or pre-empted: the requested weights are dropped
   }
   trace_mark(a, t, 1);
@@ -1171,7 +1200,7 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
     }
     if (kpad != klen)
       for (uint32_t i = threadIdx.x; i < nb * (kpad - klen); i += kThreads) xs[(size_t)(i / (kpad - klen)) * xstride + klen + i % (kpad - klen)] = 0.f;
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wavefront's copies have landed
+    drain_vmem();   // this wavefront's copies have landed
   };
   // sums of squares of the staged rows (before the gains), needed only by the epilogue: taken
   // behind the chunk's multiplies by wavefronts 0..3 (rows w, w + 4, ...), which are through their
@@ -1256,6 +1285,7 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
     if (pro_norm) row_squares(c);   // (the chunk is still staged: the next barrier is ahead)
   }
   trace_mark(a, t, 8);
+  drain_vmem();   // (nothing but loads past the range)
   // ---- the column groups of a packed multiply added up: afterwards column b < nb holds the sum
   if (PACK != 1) {
 #pragma unroll
@@ -1283,13 +1313,13 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   return kLinDone;
 }
 
-template <class RowOff, class SrcRow, class Wait>
+template <class RowOff, class SrcRow, class Probe, class Wait>
 __device__ __forceinline__ uint32_t mfma_job(const StepArgs& a, const TaskDesc& t, float* lds, float* ssq, const MfmaGeom& G,
                                              const uint16_t* wbase, RowOff row_off, SrcRow src_row, bool pro_norm,
-                                             const uint16_t* gain, Wait wait_fn) {
-  if (G.nb <= 4u) return mfma_job_packed<3>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, wait_fn);
-  if (G.nb <= 8u) return mfma_job_packed<2>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, wait_fn);
-  return mfma_job_packed<1>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, wait_fn);
+                                             const uint16_t* gain, Probe probe_fn, Wait wait_fn) {
+  if (G.nb <= 4u) return mfma_job_packed<3>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, probe_fn, wait_fn);
+  if (G.nb <= 8u) return mfma_job_packed<2>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, probe_fn, wait_fn);
+  return mfma_job_packed<1>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, probe_fn, wait_fn);
 }
 
 // Dot product of weight row r (16-row tile r / 16) with batch column bb from the partial tiles a
@@ -1355,9 +1385,10 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
       const uint32_t wrow = gateup ? ((r >> 1) + ((r & 1u) ? t.p0 : 0u)) : r;
       return wrow * ldw * 2u;   // bytes from the task's first row; the host checks that they stay below 4 GB
     };
-    auto wait_fn = [&]() -> uint32_t {
+    auto probe_fn = [&]() { return linear_probe<Svc>(a, r0 == 0 ? wait_ev : -1, wave, lane); };
+    auto wait_fn = [&](const EventProbe& probe) -> uint32_t {
       if (wait_ev >= 0 && r0 == 0) {
-        const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc);
+        const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc, probe);
         if (w != kLinDone) return w;
       }
       // the residual slice of this tile goes out first (tile-local, small): its round trip overlaps the staging
@@ -1370,7 +1401,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
       return kLinDone;
     };
     {
-      const uint32_t w = mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, wait_fn);
+      const uint32_t w = mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn);
       if (w != kLinDone) return w;
     }
     trace_mark(a, t, 3);
@@ -1398,7 +1429,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
   if (MEGA || splitk) {
     // every wavefront's coherent stores complete before anyone is told
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    drain_vmem();
     lds_barrier();
   }
   if (splitk) {
@@ -1424,7 +1455,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
         st_act(xout + (size_t)(t.b0 + bb) * Hs + row0 + cc, v);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      drain_vmem();
     }
     lds_barrier();
   }
@@ -1620,13 +1651,14 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
     return wrow * K * 2u;   // bytes from the expert's first row
   };
   auto src_row = [&](uint32_t b) { return t.in + (size_t)__builtin_amdgcn_readfirstlane(rowin[b]) * t.ld_in; };   // uniform: scalar base addresses
-  auto wait_fn = [&]() -> uint32_t {
+  auto probe_fn = [&]() { return linear_probe<NoJit>(a, wait_ev, wave, lane); };
+  auto wait_fn = [&](const EventProbe& probe) -> uint32_t {
     if (wait_ev < 0) return kLinDone;
-    const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, NoJit{});
+    const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, NoJit{}, probe);
     trace_mark(a, t, 1);
     return w;
   };
-  if (mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, wait_fn) != kLinDone) return false;
+  if (mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn) != kLinDone) return false;
   const uint32_t ncols = (ntile * 16u) >> gateup, col0 = (tile0 * 16u) >> gateup;
   const uint32_t sh = ne <= 1u ? 0u : (ne <= 2u ? 1u : (ne <= 4u ? 2u : (ne <= 8u ? 3u : 4u)));
   for (uint32_t i = threadIdx.x; i < ncols << sh; i += kThreads) {
@@ -2330,7 +2362,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     // Arrival counter of (layer, sequence, KV head): the chunk task that arrives last sees all C
     // partials complete and merges them into the attention output.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    drain_vmem();
     __syncthreads();
     if (threadIdx.x == 0) {
       uint32_t* cnt = a.g->grp_counters + t.p2 + b * nkv + g;
@@ -2451,7 +2483,7 @@ __device__ __forceinline__ void body_argmax(const TaskDesc& t, const StepArgs& a
         float* pairs = t.out + (size_t)b * t.ld_out;
         st_act(pairs + 2u * j, m);
         st_act_u32((uint32_t*)pairs + 2u * j + 1u, mi);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the pair is in place before the arrival counts
+        drain_vmem();   // the pair is in place before the arrival counts
         uint32_t* cnt = a.g->grp_counters + t.p2 + b;
         const uint32_t old = __hip_atomic_fetch_add(as_global(cnt), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         pick = (old + 1u) % T == 0u;   // every step adds exactly T
@@ -2579,7 +2611,7 @@ __device__ __forceinline__ void body_serve(const StepArgs& a) {
           st_act_u32(to + i, v);
           st_act_u32(from + i, i == 0u ? src : 0xFFFFFFFFu);   // vacated (a later move may fill it again)
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the next move may read what this one wrote
+        drain_vmem();   // the next move may read what this one wrote
       }
       const int src_lane = (int)my_src;
       const int32_t req_m = __shfl(req, src_lane, 64);
@@ -2593,7 +2625,7 @@ __device__ __forceinline__ void body_serve(const StepArgs& a) {
     }
   }
   // the pages pushed above may be popped below, by other lanes: the stores must have completed
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  drain_vmem();
   // ---- (2) arrivals enter, in order, while their pages are there
   const bool idle = mine && req < 0;
   const uint64_t idle_mask = __ballot(idle);
@@ -2802,7 +2834,7 @@ __device__ __forceinline__ void notify_event(const StepArgs& a, int32_t e) {
 __device__ __forceinline__ void signal_event(const StepArgs& a, const TaskDesc& t, int32_t e) {
   // every wavefront waits until its own agent-scope stores have completed at the coherence point
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  drain_vmem();
   trace_mark(a, t, 6);
   __syncthreads();
   trace_mark(a, t, 7);
@@ -2840,7 +2872,7 @@ __device__ __forceinline__ void poll_event_or_jit_wave0(const StepArgs& a, int32
 // then notify the event.
 __device__ __forceinline__ void signal_from_wave0(const StepArgs& a, const TaskDesc& t, int32_t e, int lane) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  drain_vmem();
   trace_mark(a, t, 7);
   if (lane == 0) notify_event(a, e);
 }
