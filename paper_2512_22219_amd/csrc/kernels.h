@@ -1409,9 +1409,11 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
     const uint32_t Rj = min(R - r0, kMfmaJobRows), cj = r0 >> gateup, nj = Rj >> gateup;   // the job's rows, columns
     const MfmaGeom G = mfma_geom(K, nb, (Rj + 15u) / 16u, wave);
     auto row_off = [&](uint32_t rt, uint32_t row) {       // row: this lane's row of the 16-row tile
-      const uint32_t r = r0 + min(rt * 16u + row, Rj - 1u);    // rows past the end repeat the last one
+      const uint32_t r = min(rt * 16u + row, Rj - 1u);    // rows past the end repeat the last one
       const uint32_t wrow = gateup ? ((r >> 1) + ((r & 1u) ? t.p0 : 0u)) : r;
-      return wrow * ldw * 2u;   // bytes from the task's first row; the host checks that they stay below 4 GB
+      // bytes from the job's first row: below 4 GB also where one task holds all of a larger matrix (batch 3
+      // and 4 take any vocabulary; the gate/up halves of inputs that fit the LDS lie well within 4 GB)
+      return wrow * ldw * 2u;
     };
     auto probe_fn = [&]() { return linear_probe<Svc>(a, r0 == 0 ? wait_ev : -1, wave, lane); };
     auto wait_fn = [&](const EventProbe& probe) -> uint32_t {
@@ -1429,7 +1431,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
       return kLinDone;
     };
     {
-      const uint32_t w = mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn);
+      const uint32_t w = mfma_job(a, t, lds, ssq, G, W + (size_t)cj * ldw, row_off, src_row, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn);
       if (w != kLinDone) return w;
     }
     trace_mark(a, t, 3);
