@@ -171,7 +171,10 @@ __device__ __forceinline__ u32x4 ld_stream16(const void* p) {
 // range check: lanes at or past the end touch no memory and get zeros, and end = 0 is a load that costs an
 // issue slot.  The pipelines below issue the same number of loads whatever there is left to fetch,
 // because the compiler counts the loads in flight at compile time: behind a branch around some of them it
-// waits for everything older.  (off + 16 must not wrap; p uniform.)
+// waits for everything older.  (off + 16 must not wrap; p uniform.)  Matrix-core tasks, us a step against
+// reading one cached line instead: 8B layers at batch 16 1283 -> 1244, odd sizes at batch 5 595 -> 574.
+// Not for the vector body: such a load still takes 16 cycles of the CU's address unit, and the 36 a short
+// task has no use for, times eight wavefronts, cost more than exact counts give (8B, batch 1: 2798 -> 3129).
 __device__ __forceinline__ u32x4 ld_stream16_ranged(const void* p, uint32_t end, uint32_t off) {
   const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)end, 0x00020000);
   return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 2));   // 2: non-temporal
@@ -624,7 +627,10 @@ struct JitWatch {
 // complete in the order they were issued, so a poll behind the requests comes back behind the weights -- 3
 // to 5 us when every compute unit asks for its share at once, which is what happens after an operator's
 // last tasks.  The worker that finished last finds the event activated and stages its input behind
-// the weights at once instead of a round trip after them.
+// the weights at once instead of a round trip after them.  With the exact load counts that it needs
+// (drain_vmem), us a step: 8B layers at batch 8 1117 -> 1069, at batch 16 1245 -> 1195, 4B class 859 -> 828.
+// (Input ahead of the weights where the event is active, behind a barrier that shares the probe: 1154 at
+// batch 8 -- everybody's weights leave a round trip later.)
 template <class Svc>
 __device__ __forceinline__ EventProbe linear_probe(const StepArgs& a, int32_t wait_ev, uint32_t wave, int lane) {
   EventProbe p;   // (not reached)
@@ -635,6 +641,7 @@ __device__ __forceinline__ EventProbe linear_probe(const StepArgs& a, int32_t wa
 // its two events, six lines -- into the scalar cache.  Cold, a task pays a chain of three misses
 // before its first request and another before its notification, 0.7 us each, on the path from
 // one operator to the next.  One wavefront does it while the first one polls for this task's event.
+// (us a step: 8B at batch 1 2830 -> 2799, 1B class 793 -> 788, serving burst 9515 -> 9378.)
 __device__ __forceinline__ void warm_descriptors(const StepArgs& a, uint32_t ti) {
   const MPK_CONST TaskDesc* td = (const MPK_CONST TaskDesc*)(a.tasks + ti);
   const int32_t dep = td->dep_event, trig = td->trig_event;
@@ -956,8 +963,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   return kLinDone;
 }
 
-// ------------------------------------------------------------------------------ linear tasks, batch 5..16
-// The same operator for 5 to 16 batch rows, on the matrix cores.  At batch 8 the vector ALUs
+// ------------------------------------------------------------------------------ linear tasks, batch 3..16
+// The same operator for 3 to 16 batch rows, on the matrix cores.  At batch 8 the vector ALUs
 // would need about as many cycles for the multiply-adds as HBM needs to deliver the weights; one
 // v_mfma_f32_16x16x32_bf16 does 16 weight rows x 32 inputs x 16 batch columns at once.
 //   A operand = weights: lane l holds row (l % 16) of a 16-row tile and 8 of the 32 inputs of the

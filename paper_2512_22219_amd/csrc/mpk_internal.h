@@ -259,7 +259,7 @@ constexpr uint32_t kMoeMaxExperts = 512, kMoeMaxPairs = 256, kMoeMaxTopK = 16;
 constexpr uint32_t kMfmaMinBatch = 3;   // linear operators of this many rows and more run on the matrix cores
 constexpr uint32_t kMfmaJobRows = 512;  // weight rows of one matrix-core job
 
-// Matrix-core jobs (batch 5..16 and expert jobs) stage the input in LDS as fp32, a chunk of this
+// Matrix-core jobs (batch 3..16 and expert jobs) stage the input in LDS as fp32, a chunk of this
 // many inputs at a time; one definition for the host's LDS requirement and the kernels' layout.
 constexpr uint32_t mfma_kchunk(uint32_t nb) { return nb <= 8u ? 4096u : 2048u; }
 constexpr uint32_t kMfmaXPad = 32;   // floats between staged rows beyond the chunk (bank spread)
