@@ -155,8 +155,7 @@ typedef struct mpk_compile_options {
                                kernel runs until its workload is done (Section 5).  Such a
                                graph is run with mpk_decode_steps only.  How n steps are
                                issued is the library's choice: one launch of the persistent
-                               kernel, or -- for the model shapes the library has specialised
-                               kernels for, whose linear bodies run 1 to 3.5 % slower inside
+                               kernel, or -- since the linear bodies run 1 to 3.5 % slower inside
                                the step loop and whose paged attention needs slower loads
                                inside a launch of several steps -- n launches of the
                                single-step kernel back to back, with no host synchronisation

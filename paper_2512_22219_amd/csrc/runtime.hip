@@ -1,5 +1,5 @@
 // Host side of the runtime: the C ABI entry points (compile, launch, status, export, graph sets).
-// The kernels live in kernels.h and are instantiated by variants.hip, one specialised set per
+// The kernels live in kernels.h and are instantiated by variants.hip, one set per
 // translation unit; this file only picks a set and launches it.
 #include <algorithm>
 

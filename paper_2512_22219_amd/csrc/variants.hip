@@ -1,4 +1,4 @@
-// Instantiates the kernels.  Built once per specialised set with -DMPK_VARIANT_INDEX=i (the sets
+// Instantiates the kernels.  Built once per set with -DMPK_VARIANT_INDEX=i (the sets
 // compile in parallel, each in a translation unit of its own); without the definition every set is
 // instantiated here.
 #include "kernels.h"
