@@ -156,8 +156,8 @@ typedef struct mpk_compile_options {
                                graph is run with mpk_decode_steps only.  How n steps are
                                issued is the library's choice: one launch of the persistent
                                kernel, or -- since the linear bodies run 1 to 3.5 % slower inside
-                               the step loop and whose paged attention needs slower loads
-                               inside a launch of several steps -- n launches of the
+                               the step loop and paged attention needs slower loads in a
+                               launch of several steps -- n launches of the
                                single-step kernel back to back, with no host synchronisation
                                between them; 2 = always the one launch                          */
   uint32_t kv_batch;        /* number of sequences the KV cache is laid out for (the `batch`

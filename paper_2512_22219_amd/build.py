@@ -1,7 +1,7 @@
 """Build libmpk.so (host compiler + HIP runtime) for gfx950, in-tree.
 
-The kernels come in sets (batch class, with or without mixture of experts); csrc/variants.hip is compiled once per set, in parallel, and the objects are linked with
-the host side.  Objects go to _build/ next to this file (not committed)."""
+The kernels come in sets (batch class, with or without mixture of experts); csrc/variants.hip is
+compiled once per set, in parallel, and the objects are linked with the host side.  Objects go to _build/ next to this file (not committed)."""
 import os
 import re
 import subprocess
