@@ -1937,10 +1937,9 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
 //   p       = 2^(S - m), fp32, lane = (column, 4 rows of each tile)
 //   output  O[16 rows][D] += P[16][32] x V[32][D]               D / 16 multiplies
 // with v_mfma_f32_16x16x32_bf16.  Cache rows are bf16 as stored; queries and probabilities are
-// fp32 and enter as the exact sum of three bf16 terms (split_hi_mid_lo), so every product is exact
-// and the only rounding is the fp32 accumulation, as in vector arithmetic.  The 16 columns (rows of
-// P) hold the terms side by side: up to 4 query heads per KV head hi | mid | lo | 0 in four groups of
-// four (fewer heads repeat), one multiply; 8 heads hi | mid in two groups of eight and a second
+// fp32 and enter as the exact sum of three bf16 terms (split_hi_mid_lo), so every product is exact.
+// The 16 columns (rows of P) hold the terms side by side: up to 4 query heads per KV head
+// hi | mid | lo | 0 in four groups of four (fewer heads repeat), one multiply; 8 heads hi | mid in two groups of eight and a second
 // multiply with lo | 0 into the same accumulators.  Adding the column groups (one or two DPP row
 // rotations) leaves every lane with the whole score of its head.
 //
@@ -1957,6 +1956,12 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
 //   V (B operand, lane = column + 16 x row group): a lane loads its 8 rows at D / 16 consecutive
 //     elements (whole rows per instruction) and transposes the 8 x (D / 16) block in its registers
 //     (v_perm_b32); tile t then covers output elements (D / 16) column + t
+//
+// Rounding: what is left is the fp32 sums.  A score's D products go through D / 32 multiplies with
+// accumulators of their own, added pairwise: chained through one accumulator every multiply rounds at the
+// size the sum has reached, and an error of a score is a relative error of its weight (logits
+// against 64 bits, root mean square over inputs with scores up to some tens: D = 128 with 8 query heads per KV
+// head 1.53e-6 chained, 0.88e-6 pairwise, 0.99e-6 in vector arithmetic of runs of eight inputs).
 //
 // K and V rows of a block are requested ahead: the first block's before the task's event, the next
 // K as soon as K has been multiplied, the next V likewise -- 8 to 16 KB in flight per wavefront
@@ -2059,9 +2064,12 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   // sequence, chunk and chunk count the task works on, first task of that sequence
   uint32_t b = bs, c = u % Cs, C = Cs, v0 = bs * Cs;
   if (t.flags & TF_ATTN_BALANCE) attn_deal<PAGED>(a, Cs, bs * Cs + c, &b, &c, &C, &v0);
+  // a probability is 2^(s * kScale - m): one fused multiply-add and one v_exp_f32.  (The factor folded into
+  // the query rounds every query element once more.)
+  constexpr float kScale = (float)(1.4426950408889634074 / (D == 128 ? 11.313708498984760390 : 8.0));   // log2(e) / sqrt(d)
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float* qs = lds;                                   // [grp][d], times log2(e) / sqrt(d)
+  float* qs = lds;                                   // [grp][d]
   float* wpart = qs + grp * d;                       // [NW][NTERM][grp][WS]: partial outputs
   float* ml = wpart + NW * NTERM * grp * WS;         // [NW][grp][2]: running maximum and sum
   float* knew = ml + NW * grp * 2;                   // [d], [d]: the appended rows as stored; [8] their scores
@@ -2162,8 +2170,6 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     for (uint32_t i = threadIdx.x; i < per; i += kThreads) st_act(outp + i, ((i % (d + 2)) == d) ? -INFINITY : 0.f);
     return true;
   }
-  // scores are kept times log2(e), folded into the query: a probability is one v_exp_f32
-  const float q_scale = 1.44269504088896341f / sqrtf((float)d);
   const float* qsrc = t.in + (size_t)b * t.ld_in + (size_t)g * grp * d;
   uint16_t *krow = nullptr, *vrow = nullptr;   // the appended row in the cache
   if (has_new) {
@@ -2192,8 +2198,8 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
         u0 *= inv * bf16_to_f32(as_global(gq)[e]);
         u1 *= inv * bf16_to_f32(as_global(gq)[e + half]);
       }
-      qs[j * d + e] = (u0 * r.x - u1 * r.y) * q_scale;
-      qs[j * d + e + half] = (u1 * r.x + u0 * r.y) * q_scale;
+      qs[j * d + e] = u0 * r.x - u1 * r.y;
+      qs[j * d + e + half] = u1 * r.x + u0 * r.y;
     }
     if (has_new) {
       const float* ksrc = t.in + (size_t)b * t.ld_in + (size_t)(nq + g) * d;
@@ -2228,7 +2234,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
       }
     }
   } else {
-    for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) qs[i] = ld_act(qsrc + i) * q_scale;
+    for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) qs[i] = ld_act(qsrc + i);
     if (has_new && threadIdx.x < d) {   // appended by the RoPE operator's task: coherent loads, two elements a thread
       const uint16_t* row = threadIdx.x < d / 2 ? krow : vrow;
       const uint32_t e = 2u * (threadIdx.x % (d / 2)), w = ld_relaxed((const uint32_t*)(row + e));
@@ -2268,21 +2274,23 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
 #pragma unroll
     for (int k = 0; k < NT; ++k) O[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto block = [&](auto coherent, auto more, uint32_t blk) {
-      // ---- scores
+      // ---- scores: 32 inputs at a time, added up pairwise (see above)
       f32x4 S[2];
 #pragma unroll
       for (int T = 0; T < 2; ++T) {
-        S[T] = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 part[KG];
 #pragma unroll
         for (int q = 0; q < KG; ++q) {
           pair_to_operands(kreg[T][q][0], kreg[T][q][1]);
-#pragma unroll
-          for (int U = 0; U < 2; ++U) {
+          auto mul = [&](int U) {
             const bf16x8 kv = __builtin_bit_cast(bf16x8, kreg[T][q][U]);
-            S[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qop[q][U]), S[T], 0, 0, 0);
-            if constexpr (TWO) S[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qlo[q][U]), S[T], 0, 0, 0);
-          }
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (TWO) v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qlo[q][U]), v, 0, 0, 0);
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qop[q][U]), v, 0, 0, 0);
+          };
+          part[q] = mul(0) + mul(1);
         }
+        S[T] = KG == 2 ? part[0] + part[KG - 1] : part[0];
       }
       if (decltype(more)::value) request_k(coherent, blk + NW);
       float s[8];
@@ -2299,6 +2307,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
           if (blk * BLK + 16u * (k >> 2) + 4u * jg + (k & 3) >= n_old) s[k] = -INFINITY;
       }
       float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+      mx *= kScale;
       if (__any(mx > m + kLazyMax)) {   // a new maximum: the first block, and seldom after it
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -2323,7 +2332,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
       float p[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        p[k] = __builtin_amdgcn_exp2f(s[k] - m);
+        p[k] = __builtin_amdgcn_exp2f(fmaf(s[k], kScale, -m));
         lsum += p[k];
       }
       u32x4 ph, pm, pl, pop, plo;
@@ -2381,14 +2390,14 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   const uint32_t nw = min(nblk, NW);
   for (uint32_t i = threadIdx.x; i < grp * (d / 2 + 1); i += kThreads) {
     const uint32_t j = i / (d / 2 + 1), e = 2u * (i % (d / 2 + 1));   // e == d: the maximum and the sum
-    float mw[NW], M = has_new ? snew[j] : -INFINITY;
+    float mw[NW], M = has_new ? snew[j] * kScale : -INFINITY;
 #pragma unroll
     for (uint32_t w = 0; w < NW; ++w) {
       mw[w] = w < nw ? ml[(w * grp + j) * 2] : -INFINITY;
       M = fmaxf(M, mw[w]);
     }
     float x = 0.f, y = 0.f;
-    const float wn = has_new ? __builtin_amdgcn_exp2f(snew[j] - M) : 0.f;
+    const float wn = has_new ? __builtin_amdgcn_exp2f(fmaf(snew[j], kScale, -M)) : 0.f;
     if (e == d) {
       y = wn;
 #pragma unroll
