@@ -1968,6 +1968,11 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
 // (D = 128).  The requests of a round carry no branch (rows past the chunk repeat its last row), the
 // loop's last round is peeled and requests nothing.
 //
+// Infinities: a cached element may be infinite as long as it only gives scores of -infinity (weight 0), and in
+// vector arithmetic does no harm then.  Split into terms it does: infinity times the lower terms is NaN or of
+// the other sign.  A NaN among the scores never leaves the sum of the weights, so a wavefront looks at that
+// once, at the end, and where it is not finite does its rows again without the split.
+//
 // The running maximum m is only raised when a score exceeds it by more than 2^16 (lazy rescaling:
 // sums and outputs are relative to m, so any m within the fp32 range gives the same digits).
 //
@@ -2026,6 +2031,88 @@ __device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row
       M = Mn;
     }
     st_act2(o + 2u * i, ax / L, ay / L);
+  }
+}
+
+// The rows of one wavefront's blocks in vector arithmetic, into its partial results: for rows with elements that
+// are not finite, see above.  Eight lanes a row, eight rows at a time, one head after the other; a row whose
+// score is -infinity has weight 0 whatever its maximum.
+template <int D, int GRP, uint32_t NTERM, class RowOff>
+__device__ __forceinline__ void attn_rows_unsplit(const float* qs, const uint16_t* Kb, const uint16_t* Vb, RowOff row_off, uint32_t n_old,
+                                                  uint32_t wave, uint32_t nblk, float scale, float* part, float* ml) {
+  constexpr uint32_t EPL = D / 8, WS = D + 4;   // elements per lane
+  const uint32_t lane = threadIdx.x & 63, e0 = EPL * (lane & 7u);
+  auto unpack = [](const u32x4& w, float* f) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { f[2 * k] = bf16_lo(w[k]); f[2 * k + 1] = bf16_hi(w[k]); }
+  };
+#pragma unroll 1
+  for (uint32_t j = 0; j < (uint32_t)GRP; ++j) {
+    float q[EPL], acc[EPL], m = -INFINITY, l = 0.f, odd = 0.f;
+#pragma unroll
+    for (uint32_t e = 0; e < EPL; ++e) {
+      q[e] = qs[j * D + e0 + e];
+      odd = fmaf(q[e], 0.f, odd);
+      acc[e] = 0.f;
+    }
+    if (__any(odd != 0.f)) {   // a query that is not finite: no score is, and the result is NaN whatever the rows hold
+      l = acc[0] = __builtin_nanf("");
+#pragma unroll
+      for (uint32_t e = 1; e < EPL; ++e) acc[e] = l;
+    } else {
+#pragma unroll 1
+      for (uint32_t n = 0; wave + (n >> 2) * (kThreads / 64u) < nblk; ++n) {   // quarter n % 4 of the wavefront's block n / 4
+        const uint32_t i = (wave + (n >> 2) * (kThreads / 64u)) * 32u + (n & 3u) * 8u + (lane >> 3);
+        const size_t off = row_off(min(i, n_old - 1u)) + e0;
+        u32x4 kw[EPL / 8], vw[EPL / 8];
+#pragma unroll
+        for (uint32_t h = 0; h < EPL / 8; ++h) {   // (agent-scope loads are right for every kind of launch)
+          kw[h] = ld_row16_coherent(Kb + off + 8 * h);
+          vw[h] = ld_row16_coherent(Vb + off + 8 * h);
+        }
+        float x[EPL], s = 0.f;
+#pragma unroll
+        for (uint32_t h = 0; h < EPL / 8; ++h) unpack(kw[h], x + 8 * h);
+#pragma unroll
+        for (uint32_t e = 0; e < EPL; ++e) s = fmaf(x[e], q[e], s);
+        s += __shfl_xor(s, 1, 64);
+        s += __shfl_xor(s, 2, 64);
+        s += __shfl_xor(s, 4, 64);
+        if (i < n_old && s != -INFINITY) {
+          const float mn = fmaxf(m, s * scale), f = __builtin_amdgcn_exp2f(m - mn), p = __builtin_amdgcn_exp2f(fmaf(s, scale, -mn));
+          m = mn;
+          l = fmaf(l, f, p);
+#pragma unroll
+          for (uint32_t h = 0; h < EPL / 8; ++h) unpack(vw[h], x + 8 * h);
+#pragma unroll
+          for (uint32_t e = 0; e < EPL; ++e) acc[e] = fmaf(acc[e], f, p * x[e]);
+        }
+      }
+      float M = m;
+      for (int o = 8; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+      const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+      m = M;
+      l *= f;
+#pragma unroll
+      for (uint32_t e = 0; e < EPL; ++e) acc[e] *= f;
+      for (int o = 8; o < 64; o <<= 1) {
+        l += __shfl_xor(l, o, 64);
+#pragma unroll
+        for (uint32_t e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+      }
+    }
+    if (lane < 8u) {
+#pragma unroll
+      for (uint32_t e = 0; e < EPL; ++e) {
+        part[j * WS + e0 + e] = acc[e];
+#pragma unroll
+        for (uint32_t term = 1; term < NTERM; ++term) part[(term * GRP + j) * WS + e0 + e] = 0.f;
+      }
+      if (lane == 0) {
+        ml[2 * j] = m;
+        ml[2 * j + 1] = l;
+      }
+    }
   }
 }
 
@@ -2369,14 +2456,17 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     // ---- the wavefront's partial results to LDS
     lsum += __shfl_xor(lsum, 16, 64);
     lsum += __shfl_xor(lsum, 32, 64);
-    if ((uint32_t)lane < grp) {
+    const bool finite = !__any(!(lsum < INFINITY));
+    if (__builtin_expect(!finite, 0))
+      attn_rows_unsplit<D, GRP, NTERM>(qs, Kb, Vb, row_off, n_old, wave, nblk, kScale, wpart + (size_t)wave * NTERM * grp * WS, ml + wave * grp * 2);
+    if (finite && (uint32_t)lane < grp) {
       ml[(wave * grp + lane) * 2] = m;
       ml[(wave * grp + lane) * 2 + 1] = lsum;
     }
 #pragma unroll
     for (uint32_t r = 0; r < 4; ++r) {
       const uint32_t row = 4u * jg + r, term = row / HG, head = row % HG;
-      if (term < NTERM && head < grp) {
+      if (finite && term < NTERM && head < grp) {
         float* wp = wpart + (((size_t)wave * NTERM + term) * grp + head) * WS + (uint32_t)NT * col;
 #pragma unroll
         for (int k = 0; k < NT; k += 4) *(float4*)(wp + k) = make_float4(O[k][r], O[k + 1][r], O[k + 2][r], O[k + 3][r]);
@@ -2396,20 +2486,21 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
       mw[w] = w < nw ? ml[(w * grp + j) * 2] : -INFINITY;
       M = fmaxf(M, mw[w]);
     }
+    const float Mr = M == -INFINITY ? 0.f : M;   // (every score -infinity: all weights 0)
     float x = 0.f, y = 0.f;
-    const float wn = has_new ? __builtin_amdgcn_exp2f(fmaf(snew[j], kScale, -M)) : 0.f;
+    const float wn = has_new ? __builtin_amdgcn_exp2f(fmaf(snew[j], kScale, -Mr)) : 0.f;
     if (e == d) {
       y = wn;
 #pragma unroll
       for (uint32_t w = 0; w < NW; ++w)
-        if (w < nw) y = fmaf(ml[(w * grp + j) * 2 + 1], __builtin_amdgcn_exp2f(mw[w] - M), y);
+        if (w < nw) y = fmaf(ml[(w * grp + j) * 2 + 1], __builtin_amdgcn_exp2f(mw[w] - Mr), y);
       x = M;   // (a power of two, like everything the merges do with it)
     } else {
       if (has_new) { x = wn * vnew[e]; y = wn * vnew[e + 1]; }
 #pragma unroll
       for (uint32_t w = 0; w < NW; ++w) {
         if (w >= nw) continue;
-        const float f = __builtin_amdgcn_exp2f(mw[w] - M);
+        const float f = __builtin_amdgcn_exp2f(mw[w] - Mr);
         float ox = 0.f, oy = 0.f;
 #pragma unroll
         for (uint32_t term = 0; term < NTERM; ++term) {
