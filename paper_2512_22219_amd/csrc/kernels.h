@@ -690,8 +690,15 @@ __device__ __forceinline__ uint32_t linear_wait(const StepArgs& a, int32_t wait_
 template <int NB, bool MEGA, class Svc = NoJit, bool DEEP = false>
 __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
                                                 uint32_t* s_flag, const Svc& svc = Svc{}, uint32_t next_ti = 0) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: geometry stays scalar
+  // Batch 1: what is worked out from the lane number is worked out again in every task.  Otherwise the compiler
+  // keeps some thirty such values in registers across the walk's calls of the task functions, and how well
+  // this body does then hangs on which registers those happen to use (189 instead of 256 registers and
+  // 2 spilled ones; us a step: 8B 2818 -> 2794, 1B class 795 -> 785).  Not with two rows (2725 -> 2731) or a
+  // third buffer (long streams: gate/up of the 70B shape 143 -> 151 us a layer, the step unchanged).
+  uint32_t tid = threadIdx.x;
+  if constexpr (NB == 1 && !DEEP) asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: geometry stays scalar
   const uint32_t K = t.K, nb = t.b1 - t.b0, ncols = t.c1 - t.c0;
   // pages exist only in the all-ahead-of-time persistent kernel at batch 1 (the compiler sets the flags)
   constexpr bool kPages = MEGA && NB == 1 && !Svc::enabled;
@@ -746,7 +753,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     const uint16_t* gain0 = (const uint16_t*)t.w2;
 #pragma unroll
     for (int u = 0; u < kGainPre; ++u) {
-      const uint32_t i = u * kThreads + threadIdx.x;
+      const uint32_t i = u * kThreads + tid;
       gpre[u] = 0;
       if ((t.flags & TF_PRO_NORM) && i < K / 2) gpre[u] = *as_global((const uint32_t*)(gain0 + 2 * i));
     }
@@ -790,8 +797,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // overlaps the staging instead of following it
   const bool resid = t.flags & TF_EPI_RESID;
   float resv = 0.f;
-  if (resid && threadIdx.x < nb * ncols) {
-    const uint32_t bb = threadIdx.x / ncols, cc = threadIdx.x % ncols;
+  if (resid && tid < nb * ncols) {
+    const uint32_t bb = tid / ncols, cc = tid % ncols;
     resv = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc);
   }
   constexpr int kStageLoads = 12;   // coherent loads in flight per lane: 12288 inputs in one round trip
@@ -805,12 +812,12 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         float2 tmp[kStageLoads];
 #pragma unroll
         for (int u = 0; u < kStageLoads; ++u) {
-          uint32_t i = i0 + u * kThreads + threadIdx.x;
+          uint32_t i = i0 + u * kThreads + tid;
           if (i < K / 2) tmp[u] = ld_act2(src + 2 * i);
         }
 #pragma unroll
         for (int u = 0; u < kStageLoads; ++u) {
-          uint32_t i = i0 + u * kThreads + threadIdx.x;
+          uint32_t i = i0 + u * kThreads + tid;
           if (i < K / 2) {
             float2 v = tmp[u];
             if (pro_norm) {
@@ -827,7 +834,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         }
       }
     } else {
-      for (uint32_t i = threadIdx.x; i < Kp / 2; i += kThreads) dst[i] = make_float2(0.f, 0.f);
+      for (uint32_t i = tid; i < Kp / 2; i += kThreads) dst[i] = make_float2(0.f, 0.f);
     }
     if (pro_norm) {
       ss = wave_sum_dpp(ss);
@@ -835,8 +842,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     }
   }
   if (resid) {
-    if (threadIdx.x < nb * ncols) res_lds[threadIdx.x] = resv;
-    for (uint32_t i = threadIdx.x + kThreads; i < nb * ncols; i += kThreads) {   // more than 512 outputs per task: rare
+    if (tid < nb * ncols) res_lds[tid] = resv;
+    for (uint32_t i = tid + kThreads; i < nb * ncols; i += kThreads) {   // more than 512 outputs per task: rare
       uint32_t bb = i / ncols, cc = i % ncols;
       res_lds[i] = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc);
     }
@@ -2378,6 +2385,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
           part[q] = mul(0) + mul(1);
         }
         S[T] = KG == 2 ? part[0] + part[KG - 1] : part[0];
+        __builtin_amdgcn_sched_barrier(0);   // (both tiles' sums at once take five more registers, which the callers' long-lived values lose)
       }
       if (decltype(more)::value) request_k(coherent, blk + NW);
       float s[8];
