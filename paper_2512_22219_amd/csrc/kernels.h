@@ -1329,6 +1329,22 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   trace_mark(a, t, 8);
   drain_vmem();   // (nothing but loads past the range)
   // ---- the column groups of a packed multiply added up: afterwards column b < nb holds the sum
+  if (PACK == 3) {
+    // An infinite weight or input gives what vector arithmetic gives, and that is in the hi columns alone: the lower
+    // terms of a product with an infinity are NaN or of the other sign.
+    float all[4] = {0.f, 0.f, 0.f, 0.f};   // not finite if one of the sums is not
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) all[i] += acc[j][i];
+    if (__builtin_expect(__any(!(fabsf((all[0] + all[1]) + (all[2] + all[3])) < INFINITY)), 0)) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (frow >= 4u && !(fabsf(acc[j][i]) < INFINITY)) acc[j][i] = 0.f;
+    }
+  }
   if (PACK != 1) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)

@@ -1,6 +1,6 @@
-"""Infinite elements in the cache: a row whose score is -infinity has weight 0 and leaves the step's logits as
-finite as they are without it; an infinite value gives NaN in its own sequence and nowhere else.  Bounds:
-those of strict_steps (held bf16 decisions, fp64 oracle)."""
+"""Infinite elements.  In the cache: a row whose score is -infinity has weight 0 and leaves the step's logits as
+finite as they are without it; an infinite value gives NaN in its own sequence and nowhere else.  In a weight, up
+to four sequences: an infinite output of that row.  Bounds: those of strict_steps (held bf16 decisions, fp64 oracle)."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +9,7 @@ import paper_2512_22219_amd as M
 from oracle import decoder as D
 from synth import gen as G
 from synth.device import DeviceModel
-from tests.gpu_util import appended_rows, bf16_bits_to_f64, rel_err
+from tests.gpu_util import GpuDecoder, appended_rows, bf16_bits_to_f64, held_step, rel_err
 
 pytestmark = pytest.mark.gpu
 FUSED = dict(fusion=31, transitive_reduction=1)
@@ -109,3 +109,27 @@ def test_an_infinite_value_stays_in_its_sequence(head_dim, grp):
     got, want = _run(s, 6, [400, 530], {1: [40]}, {0: [100]}, **FUSED)
     assert not np.isfinite(got[0]).any() and np.isfinite(got[1]).all()
     assert np.abs(got[1] - want[1]).max() / np.abs(want[1]).max() < 2e-5
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3, 4])
+@pytest.mark.parametrize("opts", [dict(), dict(launch_mode=1)])
+def test_an_infinite_weight_gives_an_infinite_logit(batch, opts):
+    """One element of three rows of the output head, two of a fourth (not among a row's last eight, which are also
+    multiplied with the zeros behind it)."""
+    s = G.small_variant("C1", n_layers=1, hidden=264, ffn=128, vocab=300, batch=batch, max_seq=64)
+    w = G.SynthWeights(s, 9)
+    head = w.lm_head()
+    for row, cols in ((0, [(5, PLUS)]), (17, [(255, MINUS)]), (299, [(0, PLUS)]), (150, [(1, PLUS), (200, PLUS)])):
+        for c, bits in cols:
+            head[row, c] = bits
+    gpu = GpuDecoder(s, 9, **{**FUSED, **opts})
+    gpu.model.lm_head.copy_(torch.from_numpy(head.view(np.int16)).view(torch.bfloat16))
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        got, want, _, _ = held_step(D.DecoderOracle(s, w, "f64"), gpu, G.tokens(9, s), np.arange(batch, dtype=np.int32) * 7 + 3)
+    gpu.close()
+    assert np.isinf(want[:, [0, 17, 299]]).all()
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    inf, fin = np.isinf(want), np.isfinite(want)
+    assert np.array_equal(got[inf], want[inf])
+    assert np.abs(got[fin] - want[fin]).max() / np.abs(want[fin]).max() < 2e-5
