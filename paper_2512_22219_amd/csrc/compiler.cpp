@@ -1300,9 +1300,20 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
   if (C == 0) {
     // About one attention task per worker, but no chunk shorter than 128 cache positions (each
     // task has a fixed cost: event wait, query staging, the merge of its partial result).
-    // Measured: C2 (8 pairs, 1088 positions) is fastest with 8 chunks, C3 (64 pairs) with 4.
+    // Measured: C2 (8 pairs, 1088 positions) is fastest with 8 chunks, C3 (64 pairs) with 4.  No more tasks than
+    // workers (120 pairs of head size 64: two chunks 407 us a step of 6 layers, three 458) -- except one chunk
+    // between half as many pairs as workers and as many, which leaves the length deal nothing to move: a
+    // long sequence alone then waits for one workgroup a head.  A second task a pair costs 1 to 8 us a layer, so
+    // it pays where there are many rows of 256 bytes (us a step of 6 layers, one chunk / two, lengths
+    // drawn evenly | one long sequence | all alike):
+    //   batch 9 x 16, 4096 rows    653 / 611 | 641 / 497 | 550 / 627
+    //   batch 16 x 12, 2048 rows   588 / 546 | 573 / 482 | 529 / 536
+    //   batch 13 x 16, 1536 rows   564 / 554 | 541 / 476 | 513 / 522
+    //   batch 8 x 24, 2048 rows    569 / 581 | 551 / 521 | 530 / 570   (one chunk)
+    //   head size 64, 13 x 16, 2048 rows   454 / 486 | 451 / 446 | 422 / 469   (one chunk)
     const uint32_t pairs = cfg.batch * cfg.n_kv_heads;
     C = std::max(1u, opt.n_workers / pairs);
+    if (C == 1 && pairs < opt.n_workers && cfg.batch > 1 && cfg.head_dim == 128 && (uint64_t)cfg.batch * cfg.max_seq > 16384u) C = 2;
     C = std::min(C, std::max(1u, cfg.max_seq / 128u));
     C = std::max(1u, std::min(C, 64u));
   }

@@ -453,3 +453,16 @@ def test_expert_tasks_share_the_active_tiles_disjointly_in_order_and_completely(
         moe_task_share(3, tiles_per_expert, n_tasks, n_tasks)
     with pytest.raises(M.MpkError):
         moe_task_share(3, 0, n_tasks, 0)
+
+
+@pytest.mark.parametrize("batch,n_kv,head_dim,max_seq,chunks", [
+    (9, 16, 128, 4096, 2), (16, 12, 128, 2048, 2), (13, 16, 128, 1536, 2),   # many long rows: something for the length deal to move
+    (8, 24, 128, 2048, 1), (13, 16, 64, 2048, 1), (4, 48, 128, 4096, 1),     # 16384 rows or fewer, or short rows
+    (16, 16, 128, 4096, 1), (16, 24, 128, 4096, 1),                          # a pair for every worker, and more
+    (8, 16, 128, 4096, 2), (5, 24, 64, 1352, 2), (1, 8, 128, 1088, 8),       # as many tasks as workers hold
+])
+def test_default_number_of_attention_chunks(batch, n_kv, head_dim, max_seq, chunks):
+    s = G.small_variant("C1", batch=batch, n_layers=1, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=head_dim, max_seq=max_seq)
+    ex = host_graph(s, fusion=31, transitive_reduction=1, n_workers=256).export()
+    attn = [op for op in ex.ops if op["kind"] == TG.K_ATTN_PARTIAL]
+    assert [int(op["n_tasks"]) for op in attn] == [batch * n_kv * chunks]
