@@ -170,7 +170,8 @@ typedef struct mpk_compile_options {
                                proportion to the speed of the worker that runs each (Section 4.1
                                leaves the partition to the compiler: "the partitioning strategy
                                ... minimizes device memory loading"; an operator ends with its
-                               slowest task).  Batch <= 4, operators with one tile per row block
+                               slowest task).  Batch 1 and 2 (ignored above: matrix-core tasks are
+                               made of blocks of 16 rows), operators with one tile per row block
                                and at least 64 weight rows per tile, all tasks ahead-of-time; the
                                exported graph lists the boundaries                              */
   uint32_t no_lds_pages;    /* 1 = no pre-load pages in LDS.  By default, at batch 1 without

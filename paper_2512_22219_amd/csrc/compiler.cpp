@@ -1141,7 +1141,7 @@ static mpk_status validate(const mpk_model_config& c, const mpk_weight_ptrs* w,
 // worker runs which tile is only known after linearization and pre-enqueue, but it does not depend
 // on the tile SIZES: the graph is built once with even tiles, the assignment is read off, and the
 // graph is built again with the weighted column tiles.  Eligible: linear operators of the vector
-// body (batch <= 4) with one row of tiles, no head alignment and no input split, every task
+// body (batch 1 and 2) with one row of tiles, no head alignment and no input split, every task
 // ahead-of-time.
 using TileWorkers = std::vector<std::vector<int32_t>>;   // [operator][tile] -> worker, empty = not eligible
 static void apply_worker_weights(const mpk_compile_options& o, const TileWorkers& tw, HostGraph& g) {
@@ -1244,7 +1244,7 @@ mpk_status build_model_graph(const mpk_model_config& cfg, const mpk_weight_ptrs*
   if (st != MPK_OK) return st;
   bool weighted = false;
   for (int k = 0; k < 8; ++k) weighted = weighted || (opt_in.worker_weight_permille[k] != 0 && opt_in.worker_weight_permille[k] != opt_in.worker_weight_permille[0]);
-  weighted = weighted && cfg.batch <= 4;
+  weighted = weighted && cfg.batch < kMfmaMinBatch;   // (a column more or less is nothing to a body of 16-row tiles, or a whole tile)
   // tiles that will find their first rows in the LDS pages
   std::vector<std::vector<uint8_t>> ready(g.ops.size());
   bool paged = false;

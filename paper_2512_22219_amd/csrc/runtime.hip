@@ -271,7 +271,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     if (o.host_only) { set_error("xcd_balance measures on the GPU: not with host_only (set worker_weight_permille instead)"); return MPK_ERR_INVALID_ARG; }
     bool given = false;
     for (int k = 0; k < 8; ++k) given = given || o.worker_weight_permille[k] != 0;
-    if (!given && weights && weights->lm_head && cfg->batch <= 4) {
+    if (!given && weights && weights->lm_head && cfg->batch < kMfmaMinBatch) {
       st = measure_worker_speeds(weights->lm_head, (size_t)cfg->vocab * cfg->hidden * 2, o.n_workers, o.worker_weight_permille);
       if (st != MPK_OK) return st;
     }

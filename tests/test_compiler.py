@@ -466,3 +466,11 @@ def test_default_number_of_attention_chunks(batch, n_kv, head_dim, max_seq, chun
     ex = host_graph(s, fusion=31, transitive_reduction=1, n_workers=256).export()
     attn = [op for op in ex.ops if op["kind"] == TG.K_ATTN_PARTIAL]
     assert [int(op["n_tasks"]) for op in attn] == [batch * n_kv * chunks]
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3, 4, 5])
+def test_worker_speeds_resize_the_tiles_of_the_vector_body_only(batch):
+    """Batch 3 and more runs on the matrix cores, whose tasks are made of 16-row blocks (and of jobs of 512 rows)."""
+    s = G.small_variant("C2", n_layers=1, batch=batch, ffn=8192)
+    ex = host_graph(s, fusion=31, worker_weight_permille=[1047, 955] * 4).export()
+    assert bool(ex.col_begin) == (batch <= 2)
