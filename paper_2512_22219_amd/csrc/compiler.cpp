@@ -312,7 +312,8 @@ static mpk_status run_passes(PassInput& in, const mpk_compile_options& opt, Host
   }
   g.aot_off[W] = (uint32_t)g.aot.size();
 
-  // Events whose producers all have a fixed worker (AOT) count arrivals per worker group.
+  // Events whose producers all have a fixed worker (AOT) count arrivals per worker group: in hybrid graphs too,
+  // for the events whose producers the schedulers do not place (see kHierMinRequired).
   g.n_hier_events = 0;
   {
     std::vector<std::vector<uint32_t>> sub(g.events.size(), std::vector<uint32_t>(kShards, 0));
@@ -330,7 +331,9 @@ static mpk_status run_passes(PassInput& in, const mpk_compile_options& opt, Host
     auto fits = [&](uint32_t least) {
       return scratch_layout(g.events.size(), n_sharded(least), g.n_group_counters, g.arena_floats).end <= MPK_STATIC_SCRATCH_BYTES;
     };
-    const uint32_t least = !fits(kHierMinRequired) && fits(kHierMinRequiredTight) ? kHierMinRequiredTight : kHierMinRequired;
+    // (only for a graph that mpk_decode_step_static takes otherwise)
+    const bool may_be_static = n_jit == 0 && !opt.greedy_loop && !opt.kv_page_size && !(opt.debug_flags & MPK_DEBUG_TRACE);
+    const uint32_t least = may_be_static && !fits(kHierMinRequired) && fits(kHierMinRequiredTight) ? kHierMinRequiredTight : kHierMinRequired;
     for (size_t e = 0; e < g.events.size(); ++e) {
       EventDesc& ev = g.events[e];
       if (ev.required < least || has_jit_producer[e]) continue;

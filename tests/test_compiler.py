@@ -474,3 +474,21 @@ def test_worker_speeds_resize_the_tiles_of_the_vector_body_only(batch):
     s = G.small_variant("C2", n_layers=1, batch=batch, ffn=8192)
     ex = host_graph(s, fusion=31, worker_weight_permille=[1047, 955] * 4).export()
     assert bool(ex.col_begin) == (batch <= 2)
+
+
+def test_only_graphs_of_the_static_entry_point_give_up_sharded_counters_for_its_scratch_array():
+    """700 small layers at batch 4: with every event's counters on 17 lines of their own the scratch of a step
+    exceeds the 32 MiB array, so the plain graph keeps its narrow events unsharded; a graph that
+    mpk_decode_step_static refuses anyway has no reason to."""
+    s = G.small_variant("C1", batch=4, n_layers=700, max_seq=136)
+
+    def sharded(**kw):
+        ev = host_graph(s, fusion=31, transitive_reduction=1, n_workers=256, **kw).export().events
+        has_producers = ev["required"] > 0
+        return int(((ev["flags"] & 2) != 0)[has_producers].sum()), int(has_producers.sum())
+
+    n, total = sharded()
+    assert 0 < n < total
+    for kw in (dict(greedy_loop=1), dict(kv_page_size=8, kv_pages=80), dict(debug_flags=M.binding.DEBUG_TRACE)):
+        n, total = sharded(**kw)
+        assert n == total
