@@ -1151,11 +1151,11 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   }
   // load h of the k-group at input k of the rows at byte offsets ro: this lane's 8 inputs start at
   // k + lk, or are the row's last 8 when that lies past its end (their staged inputs are zeros).  Not
-  // real: past the range of the load (a matrix ends below it, its size being a multiple of 16 below 4 GB)
+  // real: a range of no bytes (a matrix is a multiple of 16 bytes below 4 GB, so a real load's end does not wrap)
   constexpr uint32_t kRange = 0xFFFFFFF0u;
   const uint16_t* wb = uniform_ptr(wbase);
   auto ld_frag = [&](uint32_t ro, uint32_t k, bool real) {
-    return ld_stream16_ranged(wb, kRange, real ? ro + 2u * min(k + lk, K - 8u) : kRange);
+    return ld_stream16_ranged(wb, real ? kRange : 0u, ro + 2u * min(k + lk, K - 8u));
   };
   // the wavefront's run of k-groups in chunk c; a chunk takes an even number of round slots
   // (>= 2), so that even slots always use fragment buffer A and odd ones B
