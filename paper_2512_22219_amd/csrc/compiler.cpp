@@ -1026,10 +1026,11 @@ static void build_descs(const mpk_model_config& c, const mpk_kv_ptrs* kv, HostGr
   }
 }
 
-// vector_need: bytes with the vector linear body (batch up to 4; 0 above), which decides what shapes
-// are accepted at batch 3 and 4 although the matrix-core body, which needs less, runs them.
-static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_t C, size_t* vector_need) {
-  size_t need = 0, need_vec = 0;
+// accept_need: the bytes that decide which graphs are accepted.  They stay those of bodies that needed more: the
+// vector linear body at batch 3 and 4, which the matrix cores run, and an attention body that kept
+// a partial result per position slot.
+static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_t C, size_t* accept_need) {
+  size_t need = 0, need_acc = 0;
   const uint32_t grp = c.n_q_heads / c.n_kv_heads;
   const uint32_t nb = c.batch <= 2 ? c.batch : (c.batch <= 4 ? 4u : 8u);   // body template sizes
   // linear tasks: staged input rows | per-row results | residual slice | partial sums of squares
@@ -1049,11 +1050,11 @@ static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_
   if (c.batch >= kMfmaMinBatch) res_rows = std::min(res_rows, kMfmaJobRows);   // (a job's)
   g.lin_res_rows_max = res_rows;
   for (auto& op : g.ops) {
-    size_t f = 0, fv = 0;
+    size_t f = 0, fa = 0;
     if (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) {
-      if (c.batch <= 4) fv = (size_t)nb * ((op.K + 4095u) / 4096u * 4096u) + 2 * (size_t)rows_max * nb + 8 * nb;
+      if (c.batch <= 4) fa = (size_t)nb * ((op.K + 4095u) / 4096u * 4096u) + 2 * (size_t)rows_max * nb + 8 * nb;
       if (c.batch < kMfmaMinBatch) {
-        f = fv;
+        f = fa;
       } else {
         // matrix-core body: the staged fp32 input, one chunk (reused for the per-wavefront
         // partial tiles) | residual slice | sums of squares | 1/rms per row
@@ -1066,16 +1067,16 @@ static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_
     }
     else if (op.kind == MPK_OP_ROUTER)
       f = (size_t)c.batch * c.top_k * 2 + (size_t)c.n_experts * (3 + 16) + 64;   // pairs | per-expert counts, offsets, masks, pair table
-    else if (op.kind == MPK_OP_ATTN_PARTIAL)
-      f = (size_t)grp * c.head_dim                                        // q
-          + (size_t)(kThreads * 8 / c.head_dim) * grp * (c.head_dim + 4) + 16 + 64;   // partials per position slot (register-resident body; the other keeps one per wavefront)
-    if (op.kind == MPK_OP_ATTN_PARTIAL && g.opt.kv_page_size)   // paged cache: + the chunk's page numbers
-      f += c.max_seq / g.opt.kv_page_size;
+    else if (op.kind == MPK_OP_ATTN_PARTIAL) {
+      const size_t pages = g.opt.kv_page_size ? c.max_seq / g.opt.kv_page_size : 0;   // paged cache: + the chunk's page numbers
+      f = attn_lds_floats(c.head_dim, grp) + pages;
+      fa = (size_t)grp * c.head_dim + (size_t)(kThreads * 8 / c.head_dim) * grp * (c.head_dim + 4) + 16 + 64 + pages;
+    }
     need = std::max(need, f);
-    need_vec = std::max(need_vec, std::max(f, fv));
+    need_acc = std::max(need_acc, std::max(f, fa));
   }
   size_t bytes = (need + kLdsReduceFloats + kLdsCtrlFloats) * sizeof(float);   // + the control words
-  *vector_need = c.batch <= 4 ? (need_vec + kLdsReduceFloats + kLdsCtrlFloats) * sizeof(float) : 0;
+  *accept_need = (need_acc + kLdsReduceFloats + kLdsCtrlFloats) * sizeof(float);
   return (uint32_t)std::max<size_t>(bytes, kMinLdsBytes);
 }
 
@@ -1343,8 +1344,8 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
   if (st != MPK_OK) return st;
   g.stats.n_pair_deps += g.stats.n_pairs_removed;
   build_descs(cfg, kv, g);
-  size_t vector_lds = 0;
-  g.lds_bytes = lds_requirement(cfg, g, C, &vector_lds);
+  size_t accept_lds = 0;
+  g.lds_bytes = lds_requirement(cfg, g, C, &accept_lds);
   if (sp.page_ready) {   // (second pass: the tile sizes already account for the pages)
     const std::vector<uint16_t> plan = page_plan(cfg, opt, g);
     bool any = false;
@@ -1359,7 +1360,7 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
     }
   }
   if (cfg.batch > 4 && g.lin_rows_max > kMfmaJobRows) { set_error("a linear task would own %u weight rows; the batch >= 5 body handles at most 512: raise tiles_linear / tiles_lm_head", g.lin_rows_max); return MPK_ERR_UNSUPPORTED; }
-  if (std::max<size_t>(g.lds_bytes, vector_lds) > 160 * 1024 && !opt.host_only) { set_error("task bodies need %zu bytes of LDS (> 160 KB): batch x input length too large", std::max<size_t>(g.lds_bytes, vector_lds)); return MPK_ERR_UNSUPPORTED; }
+  if (std::max<size_t>(g.lds_bytes, accept_lds) > 160 * 1024 && !opt.host_only) { set_error("task bodies need %zu bytes of LDS (> 160 KB): batch x input length too large", std::max<size_t>(g.lds_bytes, accept_lds)); return MPK_ERR_UNSUPPORTED; }
   // statistics
   g.stats.struct_size = sizeof(mpk_stats);
   g.stats.n_ops = (uint32_t)g.ops.size();

@@ -1715,7 +1715,6 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
     rowin[threadIdx.x] = gateup ? pair / TK : pair;
   }
   lds_barrier();
-  const uint32_t frow = lane & 15u, fk = (uint32_t)(lane >> 4) * 8u;
   auto row_off = [&](uint32_t rt, uint32_t row) {   // row: this lane's row of the 16-row tile
     const uint32_t r = (tile0 + rt) * 16u + row;    // row of the expert's gate/up-interleaved (or plain) order
     const uint32_t wrow = gateup ? ((r >> 1) + ((r & 1u) ? t.p0 : 0u)) : r;
@@ -2163,7 +2162,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   constexpr uint32_t d = D, grp = GRP, NW = kThreads / 64, per = grp * (d + 2);
   constexpr bool TWO = GRP == 8;                       // the lo terms take a second multiply
   constexpr uint32_t HG = TWO ? 8u : 4u;               // columns per term group
-  constexpr uint32_t NTERM = TWO ? 2u : 3u;            // partial outputs per wavefront and head
+  constexpr uint32_t NTERM = attn_term_groups(GRP);    // partial outputs per wavefront and head
   constexpr int KG = D / 64, NT = D / 16;              // 64-input groups of a score, output tiles
   constexpr uint32_t BLK = 32, WS = d + 4;
   using VVec = std::conditional_t<D == 128, u32x4, u32x2>;   // D / 16 elements of a value row
@@ -2186,6 +2185,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   float* vnew = knew + d;
   float* snew = vnew + d;
   uint32_t* flag = (uint32_t*)(snew + 8);
+  static_assert(grp * d + NW * NTERM * grp * WS + NW * grp * 2 + 2 * d + 8 + 16 == attn_lds_floats(D, GRP), "the host reserves this layout");
   uint32_t* pgs = flag + 16;                         // paged: the chunk's page numbers
   float* outp = t.out + (size_t)bs * t.ld_out + t.c0;
   const int32_t pos = step_position<PAGED>(a, b);    // written by the host before the launch (or by the serving task)

@@ -284,6 +284,15 @@ constexpr uint32_t kThreads = 512;        // worker workgroup size (8 wavefronts
 constexpr uint32_t kLdsReduceFloats = 1024;  // scratch for cross-wave reductions
 constexpr uint32_t kLdsCtrlFloats = 48;      // control words ahead of the task area (event-wait result, the kernel's arguments)
 constexpr uint32_t kMinLdsBytes = 84 * 1024; // > half of 160 KB: at most one worker per CU
+// LDS floats of an attention task, one definition for the host's requirement and the kernels' layout (behind them, with
+// a paged cache, the chunk's page numbers): queries [grp][d] | per wavefront its partial outputs, a row of d + 4
+// per term group (three, two with 8 query heads per KV head) and head | maxima and sums [8][grp][2] | the appended
+// key and value row [d] each | its scores [8] | flag [16].
+constexpr uint32_t attn_term_groups(uint32_t grp) { return grp == 8u ? 2u : 3u; }
+constexpr uint32_t attn_lds_floats(uint32_t d, uint32_t grp) {
+  const uint32_t waves = kThreads / 64u;
+  return grp * d + waves * attn_term_groups(grp) * grp * (d + 4u) + waves * grp * 2u + 2u * d + 8u + 16u;
+}
 // Pre-load pages in LDS (paper Section 5.3: shared-memory pages hold data pre-loaded for a task that
 // has not started): one page of 16 KB per wavefront = one half block of the vector linear body.
 constexpr uint32_t kLinPageFloats = 4096, kLinPagesFloats = 8 * kLinPageFloats;

@@ -492,3 +492,15 @@ def test_only_graphs_of_the_static_entry_point_give_up_sharded_counters_for_its_
     for kw in (dict(greedy_loop=1), dict(kv_page_size=8, kv_pages=80), dict(debug_flags=M.binding.DEBUG_TRACE)):
         n, total = sharded(**kw)
         assert n == total
+
+
+@pytest.mark.parametrize("head_dim,grp", [(64, 1), (64, 8), (128, 4), (128, 8)])
+@pytest.mark.parametrize("page,max_seq", [(0, 1024), (8, 1 << 17)])
+def test_lds_of_attention_tasks(head_dim, grp, page, max_seq):
+    """Queries, eight wavefronts' partial outputs (a row of d + 4 per term group and head), maxima and sums, the
+    appended rows and their scores, page numbers; at least 84 KB, so that one worker fits a compute unit."""
+    s = G.small_variant("C1", n_layers=1, head_dim=head_dim, n_q_heads=grp, n_kv_heads=1, max_seq=max_seq)
+    kw = dict(kv_page_size=page, kv_pages=100) if page else {}
+    terms = 2 if grp == 8 else 3
+    floats = grp * head_dim + 8 * terms * grp * (head_dim + 4) + 16 * grp + 2 * head_dim + 24 + (max_seq // page if page else 0)
+    assert host_graph(s, fusion=31, n_workers=256, **kw).stats()["lds_bytes"] == max(84 * 1024, 4 * (floats + 1024 + 48))
