@@ -146,16 +146,19 @@ def test_attention_chunk_tasks_dealt_to_the_sequences_by_length(batch, pos, opts
 @pytest.mark.parametrize("variant,opts", [
     # ffn 4360: the down projection's input is one full 4096-element segment plus a short one
     (dict(hidden=1000, ffn=4360, batch=1), dict(fusion=31, transitive_reduction=1, n_workers=13)),
+    (dict(hidden=1000, ffn=4360, batch=2), dict(fusion=31, transitive_reduction=1, n_workers=13)),
     (dict(hidden=1000, ffn=4360, batch=3), dict(fusion=31, transitive_reduction=1, n_workers=13)),
     # hidden 8200: every projection from the residual stream walks three segments, the last 8 long
     (dict(hidden=8200, ffn=696, batch=2, vocab=520), dict(fusion=31, transitive_reduction=1, n_workers=29)),
+    (dict(hidden=4104, ffn=696, batch=2, vocab=520), dict(fusion=0, n_workers=29, launch_mode=1)),
     (dict(hidden=4104, ffn=696, batch=4, vocab=520), dict(fusion=0, n_workers=29, launch_mode=1)),
     # one weight row per wavefront and fewer rows than wavefronts (vocab 40 over 7 workers)
     (dict(hidden=264, ffn=72, batch=1, vocab=40), dict(fusion=31, transitive_reduction=1, n_workers=7)),
+    (dict(hidden=264, ffn=72, batch=2, vocab=40), dict(fusion=31, transitive_reduction=1, n_workers=7)),
 ])
 def test_linear_stream_odd_shapes(variant, opts):
-    """The two-buffer weight stream of the batch <= 4 linear body on shapes that exercise its
-    corners: odd numbers of rows per wavefront (a pair with one row), inputs of several segments
+    """The two-buffer weight stream of the vector linear body (batch 1 and 2) on shapes that exercise its
+    corners, and the same shapes at batch 3 and 4 on the matrix cores: odd numbers of rows per wavefront (a pair with one row), inputs of several segments
     with a short last one, tasks with fewer rows than wavefronts, more half blocks than buffers."""
     s = G.small_variant("C1", n_layers=2, **variant)
     rng = np.random.default_rng(11)
