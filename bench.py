@@ -145,8 +145,7 @@ def measure_serving(args, config, page_size):
     through the decode path off the clock (requests are submitted longest first, so that all
     slots reach their lengths in the same iteration); then args.steps iterations -- serving
     task, decode step through the page tables, greedy sampling -- timed as ONE mpk_serve_run call
-    (one launch of the persistent kernel at batch > 4, a launch per iteration back to back with
-    no host synchronisation at batch <= 4: the library's choice)."""
+    (a launch per iteration, back to back with no host synchronisation: the library's choice)."""
     import numpy as np
     import torch
     import paper_2512_22219_amd as M

@@ -712,8 +712,10 @@ static void choose_partitions(const mpk_model_config& c, const mpk_compile_optio
         op.tb = 1;
         op.tc = std::max(1u, std::min(want, cap));
         if (op.flags & TF_SPLITK) { op.tc = W; break; }   // (row block, part) pairs, sized in build_ops
-        // the matrix-core body (batch > 4) holds at most 512 weight rows per task: whole extra
-        // rounds of tasks until the tiles fit (only when the tile count was not given)
+        // a matrix-core job holds at most 512 weight rows.  Above batch 4 a task is one job: whole extra rounds
+        // of tasks until the tiles fit (only when the tile count was not given).  At batch 3 and 4 a task of more
+        // rows runs as two jobs, which costs less than a second task a worker (us a step of 2 layers and the output
+        // head, 256 tasks / 512, batch 4: 151936 rows 396 / 421, 200064 rows 474 / 469).
         const bool given = (op.flags & TF_OUT_LOGITS) ? o.tiles_lm_head != 0 : o.tiles_linear != 0;
         const uint32_t per_row = (op.flags & TF_GATEUP) ? 2u : 1u;
         while (c.batch > 4 && !given && op.tc < cap && (nu + op.tc - 1) / op.tc * per_row > 512) op.tc = std::min(cap, op.tc + W);

@@ -48,7 +48,7 @@ enum TaskFlags : uint16_t {
                          // area, requested there by the worker's previous task
   TF_PAGE_NEXT = 2048,   // linear (batch 1): after its own requests, and before it waits for its event, the
                          // task requests the first half blocks of the worker's NEXT task into the LDS pages
-  TF_SPLITK = 256,    // linear (batch > 4): the task owns rows x ONE of `parts` input ranges; it writes
+  TF_SPLITK = 256,    // linear (batch above 4): the task owns rows x ONE of `parts` input ranges; it writes
                       // partial sums, and the task of a row block that arrives last (counter p2)
                       // adds the parts in order plus the residual into the real output (aux0).
                       // p1 = weight row length, p3 = parts | part << 8, K = length of the range
@@ -102,6 +102,10 @@ constexpr uint32_t EV_JIT = 1, EV_HIER = 2;
 // attention tasks of a KV head, the operators of small models) at 3 us.  Step times, that rule
 // against all events sharded: tiny model 77.0 -> 61.7 us, 8B shape at batch 1 3001 -> 2886 us, at
 // batch 8 (8 layers) 1209 -> 1186 us.  8 and 16 groups measured the same to 0.3 %.
+// Hybrid graphs shard every event whose producers all have a fixed worker as well.  There the arrival that
+// completes a narrow event of just-in-time tasks takes two atomics in a row instead of one and a worker looks at 16 lines;
+// it still measured faster (4 scheduler workgroups: tiny model 110.4 -> 97.0 us, 1B class at batch 1 1898 -> 1886,
+// 8B layers at batch 8 1601 -> 1585, odd sizes at batch 5 853.6 -> 852).
 // The counter blocks are part of the scratch memory of a step: a graph that only fits the static
 // scratch array (mpk_decode_step_static) with its narrow events unsharded keeps them unsharded.
 constexpr uint32_t kHierStrideWords = 64, kHierWordsPerEvent = (1 + kShards) * kHierStrideWords;

@@ -390,7 +390,7 @@ def test_weighted_column_tiles_follow_the_worker_speeds():
     assert seen_kinds == {TG.K_LINEAR, TG.K_GATEUP}     # O, down, LM head; the fused gate/up projection
     qkv = [oi for oi, op in enumerate(ex.ops) if op["kind"] == TG.K_LINEAR and op["cols"] == (shape.n_q_heads + 2 * shape.n_kv_heads) * shape.head_dim]
     assert qkv and all(oi not in ex.col_begin for oi in qkv)
-    # batch > 4 runs the matrix-core body, whose tiles are made of 16-row blocks: left alone
+    # batch 3 and more runs on the matrix cores, whose tiles are made of 16-row blocks: left alone
     big = host_graph(G.small_variant("C3", n_layers=1), fusion=31, worker_weight_permille=[1047, 955] * 4).export()
     assert not big.col_begin
 

@@ -502,10 +502,10 @@ def test_moe_routing_ties_take_the_lower_expert_index(batch):
     (dict(batch=3, n_layers=2), dict(fusion=31, transitive_reduction=1, tiles_sampling=5), 8),
     (dict(batch=2), dict(fusion=31, transitive_reduction=1, launch_mode=1, tiles_sampling=32), 5),
     (dict(), dict(fusion=0, tiles_sampling=3, debug_flags=6), 6),
-    # batch <= 4 issues a launch per step by default; greedy_loop = 2: the one launch of the loop kernel
+    # a launch per step by default; greedy_loop = 2: the one launch of the loop kernel
     (dict(), dict(fusion=31, transitive_reduction=1, greedy_loop=2), 16),
     (dict(batch=3, n_layers=2), dict(fusion=31, transitive_reduction=1, greedy_loop=2, tiles_sampling=2), 7),
-    # the kernels compiled for head dimension 128 at batch 5..16: a launch per step, and the loop kernel
+    # head dimension 128 at batch 5..16: a launch per step, and the loop kernel
     (dict(batch=8, n_layers=2, head_dim=128, n_q_heads=8, n_kv_heads=2), dict(fusion=31, transitive_reduction=1), 6),
     (dict(batch=8, n_layers=2, head_dim=128, n_q_heads=8, n_kv_heads=2), dict(fusion=31, transitive_reduction=1, greedy_loop=2), 6),
     (dict(batch=16, head_dim=128, n_q_heads=8, n_kv_heads=1, ffn=0, n_experts=16, top_k=4, expert_ffn=96), dict(fusion=31, transitive_reduction=1), 5),
@@ -669,7 +669,7 @@ POISON, JITTER = M.binding.DEBUG_POISON, M.binding.DEBUG_JITTER
     # inputs that end inside a k-group of the matrix-core body (2056 = 32 x 64 + 8): what lies
     # between the end of a staged row, or of the gains, and the end of the k-group is multiplied too
     (("C1", dict(n_layers=2, hidden=2056, ffn=3000, batch=5, max_seq=192)), dict(fusion=31, transitive_reduction=1, n_workers=24)),
-    # the kernels compiled for head dimension 128 at batch 5..16, dense (1000 inputs: under one staging tile) and experts
+    # head dimension 128 at batch 16, dense (1000 inputs: under one staging tile) and experts
     (("C1", dict(n_layers=2, hidden=1000, ffn=520, batch=16, vocab=520, head_dim=128, n_q_heads=8, n_kv_heads=2, max_seq=192)),
      dict(fusion=31, transitive_reduction=1, n_workers=24)),
     (("C1", dict(n_layers=2, hidden=528, batch=16, head_dim=128, n_q_heads=8, n_kv_heads=1, ffn=0, n_experts=16, top_k=4, expert_ffn=104, max_seq=192)),

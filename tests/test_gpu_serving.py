@@ -244,12 +244,12 @@ def _server_logits(srv, s, dev):
     (dict(batch=3, n_layers=2), 8, 3 + 12, 5, dict(debug_flags=M.binding.DEBUG_POISON | M.binding.DEBUG_JITTER)),
     (dict(batch=1, n_layers=2), 16, 1 + 3, 9, {}),
     (dict(batch=3, n_layers=2), 8, 3 + 12, 6, dict(tiles_sampling=4)),
-    # batch <= 4, one launch of the loop kernel for all iterations (the default is a launch per iteration)
+    # one launch of the loop kernel for all iterations (the default is a launch per iteration)
     (dict(batch=3, n_layers=2), 8, 3 + 12, 7, dict(greedy_loop=2)),
     (dict(batch=1, n_layers=2), 16, 1 + 3, 9, dict(greedy_loop=2, debug_flags=M.binding.DEBUG_JITTER)),
-    # batch 8: serving calls are a launch per iteration by default as well; the one launch of the loop kernel
+    # ... at batch 8
     (dict(batch=8, n_layers=2, head_dim=128, n_q_heads=4, n_kv_heads=2), 16, 8 + 14, 25, dict(greedy_loop=2)),
-    # the kernels compiled for head dimension 128 and 4 query heads per KV head (dense, batch 5..16): both launch forms
+    # 4 query heads per KV head: both launch forms
     (dict(batch=8, n_layers=2, head_dim=128, n_q_heads=8, n_kv_heads=2), 16, 8 + 14, 25, {}),
     (dict(batch=8, n_layers=2, head_dim=128, n_q_heads=8, n_kv_heads=2), 16, 8 + 14, 25, dict(greedy_loop=2)),
     (dict(batch=8, n_layers=1, head_dim=128, n_q_heads=8, n_kv_heads=1, ffn=0, n_experts=8, top_k=2, expert_ffn=64), 8, 8 + 20, 9, {}),
