@@ -1982,12 +1982,11 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
 //     elements (whole rows per instruction) and transposes the 8 x (D / 16) block in its registers
 //     (v_perm_b32); tile t then covers output elements (D / 16) column + t
 //
-// Rounding: what is left is the fp32 sums.  The multiplies of a score's D products share an accumulator by halves,
-// and the halves are added: chained through one accumulator every multiply rounds at the
+// Rounding: what is left is the fp32 sums.  A score's D products go through D / 32 multiplies with
+// accumulators of their own, added pairwise: chained through one accumulator every multiply rounds at the
 // size the sum has reached, and an error of a score is a relative error of its weight (logits
 // against 64 bits, root mean square over inputs with scores up to some tens: D = 128 with 8 query heads per KV
-// head 1.53e-6 in one chain, 0.85e-6 by halves, 0.88e-6 with an accumulator a multiply, which takes 16 more additions a
-// block; 0.99e-6 in vector arithmetic of runs of eight inputs).
+// head 1.53e-6 chained, 0.88e-6 pairwise, 0.99e-6 in vector arithmetic of runs of eight inputs).
 //
 // K and V rows of a block are requested ahead: the first block's before the task's event, the next
 // K as soon as K has been multiplied, the next V likewise -- 8 to 16 KB in flight per wavefront
@@ -2388,7 +2387,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
 #pragma unroll
     for (int k = 0; k < NT; ++k) O[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto block = [&](auto coherent, auto more, uint32_t blk) {
-      // ---- scores, by halves of the inputs (see above)
+      // ---- scores: 32 inputs at a time, added up pairwise (see above)
       f32x4 S[2];
 #pragma unroll
       for (int T = 0; T < 2; ++T) {
@@ -2396,19 +2395,13 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
 #pragma unroll
         for (int q = 0; q < KG; ++q) {
           pair_to_operands(kreg[T][q][0], kreg[T][q][1]);
-          auto mul = [&](const u32x4& k, const u32x4& x, const f32x4& c) {
-            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
+          auto mul = [&](int U) {
+            const bf16x8 kv = __builtin_bit_cast(bf16x8, kreg[T][q][U]);
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (TWO) v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qlo[q][U]), v, 0, 0, 0);
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv, __builtin_bit_cast(bf16x8, qop[q][U]), v, 0, 0, 0);
           };
-          const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-          f32x4 v = zero, u = zero;   // (D = 64: an accumulator for each half)
-          if constexpr (TWO) {        // the small terms first
-            v = mul(kreg[T][q][0], qlo[q][0], v);
-            if constexpr (KG == 2) v = mul(kreg[T][q][1], qlo[q][1], v);
-            else u = mul(kreg[T][q][1], qlo[q][1], u);
-          }
-          v = mul(kreg[T][q][0], qop[q][0], v);
-          if constexpr (KG == 2) part[q] = mul(kreg[T][q][1], qop[q][1], v);
-          else part[q] = v + mul(kreg[T][q][1], qop[q][1], u);
+          part[q] = mul(0) + mul(1);
         }
         S[T] = KG == 2 ? part[0] + part[KG - 1] : part[0];
         __builtin_amdgcn_sched_barrier(0);   // (both tiles' sums at once take five more registers, which the callers' long-lived values lose)

@@ -9,9 +9,9 @@ from synth import gen as G
 from tests.gpu_util import GpuDecoder, held_step
 
 pytestmark = pytest.mark.gpu
-# A score is 64 or 128 exact products.  Summed in 32 bits by halves, the root mean square over these inputs is
-# 0.75 .. 0.91e-6 (0.88 .. 0.99e-6 in the eight-input runs of a vector body); one accumulator for the whole
-# score gives 1.15 .. 1.53e-6 with a head size of 128.
+# A score is 64 or 128 exact products.  Summed pairwise, 32 inputs at a time, in 32 bits the root mean square over
+# these inputs is 0.75 .. 0.94e-6 (0.88 .. 0.99e-6 in the eight-input runs of a vector body); one accumulator
+# for the whole score gives 1.15 .. 1.53e-6 with a head size of 128.
 BOUND = 1.05e-6
 
 
