@@ -3449,8 +3449,8 @@ __global__ void __launch_bounds__(kThreads) mpk_loop_kernel(StepArgs a) {
 }
 
 // HYBRID: the hybrid launch (scheduler workgroups); otherwise the all-ahead-of-time walk.  Two kernels:
-// in one that holds both, the hybrid walk's spilled registers (two rows 156 against none, three buffers 175
-// against 32) are the other's too, and a reload from scratch memory waits for every weight load in flight.
+// in one that holds both, the hybrid walk's spilled registers (two rows 164 against none, three buffers 175
+// against 26) are the other's too, and a reload from scratch memory waits for every weight load in flight.
 // RUN: the instance launched once per step for a run of several steps (vector linear bodies): it
 // can find that an earlier step of the run left the server drained.  A kernel of its own, so that
 // the single-step kernel stays exactly as it is (1.2 % slower with the check compiled in).
