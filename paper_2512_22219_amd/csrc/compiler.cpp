@@ -960,7 +960,7 @@ static void build_descs(const mpk_model_config& c, const mpk_kv_ptrs* kv, HostGr
     TaskDesc& t = g.descs[i];
     t.dep_event = ht.dep_event;
     t.trig_event = ht.trig_event;
-    t.pad = i;   // own index in the linearized task list (trace slots are indexed by it)
+    t.index = (uint32_t)i;   // (trace slots are indexed by it)
     if (ht.op == MPK_TASK_DUMMY_OP) { t.kind = TK_DUMMY; continue; }
     const HostOp& op = g.ops[ht.op];
     tile_bounds(op, ht.tile, &t.b0, &t.b1, &t.c0, &t.c1);
@@ -1025,6 +1025,74 @@ static void build_descs(const mpk_model_config& c, const mpk_kv_ptrs* kv, HostGr
         t.aux1 = (uint16_t*)kv->v + (size_t)op.p0 * kv_layer;
       }
     }
+  }
+}
+
+// ------------------------------------------------------------------ marked tensors
+// Which tensors tell by themselves what has been written (kUnsetWord), and which tasks rely on it.  A tensor
+// is marked if linear or attention tasks write it and every task that reads it is a linear or attention
+// task (those look at each word that they load), or comes behind a linear operator that reads all of it (the expert
+// tasks and the combine of a mixture-of-experts layer: the router).  A task skips its event if its first input is marked; what
+// else it reads -- the residual, the rotation angles, the input of an earlier operator -- has been
+// seen by the tasks that made that input, so an event or a look at every word lies between.  Only where
+// every task is ahead-of-time.
+static void mark_tensors(HostGraph& g) {
+  g.mark_flags.clear();
+  g.marked_tensor.assign(g.tensors.size(), 0);
+  if (g.opt.launch_mode != MPK_LAUNCH_MEGA || g.stats.n_jit_tasks) return;
+  auto linear = [](const HostOp& op) { return (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) && !(op.flags & TF_SPLITK); };
+  auto attention = [](const HostOp& op) { return op.kind == MPK_OP_ATTN_PARTIAL && (op.flags & TF_ROPE_FUSED) && (op.flags & TF_ATTN_MERGE); };
+  if (g.cfg.batch >= kMfmaMinBatch) return;   // (the matrix-core body waits for events, see mark_wait)
+  std::vector<int> producer(g.tensors.size(), -1);
+  for (size_t i = 0; i < g.ops.size(); ++i) producer[g.ops[i].out_tensor] = (int)i;
+  std::vector<uint8_t> out(g.ops.size(), 0);
+  bool any = false;
+  for (size_t i = 0; i < g.ops.size(); ++i) {
+    const HostOp& p = g.ops[i];
+    if (!(linear(p) || attention(p)) || (p.flags & TF_OUT_LOGITS)) continue;
+    bool ok = true, read = false, whole = false;
+    for (const HostOp& r : g.ops) {
+      if (r.in_tensor != p.out_tensor && r.in2_tensor != p.out_tensor && r.in3_tensor != p.out_tensor) continue;
+      read = true;
+      if (linear(r) && r.in_tensor == p.out_tensor) whole = true;
+      if ((r.kind == MPK_OP_EXPERT || r.kind == MPK_OP_COMBINE) && !attention(p)) continue;
+      ok = ok && (linear(r) || (attention(r) && r.in_tensor == p.out_tensor && !attention(p)));
+    }
+    for (const HostOp& r : g.ops)
+      if ((r.kind == MPK_OP_EXPERT || r.kind == MPK_OP_COMBINE) && (r.in_tensor == p.out_tensor || r.in2_tensor == p.out_tensor || r.in3_tensor == p.out_tensor)) ok = ok && whole;
+    out[i] = ok && read;
+  }
+  auto is_marked = [&](int tensor) { return tensor >= 0 && producer[tensor] >= 0 && out[producer[tensor]]; };
+  auto skips_event = [&](const HostTask& t) {
+    return t.op != MPK_TASK_DUMMY_OP && (linear(g.ops[t.op]) || (attention(g.ops[t.op]) && out[t.op])) && is_marked(g.ops[t.op].in_tensor);
+  };
+  // A marked output is not notified: only where every task on its event skips that event.
+  for (bool changed = true; changed;) {
+    changed = false;
+    for (const HostTask& p : g.tasks) {
+      if (p.op == MPK_TASK_DUMMY_OP || !out[p.op]) continue;
+      const EventDesc& e = g.events[p.trig_event];
+      bool ok = true;
+      for (uint32_t i = e.first; i < e.last && ok; ++i) ok = skips_event(g.tasks[i]);
+      ok = ok && !(attention(g.ops[p.op]) && !is_marked(g.ops[p.op].in_tensor));   // (both ends of an attention task or neither)
+      if (!ok) { out[p.op] = 0; changed = true; }
+    }
+  }
+  for (uint8_t o : out) any = any || o;
+  if (!any) return;
+  g.mark_flags.assign(g.tasks.size(), 0);
+  for (size_t i = 0; i < g.tasks.size(); ++i) {
+    if (g.tasks[i].op == MPK_TASK_DUMMY_OP) continue;
+    const HostOp& op = g.ops[g.tasks[i].op];
+    uint16_t f = 0;
+    if (skips_event(g.tasks[i])) f |= TF_IN_MARKED | (linear(op) && is_marked(op.in2_tensor) ? TF_IN2_MARKED : 0);
+    if (out[g.tasks[i].op]) f |= TF_OUT_MARKED;
+    g.mark_flags[i] = f;
+  }
+  for (size_t i = 0; i < g.ops.size(); ++i) {
+    if (!out[i]) continue;
+    g.marked_tensor[g.ops[i].out_tensor] = 1;
+    if (g.ops[i].side_out_tensor >= 0) g.marked_tensor[g.ops[i].side_out_tensor] = 1;
   }
 }
 
@@ -1346,6 +1414,7 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
   if (st != MPK_OK) return st;
   g.stats.n_pair_deps += g.stats.n_pairs_removed;
   build_descs(cfg, kv, g);
+  mark_tensors(g);
   size_t accept_lds = 0;
   g.lds_bytes = lds_requirement(cfg, g, C, &accept_lds);
   if (sp.page_ready) {   // (second pass: the tile sizes already account for the pages)

@@ -15,7 +15,8 @@
 // are performed at the device coherence point, not in an XCD-private cache.  Producer side:
 // agent-scope stores, every wavefront waits for its own stores to complete (vmcnt 0), workgroup
 // barrier, one lane adds to the event counter.  Consumer side: one lane polls the counter,
-// workgroup barrier, then agent-scope loads.  Weights, descriptors and cache rows of earlier
+// workgroup barrier, then agent-scope loads.  A marked tensor (kUnsetWord) needs none of it: each of its
+// words says whether it has been written, the consumer's loads are its poll.  Weights, descriptors and cache rows of earlier
 // steps are immutable during a step and use ordinary (non-temporal) loads.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -50,7 +51,8 @@ struct GraphConst {
   uint32_t* err;             // [0] error code, [1] abort flag, [2..3] detail
   const double* inv_freq;    // RoPE frequencies theta^(-2i/d), i < head_dim / 2
   uint32_t attn_shape;       // attn_shape_index of the model and its cache
-  float* rope_tab;           // [batch][head_dim / 2] (cos, sin) of this step's rotation angles, written by the embedding tasks
+  float* rope_tab;           // [2][batch][head_dim / 2] (cos, sin) of a step's rotation angles, even and odd steps, written by
+                             // the embedding tasks; the copy of the other steps is put back to unset (kUnsetWord)
   uint32_t* grp_counters;    // arrival counters per (layer, sequence, KV head), monotonic
   uint64_t* trace;           // optional [n_tasks][kTraceSlots] timestamps (100 MHz), or null
   uint64_t timeout_ticks;
@@ -82,6 +84,8 @@ struct GraphConst {
   const ServeDev* serve;       // serving state, or null
   uint32_t page_shift, kv_pages;
   int32_t serve_event;         // event the serving task triggers, -1 = none
+  uint32_t mark_words;         // words of one copy of the marked tensors (0: none), copies for even and odd steps
+  float* mark_base;
 };
 
 // Which instance of the attention task runs: head_dim 64 / 128, 1 / 2 / 4 / 8 query heads per KV head,
@@ -205,7 +209,7 @@ constexpr uint32_t kServeBit = 16u;     // serving launch: positions[] and token
 constexpr uint32_t kOneStepBit = 32u;   // the launch runs ONE step (single-step entry points, a launch per step of a run):
                                         // nothing that earlier steps wrote can be stale in a cache
 __device__ __forceinline__ void trace_mark(const StepArgs& a, const TaskDesc& t, int slot) {
-  if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.pad * kTraceSlots + slot] = wall_clock64();
+  if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.index * kTraceSlots + slot] = wall_clock64();
 }
 
 // MPK_DEBUG_JITTER: a delay of 0 .. 20 us, a hash of (task, step), before the task does anything.
@@ -328,6 +332,22 @@ __device__ __forceinline__ u32x4 ld_row16_coherent(const uint16_t* p) {   // p 1
   return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
 }
 
+// 16 and 8 bytes of a buffer at byte `off`, zeros past its end.  COHERENT: performed at the device's coherence point (words
+// one by one, not 16 bytes at once) and never taken for an earlier load of the same place.
+template <bool COHERENT>
+__device__ __forceinline__ u32x4 ld_buffer16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, COHERENT ? (int)(16u | 0x80000000u) : 0));
+}
+__device__ __forceinline__ u32x2 ld_buffer8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+// Waits until at most N of this wavefront's vector-memory operations, the youngest, are in flight.
+template <int N>
+__device__ __forceinline__ void wait_vmem() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+  asm volatile("" ::: "memory");
+}
 // Waits for this wavefront's own loads and stores (and LDS operations).  A builtin and not assembly text:
 // the compiler then knows that nothing is in flight any more.  Otherwise it takes the last loads of a
 // task for pending in the next one, and copies into LDS (flat accesses to it, which may complete out of
@@ -393,7 +413,10 @@ __device__ __forceinline__ void body_embed(const TaskDesc& t, const StepArgs& a)
     if (i < half) {
       float cs, sn;
       rope_cs(a, pos, i, &cs, &sn);
-      st_act2(a.g->rope_tab + 2u * ((size_t)b * half + i), cs, sn);
+      const uint32_t copy = a.g->batch * a.g->head_dim;
+      float* tab = a.g->rope_tab + 2u * ((size_t)b * half + i);
+      st_act2(tab + (a.epoch & 1u) * copy, cs, sn);
+      st_act2(tab + (~a.epoch & 1u) * copy, __uint_as_float(kUnsetWord), __uint_as_float(kUnsetWord));
     }
   }
 }
@@ -422,6 +445,65 @@ __device__ __forceinline__ EventProbe probe_event(const StepArgs& a, int32_t e, 
 __device__ __forceinline__ bool probe_reached(const EventProbe& p);
 __device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag);
 __device__ __forceinline__ bool wait_event(const StepArgs& a, int32_t e, uint32_t* s_flag, const EventProbe& probe);
+__device__ __forceinline__ StepArgs published_args();
+
+// ------------------------------------------------------------------------------ marked tensors
+// (see kUnsetWord.)  Loads of a marked tensor are repeated until none of them finds an unset word; mark_wait says
+// whether to go round again.  What bounds a hop between two operators is the number of trips to the
+// coherence point that follow one another: five with an event (store, its acknowledgement, notification, poll,
+// input), two here.  us a step, events / marked: tiny model 57.1 / 42.6, 1B class at batch 1 784 / 747, 8B 2788 / 2758,
+// 2B class at batch 2, four tokens 2700 / 2434, 70B layers 1804 / 1795.
+// For batch 1 and 2 only: at batch 8 a worker's input is 128 KB, and 256 workers that load it before it is
+// complete, and look at every word, take more from the producers than the hop gives (8B layers at batch 8 1078 -> 1155,
+// 4B class at batch 4 811 -> 893).
+__device__ __forceinline__ float mark_clean(float v) {   // (no arithmetic gives this pattern as far as is known: made certain)
+  return __float_as_uint(v) == kUnsetWord ? __uint_as_float(0x7FC00000u) : v;
+}
+__device__ __forceinline__ bool mark_unset(float v) { return __float_as_uint(v) == kUnsetWord; }
+__device__ __forceinline__ bool mark_unset(const float2& v) { return max(__float_as_uint(v.x), __float_as_uint(v.y)) == kUnsetWord; }
+// Puts a word of the other copy back to unset (two words: p 8-byte aligned).
+__device__ __forceinline__ void mark_reset(float* p, int32_t twin) {
+  if (twin) st_act_u32((uint32_t*)(p + (ptrdiff_t)twin * 64), kUnsetWord);
+}
+__device__ __forceinline__ void mark_reset2(float* p, int32_t twin) {
+  const float u = __uint_as_float(kUnsetWord);
+  if (twin) st_act2(p + (ptrdiff_t)twin * 64, u, u);
+}
+// Control word of the LDS: set by a wavefront that gives up waiting (the step is being aborted).
+constexpr uint32_t kLdsAbortAt = 8;
+struct MarkWait {
+  uint32_t tries = 0;
+  uint64_t t0 = 0;
+};
+// The whole wavefront calls it.  True: some lane has found an unset word, load again.  False: every lane has what it
+// asked for, or the step is being aborted: mark_aborted then says so to every wavefront of the workgroup
+// behind the next barrier, and the task ends by itself (mark_report).
+__device__ __forceinline__ bool mark_wait(const StepArgs& a, bool unset, MarkWait& w) {
+  if (!__any(unset)) return false;
+  if (__builtin_expect((++w.tries & 255u) == 0, 0)) {
+    const uint64_t now = wall_clock64();
+    if (w.tries == 256u) w.t0 = now;
+    if (now - w.t0 > a.g->timeout_ticks || __builtin_amdgcn_readfirstlane(ld_relaxed(a.g->err + 1)) != 0) {
+      extern __shared__ __align__(16) float dyn_lds[];
+      ((volatile uint32_t*)dyn_lds)[kLdsAbortAt] = 1u;
+      return false;
+    }
+  }
+  return true;
+}
+__device__ __forceinline__ bool mark_aborted() {
+  extern __shared__ __align__(16) float dyn_lds[];
+  return __builtin_amdgcn_readfirstlane(((volatile uint32_t*)dyn_lds)[kLdsAbortAt]) != 0;
+}
+
+// A task has given up on its inputs: the watchdog's report, unless the step was being aborted already.
+__device__ __noinline__ void mark_report(uint32_t event) {
+  const StepArgs a = published_args();
+  if (threadIdx.x == 0 && ld_relaxed(a.g->err + 1) == 0) {
+    report(a, DE_TIMEOUT, event, blockIdx.x);
+    __hip_atomic_store(as_global(a.g->err + 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
 
 // ------------------------------------------------------------------------------ linear tasks
 // T2/T6/T9/T11/T14: y[b][c] = sum_j W[c][j] x[b][j] for output columns [c0, c1), all batch rows
@@ -615,12 +697,15 @@ __device__ __forceinline__ void poll_event_or_jit_wave0(const StepArgs& a, int32
 // NoJit: all-ahead-of-time kernels, nothing to watch.
 constexpr uint32_t kLinAbort = 0, kLinDone = 1, kLinPreempted = 2;
 struct NoJit {
-  static constexpr bool enabled = false;
+  static constexpr bool enabled = false, marks = false;
   uint32_t jit_head = 0;
   uint32_t n_next = 0, next[2] = {0, 0};   // the worker's next tasks, see warm_descriptors
 };
+struct NoJitMarks : NoJit {   // ... and the task's descriptor may be a marked one
+  static constexpr bool marks = true;
+};
 struct JitWatch {
-  static constexpr bool enabled = true;
+  static constexpr bool enabled = true, marks = false;
   uint32_t jit_head;   // the worker's consumer ticket of its just-in-time queue
 };
 // The first look at an event, by the first wavefront and ahead of the task's weight requests: loads
@@ -659,6 +744,11 @@ __device__ __forceinline__ void warm_descriptors(const StepArgs& a, uint32_t ti)
   }
   asm volatile("; descriptors of a later task" :: "s"(last), "s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]));
 }
+template <class Svc>
+__device__ __forceinline__ void warm_next(const StepArgs& a, const Svc& svc) {
+  if (svc.n_next > 0) warm_descriptors(a, svc.next[0]);
+  if (svc.n_next > 1) warm_descriptors(a, svc.next[1]);
+}
 // The wait of a linear task for its dependent event: kLinDone (activated), kLinAbort, kLinPreempted.
 template <class Svc>
 __device__ __forceinline__ uint32_t linear_wait(const StepArgs& a, int32_t wait_ev, uint32_t* s_flag, uint32_t wave, int lane,
@@ -672,10 +762,7 @@ __device__ __forceinline__ uint32_t linear_wait(const StepArgs& a, int32_t wait_
     }
   }
   if constexpr (!Svc::enabled) {
-    if (wave == 1 && svc.n_next > 0) {
-      warm_descriptors(a, svc.next[0]);
-      if (svc.n_next > 1) warm_descriptors(a, svc.next[1]);
-    }
+    if (wave == 1) warm_next(a, svc);
   }
   lds_barrier();
   return __builtin_amdgcn_readfirstlane(*s_flag);   // (uniform; tell the compiler)
@@ -714,18 +801,78 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   HalfRing h0, h1;   // local to the task: nothing is live around the task loop, so they stay in registers
   ring_clear(h0);
   ring_clear(h1);
+  const bool in_marked = Svc::marks && (t.flags & TF_IN_MARKED), in2_marked = Svc::marks && (t.flags & TF_IN2_MARKED);
+  const bool preload = !(a.flags & kNoPreloadBit);   // off: the ablation of Section 6.5, Fig. 10
+  const bool pro_norm = t.flags & TF_PRO_NORM;
+  // ---- the input rows: 16 bytes a load, kSlices loads a lane and row in flight (12288 inputs in one round trip)
+  constexpr uint32_t kSlices = 6, kSlice = 4u * kThreads, kChunk = kSlices * kSlice;   // (inputs)
+  u32x4 xin[NB][kSlices];
+  auto x_load = [&](uint32_t i0) {
+#pragma unroll
+    for (uint32_t b = 0; b < (uint32_t)NB; ++b) {
+      // (a row that does not exist is an empty buffer: zeros)
+      const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(t.in + (size_t)(t.b0 + b) * t.ld_in)), 0, b < nb ? (int)(4u * K) : 0, 0x00020000);
+#pragma unroll
+      for (uint32_t u = 0; u < kSlices; ++u)
+        if (i0 + u * kSlice < K) xin[b][u] = ld_buffer16<true>(r, 4u * (i0 + u * kSlice + 4u * tid));
+    }
+  };
+  // Every word of the loaded chunk has been written (wavefront-uniform).
+  auto x_complete = [&](uint32_t i0) {
+    uint32_t top = 0;
+#pragma unroll
+    for (uint32_t b = 0; b < (uint32_t)NB; ++b)
+#pragma unroll
+      for (uint32_t u = 0; u < kSlices; ++u)
+        if (i0 + u * kSlice < K) top = max(top, max(max(xin[b][u].x, xin[b][u].y), max(xin[b][u].z, xin[b][u].w)));
+    return !__any(top == kUnsetWord);
+  };
+  // A marked input is asked for three times: ahead of everything, between the two half blocks and behind them.  The
+  // loads of a compute unit come back in the order they were issued, those of other wavefronts included: behind both
+  // half blocks the input of a worker that is late anyway would be there 3 to 5 us after it could have
+  // been, and a worker that is early by a fraction of a microsecond finds it on the second try.
+  bool x_ok = false;
+  if (in_marked && preload) x_load(0u);
+  // the residual slice of this tile (tile-local, small): its round trip overlaps the staging
+  const bool resid = t.flags & TF_EPI_RESID;
+  float resv = 0.f;
+  const float* resp = t.in2;
+  if (resid && tid < nb * ncols) {
+    const uint32_t bb = tid / ncols, cc = tid % ncols;
+    resp += (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc;
+    if (in2_marked) resv = ld_act(resp);
+  }
+  // the first gains of a folded RMSNorm are weights: requested before the event, so that the staging is one
+  // round trip (the input) instead of two
+  constexpr uint32_t kGainPre = 2;   // slices: the first 4096 inputs
+  const auto gain = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(uniform_ptr((const uint16_t*)t.w2)), 0, pro_norm ? (int)(2u * K) : 0, 0x00020000);
+  u32x2 gpre[kGainPre];
+#pragma unroll
+  for (uint32_t u = 0; u < kGainPre; ++u) {
+    gpre[u] = u32x2{0u, 0u};
+    if (pro_norm && u * kSlice < K) gpre[u] = ld_buffer8(gain, 2u * (u * kSlice + 4u * tid));
+  }
   LinCursor rq{g.r0, 0u};   // next half block to request
   if (page_ready && lin_valid(g, rq)) lin_advance(g, rq);   // the first one is in this wavefront's page already
   // (every request site ends in an (empty) assembly statement of its own: otherwise the compiler
   // may merge the identical last loads of two sites into one whose destination is chosen at run
   // time, and a buffer addressed that way is moved from registers to scratch memory)
-  const bool preload = !(a.flags & kNoPreloadBit);   // off: the ablation of Section 6.5, Fig. 10
+  // (the waits are builtins, one on each path: the compiler's own count of the loads in flight does not survive the
+  // branches around the requests)
   if (preload && lin_valid(g, rq)) {
     lin_request(lin_half(g, rq), h0, lane);
     lin_advance(g, rq);
     asm volatile("; first half block requested" ::: "memory");
+    if (in_marked) wait_vmem<2 * kRingStages>();
+  } else if (in_marked) {
+    wait_vmem<0>();
   }
-  if (preload && lin_valid(g, rq)) {
+  if (in_marked && preload) {
+    x_ok = x_complete(0u);
+    if (!x_ok) x_load(0u);
+  }
+  const bool two = preload && lin_valid(g, rq);
+  if (two) {
     lin_request(lin_half(g, rq), h1, lane);
     lin_advance(g, rq);
     asm volatile("; second half block requested" ::: "memory");
@@ -737,26 +884,21 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // mere presence of the third buffer in the kernel costs the small shape 2 %.
   constexpr bool kThird = DEEP;
   HalfRing h2;
+  bool three = false;
   if (kThird) {
     ring_clear(h2);
-    if (preload && lin_valid(g, rq)) {
+    three = preload && lin_valid(g, rq);
+    if (three) {
       lin_request(lin_half(g, rq), h2, lane);
       lin_advance(g, rq);
       asm volatile("; third half block requested" ::: "memory");
     }
   }
-  // the first gains of a folded RMSNorm are weights too: requested before the event, so that the
-  // staging below is one round trip (the input) instead of two
-  constexpr int kGainPre = 4;   // x 512 threads x 2: the first 4096 inputs
-  uint32_t gpre[kGainPre];
-  {
-    const uint16_t* gain0 = (const uint16_t*)t.w2;
-#pragma unroll
-    for (int u = 0; u < kGainPre; ++u) {
-      const uint32_t i = u * kThreads + tid;
-      gpre[u] = 0;
-      if ((t.flags & TF_PRO_NORM) && i < K / 2) gpre[u] = *as_global((const uint32_t*)(gain0 + 2 * i));
-    }
+  if (in_marked && preload && !x_ok) {
+    if (kThird && three) wait_vmem<4 * kRingStages>();
+    else if (two) wait_vmem<2 * kRingStages>();
+    else wait_vmem<0>();
+    x_ok = x_complete(0u);
   }
   if (page_next) {
     // this task is short and has a long wait ahead: the first half block of every wavefront's
@@ -770,6 +912,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   if (wait_ev >= 0) {
     const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc, EventProbe{});
     if (w != kLinDone) return w;   // aborted, or pre-empted by a just-in-time task: the requested weights are dropped
+  } else if constexpr (Svc::marks) {
+    if (wave == 1) warm_next(a, svc);
   }
   trace_mark(a, t, 1);
   if (!preload) {   // pre-loading switched off: the first requests go out only now
@@ -791,61 +935,59 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   }
   // ---- stage the input rows in LDS.  With TF_PRO_NORM the gain is folded in here (x * g) and
   // the row's 1/rms factor is applied to the finished dot products: W (x g inv) = inv * W (x g).
-  const bool pro_norm = t.flags & TF_PRO_NORM;
-  const uint16_t* gain = (const uint16_t*)t.w2;
-  // the residual slice of this tile goes out first (tile-local, small): its round trip then
-  // overlaps the staging instead of following it
-  const bool resid = t.flags & TF_EPI_RESID;
-  float resv = 0.f;
-  if (resid && tid < nb * ncols) {
-    const uint32_t bb = tid / ncols, cc = tid % ncols;
-    resv = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc);
-  }
-  constexpr int kStageLoads = 12;   // coherent loads in flight per lane: 12288 inputs in one round trip
+  if (resid && !in_marked && tid < nb * ncols) resv = ld_act(resp);
+  float ss[NB];
 #pragma unroll
-  for (uint32_t b = 0; b < (uint32_t)NB; ++b) {
-    float2* dst = (float2*)(xs + (size_t)b * Kp);
-    float ss = 0.f;
-    if (b < nb) {
-      const float* src = t.in + (size_t)(t.b0 + b) * t.ld_in;
-      for (uint32_t i0 = 0; i0 < Kp / 2; i0 += kThreads * kStageLoads) {
-        float2 tmp[kStageLoads];
-#pragma unroll
-        for (int u = 0; u < kStageLoads; ++u) {
-          uint32_t i = i0 + u * kThreads + tid;
-          if (i < K / 2) tmp[u] = ld_act2(src + 2 * i);
-        }
-#pragma unroll
-        for (int u = 0; u < kStageLoads; ++u) {
-          uint32_t i = i0 + u * kThreads + tid;
-          if (i < K / 2) {
-            float2 v = tmp[u];
-            if (pro_norm) {
-              ss = fmaf(v.x, v.x, ss);
-              ss = fmaf(v.y, v.y, ss);
-              uint32_t g2 = (i0 == 0 && u < kGainPre) ? gpre[u < kGainPre ? u : 0] : *as_global((const uint32_t*)(gain + 2 * i));
-              v.x *= bf16_lo(g2);
-              v.y *= bf16_hi(g2);
-            }
-            dst[i] = v;
-          } else if (i < Kp / 2) {
-            dst[i] = make_float2(0.f, 0.f);
-          }
-        }
-      }
-    } else {
-      for (uint32_t i = tid; i < Kp / 2; i += kThreads) dst[i] = make_float2(0.f, 0.f);
+  for (int b = 0; b < NB; ++b) ss[b] = 0.f;
+  for (uint32_t i0 = 0; i0 < Kp; i0 += kChunk) {
+    if (i0 || !x_ok) {
+      MarkWait mw;
+      x_load(i0);
+      while (in_marked && mark_wait(a, !x_complete(i0), mw)) x_load(i0);
     }
-    if (pro_norm) {
-      ss = wave_sum_dpp(ss);
-      if (lane == 0) ssq[wave * NB + b] = ss;
+#pragma unroll
+    for (uint32_t u = 0; u < kSlices; ++u) {
+      const uint32_t i = i0 + u * kSlice + 4u * tid;
+      if (i0 + u * kSlice >= Kp) continue;
+      float gn[4] = {1.f, 1.f, 1.f, 1.f};
+      if (pro_norm) {
+        const u32x2 g2 = (i0 == 0 && u < kGainPre) ? gpre[u < kGainPre ? u : 0] : ld_buffer8(gain, 2u * i);
+        gn[0] = bf16_lo(g2.x); gn[1] = bf16_hi(g2.x); gn[2] = bf16_lo(g2.y); gn[3] = bf16_hi(g2.y);
+      }
+#pragma unroll
+      for (uint32_t b = 0; b < (uint32_t)NB; ++b) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i0 + u * kSlice < K) v = __builtin_bit_cast(float4, xin[b][u]);
+        if (pro_norm) {
+          ss[b] = fmaf(v.x, v.x, ss[b]); ss[b] = fmaf(v.y, v.y, ss[b]); ss[b] = fmaf(v.z, v.z, ss[b]); ss[b] = fmaf(v.w, v.w, ss[b]);
+          v.x *= gn[0]; v.y *= gn[1]; v.z *= gn[2]; v.w *= gn[3];
+        }
+        if (i < Kp) *(float4*)(xs + (size_t)b * Kp + i) = v;
+      }
+    }
+  }
+  if (pro_norm) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const float v = wave_sum_dpp(ss[b]);
+      if (lane == 0) ssq[wave * NB + b] = v;
     }
   }
   if (resid) {
+    MarkWait mw;
+    if (in2_marked)   // (written long ago: it is an input of this task's producers' producers)
+      while (mark_wait(a, mark_unset(resv), mw))
+        if (mark_unset(resv)) resv = ld_act(resp);
+    if (in_marked && !in2_marked && tid < nb * ncols) resv = ld_act(resp);   // (not marked: complete only now that the input is)
     if (tid < nb * ncols) res_lds[tid] = resv;
-    for (uint32_t i = tid + kThreads; i < nb * ncols; i += kThreads) {   // more than 512 outputs per task: rare
-      uint32_t bb = i / ncols, cc = i % ncols;
-      res_lds[i] = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc);
+    for (uint32_t i0 = kThreads; i0 < nb * ncols; i0 += kThreads) {   // more than 512 outputs per task: rare
+      const uint32_t i = i0 + tid, bb = i / ncols, cc = i % ncols;
+      const float* p = t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc;
+      float v = i < nb * ncols ? ld_act(p) : 0.f;
+      if (in2_marked)
+        while (mark_wait(a, mark_unset(v), mw))
+          if (mark_unset(v)) v = ld_act(p);
+      if (i < nb * ncols) res_lds[i] = v;
     }
   }
   lds_barrier();
@@ -920,6 +1062,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   lds_barrier();
   trace_mark(a, t, 3);
   // ---- wavefront 0: epilogue, outputs, notification, then its own share of the pre-load
+  const bool out_marked = Svc::marks && (t.flags & TF_OUT_MARKED);
+  const bool aborted = in_marked && mark_aborted();   // (before the last barrier: the flag is then everybody's)
   if (wave == 0) {
     float* outp = (t.flags & TF_OUT_LOGITS) ? a.logits : t.out;
     float inv_rms[NB];
@@ -946,9 +1090,11 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         v = outbuf[(size_t)cc * NB + bb] * inv;
       }
       if (t.flags & TF_EPI_RESID) v = res_lds[bb * ncols + cc] + v;
-      st_act(outp + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc, v);
+      st_act(outp + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cc, out_marked ? mark_clean(v) : v);
     }
-    if (MEGA) {   // wait for exactly these stores
+    if (out_marked)
+      for (uint32_t i = lane; i < ncols * nb; i += 64) mark_reset(outp + (size_t)(t.b0 + i / ncols) * t.ld_out + t.c0 + i % ncols, t.twin);
+    if (MEGA && !(out_marked && t.trig_event < 0)) {   // wait for exactly these stores
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       drain_vmem();
       trace_mark(a, t, 7);
@@ -967,7 +1113,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
       trace_mark(a, t, 4);
     }
   }
-  return kLinDone;
+  return aborted ? kLinAbort : kLinDone;
 }
 
 // ------------------------------------------------------------------------------ linear tasks, batch 3..16
@@ -2017,8 +2163,11 @@ __device__ __forceinline__ float row_ror(float v) {   // value of the lane N fur
 // A thread owns two adjacent output elements; all loads of up to 16 partials are in flight together
 // (the loads are what this costs: 3.3 us for 16 partials when they went out 8 at a time, 2 dwords
 // a partial, with an exp chain between).
-template <int D, int GRP>
-__device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row, uint32_t slot, uint32_t Cs, uint32_t ld, float* o) {
+// MARKED: the partials of the others say for themselves whether they are there, and the calling task's own, the
+// last of the C, is in LDS (`own`: outputs [grp][d], `own_ml`: maximum and sum [grp][2]).
+template <int D, int GRP, bool MARKED = false>
+__device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row, uint32_t slot, uint32_t Cs, uint32_t ld, float* o,
+                                                    const StepArgs& a, const TaskDesc& t, const float* own = nullptr, const float* own_ml = nullptr) {
   constexpr uint32_t per = GRP * (D + 2);
   constexpr int kAtOnce = 16;
   for (uint32_t i = threadIdx.x; i < (uint32_t)(GRP * D / 2); i += kThreads) {
@@ -2026,23 +2175,50 @@ __device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row
     float M = -INFINITY, L = 0.f, ax = 0.f, ay = 0.f;
     const float* part = row + (size_t)slot * per;
     uint32_t sl = slot;
+    const uint32_t Cm = MARKED ? C - 1u : C;   // partials in memory
+    float2 oml = make_float2(0.f, 0.f), oov = oml;
+    if (MARKED) {
+      oml = *(const float2*)(own_ml + 2 * j);
+      oov = *(const float2*)(own + j * D + e);
+    }
+    if (MARKED && C == 1u) {   // (what the general case comes to)
+      L = oml.y;
+      ax = oov.x;
+      ay = oov.y;
+    } else
     for (uint32_t c0 = 0; c0 < C; c0 += kAtOnce) {
       float2 ml[kAtOnce], ov[kAtOnce];
+      const float* part1;
+      uint32_t sl1;
+      MarkWait mw;
+      bool unset;
+      do {
+        part1 = part;
+        sl1 = sl;
+        unset = false;
 #pragma unroll
-      for (int k = 0; k < kAtOnce; ++k) {
-        ml[k] = make_float2(-INFINITY, 0.f);
-        ov[k] = make_float2(0.f, 0.f);
-        if (c0 + k < C) {
-          const float* pp = part + j * (D + 2);
-          ml[k] = ld_act2(pp + D);
-          ov[k] = ld_act2(pp + e);
-          part += per;
-          if (++sl == Cs) { sl = 0; part += ld - (size_t)Cs * per; }
+        for (int k = 0; k < kAtOnce; ++k) {
+          ml[k] = make_float2(-INFINITY, 0.f);
+          ov[k] = make_float2(0.f, 0.f);
+          if (c0 + k < Cm) {
+            const float* pp = part1 + j * (D + 2);
+            ml[k] = ld_act2(pp + D);
+            ov[k] = ld_act2(pp + e);
+            part1 += per;
+            if (++sl1 == Cs) { sl1 = 0; part1 += ld - (size_t)Cs * per; }
+          }
         }
-      }
+        if (MARKED)
+#pragma unroll
+          for (int k = 0; k < kAtOnce; ++k) unset = unset || mark_unset(ml[k]) || mark_unset(ov[k]);
+      } while (MARKED && mark_wait(a, unset, mw));
+      part = part1;
+      sl = sl1;
       float Mn = M;
 #pragma unroll
       for (int k = 0; k < kAtOnce; ++k) Mn = fmaxf(Mn, ml[k].x);
+      const bool with_own = MARKED && c0 + kAtOnce >= C;   // (the last: in the order they have where all are in memory)
+      if (with_own) Mn = fmaxf(Mn, oml.x);
       if (Mn == -INFINITY) continue;   // empty chunks only so far
       const float s0 = __builtin_amdgcn_exp2f(M - Mn);
       L *= s0; ax *= s0; ay *= s0;
@@ -2053,9 +2229,20 @@ __device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row
         ax = fmaf(w, ov[k].x, ax);
         ay = fmaf(w, ov[k].y, ay);
       }
+      if (with_own) {
+        const float w = __builtin_amdgcn_exp2f(oml.x - Mn);
+        L = fmaf(w, oml.y, L);
+        ax = fmaf(w, oov.x, ax);
+        ay = fmaf(w, oov.y, ay);
+      }
       M = Mn;
     }
-    st_act2(o + 2u * i, ax / L, ay / L);
+    if (MARKED) {
+      st_act2(o + 2u * i, mark_clean(ax / L), mark_clean(ay / L));
+      mark_reset2(o + 2u * i, t.twin);
+    } else {
+      st_act2(o + 2u * i, ax / L, ay / L);
+    }
   }
 }
 
@@ -2160,7 +2347,7 @@ __device__ __forceinline__ void attn_rows_unsplit(const float* qs, const uint16_
 // tasks, looks up its pages and requests its rows.  Table entries are read with coherent loads
 // (one per page of the chunk, all in flight together).  An entry
 // outside the pool is reported and replaced by page 0: no address ever leaves the pool.
-template <int D, int GRP, bool PAGED>
+template <int D, int GRP, bool PAGED, bool MARKED>
 __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev, uint32_t* s_flag) {
   constexpr uint32_t d = D, grp = GRP, NW = kThreads / 64, per = grp * (d + 2);
   constexpr bool TWO = GRP == 8;                       // the lo terms take a second multiply
@@ -2172,7 +2359,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   constexpr int VW = D / 32;                                 // ... in words
   const uint32_t nq = a.g->n_q, nkv = a.g->n_kv, Cs = t.p1;
   const uint32_t bs = t.b0, u = t.c0 / per, g = u / Cs;   // the task's own row: where its partial result goes
-  if (PAGED && wait_ev >= 0 && a.g->serve_event >= 0 && !wait_event(a, a.g->serve_event, s_flag)) return false;
+  if (PAGED && (wait_ev >= 0 || MARKED) && a.g->serve_event >= 0 && !wait_event(a, a.g->serve_event, s_flag)) return false;
   // sequence, chunk and chunk count the task works on, first task of that sequence
   uint32_t b = bs, c = u % Cs, C = Cs, v0 = bs * Cs;
   if (t.flags & TF_ATTN_BALANCE) attn_deal<PAGED>(a, Cs, bs * Cs + c, &b, &c, &C, &v0);
@@ -2196,6 +2383,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   const uint32_t len = bad_pos ? 0u : (uint32_t)pos + 1;
   const uint32_t t0 = chunk_begin(a, c, len, C), t1 = chunk_begin(a, c + 1u, len, C);
   const bool has_new = !bad_pos && c == C - 1;       // the chunk ends with the row appended this step
+  const bool merger = MARKED && c == C - 1;      // (the latest of the sequence's tasks in every worker's order)
   const uint32_t n_old = __builtin_amdgcn_readfirstlane(t1 - t0 - (has_new ? 1u : 0u));   // rows of earlier steps
   const uint32_t nblk = (n_old + BLK - 1u) / BLK;
   // contiguous cache: the chunk's first row; paged: the layer's pools
@@ -2280,7 +2468,17 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   }
   if (bad_pos) {
     if (threadIdx.x == 0) report(a, DE_BAD_POSITION, b, (uint32_t)pos);
-    for (uint32_t i = threadIdx.x; i < per; i += kThreads) st_act(outp + i, ((i % (d + 2)) == d) ? -INFINITY : 0.f);
+    for (uint32_t i = threadIdx.x; i < per; i += kThreads) {
+      if (!merger) st_act(outp + i, ((i % (d + 2)) == d) ? -INFINITY : 0.f);
+      if (MARKED) mark_reset(outp + i, t.twin);
+    }
+    if (merger) {
+      float* o = const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d;
+      for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) {
+        st_act(o + i, 0.f);
+        mark_reset(o + i, t.twin);
+      }
+    }
     return true;
   }
   const float* qsrc = t.in + (size_t)b * t.ld_in + (size_t)g * grp * d;
@@ -2299,52 +2497,61 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     // the input is the raw QKV projection: rotate the group's query heads here; the task of the
     // last chunk also rotates this step's key, and appends key and value to the cache
     constexpr uint32_t half = d / 2;
-    const float* angles = a.g->rope_tab + (size_t)b * d;   // of this step, from the embedding tasks
+    const float* angles = a.g->rope_tab + ((size_t)(a.epoch & 1u) * a.g->batch + b) * d;   // of this step, from the embedding tasks
     const bool qk_norm = t.flags & TF_QK_NORM;
-    for (uint32_t i = threadIdx.x; i < grp * half; i += kThreads) {
-      uint32_t j = i / half, e = i % half;
-      float u0 = ld_act(qsrc + j * d + e), u1 = ld_act(qsrc + j * d + e + half);
-      const float2 r = ld_act2(angles + 2u * e);   // (cos, sin)
+    // a thread loads a rotation pair of the queries and, from the top of the workgroup, one of the appended
+    // rows' shares -- two adjacent rotation pairs of the key or two adjacent value elements: one round trip
+    static_assert(grp * half <= kThreads && half / 2 + half <= kThreads, "a thread has one pair of each");
+    const uint32_t iq = threadIdx.x, in = kThreads - 1 - threadIdx.x;
+    const bool has_q = iq < grp * half, has_k = has_new && in < half / 2, has_v = has_new && !has_k && in < half / 2 + half;
+    const uint32_t jq = iq / half, eq = iq % half, ek = 2 * in, ev = 2 * (in - half / 2);
+    const float* kvsrc = t.in + (size_t)b * t.ld_in + (has_k ? (size_t)(nq + g) * d + ek : (size_t)(nq + nkv + g) * d + ev);
+    float u0 = 0.f, u1 = 0.f;
+    float2 lo = make_float2(0.f, 0.f), hi = lo, rq = lo, r0 = lo, r1 = lo;
+    MarkWait mw;
+    do {
+      if (has_q) {
+        u0 = ld_act(qsrc + jq * d + eq);
+        u1 = ld_act(qsrc + jq * d + eq + half);
+        rq = ld_act2(angles + 2u * eq);   // (cos, sin)
+      }
+      if (has_k || has_v) lo = ld_act2(kvsrc);
+      if (has_k) {
+        hi = ld_act2(kvsrc + half);
+        r0 = ld_act2(angles + 2u * ek);
+        r1 = ld_act2(angles + 2u * ek + 2u);
+      }
+    } while (MARKED && mark_wait(a, mark_unset(u0) || mark_unset(u1) || mark_unset(lo) || mark_unset(hi) || mark_unset(rq) || mark_unset(r0) || mark_unset(r1), mw));
+    if (has_q) {
       if (qk_norm) {   // RMSNorm over the head: its `half` threads are one aligned group of lanes
         const float inv = 1.0f / sqrtf(lane_group_sum<(int)half>(u0 * u0 + u1 * u1) / (float)d + t.f0);
         const uint16_t* gq = (const uint16_t*)t.w;
-        u0 *= inv * bf16_to_f32(as_global(gq)[e]);
-        u1 *= inv * bf16_to_f32(as_global(gq)[e + half]);
+        u0 *= inv * bf16_to_f32(as_global(gq)[eq]);
+        u1 *= inv * bf16_to_f32(as_global(gq)[eq + half]);
       }
-      qs[j * d + e] = u0 * r.x - u1 * r.y;
-      qs[j * d + e + half] = u1 * r.x + u0 * r.y;
+      qs[jq * d + eq] = fmaf(u0, rq.x, -(u1 * rq.y));   // (spelt out: the same rounding in every instance)
+      qs[jq * d + eq + half] = fmaf(u1, rq.x, u0 * rq.y);
     }
-    if (has_new) {
-      const float* ksrc = t.in + (size_t)b * t.ld_in + (size_t)(nq + g) * d;
-      const float* vsrc = t.in + (size_t)b * t.ld_in + (size_t)(nq + nkv + g) * d;
-      // threads from the top of the workgroup, so that they do not also rotate query pairs
-      for (uint32_t i = kThreads - 1 - threadIdx.x; i < half / 2 + half; i += kThreads) {
-        if (i < half / 2) {   // two adjacent rotation pairs of the key
-          uint32_t e = 2 * i;
-          float2 lo = ld_act2(ksrc + e), hi = ld_act2(ksrc + e + half);
-          const float2 r0 = ld_act2(angles + 2u * e), r1 = ld_act2(angles + 2u * e + 2u);
-          if (qk_norm) {   // the key's half/2 threads: one aligned group of lanes at the top of the workgroup
-            const float ss = lane_group_sum<(int)(half / 2)>(lo.x * lo.x + lo.y * lo.y + hi.x * hi.x + hi.y * hi.y);
-            const float inv = 1.0f / sqrtf(ss / (float)d + t.f0);
-            const uint16_t* gk = (const uint16_t*)t.w2;
-            const uint32_t g0 = *as_global((const uint32_t*)(gk + e)), g1 = *as_global((const uint32_t*)(gk + e + half));
-            lo.x *= inv * bf16_lo(g0); lo.y *= inv * bf16_hi(g0);
-            hi.x *= inv * bf16_lo(g1); hi.y *= inv * bf16_hi(g1);
-          }
-          const uint32_t w0 = (uint32_t)f32_to_bf16(lo.x * r0.x - hi.x * r0.y) | ((uint32_t)f32_to_bf16(lo.y * r1.x - hi.y * r1.y) << 16);
-          const uint32_t w1 = (uint32_t)f32_to_bf16(hi.x * r0.x + lo.x * r0.y) | ((uint32_t)f32_to_bf16(hi.y * r1.x + lo.y * r1.y) << 16);
-          st_act_u32((uint32_t*)(krow + e), w0);
-          st_act_u32((uint32_t*)(krow + e + half), w1);
-          *(float2*)(knew + e) = make_float2(bf16_lo(w0), bf16_hi(w0));   // as stored
-          *(float2*)(knew + e + half) = make_float2(bf16_lo(w1), bf16_hi(w1));
-        } else {              // two adjacent value elements
-          uint32_t e = 2 * (i - half / 2);
-          const float2 v2 = ld_act2(vsrc + e);
-          const uint32_t w = (uint32_t)f32_to_bf16(v2.x) | ((uint32_t)f32_to_bf16(v2.y) << 16);
-          st_act_u32((uint32_t*)(vrow + e), w);
-          *(float2*)(vnew + e) = make_float2(bf16_lo(w), bf16_hi(w));
-        }
+    if (has_k) {
+      if (qk_norm) {   // the key's half/2 threads: one aligned group of lanes at the top of the workgroup
+        const float ss = lane_group_sum<(int)(half / 2)>(lo.x * lo.x + lo.y * lo.y + hi.x * hi.x + hi.y * hi.y);
+        const float inv = 1.0f / sqrtf(ss / (float)d + t.f0);
+        const uint16_t* gk = (const uint16_t*)t.w2;
+        const uint32_t g0 = *as_global((const uint32_t*)(gk + ek)), g1 = *as_global((const uint32_t*)(gk + ek + half));
+        lo.x *= inv * bf16_lo(g0); lo.y *= inv * bf16_hi(g0);
+        hi.x *= inv * bf16_lo(g1); hi.y *= inv * bf16_hi(g1);
       }
+      const uint32_t w0 = (uint32_t)f32_to_bf16(fmaf(lo.x, r0.x, -(hi.x * r0.y))) | ((uint32_t)f32_to_bf16(fmaf(lo.y, r1.x, -(hi.y * r1.y))) << 16);
+      const uint32_t w1 = (uint32_t)f32_to_bf16(fmaf(hi.x, r0.x, lo.x * r0.y)) | ((uint32_t)f32_to_bf16(fmaf(hi.y, r1.x, lo.y * r1.y)) << 16);
+      st_act_u32((uint32_t*)(krow + ek), w0);
+      st_act_u32((uint32_t*)(krow + ek + half), w1);
+      *(float2*)(knew + ek) = make_float2(bf16_lo(w0), bf16_hi(w0));   // as stored
+      *(float2*)(knew + ek + half) = make_float2(bf16_lo(w1), bf16_hi(w1));
+    }
+    if (has_v) {
+      const uint32_t w = (uint32_t)f32_to_bf16(lo.x) | ((uint32_t)f32_to_bf16(lo.y) << 16);
+      st_act_u32((uint32_t*)(vrow + ev), w);
+      *(float2*)(vnew + ev) = make_float2(bf16_lo(w), bf16_hi(w));
     }
   } else {
     for (uint32_t i = threadIdx.x; i < grp * d; i += kThreads) qs[i] = ld_act(qsrc + i);
@@ -2505,6 +2712,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   trace_mark(a, t, 10);
   // ---- the wavefronts' results and the appended row -> the task's partial result, two elements a thread
   const uint32_t nw = min(nblk, NW);
+  float* own_ml = (float*)flag;   // (nobody needs the queries or the flag any more)
   for (uint32_t i = threadIdx.x; i < grp * (d / 2 + 1); i += kThreads) {
     const uint32_t j = i / (d / 2 + 1), e = 2u * (i % (d / 2 + 1));   // e == d: the maximum and the sum
     float mw[NW], M = has_new ? snew[j] * kScale : -INFINITY;
@@ -2538,10 +2746,22 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
         y = fmaf(f, oy, y);
       }
     }
-    st_act2(outp + j * (d + 2) + e, x, y);
+    if (merger) *(float2*)(e == d ? own_ml + 2u * j : qs + j * d + e) = make_float2(mark_clean(x), mark_clean(y));   // (stays here: this task merges)
+    else if (MARKED) st_act2(outp + j * (d + 2) + e, mark_clean(x), mark_clean(y));
+    else st_act2(outp + j * (d + 2) + e, x, y);
   }
+  if (MARKED)
+    for (uint32_t i = threadIdx.x; i < per / 2; i += kThreads) mark_reset2(outp + 2u * i, t.twin);
   trace_mark(a, t, 11);
-  if (t.flags & TF_ATTN_MERGE) {
+  if constexpr (MARKED) {
+    // No arrival counter: the sequence's last task in linearized order merges, and loads the others' partials
+    // until they are there.  (Every worker runs its tasks in that order, so they never wait for this one.)
+    if (merger) {
+      lds_barrier();
+      attn_merge_partials<D, GRP, true>(C, t.out + (size_t)(v0 / Cs) * t.ld_out + (size_t)g * Cs * per, v0 % Cs, Cs, t.ld_out,
+                                        const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d, a, t, qs, own_ml);
+    }
+  } else if (t.flags & TF_ATTN_MERGE) {
     // Arrival counter of (layer, sequence, KV head): the chunk task that arrives last sees all C
     // partials complete and merges them into the attention output.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -2562,8 +2782,12 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     __syncthreads();
     if (*flag) {
       // chunk k of the sequence is the partial result of task v0 + k, in that task's own slot
-      attn_merge_partials<D, GRP>(C, t.out + (size_t)(v0 / Cs) * t.ld_out + (size_t)g * Cs * per, v0 % Cs, Cs, t.ld_out, const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d);
+      attn_merge_partials<D, GRP>(C, t.out + (size_t)(v0 / Cs) * t.ld_out + (size_t)g * Cs * per, v0 % Cs, Cs, t.ld_out, const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d, a, t);
     }
+  }
+  if constexpr (MARKED) {
+    lds_barrier();
+    if (mark_aborted()) { mark_report((uint32_t)t.dep_event); return false; }
   }
   return true;
 }
@@ -3072,7 +3296,10 @@ static_assert(kLdsArgsAt * 4 + sizeof(StepArgs) <= kLdsCtrlFloats * 4, "control 
 // Thread 0 leaves the arguments in LDS; the callers' next barrier publishes them.
 __device__ __forceinline__ void publish_args(const StepArgs& a) {
   extern __shared__ __align__(16) float dyn_lds[];
-  if (threadIdx.x == 0) *(StepArgs*)(dyn_lds + kLdsArgsAt) = a;
+  if (threadIdx.x == 0) {
+    *(StepArgs*)(dyn_lds + kLdsArgsAt) = a;
+    ((uint32_t*)dyn_lds)[kLdsAbortAt] = 0u;
+  }
 }
 __device__ __forceinline__ StepArgs published_args() {
   extern __shared__ __align__(16) float dyn_lds[];
@@ -3166,7 +3393,7 @@ __device__ __noinline__ bool run_other_task(uint32_t task_index, bool skip_wait)
 // that decided everything at run time and spilled 350 registers: head size 64 at batch 1, every
 // model at batch 2 to 4).  skip_wait: the event is known to be active; signal: notify the
 // triggering event (persistent kernel).
-template <int D, int GRP, bool PAGED>
+template <int D, int GRP, bool PAGED, bool MARKED>
 __device__ __noinline__ bool run_attn_task(uint32_t task_index, bool skip_wait, bool signal) {
   const StepArgs a = published_args();
   task_index = uniform_u32(task_index);
@@ -3179,37 +3406,40 @@ __device__ __noinline__ bool run_attn_task(uint32_t task_index, bool skip_wait, 
   int32_t wait_ev = -1;
   if (signal) {
     debug_jitter(a, task_index);
-    wait_ev = (!skip_wait && t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
+    wait_ev = (!MARKED && !skip_wait && t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
     trace_mark(a, t, 0);
     if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)task_index * kTraceSlots + 5] = blockIdx.x;
   }
-  if (!body_attn_mfma<D, GRP, PAGED>(t, a, lds, wait_ev, s_flag)) return false;
+  if (!body_attn_mfma<D, GRP, PAGED, MARKED>(t, a, lds, wait_ev, s_flag)) return false;
   if (signal) {
     trace_mark(a, t, 3);
     if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
-    else __syncthreads();
+    else lds_barrier();
     trace_mark(a, t, 4);
   }
   return true;
 }
 // Runs a task that is not a linear task.  (A callee's result comes back in a vector register: it is
 // made scalar again, or the whole task loop, and every descriptor load in it, turns into per-lane code.)
-template <bool MEGA, bool MOE>
-__device__ __forceinline__ bool call_task(const StepArgs& a, uint16_t kind, uint32_t task_index, bool skip_wait) {
-  bool ok;
-  if (kind != TK_ATTN_PARTIAL) {
-    ok = run_other_task<MEGA, MOE>(task_index, skip_wait);
-  } else {
-    switch (a.g->attn_shape) {   // see attn_shape_index
+template <bool MARKED>
+__device__ __forceinline__ bool call_attn_task(const StepArgs& a, uint32_t task_index, bool skip_wait, bool signal) {
+  switch (a.g->attn_shape) {   // see attn_shape_index
 #define MPK_ATTN_CASE(D, LG)                                                                                                   \
-      case attn_shape_index(D, 1u << LG, 0): ok = run_attn_task<D, (1 << LG), false>(task_index, skip_wait, MEGA); break; \
-      case attn_shape_index(D, 1u << LG, 1): ok = run_attn_task<D, (1 << LG), true>(task_index, skip_wait, MEGA); break;
-      MPK_ATTN_CASE(64, 0) MPK_ATTN_CASE(64, 1) MPK_ATTN_CASE(64, 2) MPK_ATTN_CASE(64, 3)
-      MPK_ATTN_CASE(128, 0) MPK_ATTN_CASE(128, 1) MPK_ATTN_CASE(128, 2) MPK_ATTN_CASE(128, 3)
+    case attn_shape_index(D, 1u << LG, 0): return run_attn_task<D, (1 << LG), false, MARKED>(task_index, skip_wait, signal); \
+    case attn_shape_index(D, 1u << LG, 1): return run_attn_task<D, (1 << LG), true, MARKED>(task_index, skip_wait, signal);
+    MPK_ATTN_CASE(64, 0) MPK_ATTN_CASE(64, 1) MPK_ATTN_CASE(64, 2) MPK_ATTN_CASE(64, 3)
+    MPK_ATTN_CASE(128, 0) MPK_ATTN_CASE(128, 1) MPK_ATTN_CASE(128, 2) MPK_ATTN_CASE(128, 3)
 #undef MPK_ATTN_CASE
-      default: ok = false; break;   // (the host admits no other shape)
-    }
+    default: return false;   // (the host admits no other shape)
   }
+}
+// MARKS: the kernel runs marked descriptors (an attention task has both its input and its output marked, or neither).
+template <bool MEGA, bool MOE, bool MARKS = false>
+__device__ __forceinline__ bool call_task(const StepArgs& a, uint16_t kind, uint16_t flags, uint32_t task_index, bool skip_wait) {
+  bool ok;
+  if (kind != TK_ATTN_PARTIAL) ok = run_other_task<MEGA, MOE>(task_index, skip_wait);
+  else if (MARKS && (flags & TF_IN_MARKED)) ok = call_attn_task<true>(a, task_index, skip_wait, MEGA);
+  else ok = call_attn_task<false>(a, task_index, skip_wait, MEGA);
   return __builtin_amdgcn_readfirstlane((int)ok) != 0;
 }
 
@@ -3352,10 +3582,13 @@ __device__ __forceinline__ uint32_t pick_task(const StepArgs& a, uint32_t* ctrl,
   return pick;
 }
 
+// Batch classes whose kernels run marked descriptors.
+constexpr bool has_marks(int nb) { return nb == 1 || nb == 2 || nb == 9; }
+
 // Every task ahead-of-time: the worker walks its pre-enqueued list, each task waits for its own
 // event.  after_first_step: a task without producers (an embedding task) first waits for the
 // previous step's terminal event, i.e. for that step's sampling tasks.  Returns false on abort.
-template <int NB, bool MOE>
+template <int NB, bool MOE, bool MARKS>
 __device__ __forceinline__ bool aot_pass(const StepArgs& a, uint32_t q0, uint32_t q1, float* lds, uint32_t* s_flag,
                                          bool after_first_step) {
   for (uint32_t qi = q0; qi < q1; ++qi) {
@@ -3368,17 +3601,20 @@ __device__ __forceinline__ bool aot_pass(const StepArgs& a, uint32_t q0, uint32_
     }
     if (t.kind == TK_LINEAR) {
       debug_jitter(a, ti);
-      const int32_t wait_ev = (t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
+      const int32_t wait_ev = (!(MARKS && (t.flags & TF_IN_MARKED)) && t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
       trace_mark(a, t, 0);
-      if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.pad * kTraceSlots + 5] = blockIdx.x;
+      if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.index * kTraceSlots + 5] = blockIdx.x;
       // (the next task of this worker: a flagged task pre-loads its first half blocks into LDS pages)
-      NoJit svc;
+      std::conditional_t<MARKS, NoJitMarks, NoJit> svc;
       svc.n_next = min(q1 - qi - 1u, 2u);
       if (svc.n_next > 0) svc.next[0] = ld_u32c(a.g->aot + qi + 1);
       if (svc.n_next > 1) svc.next[1] = ld_u32c(a.g->aot + qi + 2);
-      if (!run_linear<NB, true>(t, a, lds, wait_ev, s_flag, svc, svc.next[0])) return false;
+      if (!run_linear<NB, true>(t, a, lds, wait_ev, s_flag, svc, svc.next[0])) {
+        if (MARKS && mark_aborted()) mark_report((uint32_t)t.dep_event);
+        return false;
+      }
     } else {
-      if (!call_task<true, MOE>(a, t.kind, ti, false)) return false;
+      if (!call_task<true, MOE, MARKS>(a, t.kind, t.flags, ti, false)) return false;
     }
   }
   return true;
@@ -3414,6 +3650,15 @@ __device__ __noinline__ bool serve_step_gate(StepArgs a_in, uint32_t q0, uint32_
   const StepArgs a = uniform_args(a_in);
   if (!(a.flags & kServeBit) || a.step == 0 || !serve_drained(a)) return false;
   serve_skip_steps(a, q0, q1, 1u);
+  // The marked copy that the drained step wrote is put back to unset by the first step behind it, as that
+  // step's tasks would have done; the other copy the drained step's tasks have put back.
+  const uint32_t stop = __builtin_amdgcn_readfirstlane(ld_relaxed(a.g->serve->scalars + kServeStop));
+  if (a.g->mark_words && a.epoch - stop == 1u) {
+    float* copy = a.g->mark_base + (size_t)(stop & 1u) * a.g->mark_words;
+    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < a.g->mark_words; i += gridDim.x * kThreads) st_act_u32((uint32_t*)(copy + i), kUnsetWord);
+    const uint32_t n = a.g->batch * a.g->head_dim;
+    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) st_act_u32((uint32_t*)(a.g->rope_tab + (stop & 1u) * n + i), kUnsetWord);
+  }
   return true;
 }
 
@@ -3444,7 +3689,7 @@ __global__ void __launch_bounds__(kThreads) mpk_loop_kernel(StepArgs a) {
     __syncthreads();   // (nobody is inside a task function any more)
     publish_args(a);
     __syncthreads();
-    if (!aot_pass<NB, MOE>(a, q0, q1, lds, s_flag, step > 0)) return;
+    if (!aot_pass<NB, MOE, false>(a, q0, q1, lds, s_flag, step > 0)) return;
   }
 }
 
@@ -3474,7 +3719,7 @@ __global__ void __launch_bounds__(kThreads) mpk_mega_kernel(StepArgs a) {
     // (a run of serving iterations issued as one launch per step: the launches behind the one
     // that found the server drained only settle their share of the event counters)
     if (RUN && __builtin_amdgcn_readfirstlane((int)serve_step_gate(a, q0, q1))) return;
-    aot_pass<NB, MOE>(a, q0, q1, lds, s_flag, false);
+    aot_pass<NB, MOE, has_marks(NB)>(a, q0, q1, lds, s_flag, false);
     return;
   }
   if constexpr (HYBRID) {
@@ -3487,7 +3732,7 @@ __global__ void __launch_bounds__(kThreads) mpk_mega_kernel(StepArgs a) {
       if (t.kind == TK_LINEAR) {
         debug_jitter(a, ti);
         trace_mark(a, t, 0);
-        if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.pad * kTraceSlots + 5] = blockIdx.x;
+        if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)t.index * kTraceSlots + 5] = blockIdx.x;
         const int32_t wait_ev = (t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
         uint32_t r;
         // started before its event is activated; a just-in-time task that arrives first pre-empts it
@@ -3502,11 +3747,11 @@ __global__ void __launch_bounds__(kThreads) mpk_mega_kernel(StepArgs a) {
           if (tjd.kind == TK_LINEAR) {
             debug_jitter(a, tj);
             if (run_linear<NB, true>(tjd, a, lds, -1, s_flag) != kLinDone) { r = kLinAbort; break; }
-          } else if (!call_task<true, MOE>(a, tjd.kind, tj, true)) { r = kLinAbort; break; }
+          } else if (!call_task<true, MOE>(a, tjd.kind, tjd.flags, tj, true)) { r = kLinAbort; break; }
         }
         if (r == kLinAbort) break;
       } else {
-        if (!call_task<true, MOE>(a, t.kind, ti, true)) break;
+        if (!call_task<true, MOE>(a, t.kind, t.flags, ti, true)) break;
       }
     }
     if (threadIdx.x == 0) __hip_atomic_store(as_global(a.g->wq_head + w), jit_head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3526,7 +3771,7 @@ __global__ void __launch_bounds__(kThreads) mpk_op_kernel(StepArgs a, uint32_t f
   if (t.kind == TK_LINEAR) {
     run_linear<NB, false>(t, a, lds, -1, nullptr);
   } else {
-    call_task<false, MOE>(a, t.kind, ti, true);
+    call_task<false, MOE>(a, t.kind, t.flags, ti, true);
   }
 }
 

@@ -34,7 +34,7 @@ enum TaskKind : uint16_t {
 
 enum TaskFlags : uint16_t {
   TF_PRO_NORM = 1,    // linear: RMSNorm the input row first (gain = w2, eps = f0)
-  // (2: unused)
+  TF_IN2_MARKED = 2,  // with TF_IN_MARKED: the second input is marked as well
   TF_EPI_RESID = 4,   // linear: out = in2 + W x
   TF_GATEUP = 8,      // linear: out_c = silu(W[c] x) * (W[F + c] x), F = p0
   TF_OUT_LOGITS = 16, // output pointer is the caller's logits buffer of this step
@@ -57,7 +57,21 @@ enum TaskFlags : uint16_t {
                       // head are dealt to the sequences in proportion to their lengths at run time
                       // (a task may work on another sequence than its row; its partial result
                       // still goes to its own slot)
+  TF_IN_MARKED = 16384,  // the task does not wait for its dependent event: its input tells by itself what has been written
+  TF_OUT_MARKED = 32768, // ... and so does its output: see kUnsetWord
 };
+
+// Marked tensors.  A consumer that learns from an event counter that its input is complete pays four trips
+// to the coherence point in a row: the producer's stores have to be acknowledged before it may notify, the
+// notification travels, a poll sees it, and only then is the input loaded.  In an all-ahead-of-time step
+// an activation tensor therefore says for itself which of its elements have been written: before the step
+// every word of it is kUnsetWord, a NaN pattern that no producer stores (mark_clean), and a consumer loads its input
+// at once and loads again what it finds unset.  The producer neither waits for its stores nor notifies.
+// A marked tensor has two copies, for even and odd steps; a task that writes its tile of one copy
+// puts the same tile of the other back to unset (TaskDesc::twin), which nobody reads during the step and whose
+// readers of the step before have ended with their launch.  The loop kernel, the hybrid launch and
+// per-operator launches run on the unmarked descriptors and on a third copy.
+constexpr uint32_t kUnsetWord = 0xFFFFFFFFu;
 
 struct alignas(16) TaskDesc {
   uint16_t kind, flags;
@@ -75,7 +89,9 @@ struct alignas(16) TaskDesc {
   float* out;
   void* aux0;               // K cache of the layer
   void* aux1;               // V cache of the layer
-  uint64_t pad;
+  uint32_t index;           // own index in the linearized task list
+  int32_t twin;             // TF_OUT_MARKED: from a word of the output to the same word of the other copy, in
+                            // 64-float units (0: there is no other copy)
 };
 static_assert(sizeof(TaskDesc) == 128, "TaskDesc must stay 128 bytes");
 
@@ -202,6 +218,9 @@ struct HostGraph {
   std::vector<uint32_t> aot_off, aot;
   std::vector<TaskDesc> descs;   // parallel to tasks; activation pointers hold arena offsets
                                  // until the runtime relocates them
+  std::vector<uint16_t> mark_flags;   // parallel to tasks: TF_IN_MARKED / TF_IN2_MARKED / TF_OUT_MARKED of the marked
+                                      // descriptors; empty: no task of the graph has any
+  std::vector<uint8_t> marked_tensor; // parallel to tensors
   uint32_t n_real = 0, start_event = 0, terminal_event = 0;
   size_t arena_floats = 0;
   uint32_t lds_bytes = 0;
@@ -281,7 +300,7 @@ constexpr uint32_t moe_x_floats(uint32_t batch) {
   return t8 > t16 ? t8 : t16;
 }
 
-constexpr uint32_t kRopeTabFloatsMax = 16 * 128;   // [batch][head_dim]: (cos, sin) of a step's rotation angles
+constexpr uint32_t kRopeTabFloatsMax = 2 * 16 * 128;   // [2][batch][head_dim]: (cos, sin) of a step's rotation angles
 
 // LDS layout constants shared with the kernels
 constexpr uint32_t kThreads = 512;        // worker workgroup size (8 wavefronts, two per SIMD)

@@ -52,6 +52,15 @@ __global__ void __launch_bounds__(256) fill_u32_kernel(uint32_t* p, size_t n, ui
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
+// Before a step on the static scratch array: counters to zero, marked tensors and the rope table to unset.
+__global__ void __launch_bounds__(256) static_clear_kernel(uint32_t* counters, size_t n_counters, uint32_t* arena, size_t n_arena,
+                                                           uint32_t* rope, size_t n_rope) {
+  const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = i0; i < n_counters; i += stride) counters[i] = 0u;
+  for (size_t i = i0; i < n_arena; i += stride) arena[i] = kUnsetWord;
+  for (size_t i = i0; i < n_rope; i += stride) rope[i] = kUnsetWord;
+}
+
 // MPK_DEBUG_POISON: the local data share keeps what the last workgroup on the compute unit left in
 // it.  A task that reads a word of it that the task has not written (the tail of a staged row, a
 // gain past the end of the input) normally finds an old activation there and gets away with it;
@@ -76,6 +85,9 @@ struct mpk_graph {
   int device = -1;
   // device allocations
   TaskDesc* d_tasks = nullptr;
+  TaskDesc* d_tasks_marked[2] = {nullptr, nullptr};   // the same for launches that use marked tensors (kUnsetWord), even and odd steps
+  float* d_marked = nullptr;     // their two copies of the marked tensors, mark_words each
+  size_t mark_words = 0;
   EventDesc* d_events = nullptr;
   uint32_t* d_counters = nullptr;
   uint32_t* d_aot_off = nullptr;
@@ -98,6 +110,8 @@ struct mpk_graph {
   uint32_t* d_wq_head = nullptr;
   uint32_t n_sched = 0, evq_cap = 1, wq_cap = 1;
   float* d_arena = nullptr;
+  float* d_rope = nullptr;       // rope table, behind the activations
+  size_t rope_words = 0;
   std::vector<uint32_t> op_first, op_count;   // per operator: range in op_list
   uint32_t epoch = 0;
   uint64_t timeout_ticks = 0;
@@ -126,6 +140,7 @@ struct mpk_graph {
 
 static void free_device(mpk_graph* g) {
   if (g->host_only) return;
+  (void)hipFree(g->d_tasks_marked[0]); (void)hipFree(g->d_tasks_marked[1]); (void)hipFree(g->d_marked);
   (void)hipFree(g->d_tasks); (void)hipFree(g->d_events); (void)hipFree(g->d_counters);
   (void)hipFree(g->d_aot_off); (void)hipFree(g->d_aot); (void)hipFree(g->d_op_list);
   (void)hipFree(g->d_err); (void)hipFree(g->d_arena);
@@ -306,21 +321,61 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
   }
   // activation arena + relocation of the descriptors
   const size_t rope_at = std::max<size_t>(h.arena_floats, 64);   // the rope table sits behind the activations
-  size_t arena_bytes = (rope_at + (size_t)cfg->batch * cfg->head_dim) * sizeof(float);
+  const size_t arena_bytes = (rope_at + 2 * (size_t)cfg->batch * cfg->head_dim) * sizeof(float);
   e = hipMalloc((void**)&g->d_arena, arena_bytes);
   if (e != hipSuccess) { set_error("hipMalloc(%zu) for activations failed: %s", arena_bytes, hipGetErrorString(e)); return fail(MPK_ERR_OOM); }
-  if (hipMemset(g->d_arena, 0, arena_bytes) != hipSuccess) { set_error("hipMemset failed"); return fail(MPK_ERR_HIP); }
+  g->d_rope = g->d_arena + rope_at;
+  g->rope_words = 2 * (size_t)cfg->batch * cfg->head_dim;
+  if (hipMemset(g->d_arena, 0, arena_bytes) != hipSuccess || hipMemset(g->d_rope, 0xFF, g->rope_words * sizeof(float)) != hipSuccess) { set_error("hipMemset failed"); return fail(MPK_ERR_HIP); }
   std::vector<TaskDesc> descs = h.descs;
   auto reloc = [&](const float* p) -> const float* {
     if (!p) return nullptr;
     return g->d_arena + ((uintptr_t)p / sizeof(float) - 1);
   };
-  for (auto& t : descs) {
-    t.in = reloc(t.in);
-    t.in2 = reloc(t.in2);
-    t.out = const_cast<float*>(reloc(t.out));
-    if (t.kind == TK_MOE_ROUTE || t.kind == TK_MOE_EXPERT || t.kind == TK_MOE_COMBINE || (t.flags & TF_SPLITK))
-      t.aux0 = (void*)reloc((const float*)t.aux0);
+  auto relocate = [](std::vector<TaskDesc>& d, auto&& reloc) {
+    for (auto& t : d) {
+      t.in = reloc(t.in);
+      t.in2 = reloc(t.in2);
+      t.out = const_cast<float*>(reloc(t.out));
+      if (t.kind == TK_MOE_ROUTE || t.kind == TK_MOE_EXPERT || t.kind == TK_MOE_COMBINE || (t.flags & TF_SPLITK))
+        t.aux0 = (void*)reloc((const float*)t.aux0);
+    }
+  };
+  relocate(descs, reloc);
+  // ... and the descriptors of the launches that use marked tensors, one set per copy of those
+  if (!h.mark_flags.empty()) {
+    std::vector<std::pair<size_t, int>> starts;   // first word of a tensor in the arena, the tensor
+    std::vector<size_t> at(h.tensors.size(), 0);
+    for (size_t i = 0; i < h.tensors.size(); ++i) {
+      if (h.tensors[i].offset == SIZE_MAX) continue;
+      starts.emplace_back(h.tensors[i].offset, (int)i);
+      if (!h.marked_tensor[i]) continue;
+      at[i] = g->mark_words;
+      g->mark_words += ((size_t)h.tensors[i].rows * h.tensors[i].cols + 63) / 64 * 64;
+    }
+    std::sort(starts.begin(), starts.end());
+    e = hipMalloc((void**)&g->d_marked, 2 * g->mark_words * sizeof(float));
+    if (e != hipSuccess) { set_error("hipMalloc(%zu) for activations failed: %s", 2 * g->mark_words * sizeof(float), hipGetErrorString(e)); return fail(MPK_ERR_OOM); }
+    if (hipMemset(g->d_marked, 0xFF, 2 * g->mark_words * sizeof(float)) != hipSuccess) { set_error("hipMemset failed"); return fail(MPK_ERR_HIP); }
+    for (int copy = 0; copy < 2; ++copy) {
+      std::vector<TaskDesc> d = h.descs;
+      relocate(d, [&](const float* p) -> const float* {
+        if (!p) return nullptr;
+        const size_t off = (uintptr_t)p / sizeof(float) - 1;
+        const auto it = std::prev(std::upper_bound(starts.begin(), starts.end(), std::make_pair(off, INT32_MAX)));
+        if (!h.marked_tensor[it->second]) return g->d_arena + off;
+        return g->d_marked + (size_t)copy * g->mark_words + at[it->second] + (off - it->first);
+      });
+      for (size_t i = 0; i < d.size(); ++i) {
+        d[i].flags |= h.mark_flags[i];
+        if (!(d[i].flags & TF_OUT_MARKED)) continue;
+        d[i].twin = (copy ? -1 : 1) * (int32_t)(g->mark_words / 64);
+        // nobody waits for the events of marked outputs -- except the loop kernel's launches, which count on
+        // every step's notifications
+        if (o.greedy_loop != 2) d[i].trig_event = -1;
+      }
+      if ((st = upload(&g->d_tasks_marked[copy], d)) != MPK_OK) return fail(st);
+    }
   }
   // per-operator task lists (baseline launch mode)
   std::vector<uint32_t> op_list;
@@ -388,7 +443,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     GraphConst c{};
     c.tasks = g->d_tasks; c.events = g->d_events; c.counters = g->d_counters; c.hier = g->d_hier;
     c.aot_off = g->d_aot_off; c.aot = g->d_aot; c.op_list = g->d_op_list; c.err = g->d_err;
-    c.inv_freq = g->d_inv_freq; c.rope_tab = g->d_arena + rope_at;
+    c.inv_freq = g->d_inv_freq; c.rope_tab = g->d_rope;
     c.attn_shape = attn_shape_index(h.cfg.head_dim, h.cfg.n_q_heads / h.cfg.n_kv_heads, h.opt.kv_page_size ? 1u : 0u);
     c.grp_counters = g->d_grp; c.trace = g->d_trace;
     c.timeout_ticks = g->timeout_ticks;
@@ -400,6 +455,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     c.evq_buf = g->d_evq_buf; c.evq_tail = g->d_evq_tail; c.sched_state = g->d_sched_state;
     c.sched_nev = g->d_sched_nev; c.wq_buf = g->d_wq_buf; c.wq_tail = g->d_wq_tail; c.wq_head = g->d_wq_head;
     c.start_event = h.start_event; c.terminal_event = h.terminal_event;
+    c.mark_base = g->d_marked; c.mark_words = (uint32_t)g->mark_words;
     c.page_table = nullptr; c.serve = nullptr; c.serve_event = -1;
     c.kv_pages = h.opt.kv_pages;
     for (c.page_shift = 0; h.opt.kv_page_size && (1u << c.page_shift) < h.opt.kv_page_size; ++c.page_shift) {}
@@ -423,13 +479,10 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
       if ((st = static_scratch_base(g->device, &g->static_base)) != MPK_OK) return fail(st);
       float* arena_s = (float*)(g->static_base + g->st_arena);
       std::vector<TaskDesc> ds = h.descs;
-      auto reloc_s = [&](const float* p) -> const float* { return p ? arena_s + ((uintptr_t)p / sizeof(float) - 1) : nullptr; };
-      for (auto& t : ds) {
-        t.in = reloc_s(t.in);
-        t.in2 = reloc_s(t.in2);
-        t.out = const_cast<float*>(reloc_s(t.out));
-        if (t.kind == TK_MOE_ROUTE || t.kind == TK_MOE_EXPERT || t.kind == TK_MOE_COMBINE || (t.flags & TF_SPLITK))
-          t.aux0 = (void*)reloc_s((const float*)t.aux0);
+      relocate(ds, [&](const float* p) -> const float* { return p ? arena_s + ((uintptr_t)p / sizeof(float) - 1) : nullptr; });
+      for (size_t i = 0; i < h.mark_flags.size(); ++i) {   // (one copy, unset before every step: no twin)
+        ds[i].flags |= h.mark_flags[i];
+        if (ds[i].flags & TF_OUT_MARKED) ds[i].trig_event = -1;
       }
       if ((st = upload(&g->d_tasks_static, ds)) != MPK_OK) return fail(st);
       GraphConst cs = c;
@@ -480,7 +533,8 @@ static mpk_status launch_steps(mpk_graph* g, uint32_t n_steps, const int32_t* to
   a.token_ids = token_ids; a.positions = positions; a.logits = logits_out;
   hipStream_t s = (hipStream_t)stream;
   float* arena = g->d_arena;
-  const size_t arena_words = std::max<size_t>(h.arena_floats, 64) + (static_scratch ? 0 : (size_t)h.cfg.batch * h.cfg.head_dim);   // (the rope table too)
+  uint32_t* rope = (uint32_t*)g->d_rope;
+  const size_t arena_words = std::max<size_t>(h.arena_floats, 64);
   if (static_scratch) {
     // the step's working memory is the static array: counters start from zero every time (the
     // array is shared by all graphs on this GPU), so this is always "step one"
@@ -489,13 +543,18 @@ static mpk_status launch_steps(mpk_graph* g, uint32_t n_steps, const int32_t* to
     a.counters = (uint32_t*)(g->static_base + g->st_counters);
     a.hier = (uint32_t*)(g->static_base + g->st_hier);
     arena = (float*)(g->static_base + g->st_arena);
-    const size_t words = g->st_arena / sizeof(uint32_t);   // (a few words a thread: the sharded counters of a deep model are megabytes)
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((uint32_t)std::min<size_t>(1024, std::max<size_t>(64, words / 1024))), dim3(256), 0, s,
-                       (uint32_t*)g->static_base, words, 0u);
+    rope = (uint32_t*)(g->static_base + MPK_STATIC_SCRATCH_BYTES);
+    const size_t words = g->st_arena / sizeof(uint32_t), marked = h.mark_flags.empty() ? 0 : arena_words;
+    // (a few words a thread: the sharded counters of a deep model are megabytes)
+    hipLaunchKernelGGL(static_clear_kernel, dim3((uint32_t)std::min<size_t>(1024, std::max<size_t>(64, (words + marked) / 1024))), dim3(256), 0, s,
+                       (uint32_t*)g->static_base, words, (uint32_t*)arena, marked, rope, g->rope_words);
     HIP_TRY(hipGetLastError());
   }
   if (h.opt.debug_flags & MPK_DEBUG_POISON) {
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(256), dim3(256), 0, s, (uint32_t*)arena, arena_words, 0x7FC00000u);
+    // (marked tensors and the rope table are NaN patterns before every step as it is, and have to be that one)
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(256), dim3(256), 0, s, (uint32_t*)arena, arena_words,
+                       static_scratch && !h.mark_flags.empty() ? kUnsetWord : 0x7FC00000u);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(4), dim3(256), 0, s, rope, g->rope_words, kUnsetWord);
     HIP_TRY(hipGetLastError());
     HIP_TRY(reserve_lds((const void*)lds_poison_kernel, h.lds_bytes));
     hipLaunchKernelGGL(lds_poison_kernel, dim3(512), dim3(kThreads), h.lds_bytes, s, h.lds_bytes / 4u);
@@ -529,6 +588,7 @@ static mpk_status launch_steps(mpk_graph* g, uint32_t n_steps, const int32_t* to
     if (by_step) {
       for (uint32_t i = 0; i < n_steps; ++i) {
         a.step = (uint16_t)i;
+        if (g->d_tasks_marked[0]) a.tasks = g->d_tasks_marked[a.epoch & 1u];
         hipLaunchKernelGGL(g->kv->run_step, dim3(h.opt.n_workers), dim3(kThreads), h.lds_bytes, s, a);
         ++a.epoch;
       }
@@ -536,8 +596,10 @@ static mpk_status launch_steps(mpk_graph* g, uint32_t n_steps, const int32_t* to
       hipLaunchKernelGGL(g->kv->loop, dim3(h.opt.n_workers), dim3(kThreads), h.lds_bytes, s, a);
     else if (g->n_sched)
       hipLaunchKernelGGL(g->kv->hybrid, dim3(h.opt.n_workers + h.opt.n_sched_wgs), dim3(kThreads), h.lds_bytes, s, a);
-    else
+    else {
+      if (g->d_tasks_marked[0] && !static_scratch) a.tasks = g->d_tasks_marked[a.epoch & 1u];
       hipLaunchKernelGGL(g->kv->mega, dim3(h.opt.n_workers), dim3(kThreads), h.lds_bytes, s, a);
+    }
     HIP_TRY(hipGetLastError());
   } else {
     a.n_steps = (uint16_t)n_steps;
@@ -627,6 +689,8 @@ extern "C" mpk_status mpk_graph_reset(mpk_graph* g) {
   HIP_TRY(hipMemset(g->d_err, 0, 8 * sizeof(uint32_t)));
   HIP_TRY(hipMemset(g->d_hier, 0, (size_t)std::max(g->h.n_hier_events, 1u) * kHierWordsPerEvent * sizeof(uint32_t)));
   HIP_TRY(hipMemset(g->d_grp, 0, std::max<size_t>(g->h.n_group_counters, 1) * sizeof(uint32_t)));
+  HIP_TRY(hipMemset(g->d_rope, 0xFF, g->rope_words * sizeof(float)));
+  if (g->d_marked) HIP_TRY(hipMemset(g->d_marked, 0xFF, 2 * g->mark_words * sizeof(float)));
   if (g->server) HIP_TRY(server_forget_drained(g->server));   // (step numbers start over)
   {
     const size_t ns = std::max(g->n_sched, 1u), nw = g->h.opt.n_workers;
