@@ -303,6 +303,8 @@ static mpk_status run_passes(PassInput& in, const mpk_compile_options& opt, Host
     g.tasks[i].worker = (int32_t)(cursor % W);
     queues[cursor % W].push_back(i);
     ++cursor;
+    const HostTask& t = g.tasks[i];
+    if (t.op != MPK_TASK_DUMMY_OP && t.op < g.ops.size() && t.tile + 1 == g.ops[t.op].tb * g.ops[t.op].tc) cursor += g.ops[t.op].skip_workers;
   }
   g.aot_off.assign(W + 1, 0);
   g.aot.clear();
@@ -695,9 +697,19 @@ static void tile_bounds(const HostOp& op, uint32_t tile, uint32_t* b0, uint32_t*
   *c1 = col_tile_begin(op, ic + 1) * op.unit;
 }
 
+static bool page_capable(const mpk_model_config& c, const mpk_compile_options& o) {
+  return c.batch == 1 && !o.no_lds_pages && !o.no_preload && o.n_sched_wgs == 0 && o.launch_mode == MPK_LAUNCH_MEGA;
+}
 static void choose_partitions(const mpk_model_config& c, const mpk_compile_options& o,
                               HostGraph& g) {
   const uint32_t W = o.n_workers;
+  bool pages_likely = false;   // (page_plan looks more closely)
+  for (const auto& op : g.ops) pages_likely = pages_likely || (op.kind == MPK_OP_GATEUP && page_capable(c, o) && op.K <= 4096 && (uint64_t)op.cols * 2 >= 48ull * W);
+  auto after_attention = [&](const HostOp& op) {   // reads what attention tasks have merged
+    for (const HostOp& p : g.ops)
+      if (p.kind == MPK_OP_ATTN_PARTIAL && p.out_tensor == op.in_tensor) return true;
+    return false;
+  };
   for (auto& op : g.ops) {
     uint32_t nu = op.cols / op.unit;
     switch (op.kind) {
@@ -719,6 +731,24 @@ static void choose_partitions(const mpk_model_config& c, const mpk_compile_optio
         const bool given = (op.flags & TF_OUT_LOGITS) ? o.tiles_lm_head != 0 : o.tiles_linear != 0;
         const uint32_t per_row = (op.flags & TF_GATEUP) ? 2u : 1u;
         while (c.batch > 4 && !given && op.tc < cap && (nu + op.tc - 1) / op.tc * per_row > 512) op.tc = std::min(cap, op.tc + W);
+        // O projection at batch 1 and 2: the workers that run an attention task come to it last, with none of its weights
+        // requested, and everybody waits for them.  If the others can hold all of it in their
+        // two half blocks a wavefront, they alone run it (the round-robin order hands its tasks to the workers
+        // behind the attention tasks').
+        if (c.batch < kMfmaMinBatch && !given && o.launch_mode == MPK_LAUNCH_MEGA && (o.n_sched_wgs == 0 || o.force_aot) && after_attention(op)) {
+          const uint32_t attn_tasks = c.batch * c.n_kv_heads * std::max(1u, o.attn_chunks);
+          if (attn_tasks < W) {
+            const uint32_t rows = (nu + (W - attn_tasks) - 1) / (W - attn_tasks), pairs = (rows + 1) / 2;
+            if ((pairs + 7) / 8 * ((op.K + 4095u) / 4096u) <= 2u && op.tc > W - attn_tasks) {
+              op.tc = W - attn_tasks;
+              // Where gate/up tasks find their first rows in LDS pages, their tiles are sized by who ran attention: the same
+              // workers in every layer, the next operator starts where it would have.  Elsewhere it starts
+              // behind this one's last task, and the parts that the workers play move on from layer to layer (us a
+              // step, fixed / moving: 1B class 709 / 689, 2B class at batch 2 2257 / 2200, MoE at batch 1 988 / 974).
+              if (pages_likely) op.skip_workers = attn_tasks;
+            }
+          }
+        }
         if (op.align_unit && nu % op.align_unit == 0) {
           // QKV projection: tiles that never straddle a head keep every tile in exactly one
           // attention group's producer set (no fork, hence no dummy tasks).  Every head gets the
@@ -1239,9 +1269,6 @@ static void apply_worker_weights(const mpk_compile_options& o, const TileWorkers
 // LDS floats a batch-1 linear task of this operator needs below the page area.
 static size_t lin_task_floats_b1(const HostGraph& g, const HostOp& op) {
   return (size_t)((op.K + 4095u) / 4096u * 4096u) + 2 * (size_t)g.lin_rows_max + 8;
-}
-static bool page_capable(const mpk_model_config& c, const mpk_compile_options& o) {
-  return c.batch == 1 && !o.no_lds_pages && !o.no_preload && o.n_sched_wgs == 0 && o.launch_mode == MPK_LAUNCH_MEGA && true;
 }
 
 // Which tasks get their first half blocks pre-loaded into the LDS pages by the task before them in

@@ -171,6 +171,7 @@ struct HostOp {
   uint32_t rows, cols, unit;   // output tensor [rows][cols]; columns tile in multiples of unit
   uint32_t tb, tc;
   uint32_t task_base;          // canonical id of tile 0
+  uint32_t skip_workers = 0;   // workers that the round-robin order passes over behind this operator's last task
   uint32_t jit;
   // tensors
   int out_tensor;
