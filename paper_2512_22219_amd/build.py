@@ -43,8 +43,8 @@ def build(force: bool = True, jobs: int = 8) -> str:
             (SOURCES[1], os.path.join(_OBJ, "runtime.o"), [])]
     work += [(SOURCES[2], os.path.join(_OBJ, f"variant{i}.o"), [f"-DMPK_VARIANT_INDEX={i}"])
              for i in range(_n_variants())]
-    # the matrix-core sets take longest: start them first
-    work.sort(key=lambda j: 0 if j[1].endswith(("variant3.o", "variant6.o")) else 1)
+    # the matrix-core sets with experts take longest: start them first
+    work.sort(key=lambda j: 0 if j[1].endswith(("variant8.o", "variant9.o", "variant10.o")) else 1)
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(work)))) as pool:
         objs = list(pool.map(_compile, work))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB])

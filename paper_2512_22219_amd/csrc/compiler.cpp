@@ -1148,7 +1148,6 @@ static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_
     res_rows = std::max(res_rows, col_tile_max_units(op) * op.unit);
   }
   if (c.batch >= kMfmaMinBatch) res_rows = std::min(res_rows, kMfmaJobRows);   // (a job's)
-  g.lin_res_rows_max = res_rows;
   for (auto& op : g.ops) {
     size_t f = 0, fa = 0;
     if (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) {
@@ -1157,8 +1156,9 @@ static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_
         f = fa;
       } else {
         // matrix-core body: the staged fp32 input, one chunk (reused for the per-wavefront
-        // partial tiles) | residual slice | sums of squares | 1/rms per row
-        f = (size_t)mfma_x_floats(c.batch) + (size_t)res_rows * 16 + 10 * 16;   // ... | split-K arrival flag
+        // partial tiles) | sums of squares | split-K arrival flag
+        f = (size_t)mfma_x_floats(c.batch) + 10 * 16;
+        fa = std::max(fa, f + (size_t)res_rows * 16);   // (a body that kept the residual slice too)
       }
     }
     else if (op.kind == MPK_OP_EXPERT) {

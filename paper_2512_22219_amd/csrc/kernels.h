@@ -59,7 +59,6 @@ struct GraphConst {
   uint32_t n_workers;
   uint32_t vocab, max_seq, n_q, n_kv, head_dim, batch;
   uint32_t lin_rows_max;     // largest number of weight rows (gate/up pairs count twice) of a linear task
-  uint32_t lin_res_rows_max; // largest number of columns of a linear task that adds a residual
   uint32_t lin_page_off;     // float offset of the LDS pre-load pages in the task area (0: none)
   // just-in-time launch (Section 5.2): scheduler event queues and worker task queues.  Entries
   // are 64-bit (ticket + 1) << 32 | id with tickets that only grow, so a slot is valid exactly
@@ -1187,12 +1186,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 constexpr uint32_t kMfmaFrags = 2;
 struct MfmaGeom {
   uint32_t K, nb, nrt;
-  uint32_t Kc, nchunk;   // inputs per chunk, chunks
-  uint32_t xstride;      // floats between staged rows
   uint32_t rg, rgsh, ks;   // row groups (= 1 << rgsh) x K slices = 8
   uint32_t my_g, my_s;
   uint32_t nrtw;         // row tiles of this wavefront: 0 .. 4
-  uint32_t kgpr;         // k-groups per round: 1, 2 or 4
+  uint32_t kgsh;         // k-groups per round: 1 << kgsh = 1, 2 or 4
 };
 __device__ __forceinline__ uint32_t mfma_group_tiles(uint32_t nrt, uint32_t rgsh, uint32_t g) {
   return g < nrt ? min(4u, (nrt - g + (1u << rgsh) - 1u) >> rgsh) : 0u;
@@ -1200,9 +1197,6 @@ __device__ __forceinline__ uint32_t mfma_group_tiles(uint32_t nrt, uint32_t rgsh
 __device__ __forceinline__ MfmaGeom mfma_geom(uint32_t K, uint32_t nb, uint32_t nrt, uint32_t wave) {
   MfmaGeom G;
   G.K = K; G.nb = nb; G.nrt = nrt;
-  G.Kc = mfma_kchunk(nb);
-  G.nchunk = (K + G.Kc - 1u) / G.Kc;
-  G.xstride = G.Kc + kMfmaXPad;
   const uint32_t rgsh = (nrt > 4u ? 1u : 0u) + (nrt > 8u ? 1u : 0u) + (nrt > 16u ? 1u : 0u), rg = 1u << rgsh;
   G.rg = rg;
   G.rgsh = rgsh;
@@ -1210,7 +1204,7 @@ __device__ __forceinline__ MfmaGeom mfma_geom(uint32_t K, uint32_t nb, uint32_t 
   G.my_g = wave & (rg - 1u);
   G.my_s = wave >> rgsh;
   G.nrtw = mfma_group_tiles(nrt, rgsh, G.my_g);
-  G.kgpr = G.nrtw >= 3u ? 1u : (G.nrtw == 2u ? 2u : 4u);
+  G.kgsh = G.nrtw >= 3u ? 0u : (G.nrtw == 2u ? 1u : 2u);
   return G;
 }
 
@@ -1247,7 +1241,7 @@ __device__ __forceinline__ void pair_to_operands(u32x4& l0, u32x4& l1) {
 //   wbase, row_off(rt) : weight rows start at wbase (uniform) + row_off(rt) bytes, row_off = this
 //                  lane's row of 16-row tile rt (32 bits: a scalar base and one vector offset per
 //                  load, no address pairs to keep); loads are clamped to the end of the row
-//   src_row(b)   : fp32 input row b (read with coherent loads), b < nb
+//   row_bytes(b) : byte of t.in at which fp32 input row b starts (uniform; read with coherent loads), b < nb
 //   probe_fn()   : called before any request: the first look at the event, handed to wait_fn
 //   wait_fn(p)   : called after the first two rounds of weights have been requested (cross-task
 //                  pre-loading, Section 5.3: 16 KB per wavefront, 32 MB over the chip); returns
@@ -1260,20 +1254,25 @@ __device__ __forceinline__ void pair_to_operands(u32x4& l0, u32x4& l1) {
 // the mid term of the same rows (PACK 2: two multiplies per fragment, the lo term alone in the
 // second, on accumulators of its own); up to 4 staged rows take hi | mid | lo in columns 0..3 |
 // 4..7 | 8..11 (PACK 3: one multiply).  The column groups are added up once, at the end.
-template <int PACK, class RowOff, class SrcRow, class Probe, class Wait>
+template <int PACK, class RowOff, class RowBytes, class Probe, class Wait>
 __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const TaskDesc& t, float* lds, float* ssq, const MfmaGeom& G,
-                                                    const uint16_t* wbase, RowOff row_off, SrcRow src_row, bool pro_norm,
+                                                    const uint16_t* wbase, RowOff row_off, RowBytes row_bytes, bool pro_norm,
                                                     const uint16_t* gain, Probe probe_fn, Wait wait_fn) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t K = G.K, nb = G.nb, nrt = G.nrt, Kc = G.Kc, nchunk = G.nchunk, xstride = G.xstride;
-  const uint32_t nrtw = G.nrtw, kgpr = G.kgpr, S = G.ks;
+  const uint32_t K = G.K, nb = G.nb, nrt = G.nrt;
+  constexpr uint32_t Kc = mfma_kchunk(PACK == 1 ? 16u : PACK == 2 ? 8u : 4u), xstride = Kc + kMfmaXPad;   // inputs per chunk, floats between staged rows
+  static_assert(mfma_kchunk(1) == mfma_kchunk(4) && mfma_kchunk(5) == mfma_kchunk(8) && mfma_kchunk(9) == mfma_kchunk(16), "the chunk follows from the packing");
+  // (Every quotient below is by a power of two, and a shift: the compiler does not know it of a variable, and a
+  // division is some thirty instructions, several of them in every round.)
+  const uint32_t nchunk = (K + Kc - 1u) / Kc, kgsh = G.kgsh, kgpr = 1u << kgsh, ssh = 3u - G.rgsh;   // K slices: 1 << ssh
+  const uint32_t nrtw = G.nrtw;
   float* xs = lds;
   float* part = lds;
   const uint32_t frow = lane & 15u, fk = (uint32_t)(lane >> 4) * 8u;
   constexpr uint32_t FR = kMfmaFrags, KG = 32u * FR;   // fragments per slot group, inputs per k-group
   // slot group q of a round: k-group offset inside the round, byte offset of its row tile's row
-  const uint32_t sh = kgpr == 4u ? 0u : (kgpr == 2u ? 1u : 2u);   // q >> sh = k-group offset
+  const uint32_t sh = 2u - kgsh;   // q >> sh = k-group offset
   // How the weights are loaded.  A multiply wants lane (i = l % 16, j = l / 16) to hold 8 inputs of
   // tile row i, the same 8 for all i.  Loaded that way an instruction touches 16 rows x 64 bytes --
   // half lines, which streams 12 % slower than whole lines (5.9 against 6.7 TB/s in isolation).
@@ -1308,11 +1307,11 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   // the wavefront's run of k-groups in chunk c; a chunk takes an even number of round slots
   // (>= 2), so that even slots always use fragment buffer A and odd ones B
   auto chunk_kgs = [&](uint32_t c) { return (min(Kc, K - c * Kc) + KG - 1u) / KG; };
-  auto run_lo = [&](uint32_t c) { return G.my_s * chunk_kgs(c) / S; };
-  auto run_hi = [&](uint32_t c) { return nrtw ? (G.my_s + 1u) * chunk_kgs(c) / S : 0u; };
+  auto run_lo = [&](uint32_t c) { return (G.my_s * chunk_kgs(c)) >> ssh; };
+  auto run_hi = [&](uint32_t c) { return nrtw ? ((G.my_s + 1u) * chunk_kgs(c)) >> ssh : 0u; };
   auto slots = [&](uint32_t c) {
     const uint32_t lo = run_lo(c), hi = run_hi(c);
-    const uint32_t n = hi > lo ? (hi - lo + kgpr - 1u) / kgpr : 0u;
+    const uint32_t n = hi > lo ? (hi - lo + kgpr - 1u) >> kgsh : 0u;
     return max(2u, (n + 1u) & ~1u);
   };
   // requests the 4 FR kilobytes of round slot (c, i) into buf; buf[FR Q + u] = load u of slot
@@ -1350,6 +1349,30 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
     if (pro_norm)
       for (uint32_t i = klen + threadIdx.x; i < ((klen + 127u) & ~127u); i += kThreads) gl[i] = 0;
   };
+  // Staging: the nb rows of a chunk, 256 inputs (1 KB) per instruction, a row's instructions dealt to the wavefronts,
+  // with agent-coherent loads straight into LDS.  What lies between the end of a row and the end of its last
+  // k-group is zeroed.  A rolled loop on purpose: unrolled, the addresses, LDS addresses and lane masks of all
+  // sixteen copies are worked out ahead of the chunk loop, at the start of every task, and kept in spilled registers.
+  // With one packing a kernel and no divisions 295 -> 243 spilled scalar registers; us a step: 8B layers at batch 8
+  // 1072 -> 1044, serving burst 9357 -> 8800, odd sizes at batch 5 546 -> 508, mixture of experts at batch 1 961 -> 895.
+  float rowsum = 0.f;   // lane b: this wavefront's sum of squares of staged row b
+  auto stage = [&](uint32_t c) {
+    const uint32_t k0 = c * Kc, klen = min(Kc, K - k0), kpad = (klen + 127u) & ~127u;
+    if (c) request_gains(c);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(t.in)), 0, (int)kRange, 0x00020000);
+#pragma unroll 1
+    for (uint32_t b = 0; b < nb; ++b) {
+      const uint32_t row = row_bytes(b) + 4u * k0;
+#pragma unroll
+      for (uint32_t h = 0; h < Kc / 2048u; ++h) {
+        const uint32_t seg = wave + 8u * h;
+        if (seg * 256u + 4u * (uint32_t)lane < klen)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(xs + (size_t)b * xstride + seg * 256u), 16, 16 * lane, (int)(row + 1024u * seg), 0, 16);
+      }
+    }
+    if (kpad != klen)
+      for (uint32_t i = threadIdx.x; i < nb * (kpad - klen); i += kThreads) xs[(size_t)(i / (kpad - klen)) * xstride + klen + i % (kpad - klen)] = 0.f;
+  };
   u32x4 wA[4 * FR], wB[4 * FR];
   const bool preload = !(a.flags & kNoPreloadBit);   // off: the ablation of Section 6.5, Fig. 10
   // Both rounds (16 KB per wavefront) are requested before the event.  A wavefront sees its loads
@@ -1370,28 +1393,6 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
     request_round(wA, 0u, 0u);
     asm volatile("; first round requested after the event" ::: "memory");
   }
-  // Staging: the nb rows of a chunk, 256 inputs (1 KB) per instruction, the instructions dealt
-  // round-robin to the wavefronts (16 each for a full chunk), with agent-coherent loads straight
-  // into LDS.  What lies between the end of a row and the end of its last k-group is zeroed.
-  const uint32_t wide = nb > 8u ? 1u : 0u;
-  float rowsum = 0.f;   // lane b: this wavefront's sum of squares of staged row b
-  auto stage = [&](uint32_t c) {
-    const uint32_t k0 = c * Kc, klen = min(Kc, K - k0), kpad = (klen + 127u) & ~127u;
-    if (c) request_gains(c);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t n = wave + 8u * (uint32_t)i;
-      const uint32_t b = wide ? n >> 3 : n >> 4, seg = wide ? n & 7u : n & 15u;   // Kc / 256 instructions per row
-      if (b < nb && seg * 256u < klen) {
-        const uint32_t col = seg * 256u + 4u * (uint32_t)lane;
-        if (col < klen)
-          __builtin_amdgcn_global_load_lds(as_global((const u32x4*)(src_row(b) + k0 + col)), (lds_ptr_t)(xs + (size_t)b * xstride + seg * 256u), 16, 0, 16);
-      }
-    }
-    if (kpad != klen)
-      for (uint32_t i = threadIdx.x; i < nb * (kpad - klen); i += kThreads) xs[(size_t)(i / (kpad - klen)) * xstride + klen + i % (kpad - klen)] = 0.f;
-    drain_vmem();   // this wavefront's copies have landed
-  };
   // sums of squares of the staged rows (before the gains), needed only by the epilogue: taken
   // behind the chunk's multiplies by wavefronts 0..3 (rows w, w + 4, ...), which are through their
   // share well before the upper four are (they win the arbitration on their SIMDs), so the pass is
@@ -1458,6 +1459,7 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   for (uint32_t c = 0; c < nchunk; ++c) {
     if (c) lds_barrier();   // everybody has finished with the previous chunk
     stage(c);
+    drain_vmem();   // this wavefront's copies have landed
     lds_barrier();
     if (c == 0 && !preload) request_round(wB, 0u, 1u);
     if (c == 0) {
@@ -1519,13 +1521,13 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   return kLinDone;
 }
 
-template <class RowOff, class SrcRow, class Probe, class Wait>
+template <class RowOff, class RowBytes, class Probe, class Wait>
 __device__ __forceinline__ uint32_t mfma_job(const StepArgs& a, const TaskDesc& t, float* lds, float* ssq, const MfmaGeom& G,
-                                             const uint16_t* wbase, RowOff row_off, SrcRow src_row, bool pro_norm,
+                                             const uint16_t* wbase, RowOff row_off, RowBytes row_bytes, bool pro_norm,
                                              const uint16_t* gain, Probe probe_fn, Wait wait_fn) {
-  if (G.nb <= 4u) return mfma_job_packed<3>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, probe_fn, wait_fn);
-  if (G.nb <= 8u) return mfma_job_packed<2>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, probe_fn, wait_fn);
-  return mfma_job_packed<1>(a, t, lds, ssq, G, wbase, row_off, src_row, pro_norm, gain, probe_fn, wait_fn);
+  if (G.nb <= 4u) return mfma_job_packed<3>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
+  if (G.nb <= 8u) return mfma_job_packed<2>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
+  return mfma_job_packed<1>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
 }
 
 // Dot product of weight row r (16-row tile r / 16) with batch column bb from the partial tiles a
@@ -1560,11 +1562,11 @@ __device__ __forceinline__ float mfma_inv_rms(const float* ssq, uint32_t bb, uin
   return 1.0f / sqrtf(ss / (float)K + eps);
 }
 
-// LDS of a linear task (from the task area): job buffers (mfma_x_floats) | res [residual columns][16] f32
-// | ssq [8][16] f32 | arrival flag.  A job takes up to 512 weight rows; a task of more (batch 3 and 4:
+// LDS of a linear task (from the task area): job buffers (mfma_x_floats) | ssq [8][16] f32 | arrival flag.  A job takes up to 512 weight rows; a task of more (batch 3 and 4:
 // an output head of more than 512 rows a worker, few tiles given) is worked off in several, the input staged
 // again for each.
-template <bool MEGA, class Svc = NoJit>
+// PACK: the packing of the input terms, that of the graph's batch size (mfma_pack).
+template <int PACK, bool MEGA, class Svc = NoJit>
 __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
                                                      uint32_t* s_flag, const Svc& svc = Svc{}) {
   const int lane = threadIdx.x & 63;
@@ -1573,8 +1575,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
   const uint32_t gateup = (t.flags & TF_GATEUP) ? 1u : 0u;
   const uint32_t R = ncols << gateup;            // weight rows of the task ("ring rows")
   float* part = lds;
-  float* res_lds = lds + mfma_x_floats(nb);                    // [residual columns of a job][16]
-  float* ssq = res_lds + (size_t)a.g->lin_res_rows_max * 16;   // [8][16]
+  float* ssq = lds + mfma_x_floats(nb);          // [8][16]
   // split-K task (TF_SPLITK): rows [row0, row0 + ncols) of the matrix, inputs of ONE part; the
   // weight pointer is already advanced to the part, rows are ldw apart
   const bool splitk = t.flags & TF_SPLITK;
@@ -1582,7 +1583,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
   const uint32_t Hs = t.ld_out / parts;              // columns of the real output
   const uint32_t row0 = t.c0 - my_part * Hs, ldw = splitk ? t.p1 : K;
   const uint16_t* W = (const uint16_t*)t.w + (size_t)row0 * ldw;   // the task's first row (gate/up: of the gate rows)
-  auto src_row = [&](uint32_t b) { return t.in + (size_t)(t.b0 + b) * t.ld_in; };
+  auto row_bytes = [&](uint32_t b) { return 4u * (t.b0 + b) * t.ld_in; };   // (at most 16 rows)
   const bool pro_norm = t.flags & TF_PRO_NORM;
   for (uint32_t r0 = 0; r0 < R; r0 += kMfmaJobRows) {
     const uint32_t Rj = min(R - r0, kMfmaJobRows), cj = r0 >> gateup, nj = Rj >> gateup;   // the job's rows, columns
@@ -1595,31 +1596,33 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
       return wrow * ldw * 2u;
     };
     auto probe_fn = [&]() { return linear_probe<Svc>(a, r0 == 0 ? wait_ev : -1, wave, lane); };
+    // the residual slice of this tile goes out ahead of the input (tile-local, small), a thread loads that of its first output:
+    // its round trip overlaps the staging
+    const uint32_t bsh = nb <= 4u ? 2u : (nb <= 8u ? 3u : 4u);   // batch columns padded to 4, 8 or 16 lanes: no division
+    const bool resid = (t.flags & TF_EPI_RESID) && !splitk;
+    float resv = 0.f;
+    auto load_resid = [&]() {
+      const uint32_t cc = threadIdx.x >> bsh, bb = threadIdx.x & ((1u << bsh) - 1u);
+      if (resid && bb < nb && cc < nj) resv = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cj + cc);
+    };
     auto wait_fn = [&](const EventProbe& probe) -> uint32_t {
       if (wait_ev >= 0 && r0 == 0) {
         const uint32_t w = linear_wait(a, wait_ev, s_flag, wave, lane, svc, probe);
         if (w != kLinDone) return w;
       }
-      // the residual slice of this tile goes out first (tile-local, small): its round trip overlaps the staging
-      if ((t.flags & TF_EPI_RESID) && !splitk) {
-        for (uint32_t i = threadIdx.x; i < nb * nj; i += kThreads) {
-          uint32_t bb = i / nj, cc = i % nj;
-          res_lds[cc * 16 + bb] = ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cj + cc);
-        }
-      }
+      load_resid();
       return kLinDone;
     };
     {
-      const uint32_t w = mfma_job(a, t, lds, ssq, G, W + (size_t)cj * ldw, row_off, src_row, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn);
+      const uint32_t w = mfma_job_packed<PACK>(a, t, lds, ssq, G, W + (size_t)cj * ldw, row_off, row_bytes, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn);
       if (w != kLinDone) return w;
     }
     trace_mark(a, t, 3);
     // ---- all wavefronts: add the K slices in order, epilogue, outputs; then the notification
     {
       float* outp = (t.flags & TF_OUT_LOGITS) ? a.logits : t.out;
-      const uint32_t sh = nb <= 4u ? 2u : (nb <= 8u ? 3u : 4u);   // batch columns padded to 4, 8 or 16 lanes: no division
-      for (uint32_t i = threadIdx.x; i < nj << sh; i += kThreads) {
-        const uint32_t cc = i >> sh, bb = i & ((1u << sh) - 1u);
+      for (uint32_t i = threadIdx.x; i < nj << bsh; i += kThreads) {
+        const uint32_t cc = i >> bsh, bb = i & ((1u << bsh) - 1u);
         if (bb >= nb) continue;
         const float inv = pro_norm ? mfma_inv_rms(ssq, bb, K, t.f0) : 1.0f;
         float v;
@@ -1629,7 +1632,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
         } else {
           v = mfma_dot(part, G, cc, bb) * inv;
         }
-        if ((t.flags & TF_EPI_RESID) && !splitk) v = res_lds[cc * 16 + bb] + v;
+        if (resid) v = (i < kThreads ? resv : ld_act(t.in2 + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cj + cc)) + v;
         st_act(outp + (size_t)(t.b0 + bb) * t.ld_out + t.c0 + cj + cc, v);   // split-K: the partial sums of this part
       }
     }
@@ -1869,7 +1872,7 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
     const uint32_t wrow = gateup ? ((r >> 1) + ((r & 1u) ? t.p0 : 0u)) : r;
     return wrow * K * 2u;   // bytes from the expert's first row
   };
-  auto src_row = [&](uint32_t b) { return t.in + (size_t)__builtin_amdgcn_readfirstlane(rowin[b]) * t.ld_in; };   // uniform: scalar base addresses
+  auto row_bytes = [&](uint32_t b) { return 4u * (uint32_t)__builtin_amdgcn_readfirstlane(rowin[b]) * t.ld_in; };   // (at most 256 pairs)
   auto probe_fn = [&]() { return linear_probe<NoJit>(a, wait_ev, wave, lane); };
   auto wait_fn = [&](const EventProbe& probe) -> uint32_t {
     if (wait_ev < 0) return kLinDone;
@@ -1877,7 +1880,7 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
     trace_mark(a, t, 1);
     return w;
   };
-  if (mfma_job(a, t, lds, ssq, G, W, row_off, src_row, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn) != kLinDone) return false;
+  if (mfma_job(a, t, lds, ssq, G, W, row_off, row_bytes, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn) != kLinDone) return false;
   const uint32_t ncols = (ntile * 16u) >> gateup, col0 = (tile0 * 16u) >> gateup;
   const uint32_t sh = ne <= 1u ? 0u : (ne <= 2u ? 1u : (ne <= 4u ? 2u : (ne <= 8u ? 3u : 4u)));
   for (uint32_t i = threadIdx.x; i < ncols << sh; i += kThreads) {
@@ -3102,11 +3105,12 @@ __device__ __forceinline__ void body_serve(const StepArgs& a) {
 // NB, the batch class, pins the linear body of a kernel: a kernel that carries a single one keeps its
 // register allocation (nearly) free of spills, one that decides between them at run time does not.
 //   1: one row, vector body; 9: one row, large tasks: three weight buffers; 2: two rows, vector body;
-//   8: 3 .. 16 rows, matrix cores
+//   4, 8, 16: up to that many rows, matrix cores -- a kernel for each packing of the input terms (in one kernel
+//   for all the three bodies had 398 to 431 spilled scalar registers)
 template <int NB, bool MEGA, class Svc = NoJit>
 __device__ __forceinline__ uint32_t run_linear(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
                                            uint32_t* s_flag, const Svc& svc = Svc{}, uint32_t next_ti = 0) {
-  if constexpr (NB == 8) return linear_task_mfma<MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);
+  if constexpr (NB == 4 || NB == 8 || NB == 16) return linear_task_mfma<NB == 4 ? 3 : NB == 8 ? 2 : 1, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);
   else if constexpr (NB == 9) return linear_task<1, MEGA, Svc, true>(t, a, lds, wait_ev, s_flag, svc, next_ti);
   else return linear_task<NB, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc, next_ti);
 }
@@ -3789,8 +3793,9 @@ struct KernelVariant {
 };
 // index, batch class, mixture of experts
 #define MPK_VARIANT_LIST(X) \
-  X(0, 1, false) X(1, 9, false) X(2, 2, false) X(3, 8, false) X(4, 1, true) X(5, 2, true) X(6, 8, true)
-constexpr int kNumVariants = 7;
+  X(0, 1, false) X(1, 9, false) X(2, 2, false) X(3, 4, false) X(4, 8, false) X(5, 16, false) \
+  X(6, 1, true) X(7, 2, true) X(8, 4, true) X(9, 8, true) X(10, 16, true)
+constexpr int kNumVariants = 11;
 #define MPK_DECLARE_VARIANT(I, N, M) const KernelVariant* kernel_variant_##I();
 MPK_VARIANT_LIST(MPK_DECLARE_VARIANT)
 #undef MPK_DECLARE_VARIANT

@@ -16,7 +16,7 @@ static const KernelVariant* variant_at(int i) {
 
 // The kernel set of a batch size; null: none (the host admits no such batch).
 static const KernelVariant* pick_variant(uint32_t batch, bool moe, bool large_tasks) {
-  const int nb = batch == 1 ? (large_tasks && !moe ? 9 : 1) : batch < kMfmaMinBatch ? 2 : 8;
+  const int nb = batch == 1 ? (large_tasks && !moe ? 9 : 1) : batch < kMfmaMinBatch ? 2 : batch <= 4 ? 4 : batch <= 8 ? 8 : batch <= 16 ? 16 : 0;
   for (int i = 0; i < kNumVariants; ++i)
     if (variant_at(i)->nb == nb && variant_at(i)->moe == moe) return variant_at(i);
   return nullptr;
@@ -450,7 +450,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     c.n_workers = h.opt.n_workers;
     c.vocab = h.cfg.vocab; c.max_seq = h.cfg.max_seq; c.n_q = h.cfg.n_q_heads;
     c.n_kv = h.cfg.n_kv_heads; c.head_dim = h.cfg.head_dim; c.batch = h.cfg.batch;
-    c.lin_rows_max = h.lin_rows_max; c.lin_res_rows_max = h.lin_res_rows_max; c.lin_page_off = h.lin_page_off;
+    c.lin_rows_max = h.lin_rows_max; c.lin_page_off = h.lin_page_off;
     c.n_sched = g->n_sched; c.evq_cap = g->evq_cap; c.wq_cap = g->wq_cap;
     c.evq_buf = g->d_evq_buf; c.evq_tail = g->d_evq_tail; c.sched_state = g->d_sched_state;
     c.sched_nev = g->d_sched_nev; c.wq_buf = g->d_wq_buf; c.wq_tail = g->d_wq_tail; c.wq_head = g->d_wq_head;

@@ -47,5 +47,16 @@ MPK_DEFINE_VARIANT(5)
 #if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 6
 MPK_DEFINE_VARIANT(6)
 #endif
-
+#if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 7
+MPK_DEFINE_VARIANT(7)
+#endif
+#if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 8
+MPK_DEFINE_VARIANT(8)
+#endif
+#if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 9
+MPK_DEFINE_VARIANT(9)
+#endif
+#if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 10
+MPK_DEFINE_VARIANT(10)
+#endif
 }  // namespace mpk
