@@ -2716,8 +2716,11 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   // ---- the wavefronts' results and the appended row -> the task's partial result, two elements a thread
   const uint32_t nw = min(nblk, NW);
   float* own_ml = (float*)flag;   // (nobody needs the queries or the flag any more)
-  for (uint32_t i = threadIdx.x; i < grp * (d / 2 + 1); i += kThreads) {
-    const uint32_t j = i / (d / 2 + 1), e = 2u * (i % (d / 2 + 1));   // e == d: the maximum and the sum
+  // (the thread of a head's first elements leaves its maximum and sum as well: threads of their own for those were
+  // a second round of a loop with 8 heads of 128 elements, 1.0 us a task against 0.8 .. 1.8)
+  static_assert(grp * d / 2 <= kThreads, "a thread has two elements");
+  if (threadIdx.x < grp * d / 2) {
+    const uint32_t j = threadIdx.x / (d / 2), e = 2u * (threadIdx.x % (d / 2));
     float mw[NW], M = has_new ? snew[j] * kScale : -INFINITY;
 #pragma unroll
     for (uint32_t w = 0; w < NW; ++w) {
@@ -2727,31 +2730,30 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     const float Mr = M == -INFINITY ? 0.f : M;   // (every score -infinity: all weights 0)
     float x = 0.f, y = 0.f;
     const float wn = has_new ? __builtin_amdgcn_exp2f(fmaf(snew[j], kScale, -Mr)) : 0.f;
-    if (e == d) {
-      y = wn;
+    float l = wn;
+    if (has_new) { x = wn * vnew[e]; y = wn * vnew[e + 1]; }
 #pragma unroll
-      for (uint32_t w = 0; w < NW; ++w)
-        if (w < nw) y = fmaf(ml[(w * grp + j) * 2 + 1], __builtin_amdgcn_exp2f(mw[w] - Mr), y);
-      x = M;   // (a power of two, like everything the merges do with it)
-    } else {
-      if (has_new) { x = wn * vnew[e]; y = wn * vnew[e + 1]; }
+    for (uint32_t w = 0; w < NW; ++w) {
+      if (w >= nw) continue;
+      const float f = __builtin_amdgcn_exp2f(mw[w] - Mr);
+      l = fmaf(ml[(w * grp + j) * 2 + 1], f, l);
+      float ox = 0.f, oy = 0.f;
 #pragma unroll
-      for (uint32_t w = 0; w < NW; ++w) {
-        if (w >= nw) continue;
-        const float f = __builtin_amdgcn_exp2f(mw[w] - Mr);
-        float ox = 0.f, oy = 0.f;
-#pragma unroll
-        for (uint32_t term = 0; term < NTERM; ++term) {
-          const float2 v = *(const float2*)(wpart + (((size_t)w * NTERM + term) * grp + j) * WS + e);
-          ox += v.x; oy += v.y;
-        }
-        x = fmaf(f, ox, x);
-        y = fmaf(f, oy, y);
+      for (uint32_t term = 0; term < NTERM; ++term) {
+        const float2 v = *(const float2*)(wpart + (((size_t)w * NTERM + term) * grp + j) * WS + e);
+        ox += v.x; oy += v.y;
       }
+      x = fmaf(f, ox, x);
+      y = fmaf(f, oy, y);
     }
-    if (merger) *(float2*)(e == d ? own_ml + 2u * j : qs + j * d + e) = make_float2(mark_clean(x), mark_clean(y));   // (stays here: this task merges)
-    else if (MARKED) st_act2(outp + j * (d + 2) + e, mark_clean(x), mark_clean(y));
-    else st_act2(outp + j * (d + 2) + e, x, y);
+    // (M is a power of two's exponent, like everything the merges do with it)
+    if (merger) {   // (stays here: this task merges)
+      *(float2*)(qs + j * d + e) = make_float2(mark_clean(x), mark_clean(y));
+      if (e == 0) *(float2*)(own_ml + 2u * j) = make_float2(mark_clean(M), mark_clean(l));
+    } else {
+      st_act2(outp + j * (d + 2) + e, MARKED ? mark_clean(x) : x, MARKED ? mark_clean(y) : y);
+      if (e == 0) st_act2(outp + j * (d + 2) + d, MARKED ? mark_clean(M) : M, MARKED ? mark_clean(l) : l);
+    }
   }
   if (MARKED)
     for (uint32_t i = threadIdx.x; i < per / 2; i += kThreads) mark_reset2(outp + 2u * i, t.twin);
