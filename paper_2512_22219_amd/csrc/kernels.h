@@ -1521,13 +1521,17 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   return kLinDone;
 }
 
-template <class RowOff, class RowBytes, class Probe, class Wait>
+// NB: the largest number of staged rows there can be (an expert has at most as many tokens as the batch).
+template <int NB, class RowOff, class RowBytes, class Probe, class Wait>
 __device__ __forceinline__ uint32_t mfma_job(const StepArgs& a, const TaskDesc& t, float* lds, float* ssq, const MfmaGeom& G,
                                              const uint16_t* wbase, RowOff row_off, RowBytes row_bytes, bool pro_norm,
                                              const uint16_t* gain, Probe probe_fn, Wait wait_fn) {
-  if (G.nb <= 4u) return mfma_job_packed<3>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
-  if (G.nb <= 8u) return mfma_job_packed<2>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
-  return mfma_job_packed<1>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
+  if (NB <= 4 || G.nb <= 4u) return mfma_job_packed<3>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
+  if constexpr (NB > 4) {
+    if (NB <= 8 || G.nb <= 8u) return mfma_job_packed<2>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
+  }
+  if constexpr (NB > 8) return mfma_job_packed<1>(a, t, lds, ssq, G, wbase, row_off, row_bytes, pro_norm, gain, probe_fn, wait_fn);
+  return kLinAbort;
 }
 
 // Dot product of weight row r (16-row tile r / 16) with batch column bb from the partial tiles a
@@ -1848,6 +1852,7 @@ __device__ __forceinline__ void body_moe_route(const TaskDesc& t, const StepArgs
 // wait_ev >= 0: the job's inputs exist only once that event is activated (the first job of a
 // second-stage expert task, see run_moe_task): it is waited for behind the job's first weight
 // requests.  Returns false when the step is being aborted.
+template <int NB>
 __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs& a, float* lds, const uint16_t* W,
                                                uint32_t tile0, uint32_t ntile, uint32_t ne, const uint32_t* plist,
                                                uint32_t TK, int32_t wait_ev, uint32_t* s_flag) {
@@ -1872,7 +1877,9 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
     const uint32_t wrow = gateup ? ((r >> 1) + ((r & 1u) ? t.p0 : 0u)) : r;
     return wrow * K * 2u;   // bytes from the expert's first row
   };
-  auto row_bytes = [&](uint32_t b) { return 4u * (uint32_t)__builtin_amdgcn_readfirstlane(rowin[b]) * t.ld_in; };   // (at most 256 pairs)
+  // (a lane holds a row's index: read from LDS as they are needed, each read would wait for the copies under way into LDS)
+  const uint32_t in_row = rowin[min((uint32_t)lane, ne - 1u)];
+  auto row_bytes = [&](uint32_t b) { return 4u * (uint32_t)__builtin_amdgcn_readlane((int)in_row, (int)b) * t.ld_in; };   // (at most 256 pairs)
   auto probe_fn = [&]() { return linear_probe<NoJit>(a, wait_ev, wave, lane); };
   auto wait_fn = [&](const EventProbe& probe) -> uint32_t {
     if (wait_ev < 0) return kLinDone;
@@ -1880,7 +1887,7 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
     trace_mark(a, t, 1);
     return w;
   };
-  if (mfma_job(a, t, lds, ssq, G, W, row_off, row_bytes, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn) != kLinDone) return false;
+  if (mfma_job<NB>(a, t, lds, ssq, G, W, row_off, row_bytes, pro_norm, (const uint16_t*)t.w2, probe_fn, wait_fn) != kLinDone) return false;
   const uint32_t ncols = (ntile * 16u) >> gateup, col0 = (tile0 * 16u) >> gateup;
   const uint32_t sh = ne <= 1u ? 0u : (ne <= 2u ? 1u : (ne <= 4u ? 2u : (ne <= 8u ? 3u : 4u)));
   for (uint32_t i = threadIdx.x; i < ncols << sh; i += kThreads) {
@@ -1905,8 +1912,8 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
 // Section 6.4); a task's share is worked off in jobs of at most 32 tiles that stay inside one expert.
 // wait_ev >= 0: the caller has NOT waited for the task's event yet (only for the routing task's,
 // so the meta-tensor is this step's); the first job does, behind its first weight requests.
-__device__ __forceinline__ bool body_moe_expert(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev = -1,
-                                                uint32_t* s_flag = nullptr) {
+template <int NB>
+__device__ __forceinline__ bool body_moe_expert(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev, uint32_t* s_flag) {
   const uint32_t* meta = (const uint32_t*)t.in2;
   const uint32_t E = t.p3 & 0xFFFFu, TK = t.p3 >> 16, NT = t.p1, rows_per_expert = t.p2;
   const uint32_t tiles_per_expert = rows_per_expert / 16u;
@@ -1927,12 +1934,12 @@ __device__ __forceinline__ bool body_moe_expert(const TaskDesc& t, const StepArg
     const uint32_t e = min(__builtin_amdgcn_readfirstlane(mlds[2 + ai]), E);   // (E: rejected below; the two reads stay inside the copy)
     const uint32_t ne = __builtin_amdgcn_readfirstlane(mlds[2 + E + min(e, E - 1u)]);
     const uint32_t po = __builtin_amdgcn_readfirstlane(mlds[2 + 2 * E + min(e, E - 1u)]);
-    if (e >= E || ne == 0 || ne > 16u || po + ne > P) {   // never index with a damaged meta-tensor
+    if (e >= E || ne == 0 || ne > (uint32_t)NB || po + ne > P) {   // never index with a damaged meta-tensor
       if (threadIdx.x == 0) report(a, DE_BAD_META, e, ne);
       break;
     }
     const uint16_t* W = (const uint16_t*)t.w + (size_t)e * rows_per_expert * t.K;
-    if (!moe_expert_job(t, a, lds, W, tile0, ntile, ne, mlds + 2 + 3 * E + po, TK, wait_ev, s_flag)) return false;
+    if (!moe_expert_job<NB>(t, a, lds, W, tile0, ntile, ne, mlds + 2 + 3 * E + po, TK, wait_ev, s_flag)) return false;
     wait_ev = -1;
     u0 += ntile;
   }
@@ -3117,8 +3124,10 @@ __device__ __forceinline__ uint32_t run_linear(const TaskDesc& t, const StepArgs
   else return linear_task<NB, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc, next_ti);
 }
 
-// Runs one task that is neither a linear nor an attention task.  wait_ev >= 0: the task must first
+// Runs one task that is neither a linear nor an attention nor an expert task.  wait_ev >= 0: the task must first
 // wait for that event (persistent kernel).
+// (Kernels for dense models are built without the mixture-of-experts bodies.)
+template <bool MOE>
 __device__ __forceinline__ bool run_task(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev, uint32_t* s_flag) {
   if (wait_ev >= 0 && !wait_event(a, wait_ev, s_flag)) return false;
   trace_mark(a, t, 1);
@@ -3131,6 +3140,8 @@ __device__ __forceinline__ bool run_task(const TaskDesc& t, const StepArgs& a, f
     case TK_SWIGLU: body_swiglu(t); break;
     case TK_ARGMAX: body_argmax(t, a, lds); break;
     case TK_SERVE: body_serve(a); break;
+    case TK_MOE_ROUTE: if (MOE) body_moe_route(t, a, lds); break;
+    case TK_MOE_COMBINE: if (MOE) body_moe_combine(t, a); break;
     default: break;   // TK_DUMMY: no computation (normalization, Section 4.1)
   }
   return true;
@@ -3312,19 +3323,18 @@ __device__ __forceinline__ StepArgs published_args() {
   return uniform_args(*(const StepArgs*)(dyn_lds + kLdsArgsAt));
 }
 
-// Mixture-of-experts tasks: inlined into run_other_task of the MoE kernels.  (As a real function of
-// its own -- so that attention calls would not have to save the many callee-saved registers the
-// expert jobs use -- every MoE task paid two nested calls, each with its by-value argument copies
-// and register saves: measured 3 to 4 % slower per step on the MoE shape.)
-template <bool MEGA>
-__device__ __forceinline__ bool run_moe_task(const StepArgs& a, uint32_t task_index, bool skip_wait) {
-  extern __shared__ __align__(16) float dyn_lds[];
-  float* lds = dyn_lds + kLdsCtrlFloats;
-  uint32_t* s_flag = (uint32_t*)dyn_lds;
-  const TaskDesc t = ld_task(a, task_index);
+// An expert task.  Inlined into the all-ahead-of-time walk from batch 3 on, which has nothing live across it: as a
+// real function it saves 89 registers a lane on entry and restores them on exit, 0.2 MB a worker and call (a quarter
+// of the expert stages' traffic at batch 16; us a step of the mixture-of-experts layers: batch 16 1525 -> 1430,
+// 8 1115 -> 1047, 4 825 -> 769).  The other kernels call it (run_expert_task), as do the sets of one and two rows, whose
+// vector body would spill 28 to 40 registers beside it; called directly and not from within run_other_task, with one
+// packing and one call site, batch 1 899 -> 843.
+template <int NB, bool MEGA>
+__device__ __forceinline__ bool expert_task(const StepArgs& a, const TaskDesc& t, uint32_t task_index, bool skip_wait, float* lds, uint32_t* s_flag) {
+  int32_t wait_ev = -1;
   if (MEGA) {
     debug_jitter(a, task_index);
-    const int32_t wait_ev = (!skip_wait && t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
+    wait_ev = (!skip_wait && t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
     trace_mark(a, t, 0);
     if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)task_index * kTraceSlots + 5] = blockIdx.x;
     // Cross-task pre-loading (Section 5.3) for the experts' second stage: which experts are active
@@ -3333,23 +3343,14 @@ __device__ __forceinline__ bool run_moe_task(const StepArgs& a, uint32_t task_in
     // waits for that event -- activated before the first stage could start, so this returns at
     // once and only orders the reads of the meta-tensor -- finds its first job and requests that
     // job's first weights, and only then waits for its own event.
-    if (wait_ev >= 0 && t.kind == TK_MOE_EXPERT && t.aux1 != nullptr && !(a.flags & kNoPreloadBit)) {
-      if (!wait_event(a, (int32_t)(uintptr_t)t.aux1 - 1, s_flag)) return false;
-      if (!body_moe_expert(t, a, lds, wait_ev, s_flag)) return false;
-      trace_mark(a, t, 3);
-      if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
-      else __syncthreads();
-      trace_mark(a, t, 4);
-      return true;
+    const bool second = wait_ev >= 0 && t.aux1 != nullptr && !(a.flags & kNoPreloadBit);
+    if (wait_ev >= 0 && !wait_event(a, second ? (int32_t)(uintptr_t)t.aux1 - 1 : wait_ev, s_flag)) return false;
+    if (!second) {
+      wait_ev = -1;
+      trace_mark(a, t, 1);
     }
-    if (wait_ev >= 0 && !wait_event(a, wait_ev, s_flag)) return false;
-    trace_mark(a, t, 1);
   }
-  switch (t.kind) {
-    case TK_MOE_ROUTE: body_moe_route(t, a, lds); break;
-    case TK_MOE_EXPERT: body_moe_expert(t, a, lds); break;
-    default: body_moe_combine(t, a); break;
-  }
+  if (!body_moe_expert<NB>(t, a, lds, wait_ev, s_flag)) return false;
   if (MEGA) {
     trace_mark(a, t, 3);
     if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
@@ -3358,7 +3359,14 @@ __device__ __forceinline__ bool run_moe_task(const StepArgs& a, uint32_t task_in
   }
   return true;
 }
-__device__ __forceinline__ bool is_moe_kind(uint16_t kind) { return kind >= TK_MOE_ROUTE && kind <= TK_MOE_COMBINE; }
+
+template <int NB, bool MEGA>
+__device__ __noinline__ bool run_expert_task(uint32_t task_index, bool skip_wait) {
+  const StepArgs a = published_args();
+  task_index = uniform_u32(task_index);
+  extern __shared__ __align__(16) float dyn_lds[];
+  return expert_task<NB, MEGA>(a, ld_task(a, task_index), task_index, uniform_u32(skip_wait) != 0, dyn_lds + kLdsCtrlFloats, (uint32_t*)dyn_lds);
+}
 
 // Everything that is not a linear task runs in a function of its own (a real call): its
 // thread-index arithmetic and temporaries then get their own register allocation instead of being
@@ -3374,8 +3382,6 @@ __device__ __noinline__ bool run_other_task(uint32_t task_index, bool skip_wait)
   float* lds = dyn_lds + kLdsCtrlFloats;
   uint32_t* s_flag = (uint32_t*)dyn_lds;
   const TaskDesc t = ld_task(a, task_index);
-  // (kernels for dense models are built without the mixture-of-experts bodies)
-  if (MOE && is_moe_kind(t.kind)) return run_moe_task<MEGA>(a, task_index, skip_wait);
   int32_t wait_ev = -1;
   if (MEGA) {
     debug_jitter(a, task_index);
@@ -3383,7 +3389,7 @@ __device__ __noinline__ bool run_other_task(uint32_t task_index, bool skip_wait)
     trace_mark(a, t, 0);
     if ((a.flags & kTraceBit) && threadIdx.x == 0) as_global(a.g->trace)[(size_t)task_index * kTraceSlots + 5] = blockIdx.x;
   }
-  if (!run_task(t, a, lds, wait_ev, s_flag)) return false;
+  if (!run_task<MOE>(t, a, lds, wait_ev, s_flag)) return false;
   if (MEGA) {
     trace_mark(a, t, 3);
     if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
@@ -3440,10 +3446,11 @@ __device__ __forceinline__ bool call_attn_task(const StepArgs& a, uint32_t task_
   }
 }
 // MARKS: the kernel runs marked descriptors (an attention task has both its input and its output marked, or neither).
-template <bool MEGA, bool MOE, bool MARKS = false>
+template <int NB, bool MEGA, bool MOE, bool MARKS = false>
 __device__ __forceinline__ bool call_task(const StepArgs& a, uint16_t kind, uint16_t flags, uint32_t task_index, bool skip_wait) {
   bool ok;
-  if (kind != TK_ATTN_PARTIAL) ok = run_other_task<MEGA, MOE>(task_index, skip_wait);
+  if (MOE && kind == TK_MOE_EXPERT) ok = run_expert_task<NB == 9 ? 1 : NB, MEGA>(task_index, skip_wait);
+  else if (kind != TK_ATTN_PARTIAL) ok = run_other_task<MEGA, MOE>(task_index, skip_wait);
   else if (MARKS && (flags & TF_IN_MARKED)) ok = call_attn_task<true>(a, task_index, skip_wait, MEGA);
   else ok = call_attn_task<false>(a, task_index, skip_wait, MEGA);
   return __builtin_amdgcn_readfirstlane((int)ok) != 0;
@@ -3594,7 +3601,7 @@ constexpr bool has_marks(int nb) { return nb == 1 || nb == 2 || nb == 9; }
 // Every task ahead-of-time: the worker walks its pre-enqueued list, each task waits for its own
 // event.  after_first_step: a task without producers (an embedding task) first waits for the
 // previous step's terminal event, i.e. for that step's sampling tasks.  Returns false on abort.
-template <int NB, bool MOE, bool MARKS>
+template <int NB, bool MOE, bool MARKS, bool SINGLE>
 __device__ __forceinline__ bool aot_pass(const StepArgs& a, uint32_t q0, uint32_t q1, float* lds, uint32_t* s_flag,
                                          bool after_first_step) {
   for (uint32_t qi = q0; qi < q1; ++qi) {
@@ -3619,8 +3626,10 @@ __device__ __forceinline__ bool aot_pass(const StepArgs& a, uint32_t q0, uint32_
         if (MARKS && mark_aborted()) mark_report((uint32_t)t.dep_event);
         return false;
       }
+    } else if (MOE && SINGLE && NB >= 4 && NB != 9 && t.kind == TK_MOE_EXPERT) {
+      if (!expert_task<NB == 9 ? 1 : NB, true>(a, t, ti, false, lds, s_flag)) return false;
     } else {
-      if (!call_task<true, MOE, MARKS>(a, t.kind, t.flags, ti, false)) return false;
+      if (!call_task<NB, true, MOE, MARKS>(a, t.kind, t.flags, ti, false)) return false;
     }
   }
   return true;
@@ -3695,7 +3704,7 @@ __global__ void __launch_bounds__(kThreads) mpk_loop_kernel(StepArgs a) {
     __syncthreads();   // (nobody is inside a task function any more)
     publish_args(a);
     __syncthreads();
-    if (!aot_pass<NB, MOE, false>(a, q0, q1, lds, s_flag, step > 0)) return;
+    if (!aot_pass<NB, MOE, false, false>(a, q0, q1, lds, s_flag, step > 0)) return;
   }
 }
 
@@ -3725,7 +3734,7 @@ __global__ void __launch_bounds__(kThreads) mpk_mega_kernel(StepArgs a) {
     // (a run of serving iterations issued as one launch per step: the launches behind the one
     // that found the server drained only settle their share of the event counters)
     if (RUN && __builtin_amdgcn_readfirstlane((int)serve_step_gate(a, q0, q1))) return;
-    aot_pass<NB, MOE, has_marks(NB)>(a, q0, q1, lds, s_flag, false);
+    aot_pass<NB, MOE, has_marks(NB), true>(a, q0, q1, lds, s_flag, false);
     return;
   }
   if constexpr (HYBRID) {
@@ -3753,11 +3762,11 @@ __global__ void __launch_bounds__(kThreads) mpk_mega_kernel(StepArgs a) {
           if (tjd.kind == TK_LINEAR) {
             debug_jitter(a, tj);
             if (run_linear<NB, true>(tjd, a, lds, -1, s_flag) != kLinDone) { r = kLinAbort; break; }
-          } else if (!call_task<true, MOE>(a, tjd.kind, tjd.flags, tj, true)) { r = kLinAbort; break; }
+          } else if (!call_task<NB, true, MOE>(a, tjd.kind, tjd.flags, tj, true)) { r = kLinAbort; break; }
         }
         if (r == kLinAbort) break;
       } else {
-        if (!call_task<true, MOE>(a, t.kind, t.flags, ti, true)) break;
+        if (!call_task<NB, true, MOE>(a, t.kind, t.flags, ti, true)) break;
       }
     }
     if (threadIdx.x == 0) __hip_atomic_store(as_global(a.g->wq_head + w), jit_head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3777,7 +3786,7 @@ __global__ void __launch_bounds__(kThreads) mpk_op_kernel(StepArgs a, uint32_t f
   if (t.kind == TK_LINEAR) {
     run_linear<NB, false>(t, a, lds, -1, nullptr);
   } else {
-    call_task<false, MOE>(a, t.kind, t.flags, ti, true);
+    call_task<NB, false, MOE>(a, t.kind, t.flags, ti, true);
   }
 }
 

@@ -272,6 +272,14 @@ constexpr uint32_t kMoeSwitchTiles = 8;   // (4: +1.5 % per step on the mixture-
 MPK_HOST_DEVICE inline void moe_task_share(uint32_t n_active, uint32_t tiles_per_expert, uint32_t n_tasks, uint32_t task,
                                            uint32_t* first, uint32_t* last) {
   const uint64_t period = (uint64_t)tiles_per_expert + kMoeSwitchTiles, cost = (uint64_t)n_active * period;
+  if (cost * n_tasks <= 0xFFFFFFFFull) {   // (any model there is.  A 64-bit division is a hundred instructions, and there are six)
+    const uint32_t p = (uint32_t)period, c = (uint32_t)cost;
+    const uint32_t x0 = c * task / n_tasks, x1 = c * (task + 1u) / n_tasks, q0 = x0 / p, q1 = x1 / p;
+    const uint32_t r0 = x0 - q0 * p, r1 = x1 - q1 * p;
+    *first = q0 * tiles_per_expert + (r0 < tiles_per_expert ? r0 : tiles_per_expert);
+    *last = q1 * tiles_per_expert + (r1 < tiles_per_expert ? r1 : tiles_per_expert);
+    return;
+  }
   const uint64_t x0 = cost * task / n_tasks, x1 = cost * ((uint64_t)task + 1u) / n_tasks;
   const uint64_t r0 = x0 % period, r1 = x1 % period;
   *first = (uint32_t)(x0 / period) * tiles_per_expert + (uint32_t)(r0 < tiles_per_expert ? r0 : tiles_per_expert);

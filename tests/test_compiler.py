@@ -504,3 +504,19 @@ def test_lds_of_attention_tasks(head_dim, grp, page, max_seq):
     terms = 2 if grp == 8 else 3
     floats = grp * head_dim + 8 * terms * grp * (head_dim + 4) + 16 * grp + 2 * head_dim + 24 + (max_seq // page if page else 0)
     assert host_graph(s, fusion=31, n_workers=256, **kw).stats()["lds_bytes"] == max(84 * 1024, 4 * (floats + 1024 + 48))
+
+
+@pytest.mark.parametrize("n_active,tiles,n_tasks", [(8, 96, 256), (1, 1, 1), (0, 96, 256), (128, 96, 256), (512, 16375, 512),
+                                                    (512, 16376, 512), (512, 16377, 512), (512, 1 << 20, 512)])
+def test_expert_shares_are_the_same_in_32_and_in_64_bits(n_active, tiles, n_tasks):
+    """The split is worked out in 32 bits where the products fit them (experts x (tiles + 8) x tasks up to
+    2^32 - 1: 512 experts of 16375 tiles for 512 tasks, not 16376), in 64 above: the same shares."""
+    from paper_2512_22219_amd.binding import moe_task_share
+    period = tiles + 8
+
+    def at(task):
+        q, r = divmod(n_active * period * task // n_tasks, period)
+        return q * tiles + min(r, tiles)
+
+    for task in range(n_tasks):
+        assert moe_task_share(n_active, tiles, n_tasks, task) == (at(task), at(task + 1))
