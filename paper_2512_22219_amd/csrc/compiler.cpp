@@ -704,7 +704,7 @@ static void choose_partitions(const mpk_model_config& c, const mpk_compile_optio
                               HostGraph& g) {
   const uint32_t W = o.n_workers;
   bool pages_likely = false;   // (page_plan looks more closely)
-  for (const auto& op : g.ops) pages_likely = pages_likely || (op.kind == MPK_OP_GATEUP && page_capable(c, o) && op.K <= 4096 && (uint64_t)op.cols * 2 >= 48ull * W);
+  for (const auto& op : g.ops) pages_likely = pages_likely || (op.kind == MPK_OP_GATEUP && page_capable(c, o) && op.K <= 4096 && (uint64_t)op.cols * 2 >= 48ull * lin_pack(op.K, op.cols * 2 / W) * W);
   auto after_attention = [&](const HostOp& op) {   // reads what attention tasks have merged
     for (const HostOp& p : g.ops)
       if (p.kind == MPK_OP_ATTN_PARTIAL && p.out_tensor == op.in_tensor) return true;
@@ -807,6 +807,10 @@ static void choose_partitions(const mpk_model_config& c, const mpk_compile_optio
         op.tc = 1;
     }
   }
+  // (the output head's tasks are packed where a layer's are; for it alone the set is not changed)
+  for (const auto& op : g.ops)
+    if (c.batch < kMfmaMinBatch && !c.n_experts && op.layer >= 0 && (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) &&
+        lin_pack(op.K, op.cols * ((op.flags & TF_GATEUP) ? 2u : 1u) / op.tc) > 1u) g.packed_rows = true;
   uint32_t base = 0;
   for (auto& op : g.ops) {
     op.task_base = base;
@@ -1296,7 +1300,7 @@ static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_comp
       const uint64_t cur_rows = (uint64_t)cur->cols * ((cur->flags & TF_GATEUP) ? 2u : 1u) / cur->tc;
       const uint64_t next_rows = (uint64_t)next->cols * ((next->flags & TF_GATEUP) ? 2u : 1u) / next->tc;
       if (cur_rows * cur->K * 2 > 256 * 1024) continue;
-      if (next->K > 4096 || next_rows < 48 || (next->flags & TF_SPLITK) || next->seg_tiles) continue;
+      if (next->K > 4096 || next_rows < 48 * (g.packed_rows ? lin_pack(next->K, (uint32_t)next_rows) : 1u) || (next->flags & TF_SPLITK) || next->seg_tiles) continue;
       if (lin_task_floats_b1(g, *cur) > room || lin_task_floats_b1(g, *next) > room) continue;
       plan[g.aot[qi]] |= TF_PAGE_NEXT;
       plan[g.aot[qi + 1]] |= TF_PAGE_READY;
@@ -1315,7 +1319,7 @@ static void apply_page_sizes(const std::vector<std::vector<uint8_t>>& ready, Hos
     const uint32_t n_ready = (uint32_t)std::count(ready[oi].begin(), ready[oi].end(), (uint8_t)1);
     if (n_ready == 0 || n_ready == op.tc) continue;          // all alike: the even split is right
     const uint32_t nu = op.cols / op.unit;
-    const uint32_t bonus = kLinPageUnits / ((op.flags & TF_GATEUP) ? 2u : 1u) / std::max(1u, op.unit);
+    const uint32_t bonus = kLinPageUnits * (g.packed_rows ? lin_pack(op.K, op.cols * ((op.flags & TF_GATEUP) ? 2u : 1u) / op.tc) : 1u) / ((op.flags & TF_GATEUP) ? 2u : 1u) / std::max(1u, op.unit);
     const uint64_t total = (uint64_t)nu + (uint64_t)bonus * (op.tc - n_ready);
     const uint32_t x = (uint32_t)(total / op.tc);            // size of a pre-loaded tile
     if (x <= bonus + 8) continue;

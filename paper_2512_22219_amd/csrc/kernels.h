@@ -261,6 +261,22 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return (__int_as_float(__builtin_amdgcn_readlane(u, 0)) + __int_as_float(__builtin_amdgcn_readlane(u, 16))) +
          (__int_as_float(__builtin_amdgcn_readlane(u, 32)) + __int_as_float(__builtin_amdgcn_readlane(u, 48)));
 }
+// Four sums at once: every lane of the wavefront's row r of 16 lanes gets the sum of value 0, 2, 1, 3 for r = 0, 1, 2, 3
+// (halves of two values, then rows of two such pairs, put side by side by a swap and added).
+__device__ __forceinline__ float wave_sum4(float v0, float v1, float v2, float v3) {
+  auto swap_add = [](auto sw) { return __uint_as_float(sw[0]) + __uint_as_float(sw[1]); };
+  const float a = swap_add(__builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false));
+  const float b = swap_add(__builtin_amdgcn_permlane32_swap(__float_as_uint(v2), __float_as_uint(v3), false, false));
+  float v = swap_add(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+  auto dpp = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  v += dpp(v, std::integral_constant<int, 0xB1>{});
+  v += dpp(v, std::integral_constant<int, 0x4E>{});
+  v += dpp(v, std::integral_constant<int, 0x141>{});
+  v += dpp(v, std::integral_constant<int, 0x140>{});
+  return v;
+}
 // ... and the largest / smallest value of the wavefront the same way
 template <class Op>
 __device__ __forceinline__ uint32_t wave_reduce_dpp(uint32_t v, Op op) {
@@ -547,91 +563,136 @@ __device__ __forceinline__ void ring_clear(HalfRing& ring) {
     for (int u = 0; u < kRingStages; ++u) ring.s[i][u] = u32x4{0, 0, 0, 0};
 }
 
+// Short rows are packed: with K <= 2048 (1024) inputs, two (four) weight rows share one of the half block's
+// rows, four (two) stages each, and the staged input is in LDS as often, so that loads and multiplies are
+// those of one row of 4096.  (A row of 2048 alone left half of every half block's loads to repeat its last 16 bytes.)
+// The sums are kept apart per two stages and put together at the end of a row.  us a step: 1B class at batch 1 702 ->
+// 630 (gate/up phase of a layer 15.2 -> 11.8 us), 2B class at batch 2, four tokens 2190 -> 2135.
+//
+// A kernel set of its own for models with packed tasks: where none is, the choice costs every task 0.3 us (8B at
+// batch 1 2736 -> 2789 us a step, tiny model 42.0 -> 44.7).
+//
 // Wavefront-uniform view of one linear task for one wavefront.
+template <bool PACKED>
 struct LinGeom {
   const uint16_t* W;
   uint32_t K, c0, F, gateup;
   uint32_t r0, r1;    // ring rows [r0, r1) of this wavefront within the task
   uint32_t nseg;      // segments per row
+  uint32_t packed;    // weight rows per row of a half block: 1, 2 or 4
+  __device__ __forceinline__ uint32_t pack() const { return PACKED ? packed : 1u; }
 };
 
-__device__ __forceinline__ LinGeom lin_geom(const TaskDesc& t, uint32_t wave) {
-  LinGeom g;
+template <bool PACKED>
+__device__ __forceinline__ LinGeom<PACKED> lin_geom(const TaskDesc& t, uint32_t wave) {
+  LinGeom<PACKED> g;
+
   g.W = (const uint16_t*)t.w;
   g.K = t.K;
   g.c0 = t.c0;
   g.F = t.p0;
   g.gateup = (t.flags & TF_GATEUP) ? 1u : 0u;
   const uint32_t R = (t.c1 - t.c0) << g.gateup;
+  g.packed = PACKED ? lin_pack(t.K, R) : 1u;
   constexpr uint32_t NW = kThreads / 64;
-  // rows are dealt in pairs (a half block holds two; a (gate, up) pair stays in one wavefront):
-  // every wavefront gets floor(pairs / 8) of them and the first pairs % 8 wavefronts one more, so
+  // rows are dealt in pairs, packed ones in fours or eights (a half block holds as many; a (gate, up) pair stays in
+  // one wavefront): every wavefront gets floor(pairs / 8) of them and the first pairs % 8 wavefronts one more, so
   // that a tile of any size -- tiles sized by worker speed are seldom multiples of 16 rows --
   // loads the wavefronts to within one pair of each other
-  const uint32_t P = (R + 1u) / 2u, base = P / NW, extra = P % NW;
+  const uint32_t per = 2u * g.pack(), psh = g.pack() == 4u ? 3u : g.pack();   // (per = 1 << psh)
+  const uint32_t P = (R + per - 1u) >> psh, base = P / NW, extra = P % NW;
   const uint32_t p0 = wave * base + min(wave, extra), p1 = p0 + base + (wave < extra ? 1u : 0u);
-  g.r0 = min(2u * p0, R);
-  g.r1 = min(2u * p1, R);
+  g.r0 = min(per * p0, R);
+  g.r1 = min(per * p1, R);
   g.nseg = (t.K + kSegLen - 1u) / kSegLen;
   return g;
 }
 
-// Position of a wavefront in its sequence of half blocks: rows [row0, row0 + 2) x segment `seg`,
+// Position of a wavefront in its sequence of half blocks: rows [row0, row0 + 2 pack) x segment `seg`,
 // segments of a pair first.  Two of them walk the sequence: one requests, one consumes.
 struct LinCursor {
   uint32_t row0, seg;
 };
-__device__ __forceinline__ bool lin_valid(const LinGeom& g, const LinCursor& c) { return c.row0 < g.r1; }
-__device__ __forceinline__ void lin_advance(const LinGeom& g, LinCursor& c) {
+template <bool PACKED>
+__device__ __forceinline__ bool lin_valid(const LinGeom<PACKED>& g, const LinCursor& c) { return c.row0 < g.r1; }
+template <bool PACKED>
+__device__ __forceinline__ void lin_advance(const LinGeom<PACKED>& g, LinCursor& c) {
   if (++c.seg == g.nseg) {
     c.seg = 0;
-    c.row0 += kHalfRows;
+    c.row0 += kHalfRows * g.pack();
   }
 }
 
-// The half block at a cursor.
+// The half block at a cursor.  Weight row s (below pack) of half-block row i: without gate/up ring row row0 + i pack + s;
+// with it row0 + 2 s + i, so that i = 0 are gate rows and i = 1 their up rows.  Either way the weight rows of a
+// half-block row follow one another in memory.
 struct LinHalf {
-  const uint16_t* p[kHalfRows];   // row start + segment start (a second row past the end repeats the first)
-  uint32_t row0, nrows, seg, seglen;
+  const uint16_t* p[kHalfRows];   // weight row 0, segment start (a half-block row without any repeats the first)
+  uint32_t n[kHalfRows];          // weight rows there are (at least 1)
+  uint32_t row0, nrows, seg, seglen;   // (nrows: ring rows, of unpacked ones)
 };
 
-__device__ __forceinline__ LinHalf lin_half(const LinGeom& g, const LinCursor& c) {
+template <bool PACKED>
+__device__ __forceinline__ LinHalf lin_half(const LinGeom<PACKED>& g, const LinCursor& c) {
   LinHalf B;
   B.seg = c.seg;
   B.row0 = c.row0;
-  B.nrows = min(g.r1 - c.row0, (uint32_t)kHalfRows);
   B.seglen = min(kSegLen, g.K - c.seg * kSegLen);
+  const uint32_t left = g.r1 - c.row0;   // ring rows
+  B.nrows = min(left, (uint32_t)kHalfRows);
 #pragma unroll
   for (int i = 0; i < kHalfRows; ++i) {
-    const uint32_t r = B.row0 + min((uint32_t)i, B.nrows - 1u);
-    const uint32_t wrow = g.gateup ? (g.c0 + (r >> 1) + ((r & 1u) ? g.F : 0u)) : g.c0 + r;
+    uint32_t wrow;
+    if constexpr (!PACKED) {
+      const uint32_t r = c.row0 + min((uint32_t)i, B.nrows - 1u);
+      wrow = g.gateup ? (g.c0 + (r >> 1) + ((r & 1u) ? g.F : 0u)) : g.c0 + r;
+      B.n[i] = 1u;
+    } else if (g.gateup) {   // (pairs are never cut: left is even)
+      wrow = g.c0 + (c.row0 >> 1) + (i ? g.F : 0u);
+      B.n[i] = min(g.pack(), left >> 1);
+    } else {
+      const bool there = left > (uint32_t)i * g.pack();
+      wrow = g.c0 + c.row0 + (there ? (uint32_t)i * g.pack() : 0u);
+      B.n[i] = min(g.pack(), there ? left - (uint32_t)i * g.pack() : left);
+    }
     B.p[i] = g.W + (size_t)wrow * g.K + c.seg * kSegLen;
   }
   return B;
 }
 
-// Requests a half block, stage by stage.  Lanes past the end of a short segment re-read its last
-// 16 bytes (the staged input is zero there), so every lane takes part in every load.
-__device__ __forceinline__ void lin_request(const LinHalf& B, HalfRing& ring, int lane) {
-  if (B.seglen == kSegLen) {   // full segment: one base address per row, constant stage offsets
+// This lane's element of stage u of half-block row i: past the end of a short segment (or of a packed row) the row's last
+// 16 bytes (the staged input is zero there), for a weight row that does not exist the last one that does -- so every
+// lane takes part in every load.
+template <bool PACKED>
+__device__ __forceinline__ const uint16_t* lin_lane(const LinGeom<PACKED>& g, const LinHalf& B, int i, int u, int lane) {
+  const uint32_t sh = g.pack() == 1u ? 3u : (g.pack() == 2u ? 2u : 1u);   // 1 << sh stages a weight row
+  const uint32_t o = min(((uint32_t)u & ((1u << sh) - 1u)) * 512u + (uint32_t)lane * 8u, B.seglen - 8u);
+  return B.p[i] + min((uint32_t)u >> sh, B.n[i] - 1u) * g.K + o;
+}
+template <bool PACKED>
+__device__ __forceinline__ bool lin_full(const LinGeom<PACKED>& g, const LinHalf& B) {   // 4096 inputs in a row of memory, twice
+  return B.seglen * g.pack() == kSegLen && B.n[0] == g.pack() && B.n[1] == g.pack();
+}
+// Requests a half block, stage by stage.
+template <bool PACKED>
+__device__ __forceinline__ void lin_request(const LinGeom<PACKED>& g, const LinHalf& B, HalfRing& ring, int lane) {
+  if (lin_full(g, B)) {   // one base address per row, constant stage offsets
 #pragma unroll
     for (int u = 0; u < kRingStages; ++u)
 #pragma unroll
       for (int i = 0; i < kHalfRows; ++i) ring.s[i][u] = ld_stream16(B.p[i] + lane * 8 + u * 512);
   } else {
 #pragma unroll
-    for (int u = 0; u < kRingStages; ++u) {
-      const uint32_t o = min((uint32_t)u * 512u + (uint32_t)lane * 8u, B.seglen - 8u);
+    for (int u = 0; u < kRingStages; ++u)
 #pragma unroll
-      for (int i = 0; i < kHalfRows; ++i) ring.s[i][u] = ld_stream16(B.p[i] + o);
-    }
+      for (int i = 0; i < kHalfRows; ++i) ring.s[i][u] = ld_stream16(lin_lane(g, B, i, u, lane));
   }
 }
 
 // Adds the half block's partial dot products to acc.
-template <int NB>
+template <int NB, int NG>   // NG: sums per half-block row, of 8 / NG stages each
 __device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ring, const float* xs, uint32_t Kp,
-                                            int lane, float (&acc)[kHalfRows][NB]) {
+                                            int lane, float (&acc)[kHalfRows][NG][NB]) {
 #pragma unroll
   for (int u = 0; u < kRingStages; ++u) {
 #pragma unroll
@@ -639,7 +700,7 @@ __device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ri
       const float4* xp = (const float4*)(xs + (size_t)b * Kp + B.seg * kSegLen + u * 512 + lane * 8);
       const float4 x0 = xp[0], x1 = xp[1];
 #pragma unroll
-      for (int i = 0; i < kHalfRows; ++i) acc[i][b] = dot8(ring.s[i][u], x0, x1, acc[i][b]);
+      for (int i = 0; i < kHalfRows; ++i) acc[i][u * NG / kRingStages][b] = dot8(ring.s[i][u], x0, x1, acc[i][u * NG / kRingStages][b]);
     }
   }
 }
@@ -649,18 +710,18 @@ __device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ri
 // [row 0..1][stage 0..7][lane] x 16 bytes.  The loads go from device memory straight into LDS (no
 // registers), so a page can be filled by one task and consumed by the worker's next one.
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
-__device__ __forceinline__ void lin_request_page(const LinHalf& B, u32x4* page, int lane) {
+template <bool PACKED>
+__device__ __forceinline__ void lin_request_page(const LinGeom<PACKED>& g, const LinHalf& B, u32x4* page, int lane) {
 #pragma unroll
   for (int u = 0; u < kRingStages; ++u) {
-    const uint32_t o = min((uint32_t)u * 512u + (uint32_t)lane * 8u, B.seglen - 8u);
 #pragma unroll
     for (int i = 0; i < kHalfRows; ++i)
-      __builtin_amdgcn_global_load_lds(as_global((const u32x4*)(B.p[i] + o)), (lds_ptr_t)(page + (i * kRingStages + u) * 64), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(as_global((const u32x4*)lin_lane(g, B, i, u, lane)), (lds_ptr_t)(page + (i * kRingStages + u) * 64), 16, 0, 0);
   }
 }
-template <int NB>
+template <int NB, int NG>
 __device__ __forceinline__ void lin_consume_page(const LinHalf& B, const u32x4* page, const float* xs, uint32_t Kp,
-                                                 int lane, float (&acc)[kHalfRows][NB]) {
+                                                 int lane, float (&acc)[kHalfRows][NG][NB]) {
 #pragma unroll
   for (int u = 0; u < kRingStages; ++u) {
 #pragma unroll
@@ -668,7 +729,8 @@ __device__ __forceinline__ void lin_consume_page(const LinHalf& B, const u32x4* 
       const float4* xp = (const float4*)(xs + (size_t)b * Kp + B.seg * kSegLen + u * 512 + lane * 8);
       const float4 x0 = xp[0], x1 = xp[1];
 #pragma unroll
-      for (int i = 0; i < kHalfRows; ++i) acc[i][b] = dot8(page[(i * kRingStages + u) * 64 + lane], x0, x1, acc[i][b]);
+      for (int i = 0; i < kHalfRows; ++i)
+        acc[i][u * NG / kRingStages][b] = dot8(page[(i * kRingStages + u) * 64 + lane], x0, x1, acc[i][u * NG / kRingStages][b]);
     }
   }
 }
@@ -773,7 +835,7 @@ __device__ __forceinline__ uint32_t linear_wait(const StepArgs& a, int32_t wait_
 //
 // Runs task `t`.  wait_ev >= 0: wait for that event first (persistent kernel).  Returns whether
 // the step is still alive (false: watchdog / abort).
-template <int NB, bool MEGA, class Svc = NoJit, bool DEEP = false>
+template <int NB, bool MEGA, class Svc = NoJit, bool DEEP = false, bool PACKED = false>
 __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
                                                 uint32_t* s_flag, const Svc& svc = Svc{}, uint32_t next_ti = 0) {
   // Batch 1: what is worked out from the lane number is worked out again in every task.  Otherwise the compiler
@@ -796,7 +858,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   float* outbuf = xs + (size_t)NB * Kp;              // [rows_max][NB]
   float* res_lds = outbuf + (size_t)rows_max * NB;   // [rows_max][NB]
   float* ssq = res_lds + (size_t)rows_max * NB;      // [8][NB]
-  const LinGeom g = lin_geom(t, wave);
+  constexpr int NG = PACKED ? 4 : 1;
+  const auto g = lin_geom<PACKED>(t, wave);
   HalfRing h0, h1;   // local to the task: nothing is live around the task loop, so they stay in registers
   ring_clear(h0);
   ring_clear(h1);
@@ -859,7 +922,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // (the waits are builtins, one on each path: the compiler's own count of the loads in flight does not survive the
   // branches around the requests)
   if (preload && lin_valid(g, rq)) {
-    lin_request(lin_half(g, rq), h0, lane);
+    lin_request(g, lin_half(g, rq), h0, lane);
     lin_advance(g, rq);
     asm volatile("; first half block requested" ::: "memory");
     if (in_marked) wait_vmem<2 * kRingStages>();
@@ -872,7 +935,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   }
   const bool two = preload && lin_valid(g, rq);
   if (two) {
-    lin_request(lin_half(g, rq), h1, lane);
+    lin_request(g, lin_half(g, rq), h1, lane);
     lin_advance(g, rq);
     asm volatile("; second half block requested" ::: "memory");
   }
@@ -888,7 +951,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     ring_clear(h2);
     three = preload && lin_valid(g, rq);
     if (three) {
-      lin_request(lin_half(g, rq), h2, lane);
+      lin_request(g, lin_half(g, rq), h2, lane);
       lin_advance(g, rq);
       asm volatile("; third half block requested" ::: "memory");
     }
@@ -903,9 +966,9 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     // this task is short and has a long wait ahead: the first half block of every wavefront's
     // share of the worker's NEXT task goes into the pages now, two tasks ahead of its use
     const TaskDesc tn = ld_task(a, next_ti);
-    const LinGeom gn = lin_geom(tn, wave);
+    const auto gn = lin_geom<PACKED>(tn, wave);
     const LinCursor cn{gn.r0, 0u};
-    if (lin_valid(gn, cn)) lin_request_page(lin_half(gn, cn), page, lane);
+    if (lin_valid(gn, cn)) lin_request_page(gn, lin_half(gn, cn), page, lane);
   }
   // ---- dependent event: wavefront 0 polls, the others wait at the barrier
   if (wait_ev >= 0) {
@@ -917,17 +980,17 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   trace_mark(a, t, 1);
   if (!preload) {   // pre-loading switched off: the first requests go out only now
     if (lin_valid(g, rq)) {
-      lin_request(lin_half(g, rq), h0, lane);
+      lin_request(g, lin_half(g, rq), h0, lane);
       lin_advance(g, rq);
       asm volatile("; first half block requested after the event" ::: "memory");
     }
     if (lin_valid(g, rq)) {
-      lin_request(lin_half(g, rq), h1, lane);
+      lin_request(g, lin_half(g, rq), h1, lane);
       lin_advance(g, rq);
       asm volatile("; second half block requested after the event" ::: "memory");
     }
     if (kThird && lin_valid(g, rq)) {
-      lin_request(lin_half(g, rq), h2, lane);
+      lin_request(g, lin_half(g, rq), h2, lane);
       lin_advance(g, rq);
       asm volatile("; third half block requested after the event" ::: "memory");
     }
@@ -961,7 +1024,11 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
           ss[b] = fmaf(v.x, v.x, ss[b]); ss[b] = fmaf(v.y, v.y, ss[b]); ss[b] = fmaf(v.z, v.z, ss[b]); ss[b] = fmaf(v.w, v.w, ss[b]);
           v.x *= gn[0]; v.y *= gn[1]; v.z *= gn[2]; v.w *= gn[3];
         }
-        if (i < Kp) *(float4*)(xs + (size_t)b * Kp + i) = v;
+        if (g.pack() == 1u) {
+          if (i < Kp) *(float4*)(xs + (size_t)b * Kp + i) = v;
+        } else if (i < kSegLen / g.pack()) {   // (zeros past the input's end)
+          for (uint32_t s = 0; s < kSegLen; s += kSegLen / g.pack()) *(float4*)(xs + (size_t)b * Kp + s + i) = v;
+        }
       }
     }
   }
@@ -993,52 +1060,78 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   trace_mark(a, t, 2);
   // ---- stream this wavefront's rows: the two buffers in turn
   {
-    float acc[kHalfRows][NB];
+    float acc[kHalfRows][NG][NB];
 #pragma unroll
     for (int i = 0; i < kHalfRows; ++i)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) acc[i][b] = 0.f;
-    // the pair of rows is complete with its last segment: reduce across lanes, results to LDS
+      for (int q = 0; q < NG; ++q)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[i][q][b] = 0.f;
+    // the rows are complete with their last segment: reduce across lanes, results to LDS
     auto finish = [&](const LinHalf& B) {
-      if (B.seg + 1 == g.nseg) {
+      if (B.seg + 1 != g.nseg) return;
+      if (g.pack() == 1u) {
 #pragma unroll
         for (int i = 0; i < kHalfRows; ++i)
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
-            const float v = wave_sum_dpp(acc[i][b]);
+            float v = acc[i][0][b];
+            if constexpr (PACKED) v = (v + acc[i][1][b]) + (acc[i][2][b] + acc[i][3][b]);
+            v = wave_sum_dpp(v);
             if (lane == 0 && (uint32_t)i < B.nrows) outbuf[(size_t)(B.row0 + i) * NB + b] = v;
-            acc[i][b] = 0.f;
           }
+      } else if constexpr (PACKED) {
+        auto out4 = [&](float v, uint32_t i, uint32_t q, int b) {   // (a row of 16 lanes has sum q of half-block row i)
+          const uint32_t s = g.pack() == 2u ? q >> 1 : q, r = B.row0 + (g.gateup ? 2u * s + i : i * g.pack() + s);
+          if ((lane & 15) == 0 && r < g.r1) outbuf[(size_t)r * NB + b] = v;
+        };
+        const uint32_t row = (uint32_t)lane >> 4, k = (row >> 1) | ((row & 1u) << 1);   // the row has value k of a wave_sum4
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          if (g.pack() == 2u) {
+            out4(wave_sum4(acc[0][0][b] + acc[0][1][b], acc[0][2][b] + acc[0][3][b], acc[1][0][b] + acc[1][1][b], acc[1][2][b] + acc[1][3][b]),
+                 k >> 1, 2u * (k & 1u), b);
+          } else {
+            out4(wave_sum4(acc[0][0][b], acc[0][1][b], acc[0][2][b], acc[0][3][b]), 0u, k, b);
+            out4(wave_sum4(acc[1][0][b], acc[1][1][b], acc[1][2][b], acc[1][3][b]), 1u, k, b);
+          }
+        }
       }
+#pragma unroll
+      for (int i = 0; i < kHalfRows; ++i)
+#pragma unroll
+        for (int q = 0; q < NG; ++q)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) acc[i][q][b] = 0.f;
     };
     LinCursor cs{g.r0, 0u};
     if (page_ready && lin_valid(g, cs)) {   // (requested a whole task ago: long since landed)
       const LinHalf B = lin_half(g, cs);
-      lin_consume_page<NB>(B, page, xs, Kp, lane, acc);
+      lin_consume_page<NB, NG>(B, page, xs, Kp, lane, acc);
       finish(B);
       lin_advance(g, cs);
     }
     while (lin_valid(g, cs)) {
       {
         const LinHalf B = lin_half(g, cs);
-        lin_consume<NB>(B, h0, xs, Kp, lane, acc);
+        lin_consume<NB, NG>(B, h0, xs, Kp, lane, acc);
         finish(B);
         lin_advance(g, cs);
       }
       if (lin_valid(g, rq)) {
-        lin_request(lin_half(g, rq), h0, lane);
+        lin_request(g, lin_half(g, rq), h0, lane);
         lin_advance(g, rq);
         asm volatile("; first buffer requested again" ::: "memory");
       }
       if (!lin_valid(g, cs)) break;
       {
         const LinHalf B = lin_half(g, cs);
-        lin_consume<NB>(B, h1, xs, Kp, lane, acc);
+        lin_consume<NB, NG>(B, h1, xs, Kp, lane, acc);
         finish(B);
         lin_advance(g, cs);
       }
       if (lin_valid(g, rq)) {
-        lin_request(lin_half(g, rq), h1, lane);
+        lin_request(g, lin_half(g, rq), h1, lane);
         lin_advance(g, rq);
         asm volatile("; second buffer requested again" ::: "memory");
       }
@@ -1046,12 +1139,12 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         if (!lin_valid(g, cs)) break;
         {
           const LinHalf B = lin_half(g, cs);
-          lin_consume<NB>(B, h2, xs, Kp, lane, acc);
+          lin_consume<NB, NG>(B, h2, xs, Kp, lane, acc);
           finish(B);
           lin_advance(g, cs);
         }
         if (lin_valid(g, rq)) {
-          lin_request(lin_half(g, rq), h2, lane);
+          lin_request(g, lin_half(g, rq), h2, lane);
           lin_advance(g, rq);
           asm volatile("; third buffer requested again" ::: "memory");
         }
@@ -3114,6 +3207,7 @@ __device__ __forceinline__ void body_serve(const StepArgs& a) {
 // NB, the batch class, pins the linear body of a kernel: a kernel that carries a single one keeps its
 // register allocation (nearly) free of spills, one that decides between them at run time does not.
 //   1: one row, vector body; 9: one row, large tasks: three weight buffers; 2: two rows, vector body;
+//   11, 12: one and two rows, vector body, short weight rows packed (see LinGeom);
 //   4, 8, 16: up to that many rows, matrix cores -- a kernel for each packing of the input terms (in one kernel
 //   for all the three bodies had 398 to 431 spilled scalar registers)
 template <int NB, bool MEGA, class Svc = NoJit>
@@ -3121,6 +3215,7 @@ __device__ __forceinline__ uint32_t run_linear(const TaskDesc& t, const StepArgs
                                            uint32_t* s_flag, const Svc& svc = Svc{}, uint32_t next_ti = 0) {
   if constexpr (NB == 4 || NB == 8 || NB == 16) return linear_task_mfma<NB == 4 ? 3 : NB == 8 ? 2 : 1, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc);
   else if constexpr (NB == 9) return linear_task<1, MEGA, Svc, true>(t, a, lds, wait_ev, s_flag, svc, next_ti);
+  else if constexpr (NB == 11 || NB == 12) return linear_task<NB - 10, MEGA, Svc, false, true>(t, a, lds, wait_ev, s_flag, svc, next_ti);
   else return linear_task<NB, MEGA, Svc>(t, a, lds, wait_ev, s_flag, svc, next_ti);
 }
 
@@ -3596,7 +3691,7 @@ __device__ __forceinline__ uint32_t pick_task(const StepArgs& a, uint32_t* ctrl,
 }
 
 // Batch classes whose kernels run marked descriptors.
-constexpr bool has_marks(int nb) { return nb == 1 || nb == 2 || nb == 9; }
+constexpr bool has_marks(int nb) { return nb == 1 || nb == 2 || nb == 9 || nb == 11 || nb == 12; }
 
 // Every task ahead-of-time: the worker walks its pre-enqueued list, each task waits for its own
 // event.  after_first_step: a task without producers (an embedding task) first waits for the
@@ -3626,7 +3721,7 @@ __device__ __forceinline__ bool aot_pass(const StepArgs& a, uint32_t q0, uint32_
         if (MARKS && mark_aborted()) mark_report((uint32_t)t.dep_event);
         return false;
       }
-    } else if (MOE && SINGLE && NB >= 4 && NB != 9 && t.kind == TK_MOE_EXPERT) {
+    } else if (MOE && SINGLE && !has_marks(NB) && t.kind == TK_MOE_EXPERT) {
       if (!expert_task<NB == 9 ? 1 : NB, true>(a, t, ti, false, lds, s_flag)) return false;
     } else {
       if (!call_task<NB, true, MOE, MARKS>(a, t.kind, t.flags, ti, false)) return false;
@@ -3805,8 +3900,8 @@ struct KernelVariant {
 // index, batch class, mixture of experts
 #define MPK_VARIANT_LIST(X) \
   X(0, 1, false) X(1, 9, false) X(2, 2, false) X(3, 4, false) X(4, 8, false) X(5, 16, false) \
-  X(6, 1, true) X(7, 2, true) X(8, 4, true) X(9, 8, true) X(10, 16, true)
-constexpr int kNumVariants = 11;
+  X(6, 1, true) X(7, 2, true) X(8, 4, true) X(9, 8, true) X(10, 16, true) X(11, 11, false) X(12, 12, false)
+constexpr int kNumVariants = 13;
 #define MPK_DECLARE_VARIANT(I, N, M) const KernelVariant* kernel_variant_##I();
 MPK_VARIANT_LIST(MPK_DECLARE_VARIANT)
 #undef MPK_DECLARE_VARIANT

@@ -229,6 +229,7 @@ struct HostGraph {
   uint32_t n_group_counters_attn = 0, n_splitk_counters = 0;
   uint32_t n_hier_events = 0;
   uint32_t lin_rows_max = 0;       // largest weight-row count of one linear task (gate/up pairs twice)
+  bool packed_rows = false;        // some operator of a layer has tasks with packed weight rows (lin_pack)
   uint32_t lin_page_off = 0;       // float offset (in the task area of the LDS) of the pre-load pages, 0 = none
   std::vector<size_t> moe_meta_offset;   // per MoE layer: float offset of its meta-tensor in the arena
   std::vector<double> inv_freq;    // RoPE frequencies theta^(-2i/d), i < d/2
@@ -324,6 +325,10 @@ constexpr uint32_t attn_lds_floats(uint32_t d, uint32_t grp) {
   const uint32_t waves = kThreads / 64u;
   return grp * d + waves * attn_term_groups(grp) * grp * (d + 4u) + waves * grp * 2u + 2u * d + 8u + 16u;
 }
+// Weight rows (gate/up pairs count twice) that share one of the two 4096-input rows of a half block of the vector linear
+// body in a task of `rows`, see LinGeom.  Only where every wavefront then still has a half block: with fewer rows the
+// sums of a row at a time over all wavefronts are what the task is made of.
+constexpr uint32_t lin_pack(uint32_t K, uint32_t rows) { return K <= 1024u && rows >= 64u ? 4u : (K <= 2048u && rows >= 32u ? 2u : 1u); }
 // Pre-load pages in LDS (paper Section 5.3: shared-memory pages hold data pre-loaded for a task that
 // has not started): one page of 16 KB per wavefront = one half block of the vector linear body.
 constexpr uint32_t kLinPageFloats = 4096, kLinPagesFloats = 8 * kLinPageFloats;

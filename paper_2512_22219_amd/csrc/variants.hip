@@ -59,4 +59,11 @@ MPK_DEFINE_VARIANT(9)
 #if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 10
 MPK_DEFINE_VARIANT(10)
 #endif
+#if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 11
+MPK_DEFINE_VARIANT(11)
+#endif
+#if !defined(MPK_VARIANT_INDEX) || MPK_VARIANT_INDEX == 12
+MPK_DEFINE_VARIANT(12)
+#endif
+
 }  // namespace mpk
