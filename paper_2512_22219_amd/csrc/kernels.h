@@ -744,7 +744,8 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-__device__ __forceinline__ void signal_from_wave0(const StepArgs& a, const TaskDesc& t, int32_t e, int lane);
+__device__ __forceinline__ void signal_from_wave0(const StepArgs& a, const TaskDesc& t, int lane);
+__device__ __forceinline__ void notify_task(const StepArgs& a, const TaskDesc& t);
 __device__ __forceinline__ void notify_event(const StepArgs& a, int32_t e);
 __device__ __forceinline__ void poll_event_wave0(const StepArgs& a, int32_t e, uint32_t* s_flag, int lane);
 __device__ __forceinline__ void poll_event_or_jit_wave0(const StepArgs& a, int32_t e, uint32_t* s_flag, int lane, uint32_t jit_head);
@@ -1201,7 +1202,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     // measured too: 0.6 % slower per step on the 8B shape.)
     lds_barrier();
     if (wave == 0) {
-      if (t.trig_event >= 0 && lane == 0) notify_event(a, t.trig_event);
+      if (t.trig_event >= 0 && lane == 0) notify_task(a, t);
       trace_mark(a, t, 4);
     }
   }
@@ -1769,7 +1770,7 @@ __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const St
     lds_barrier();
   }
   if (wave == 0) {
-    if (MEGA && t.trig_event >= 0) signal_from_wave0(a, t, t.trig_event, lane);
+    if (MEGA && t.trig_event >= 0) signal_from_wave0(a, t, lane);
     trace_mark(a, t, 4);
   }
   lds_barrier();   // the partial buffer is reused by the next task
@@ -3350,14 +3351,26 @@ __device__ __forceinline__ void notify_event(const StepArgs& a, int32_t e) {
   }
 }
 
-__device__ __forceinline__ void signal_event(const StepArgs& a, const TaskDesc& t, int32_t e) {
+// One lane: a task's notification.  Where the descriptor names the counter (a task with a worker of its own, no scheduler
+// to tell), the event's record is not looked at: two dependent scalar reads less between the stores'
+// acknowledgement and the notification.
+__device__ __forceinline__ void notify_task(const StepArgs& a, const TaskDesc& t) {
+  if (t.twin > 0 && !(t.flags & TF_OUT_MARKED)) {
+    if ((a.flags & kLoseNotifyBit) && blockIdx.x == 0) return;
+    __hip_atomic_fetch_add(as_global(a.hier + (uint32_t)t.twin - 1u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    notify_event(a, t.trig_event);
+  }
+}
+
+__device__ __forceinline__ void signal_event(const StepArgs& a, const TaskDesc& t) {
   // every wavefront waits until its own agent-scope stores have completed at the coherence point
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   drain_vmem();
   trace_mark(a, t, 6);
   __syncthreads();
   trace_mark(a, t, 7);
-  if (threadIdx.x == 0) notify_event(a, e);
+  if (threadIdx.x == 0) notify_task(a, t);
 }
 
 // Wavefront 0 only: like poll_event_wave0, but also watches the worker's just-in-time queue.
@@ -3389,11 +3402,11 @@ __device__ __forceinline__ void poll_event_or_jit_wave0(const StepArgs& a, int32
 
 // Wavefront 0 only, after a workgroup barrier: wait for this wavefront's own coherent stores,
 // then notify the event.
-__device__ __forceinline__ void signal_from_wave0(const StepArgs& a, const TaskDesc& t, int32_t e, int lane) {
+__device__ __forceinline__ void signal_from_wave0(const StepArgs& a, const TaskDesc& t, int lane) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   drain_vmem();
   trace_mark(a, t, 7);
-  if (lane == 0) notify_event(a, e);
+  if (lane == 0) notify_task(a, t);
 }
 
 // The first 192 bytes of the dynamic LDS are control words ([0] = result of the last event wait;
@@ -3448,7 +3461,7 @@ __device__ __forceinline__ bool expert_task(const StepArgs& a, const TaskDesc& t
   if (!body_moe_expert<NB>(t, a, lds, wait_ev, s_flag)) return false;
   if (MEGA) {
     trace_mark(a, t, 3);
-    if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
+    if (t.trig_event >= 0) signal_event(a, t);
     else __syncthreads();
     trace_mark(a, t, 4);
   }
@@ -3487,7 +3500,7 @@ __device__ __noinline__ bool run_other_task(uint32_t task_index, bool skip_wait)
   if (!run_task<MOE>(t, a, lds, wait_ev, s_flag)) return false;
   if (MEGA) {
     trace_mark(a, t, 3);
-    if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
+    if (t.trig_event >= 0) signal_event(a, t);
     else __syncthreads();
     trace_mark(a, t, 4);
   }
@@ -3520,7 +3533,7 @@ __device__ __noinline__ bool run_attn_task(uint32_t task_index, bool skip_wait, 
   if (!body_attn_mfma<D, GRP, PAGED, MARKED>(t, a, lds, wait_ev, s_flag)) return false;
   if (signal) {
     trace_mark(a, t, 3);
-    if (t.trig_event >= 0) signal_event(a, t, t.trig_event);
+    if (t.trig_event >= 0) signal_event(a, t);
     else lds_barrier();
     trace_mark(a, t, 4);
   }

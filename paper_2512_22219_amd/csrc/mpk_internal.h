@@ -91,7 +91,8 @@ struct alignas(16) TaskDesc {
   void* aux1;               // V cache of the layer
   uint32_t index;           // own index in the linearized task list
   int32_t twin;             // TF_OUT_MARKED: from a word of the output to the same word of the other copy, in
-                            // 64-float units (0: there is no other copy)
+                            // 64-float units (0: there is no other copy).  Other tasks: 1 + the word of the sharded
+                            // counters that their notification adds to (0: see the event's record)
 };
 static_assert(sizeof(TaskDesc) == 128, "TaskDesc must stay 128 bytes");
 

@@ -342,6 +342,17 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     }
   };
   relocate(descs, reloc);
+  // the counter a task with a fixed worker adds to: its producer group's of the event it triggers
+  auto name_counters = [&](std::vector<TaskDesc>& d) {
+    for (size_t i = 0; i < d.size(); ++i) {
+      if (d[i].trig_event < 0 || (d[i].flags & TF_OUT_MARKED) || h.tasks[i].worker < 0) continue;
+      const EventDesc& ev = h.events[d[i].trig_event];
+      if ((ev.flags & (EV_HIER | EV_JIT)) != EV_HIER) continue;
+      const uint64_t word = (uint64_t)ev.hier_slot * kHierWordsPerEvent + (1u + (uint32_t)h.tasks[i].worker % kShards) * kHierStrideWords;
+      if (word < INT32_MAX) d[i].twin = (int32_t)word + 1;
+    }
+  };
+  name_counters(descs);
   // ... and the descriptors of the launches that use marked tensors, one set per copy of those
   if (!h.mark_flags.empty()) {
     std::vector<std::pair<size_t, int>> starts;   // first word of a tensor in the arena, the tensor
@@ -374,6 +385,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
         // every step's notifications
         if (o.greedy_loop != 2) d[i].trig_event = -1;
       }
+      name_counters(d);
       if ((st = upload(&g->d_tasks_marked[copy], d)) != MPK_OK) return fail(st);
     }
   }
@@ -484,6 +496,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
         ds[i].flags |= h.mark_flags[i];
         if (ds[i].flags & TF_OUT_MARKED) ds[i].trig_event = -1;
       }
+      name_counters(ds);
       if ((st = upload(&g->d_tasks_static, ds)) != MPK_OK) return fail(st);
       GraphConst cs = c;
       cs.tasks = g->d_tasks_static;
