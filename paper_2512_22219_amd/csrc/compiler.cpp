@@ -1074,6 +1074,9 @@ static void mark_tensors(HostGraph& g) {
   g.mark_flags.clear();
   g.marked_tensor.assign(g.tensors.size(), 0);
   if (g.opt.launch_mode != MPK_LAUNCH_MEGA || g.stats.n_jit_tasks) return;
+  // Every launch of a graph has to use the two copies, or an odd number of steps between two that do leaves what the first
+  // one wrote for the second to read: not where calls of several steps run the loop kernel.
+  if (g.opt.greedy_loop == 2) return;
   auto linear = [](const HostOp& op) { return (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) && !(op.flags & TF_SPLITK); };
   auto attention = [](const HostOp& op) { return op.kind == MPK_OP_ATTN_PARTIAL && (op.flags & TF_ROPE_FUSED) && (op.flags & TF_ATTN_MERGE); };
   if (g.cfg.batch >= kMfmaMinBatch) return;   // (the matrix-core body waits for events, see mark_wait)

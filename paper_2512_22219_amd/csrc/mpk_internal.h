@@ -69,8 +69,8 @@ enum TaskFlags : uint16_t {
 // at once and loads again what it finds unset.  The producer neither waits for its stores nor notifies.
 // A marked tensor has two copies, for even and odd steps; a task that writes its tile of one copy
 // puts the same tile of the other back to unset (TaskDesc::twin), which nobody reads during the step and whose
-// readers of the step before have ended with their launch.  The loop kernel, the hybrid launch and
-// per-operator launches run on the unmarked descriptors and on a third copy.
+// readers of the step before have ended with their launch.  Hybrid and per-operator launches and graphs compiled for the
+// loop kernel run on the unmarked descriptors and the arena: all launches of a graph use the copies, or none.
 constexpr uint32_t kUnsetWord = 0xFFFFFFFFu;
 
 struct alignas(16) TaskDesc {

@@ -381,9 +381,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
         d[i].flags |= h.mark_flags[i];
         if (!(d[i].flags & TF_OUT_MARKED)) continue;
         d[i].twin = (copy ? -1 : 1) * (int32_t)(g->mark_words / 64);
-        // nobody waits for the events of marked outputs -- except the loop kernel's launches, which count on
-        // every step's notifications
-        if (o.greedy_loop != 2) d[i].trig_event = -1;
+        d[i].trig_event = -1;   // nobody waits for the events of marked outputs
       }
       name_counters(d);
       if ((st = upload(&g->d_tasks_marked[copy], d)) != MPK_OK) return fail(st);

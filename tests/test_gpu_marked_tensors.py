@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 FUSED = dict(fusion=31, transitive_reduction=1)
 
 
-def _greedy(s, model, n, **opts):
+def _greedy(s, model, n, calls=None, **opts):
     dev = model.device
     model.reset_kv()
     g = M.compile_graph(s, model.weight_ptrs(), model.kv_ptrs(), **opts)
@@ -26,7 +26,10 @@ def _greedy(s, model, n, **opts):
     picked = torch.empty((n, s.batch), dtype=torch.int32, device=dev)
     logits = torch.empty((s.batch, s.vocab), dtype=torch.float32, device=dev)
     every = torch.empty((n, s.batch, s.vocab), dtype=torch.float32, device=dev)
-    g.decode_steps(n, tok.data_ptr(), pos.data_ptr(), picked.data_ptr(), logits.data_ptr(), every.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    at = 0
+    for k in calls or [n]:
+        g.decode_steps(k, tok.data_ptr(), pos.data_ptr(), picked[at].data_ptr(), logits.data_ptr(), every[at].data_ptr(), torch.cuda.current_stream().cuda_stream)
+        at += k
     torch.cuda.synchronize()
     g.status()
     g.destroy()
@@ -58,6 +61,18 @@ def test_marked_launches_equal_unmarked_ones(kw, debug):
     few, _ = _greedy(s, model, n, greedy_loop=1, n_workers=29, **FUSED)   # several tasks of an operator per worker
     ref, _ = _greedy(s, model, n, greedy_loop=1, launch_mode=1, n_workers=29, **FUSED)
     assert np.array_equal(few, ref)
+
+
+@pytest.mark.parametrize("calls", [[1, 3, 1, 2, 1], [1, 2, 1, 1, 3]])
+@pytest.mark.parametrize("greedy_loop", [1, 2])
+def test_calls_of_one_step_between_calls_of_several(greedy_loop, calls):
+    """With greedy_loop = 2 a call of several steps is one launch of the loop kernel, which leaves marked copies alone: a
+    copy that a single step wrote would be taken for the output of a step of the same parity behind it."""
+    s = G.small_variant("C1", batch=2)
+    model, n = DeviceModel(s, 1), sum(calls)
+    want, tokens = _greedy(s, model, n, greedy_loop=1, launch_mode=1, **FUSED)
+    got, picked = _greedy(s, model, n, calls, greedy_loop=greedy_loop, **FUSED)
+    assert np.array_equal(got, want) and np.array_equal(picked, tokens)
 
 
 @pytest.mark.parametrize("opts", [dict(fusion=31), dict(fusion=15, transitive_reduction=1), dict(fusion=30, transitive_reduction=1),
