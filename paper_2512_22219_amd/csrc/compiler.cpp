@@ -1422,12 +1422,7 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
     const uint32_t pairs = cfg.batch * cfg.n_kv_heads;
     C = std::max(1u, opt.n_workers / pairs);
     if (C == 1 && pairs < opt.n_workers && cfg.batch > 1 && cfg.head_dim == 128 && (uint64_t)cfg.batch * cfg.max_seq > 16384u) C = 2;
-    // A QKV projection too large to be pre-loaded whole takes every worker, and then an O projection that waits for
-    // as few attention workers as possible is worth longer chunks (70B layers at batch 1, 2048 rows: 16 chunks
-    // 1765 us a step, 8 1732, 4 1700, 2 1700).
-    const uint64_t qkv_bytes = (uint64_t)(cfg.n_q_heads + 2 * cfg.n_kv_heads) * cfg.head_dim * cfg.hidden * 2;
-    const bool large_qkv = cfg.batch < kMfmaMinBatch && qkv_bytes / opt.n_workers > 256u * 1024u;
-    C = std::min(C, std::max(1u, cfg.max_seq / (large_qkv ? 512u : 128u)));
+    C = std::min(C, std::max(1u, cfg.max_seq / 128u));
     C = std::max(1u, std::min(C, 64u));
   }
   if (C > 64) { set_error("attn_chunks %u too large (max 64)", C); return MPK_ERR_INVALID_ARG; }

@@ -468,6 +468,17 @@ def test_default_number_of_attention_chunks(batch, n_kv, head_dim, max_seq, chun
     assert [int(op["n_tasks"]) for op in attn] == [batch * n_kv * chunks]
 
 
+@pytest.mark.parametrize("batch,chunks", [(1, 16), (2, 16)])
+def test_size_of_the_projections_does_not_change_the_attention_chunks(batch, chunks):
+    """A chunk's length is part of the order in which a row's attention is added up: 128 cached positions
+    of the largest sequence where there are workers enough, whatever else the model does."""
+    for hidden in (256, 8192):
+        s = G.small_variant("C5", n_layers=1, hidden=hidden, ffn=1024, vocab=1000, batch=batch)
+        ex = host_graph(s, fusion=31, transitive_reduction=1, n_workers=256).export()
+        attn = [op for op in ex.ops if op["kind"] == TG.K_ATTN_PARTIAL]
+        assert [int(op["n_tasks"]) for op in attn] == [batch * 8 * chunks]
+
+
 @pytest.mark.parametrize("batch", [1, 2, 3, 4, 5])
 def test_worker_speeds_resize_the_tiles_of_the_vector_body_only(batch):
     """Batch 3 and more runs on the matrix cores, whose tasks are made of 16-row blocks (and of jobs of 512 rows)."""
