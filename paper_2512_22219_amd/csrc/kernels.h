@@ -261,6 +261,36 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return (__int_as_float(__builtin_amdgcn_readlane(u, 0)) + __int_as_float(__builtin_amdgcn_readlane(u, 16))) +
          (__int_as_float(__builtin_amdgcn_readlane(u, 32)) + __int_as_float(__builtin_amdgcn_readlane(u, 48)));
 }
+// Sum of squares of a row staged 16 bytes a lane, in the order that 8 bytes a lane has: there lane i of wavefront w takes the
+// pairs of inputs u * 512 + 64 w + i, u after u, and the lanes are added by wave_sum_dpp.  Sums of squares reach every
+// output of a projection, and a last bit of them decides which way appended bf16 rows round: a wider load must not
+// move them.  A load's lower 32 lanes hold an even u, the upper ones the next, lane l (of 32) the pairs of lanes
+// 2 l and 2 l + 1: lower lane l sums for lane 2 l, upper lane l for lane 2 l + 1, after an exchange of halves.
+struct SumSq {
+  float s = 0.f;
+  __device__ __forceinline__ void add(const float4& v) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.x), __float_as_uint(v.z), false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.y), __float_as_uint(v.w), false, false);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float a = __uint_as_float(x[h]), b = __uint_as_float(y[h]);
+      s = fmaf(b, b, fmaf(a, a, s));
+    }
+  }
+  __device__ __forceinline__ float sum() const {
+    auto dpp = [](float x, auto ctrl) {
+      return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    const auto o = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    float v = __uint_as_float(o[0]) + __uint_as_float(o[1]);   // lane ^ 1
+    v += dpp(v, std::integral_constant<int, 0xB1>{});          // lane ^ 2
+    v += dpp(v, std::integral_constant<int, 0x4E>{});          // mirror of 8
+    v += dpp(v, std::integral_constant<int, 0x141>{});         // mirror of 16
+    const int u = __float_as_int(v);
+    return (__int_as_float(__builtin_amdgcn_readlane(u, 0)) + __int_as_float(__builtin_amdgcn_readlane(u, 8))) +
+           (__int_as_float(__builtin_amdgcn_readlane(u, 16)) + __int_as_float(__builtin_amdgcn_readlane(u, 24)));
+  }
+};
 // Four sums at once: every lane of the wavefront's row r of 16 lanes gets the sum of value 0, 2, 1, 3 for r = 0, 1, 2, 3
 // (halves of two values, then rows of two such pairs, put side by side by a swap and added).
 __device__ __forceinline__ float wave_sum4(float v0, float v1, float v2, float v3) {
@@ -869,6 +899,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   const bool pro_norm = t.flags & TF_PRO_NORM;
   // ---- the input rows: 16 bytes a load, kSlices loads a lane and row in flight (12288 inputs in one round trip)
   constexpr uint32_t kSlices = 6, kSlice = 4u * kThreads, kChunk = kSlices * kSlice;   // (inputs)
+  // this lane's inputs of a slice: 512 bytes of one half of it for the lower 32 lanes, of the other half for the upper (see SumSq)
+  const uint32_t xat = 128u * wave + 4u * ((uint32_t)lane & 31u) + (kSlice / 2u) * ((uint32_t)lane >> 5);
   u32x4 xin[NB][kSlices];
   auto x_load = [&](uint32_t i0) {
 #pragma unroll
@@ -877,7 +909,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
       const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(t.in + (size_t)(t.b0 + b) * t.ld_in)), 0, b < nb ? (int)(4u * K) : 0, 0x00020000);
 #pragma unroll
       for (uint32_t u = 0; u < kSlices; ++u)
-        if (i0 + u * kSlice < K) xin[b][u] = ld_buffer16<true>(r, 4u * (i0 + u * kSlice + 4u * tid));
+        if (i0 + u * kSlice < K) xin[b][u] = ld_buffer16<true>(r, 4u * (i0 + u * kSlice + xat));
     }
   };
   // Every word of the loaded chunk has been written (wavefront-uniform).
@@ -913,7 +945,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
 #pragma unroll
   for (uint32_t u = 0; u < kGainPre; ++u) {
     gpre[u] = u32x2{0u, 0u};
-    if (pro_norm && u * kSlice < K) gpre[u] = ld_buffer8(gain, 2u * (u * kSlice + 4u * tid));
+    if (pro_norm && u * kSlice < K) gpre[u] = ld_buffer8(gain, 2u * (u * kSlice + xat));
   }
   LinCursor rq{g.r0, 0u};   // next half block to request
   if (page_ready && lin_valid(g, rq)) lin_advance(g, rq);   // the first one is in this wavefront's page already
@@ -999,9 +1031,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // ---- stage the input rows in LDS.  With TF_PRO_NORM the gain is folded in here (x * g) and
   // the row's 1/rms factor is applied to the finished dot products: W (x g inv) = inv * W (x g).
   if (resid && !in_marked && tid < nb * ncols) resv = ld_act(resp);
-  float ss[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) ss[b] = 0.f;
+  SumSq ss[NB];
   for (uint32_t i0 = 0; i0 < Kp; i0 += kChunk) {
     if (i0 || !x_ok) {
       MarkWait mw;
@@ -1010,7 +1040,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     }
 #pragma unroll
     for (uint32_t u = 0; u < kSlices; ++u) {
-      const uint32_t i = i0 + u * kSlice + 4u * tid;
+      const uint32_t i = i0 + u * kSlice + xat;
       if (i0 + u * kSlice >= Kp) continue;
       float gn[4] = {1.f, 1.f, 1.f, 1.f};
       if (pro_norm) {
@@ -1022,7 +1052,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (i0 + u * kSlice < K) v = __builtin_bit_cast(float4, xin[b][u]);
         if (pro_norm) {
-          ss[b] = fmaf(v.x, v.x, ss[b]); ss[b] = fmaf(v.y, v.y, ss[b]); ss[b] = fmaf(v.z, v.z, ss[b]); ss[b] = fmaf(v.w, v.w, ss[b]);
+          if (i0 + u * kSlice < K) ss[b].add(v);
           v.x *= gn[0]; v.y *= gn[1]; v.z *= gn[2]; v.w *= gn[3];
         }
         if (g.pack() == 1u) {
@@ -1036,7 +1066,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   if (pro_norm) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const float v = wave_sum_dpp(ss[b]);
+      const float v = ss[b].sum();
       if (lane == 0) ssq[wave * NB + b] = v;
     }
   }
