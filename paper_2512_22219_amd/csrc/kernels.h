@@ -291,21 +291,23 @@ struct SumSq {
            (__int_as_float(__builtin_amdgcn_readlane(u, 16)) + __int_as_float(__builtin_amdgcn_readlane(u, 24)));
   }
 };
-// Four sums at once: every lane of the wavefront's row r of 16 lanes gets the sum of value 0, 2, 1, 3 for r = 0, 1, 2, 3
-// (halves of two values, then rows of two such pairs, put side by side by a swap and added).
+// Four sums at once, each as wave_sum_dpp adds it up: every lane of the wavefront's row r of 16 lanes gets that of value r
+// (sums of each row, then neighbouring rows of two values, and halves of two such pairs, put side by side by a swap and added).
 __device__ __forceinline__ float wave_sum4(float v0, float v1, float v2, float v3) {
-  auto swap_add = [](auto sw) { return __uint_as_float(sw[0]) + __uint_as_float(sw[1]); };
-  const float a = swap_add(__builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false));
-  const float b = swap_add(__builtin_amdgcn_permlane32_swap(__float_as_uint(v2), __float_as_uint(v3), false, false));
-  float v = swap_add(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false));
   auto dpp = [](float x, auto ctrl) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
   };
-  v += dpp(v, std::integral_constant<int, 0xB1>{});
-  v += dpp(v, std::integral_constant<int, 0x4E>{});
-  v += dpp(v, std::integral_constant<int, 0x141>{});
-  v += dpp(v, std::integral_constant<int, 0x140>{});
-  return v;
+  auto row_sum = [&](float v) {
+    v += dpp(v, std::integral_constant<int, 0xB1>{});
+    v += dpp(v, std::integral_constant<int, 0x4E>{});
+    v += dpp(v, std::integral_constant<int, 0x141>{});
+    v += dpp(v, std::integral_constant<int, 0x140>{});
+    return __float_as_uint(v);
+  };
+  auto swap_add = [](auto sw) { return __uint_as_float(sw[0]) + __uint_as_float(sw[1]); };
+  const float a = swap_add(__builtin_amdgcn_permlane16_swap(row_sum(v0), row_sum(v1), false, false));
+  const float b = swap_add(__builtin_amdgcn_permlane16_swap(row_sum(v2), row_sum(v3), false, false));
+  return swap_add(__builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false));
 }
 // ... and the largest / smallest value of the wavefront the same way
 template <class Op>
@@ -596,7 +598,7 @@ __device__ __forceinline__ void ring_clear(HalfRing& ring) {
 // Short rows are packed: with K <= 2048 (1024) inputs, two (four) weight rows share one of the half block's
 // rows, four (two) stages each, and the staged input is in LDS as often, so that loads and multiplies are
 // those of one row of 4096.  (A row of 2048 alone left half of every half block's loads to repeat its last 16 bytes.)
-// The sums are kept apart per two stages and put together at the end of a row.  us a step: 1B class at batch 1 702 ->
+// Sums are kept per two stages and handed on within a weight row (lin_chain).  us a step: 1B class at batch 1 702 ->
 // 630 (gate/up phase of a layer 15.2 -> 11.8 us), 2B class at batch 2, four tokens 2190 -> 2135.
 //
 // A kernel set of its own for models with packed tasks: where none is, the choice costs every task 0.3 us (8B at
@@ -719,12 +721,29 @@ __device__ __forceinline__ void lin_request(const LinGeom<PACKED>& g, const LinH
   }
 }
 
+// Sums of a half-block row: one, or (packed kernels) one for every two stages.  A weight row of more stages than two goes on
+// with the sum of the stages before, as it would in a half-block row of its own: what is packed and how
+// does not change the order in which a row is added up.  A row's sum is the one of its last stages.
+template <int NB, int NG>
+__device__ __forceinline__ void lin_chain(int u, uint32_t pack, float (&acc)[kHalfRows][NG][NB]) {
+  if constexpr (NG > 1) {
+    static_assert(NG * 2 == kRingStages, "two stages a sum");
+    if (u & 1) return;
+    const bool goes_on = u == 0 || u == 4 ? pack == 1u : pack <= 2u;   // (u == 0: segments of a long row)
+    const int q = u / 2, from = (q + NG - 1) % NG;
+#pragma unroll
+    for (int i = 0; i < kHalfRows; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[i][q][b] = goes_on ? acc[i][from][b] : 0.f;
+  }
+}
 // Adds the half block's partial dot products to acc.
 template <int NB, int NG>   // NG: sums per half-block row, of 8 / NG stages each
 __device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ring, const float* xs, uint32_t Kp,
-                                            int lane, float (&acc)[kHalfRows][NG][NB]) {
+                                            int lane, uint32_t pack, float (&acc)[kHalfRows][NG][NB]) {
 #pragma unroll
   for (int u = 0; u < kRingStages; ++u) {
+    lin_chain<NB, NG>(u, pack, acc);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const float4* xp = (const float4*)(xs + (size_t)b * Kp + B.seg * kSegLen + u * 512 + lane * 8);
@@ -751,9 +770,10 @@ __device__ __forceinline__ void lin_request_page(const LinGeom<PACKED>& g, const
 }
 template <int NB, int NG>
 __device__ __forceinline__ void lin_consume_page(const LinHalf& B, const u32x4* page, const float* xs, uint32_t Kp,
-                                                 int lane, float (&acc)[kHalfRows][NG][NB]) {
+                                                 int lane, uint32_t pack, float (&acc)[kHalfRows][NG][NB]) {
 #pragma unroll
   for (int u = 0; u < kRingStages; ++u) {
+    lin_chain<NB, NG>(u, pack, acc);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const float4* xp = (const float4*)(xs + (size_t)b * Kp + B.seg * kSegLen + u * 512 + lane * 8);
@@ -1106,22 +1126,19 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         for (int i = 0; i < kHalfRows; ++i)
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
-            float v = acc[i][0][b];
-            if constexpr (PACKED) v = (v + acc[i][1][b]) + (acc[i][2][b] + acc[i][3][b]);
-            v = wave_sum_dpp(v);
+            const float v = wave_sum_dpp(acc[i][NG - 1][b]);
             if (lane == 0 && (uint32_t)i < B.nrows) outbuf[(size_t)(B.row0 + i) * NB + b] = v;
           }
       } else if constexpr (PACKED) {
-        auto out4 = [&](float v, uint32_t i, uint32_t q, int b) {   // (a row of 16 lanes has sum q of half-block row i)
-          const uint32_t s = g.pack() == 2u ? q >> 1 : q, r = B.row0 + (g.gateup ? 2u * s + i : i * g.pack() + s);
+        auto out4 = [&](float v, uint32_t i, uint32_t s, int b) {   // (a row of 16 lanes has weight row s of half-block row i)
+          const uint32_t r = B.row0 + (g.gateup ? 2u * s + i : i * g.pack() + s);
           if ((lane & 15) == 0 && r < g.r1) outbuf[(size_t)r * NB + b] = v;
         };
-        const uint32_t row = (uint32_t)lane >> 4, k = (row >> 1) | ((row & 1u) << 1);   // the row has value k of a wave_sum4
+        const uint32_t k = (uint32_t)lane >> 4;   // the row of lanes has value k of a wave_sum4
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
           if (g.pack() == 2u) {
-            out4(wave_sum4(acc[0][0][b] + acc[0][1][b], acc[0][2][b] + acc[0][3][b], acc[1][0][b] + acc[1][1][b], acc[1][2][b] + acc[1][3][b]),
-                 k >> 1, 2u * (k & 1u), b);
+            out4(wave_sum4(acc[0][1][b], acc[0][3][b], acc[1][1][b], acc[1][3][b]), k >> 1, k & 1u, b);
           } else {
             out4(wave_sum4(acc[0][0][b], acc[0][1][b], acc[0][2][b], acc[0][3][b]), 0u, k, b);
             out4(wave_sum4(acc[1][0][b], acc[1][1][b], acc[1][2][b], acc[1][3][b]), 1u, k, b);
@@ -1138,14 +1155,14 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     LinCursor cs{g.r0, 0u};
     if (page_ready && lin_valid(g, cs)) {   // (requested a whole task ago: long since landed)
       const LinHalf B = lin_half(g, cs);
-      lin_consume_page<NB, NG>(B, page, xs, Kp, lane, acc);
+      lin_consume_page<NB, NG>(B, page, xs, Kp, lane, g.pack(), acc);
       finish(B);
       lin_advance(g, cs);
     }
     while (lin_valid(g, cs)) {
       {
         const LinHalf B = lin_half(g, cs);
-        lin_consume<NB, NG>(B, h0, xs, Kp, lane, acc);
+        lin_consume<NB, NG>(B, h0, xs, Kp, lane, g.pack(), acc);
         finish(B);
         lin_advance(g, cs);
       }
@@ -1157,7 +1174,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
       if (!lin_valid(g, cs)) break;
       {
         const LinHalf B = lin_half(g, cs);
-        lin_consume<NB, NG>(B, h1, xs, Kp, lane, acc);
+        lin_consume<NB, NG>(B, h1, xs, Kp, lane, g.pack(), acc);
         finish(B);
         lin_advance(g, cs);
       }
@@ -1170,7 +1187,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         if (!lin_valid(g, cs)) break;
         {
           const LinHalf B = lin_half(g, cs);
-          lin_consume<NB, NG>(B, h2, xs, Kp, lane, acc);
+          lin_consume<NB, NG>(B, h2, xs, Kp, lane, g.pack(), acc);
           finish(B);
           lin_advance(g, cs);
         }

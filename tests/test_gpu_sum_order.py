@@ -75,3 +75,23 @@ def test_order_of_the_sums_of_squares(hidden, batch):
         for b, t in enumerate(tokens):
             inv = f32(1) / np.sqrt(_sum_of_squares(x[t]) / f32(hidden) + f32(s.rms_eps))
             assert np.array_equal(got[b], x[t][at] * inv), (i, b)
+
+
+@pytest.mark.parametrize("batch", [1, 2])
+@pytest.mark.parametrize("kw,workers", [
+    (dict(hidden=2048, ffn=2048, vocab=1000), 13),    # two rows a half-block row, full
+    (dict(hidden=2040, ffn=2056, vocab=1003), 11),    # ... the input ends inside; a projection that is not packed beside it
+    (dict(hidden=1032, ffn=8200, vocab=997), 13),     # ... by 8 inputs past four a row; a row of three segments
+    (dict(hidden=1024, ffn=1024, vocab=2000), 9),     # four a row, full
+    (dict(hidden=256, ffn=688, vocab=1024), 5),       # the shortest rows
+])
+def test_packed_rows_are_added_up_like_rows_of_their_own(kw, workers, batch):
+    """With 256 workers no task has rows enough to be packed, with few all have; every output is a whole row's sum
+    either way."""
+    s = G.small_variant("C1", batch=batch, **kw)
+    model, rng = DeviceModel(s, 1), np.random.default_rng(workers)
+    for _ in range(2):
+        tokens = rng.integers(0, s.vocab, batch)
+        want = _logits(s, model, tokens, n_workers=256, attn_chunks=1)
+        got = _logits(s, model, tokens, n_workers=workers, attn_chunks=1)
+        assert np.isfinite(want).all() and np.array_equal(got, want)
