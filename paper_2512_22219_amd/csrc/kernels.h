@@ -2675,7 +2675,8 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     } while (MARKED && mark_wait(a, mark_unset(u0) || mark_unset(u1) || mark_unset(lo) || mark_unset(hi) || mark_unset(rq) || mark_unset(r0) || mark_unset(r1), mw));
     if (has_q) {
       if (qk_norm) {   // RMSNorm over the head: its `half` threads are one aligned group of lanes
-        const float inv = 1.0f / sqrtf(lane_group_sum<(int)half>(u0 * u0 + u1 * u1) / (float)d + t.f0);
+        // (spelt out like the rotation below: left to the compiler, which square is rounded first depends on the code around it)
+        const float inv = 1.0f / sqrtf(lane_group_sum<(int)half>(fmaf(u0, u0, u1 * u1)) / (float)d + t.f0);
         const uint16_t* gq = (const uint16_t*)t.w;
         u0 *= inv * bf16_to_f32(as_global(gq)[eq]);
         u1 *= inv * bf16_to_f32(as_global(gq)[eq + half]);
@@ -2685,7 +2686,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     }
     if (has_k) {
       if (qk_norm) {   // the key's half/2 threads: one aligned group of lanes at the top of the workgroup
-        const float ss = lane_group_sum<(int)(half / 2)>(lo.x * lo.x + lo.y * lo.y + hi.x * hi.x + hi.y * hi.y);
+        const float ss = lane_group_sum<(int)(half / 2)>(fmaf(hi.y, hi.y, fmaf(hi.x, hi.x, fmaf(lo.x, lo.x, lo.y * lo.y))));
         const float inv = 1.0f / sqrtf(ss / (float)d + t.f0);
         const uint16_t* gk = (const uint16_t*)t.w2;
         const uint32_t g0 = *as_global((const uint32_t*)(gk + ek)), g1 = *as_global((const uint32_t*)(gk + ek + half));
