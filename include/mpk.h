@@ -366,6 +366,24 @@ enum {
 
 mpk_status mpk_graph_export(const mpk_graph *g, void *buf, size_t cap, size_t *need);
 
+/* How the tasks are run, in linearized order, for tests and inspection: which tasks of a single-step launch learn from
+ * the words of their input instead of an event that it is complete (and who writes for such readers), and, for
+ * linear tasks, their inputs, outputs (rows x columns) and how many weight rows the vector body (batch 1 and 2) loads as
+ * one row of 4096 inputs (1: each by itself; 0: another body).  buf == NULL returns the element count in *need.
+ * Works on host_only graphs; a generic task DAG's entries are all 0. */
+typedef struct mpk_task_form {
+  uint32_t marks;   /* MPK_FORM_* */
+  uint32_t packed;
+  uint32_t inputs, outputs;
+} mpk_task_form;
+enum {
+  MPK_FORM_INPUT_MARKED = 1,    /* waits on the words of its input, not on its dependent event   */
+  MPK_FORM_RESIDUAL_MARKED = 2, /* ... and on those of its residual                               */
+  MPK_FORM_OUTPUT_MARKED = 4,   /* its consumers do: it triggers no event                         */
+  MPK_FORM_RESIDUAL = 8         /* a linear task that adds a residual                             */
+};
+mpk_status mpk_graph_task_forms(const mpk_graph *g, mpk_task_form *buf, size_t cap, size_t *need);
+
 /* Per-task timeline of the LAST decode step of a graph compiled with MPK_DEBUG_TRACE (the
  * counterpart of the paper's run-time overhead accounting, Section 6.5 "kernel-launch
  * reduction").  buf: host u64 [n_tasks][12] in linearized task order, ticks of the 100 MHz device

@@ -93,6 +93,8 @@ EXPORT_OP = np.dtype([("kind", "<u4"), ("layer", "<i4"), ("tb", "<u4"), ("tc", "
                       ("n_tasks", "<u4"), ("jit", "<u4"), ("rows", "<u4"), ("cols", "<u4")])
 EXPORT_TASK = np.dtype([("op", "<u4"), ("tile", "<u4"), ("dep_event", "<i4"),
                         ("trig_event", "<i4"), ("worker", "<i4"), ("jit", "<u4")])
+TASK_FORM = np.dtype([("marks", "<u4"), ("packed", "<u4"), ("inputs", "<u4"), ("outputs", "<u4")])
+FORM_INPUT_MARKED, FORM_RESIDUAL_MARKED, FORM_OUTPUT_MARKED, FORM_RESIDUAL = 1, 2, 4, 8
 EXPORT_EVENT = np.dtype([("required", "<u4"), ("first", "<u4"), ("last", "<u4"),
                          ("flags", "<u4")])
 
@@ -103,7 +105,7 @@ SYMBOLS = ("mpk_compile", "mpk_compile_dag", "mpk_decode_step", "mpk_decode_step
            "mpk_set_destroy", "mpk_last_error", "mpk_graph_destroy", "mpk_static_scratch_need",
            "mpk_graph_set_page_table", "mpk_serve_create", "mpk_serve_submit", "mpk_serve_run",
            "mpk_serve_result", "mpk_serve_state", "mpk_serve_logits", "mpk_serve_destroy",
-           "mpk_serve_create_set", "mpk_serve_last_batch", "mpk_serve_status")
+           "mpk_serve_create_set", "mpk_serve_last_batch", "mpk_serve_status", "mpk_graph_task_forms")
 DEBUG_TRACE, DEBUG_POISON, DEBUG_JITTER, DEBUG_LOSE_NOTIFY = 1, 2, 4, 8
 
 _lib = None
@@ -133,6 +135,8 @@ def lib():
         L.mpk_graph_export.argtypes = [vp, vp, C.c_size_t, C.POINTER(C.c_size_t)]
         L.mpk_graph_trace.argtypes = [vp, vp, C.c_size_t, C.POINTER(C.c_size_t)]
         L.mpk_graph_moe_active.argtypes = [vp, vp, C.c_size_t, C.POINTER(C.c_size_t)]
+        L.mpk_graph_task_forms.argtypes = [vp, vp, C.c_size_t, C.POINTER(C.c_size_t)]
+        L.mpk_graph_task_forms.restype = C.c_int
         L.mpk_moe_task_share.argtypes = [C.c_uint32] * 4 + [C.POINTER(C.c_uint32)] * 2
         L.mpk_graph_moe_selection.argtypes = [vp, vp, vp, C.c_size_t, C.POINTER(C.c_size_t)]
         L.mpk_last_error.restype = C.c_char_p
@@ -284,6 +288,14 @@ class Graph:
         buf = C.create_string_buffer(need.value)
         _check(lib().mpk_graph_export(self._h, buf, need.value, C.byref(need)))
         return Export(buf.raw)
+
+    def task_forms(self) -> np.ndarray:
+        """TASK_FORM records in linearized task order (see mpk.h)."""
+        need = C.c_size_t(0)
+        _check(lib().mpk_graph_task_forms(self._h, None, 0, C.byref(need)))
+        buf = np.zeros(need.value, TASK_FORM)
+        _check(lib().mpk_graph_task_forms(self._h, buf.ctypes.data, need.value, C.byref(need)))
+        return buf
 
     def trace(self) -> np.ndarray:
         need = C.c_size_t(0)

@@ -1100,8 +1100,16 @@ static void mark_tensors(HostGraph& g) {
     out[i] = ok && read;
   }
   auto is_marked = [&](int tensor) { return tensor >= 0 && producer[tensor] >= 0 && out[producer[tensor]]; };
+  std::vector<uint32_t> outputs(g.ops.size(), 0);   // of an operator's largest task
+  for (size_t i = 0; i < g.tasks.size(); ++i)
+    if (g.tasks[i].op != MPK_TASK_DUMMY_OP)
+      outputs[g.tasks[i].op] = std::max(outputs[g.tasks[i].op], (g.descs[i].b1 - g.descs[i].b0) * (g.descs[i].c1 - g.descs[i].c0));
   auto skips_event = [&](const HostTask& t) {
-    return t.op != MPK_TASK_DUMMY_OP && (linear(g.ops[t.op]) || (attention(g.ops[t.op]) && out[t.op])) && is_marked(g.ops[t.op].in_tensor);
+    if (t.op == MPK_TASK_DUMMY_OP) return false;
+    const HostOp& op = g.ops[t.op];
+    // (a residual that nothing vouches for keeps its operator's event)
+    if (linear(op) && (op.flags & TF_EPI_RESID) && !is_marked(op.in2_tensor) && !lin_resid_seen(op.K, outputs[t.op])) return false;
+    return (linear(op) || (attention(op) && out[t.op])) && is_marked(op.in_tensor);
   };
   // A marked output is not notified: only where every task on its event skips that event.
   for (bool changed = true; changed;) {
@@ -1556,6 +1564,22 @@ void export_graph(const HostGraph& g, void* buf) {
     const uint32_t hdr[2] = {(uint32_t)oi, (uint32_t)op.col_begin.size()};
     memcpy(p, hdr, 8); p += 8;
     for (uint32_t b : op.col_begin) { const uint32_t c = b * op.unit; memcpy(p, &c, 4); p += 4; }
+  }
+}
+
+void task_forms(const HostGraph& g, mpk_task_form* out) {
+  for (size_t i = 0; i < g.tasks.size(); ++i) {
+    out[i] = mpk_task_form{};
+    if (i >= g.descs.size()) continue;   // (a generic DAG has no bodies)
+    const TaskDesc& t = g.descs[i];
+    const uint16_t marks = g.mark_flags.empty() ? 0 : g.mark_flags[i];
+    out[i].marks = ((marks & TF_IN_MARKED) ? MPK_FORM_INPUT_MARKED : 0u) | ((marks & TF_IN2_MARKED) ? MPK_FORM_RESIDUAL_MARKED : 0u) |
+                   ((marks & TF_OUT_MARKED) ? MPK_FORM_OUTPUT_MARKED : 0u);
+    if (t.kind != TK_LINEAR) continue;
+    if (t.flags & TF_EPI_RESID) out[i].marks |= MPK_FORM_RESIDUAL;
+    out[i].inputs = t.K;
+    out[i].outputs = (t.b1 - t.b0) * (t.c1 - t.c0);
+    if (g.cfg.batch < kMfmaMinBatch) out[i].packed = g.packed_rows ? lin_pack(t.K, (t.c1 - t.c0) << ((t.flags & TF_GATEUP) ? 1 : 0)) : 1u;
   }
 }
 

@@ -36,6 +36,7 @@ namespace mpk {
 const char* last_error();
 size_t export_size(const HostGraph& g);
 void export_graph(const HostGraph& g, void* buf);
+void task_forms(const HostGraph& g, mpk_task_form* out);
 
 // Everything that is fixed for the lifetime of a graph lives in one device-resident record that
 // the kernels reach through a pointer (uniform address -> scalar loads on demand, nothing is
@@ -920,7 +921,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // ---- the input rows: 16 bytes a load, kSlices loads a lane and row in flight (12288 inputs in one round trip)
   constexpr uint32_t kSlices = 6, kSlice = 4u * kThreads, kChunk = kSlices * kSlice;   // (inputs)
   // this lane's inputs of a slice: 512 bytes of one half of it for the lower 32 lanes, of the other half for the upper (see SumSq)
-  const uint32_t xat = 128u * wave + 4u * ((uint32_t)lane & 31u) + (kSlice / 2u) * ((uint32_t)lane >> 5);
+  const uint32_t xat = kLinWaveInputs * wave + 4u * ((uint32_t)lane & 31u) + (kSlice / 2u) * ((uint32_t)lane >> 5);
   u32x4 xin[NB][kSlices];
   auto x_load = [&](uint32_t i0) {
 #pragma unroll
@@ -1095,7 +1096,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     if (in2_marked)   // (written long ago: it is an input of this task's producers' producers)
       while (mark_wait(a, mark_unset(resv), mw))
         if (mark_unset(resv)) resv = ld_act(resp);
-    if (in_marked && !in2_marked && tid < nb * ncols) resv = ld_act(resp);   // (not marked: complete only now that the input is)
+    // (not marked: complete only now that this wavefront has seen input; without any it has no output here, see lin_resid_seen)
+    if (in_marked && !in2_marked && tid < nb * ncols) resv = ld_act(resp);
     if (tid < nb * ncols) res_lds[tid] = resv;
     for (uint32_t i0 = kThreads; i0 < nb * ncols; i0 += kThreads) {   // more than 512 outputs per task: rare
       const uint32_t i = i0 + tid, bb = i / ncols, cc = i % ncols;

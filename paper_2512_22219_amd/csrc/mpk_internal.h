@@ -72,6 +72,14 @@ enum TaskFlags : uint16_t {
 // readers of the step before have ended with their launch.  Hybrid and per-operator launches and graphs compiled for the
 // loop kernel run on the unmarked descriptors and the arena: all launches of a graph use the copies, or none.
 constexpr uint32_t kUnsetWord = 0xFFFFFFFFu;
+// A wavefront of the vector linear body looks at the words of the input that it loads itself: wavefront w, of every 2048
+// inputs, at those from kLinWaveInputs w on.  An unmarked residual is complete once any word of a marked input is (whoever
+// wrote that has seen it), but a wavefront that owns no word of a short input has seen nothing.  Whether
+// none of those loads a part of the residual: thread i loads that of outputs i, i + 512, ...
+constexpr uint32_t kLinWaveInputs = 128;
+constexpr bool lin_resid_seen(uint32_t K, uint32_t outputs) {
+  return K > 7u * kLinWaveInputs || outputs <= 64u * ((K + kLinWaveInputs - 1u) / kLinWaveInputs);
+}
 
 struct alignas(16) TaskDesc {
   uint16_t kind, flags;

@@ -734,6 +734,16 @@ extern "C" mpk_status mpk_graph_export(const mpk_graph* g, void* buf, size_t cap
   return MPK_OK;
 }
 
+extern "C" mpk_status mpk_graph_task_forms(const mpk_graph* g, mpk_task_form* buf, size_t cap, size_t* need) {
+  if (!g) { set_error("NULL graph"); return MPK_ERR_INVALID_ARG; }
+  const size_t n = g->h.tasks.size();
+  if (need) *need = n;
+  if (!buf) return MPK_OK;
+  if (cap < n) { set_error("buffer too small: %zu < %zu", cap, n); return MPK_ERR_INVALID_ARG; }
+  task_forms(g->h, buf);
+  return MPK_OK;
+}
+
 extern "C" mpk_status mpk_graph_trace(mpk_graph* g, uint64_t* buf, size_t cap, size_t* need) {
   if (!g) { set_error("NULL graph"); return MPK_ERR_INVALID_ARG; }
   if (g->host_only || !g->d_trace) { set_error("graph was not compiled with MPK_DEBUG_TRACE"); return MPK_ERR_INVALID_ARG; }

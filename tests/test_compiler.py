@@ -531,3 +531,30 @@ def test_expert_shares_are_the_same_in_32_and_in_64_bits(n_active, tiles, n_task
 
     for task in range(n_tasks):
         assert moe_task_share(n_active, tiles, n_tasks, task) == (at(task), at(task + 1))
+
+
+def _marks(shape, **opts):
+    """Per operator kind of the first layer (and the head): the set of its tasks' marks; and all (export, forms)."""
+    g = host_graph(shape, **{**dict(n_workers=256), **opts})
+    return g.export(), g.task_forms()
+
+
+@pytest.mark.parametrize("kw,opts", [
+    (dict(), dict(tiles_linear=2)), (dict(batch=2), dict(tiles_linear=2)),       # 128 outputs a task of 256 inputs
+    (dict(hidden=512, batch=2), dict(n_workers=15)), (dict(hidden=512, batch=2), dict(n_workers=14)),
+    (dict(hidden=1032, n_q_heads=2, n_kv_heads=1, batch=2), dict(tiles_linear=1)),     # more outputs than threads
+    (dict(ffn=0, n_experts=16, top_k=4, expert_ffn=64), dict(n_workers=11)),     # every layer's residual is unmarked
+    (dict(ffn=0, n_experts=16, top_k=4, expert_ffn=64, batch=2), dict(tiles_linear=3)),
+    (dict(hidden=4096, n_q_heads=16, batch=2), dict(tiles_linear=2)),            # 1024 inputs: every wavefront has some
+])
+def test_unmarked_residuals_are_read_only_by_wavefronts_that_have_seen_the_input(kw, opts):
+    """Thread i of 512 loads the residual of outputs i, i + 512, ...; wavefront w has looked at an input word only if the
+    input is longer than 128 w.  A task for which the two do not match has to keep its event."""
+    ex, forms = _marks(G.small_variant("C1", **kw), fusion=31, transitive_reduction=1, **opts)
+    resid = (forms["marks"] & M.binding.FORM_RESIDUAL) != 0
+    assert resid.any()
+    for f in forms[resid]:
+        if f["marks"] & M.binding.FORM_RESIDUAL_MARKED or not f["marks"] & M.binding.FORM_INPUT_MARKED:
+            continue
+        loads = {i % 512 // 64 for i in range(int(f["outputs"]))}
+        assert all(128 * w < f["inputs"] for w in loads), f

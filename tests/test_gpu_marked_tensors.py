@@ -63,6 +63,23 @@ def test_marked_launches_equal_unmarked_ones(kw, debug):
     assert np.array_equal(few, ref)
 
 
+@pytest.mark.parametrize("kw,opts", [
+    (dict(), dict(tiles_linear=2)), (dict(batch=2), dict(tiles_linear=2)), (dict(hidden=512, batch=2), dict(n_workers=15)),
+    (dict(n_experts=16, top_k=4, ffn=0, expert_ffn=64), dict(n_workers=11)),
+    (dict(n_experts=16, top_k=4, ffn=0, expert_ffn=64, batch=2), dict(tiles_linear=3)),
+    (dict(hidden=4096, n_q_heads=16, batch=2), dict(tiles_linear=2)),
+])
+@pytest.mark.parametrize("debug", [0, 4])
+def test_large_tiles_whose_residual_is_not_marked(kw, opts, debug):
+    """More outputs a task than wavefronts with input: the residual (an embedding row, another one in every step; a
+    combined expert output) must not be read ahead of the operators that write it."""
+    s = G.small_variant("C1", **kw)
+    model, n = DeviceModel(s, 1), 5
+    want, tokens = _greedy(s, model, n, greedy_loop=1, launch_mode=1, **FUSED, **opts)
+    got, picked = _greedy(s, model, n, greedy_loop=1, debug_flags=debug, **FUSED, **opts)
+    assert np.isfinite(want).all() and np.array_equal(got, want) and np.array_equal(picked, tokens)
+
+
 @pytest.mark.parametrize("calls", [[1, 3, 1, 2, 1], [1, 2, 1, 1, 3]])
 @pytest.mark.parametrize("greedy_loop", [1, 2])
 def test_calls_of_one_step_between_calls_of_several(greedy_loop, calls):
