@@ -700,11 +700,20 @@ static void tile_bounds(const HostOp& op, uint32_t tile, uint32_t* b0, uint32_t*
 static bool page_capable(const mpk_model_config& c, const mpk_compile_options& o) {
   return c.batch == 1 && !o.no_lds_pages && !o.no_preload && o.n_sched_wgs == 0 && o.launch_mode == MPK_LAUNCH_MEGA;
 }
+static uint64_t step_weight_bytes(const mpk_model_config& c) {
+  const uint64_t qkv_rows = (uint64_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+  return (uint64_t)c.batch * c.hidden * 2 + (uint64_t)c.hidden * 2 + (uint64_t)c.vocab * c.hidden * 2 +
+         (uint64_t)c.n_layers * 2 * (2ull * c.hidden + qkv_rows * c.hidden + (uint64_t)c.hidden * c.n_q_heads * c.head_dim +
+                                     (c.n_experts ? (uint64_t)c.n_experts * c.hidden : 3ull * c.ffn * c.hidden));
+}
 static void choose_partitions(const mpk_model_config& c, const mpk_compile_options& o,
                               HostGraph& g) {
   const uint32_t W = o.n_workers;
+  g.large_tasks = step_weight_bytes(c) / std::max(1u, c.n_layers) / std::max(1u, W) >= (3u << 20);
+  // (no set packs rows and has a third weight buffer or experts; whatever is sized by packing asks here)
+  const bool may_pack = c.batch < kMfmaMinBatch && !c.n_experts && !g.large_tasks;
   bool pages_likely = false;   // (page_plan looks more closely)
-  for (const auto& op : g.ops) pages_likely = pages_likely || (op.kind == MPK_OP_GATEUP && page_capable(c, o) && op.K <= 4096 && (uint64_t)op.cols * 2 >= 48ull * lin_pack(op.K, op.cols * 2 / W) * W);
+  for (const auto& op : g.ops) pages_likely = pages_likely || (op.kind == MPK_OP_GATEUP && page_capable(c, o) && op.K <= 4096 && (uint64_t)op.cols * 2 >= 48ull * (may_pack ? lin_pack(op.K, op.cols * 2 / W) : 1u) * W);
   auto after_attention = [&](const HostOp& op) {   // reads what attention tasks have merged
     for (const HostOp& p : g.ops)
       if (p.kind == MPK_OP_ATTN_PARTIAL && p.out_tensor == op.in_tensor) return true;
@@ -809,7 +818,7 @@ static void choose_partitions(const mpk_model_config& c, const mpk_compile_optio
   }
   // (the output head's tasks are packed where a layer's are; for it alone the set is not changed)
   for (const auto& op : g.ops)
-    if (c.batch < kMfmaMinBatch && !c.n_experts && op.layer >= 0 && (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) &&
+    if (may_pack && op.layer >= 0 && (op.kind == MPK_OP_LINEAR || op.kind == MPK_OP_GATEUP) &&
         lin_pack(op.K, op.cols * ((op.flags & TF_GATEUP) ? 2u : 1u) / op.tc) > 1u) g.packed_rows = true;
   uint32_t base = 0;
   for (auto& op : g.ops) {
@@ -1479,14 +1488,7 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
   g.stats.n_ops = (uint32_t)g.ops.size();
   g.stats.lds_bytes = g.lds_bytes;
   g.stats.act_bytes = g.arena_floats * sizeof(float);
-  uint64_t wb = (uint64_t)cfg.batch * cfg.hidden * 2 + (uint64_t)cfg.hidden * 2 +
-                (uint64_t)cfg.vocab * cfg.hidden * 2;
-  uint64_t qkv_rows = (uint64_t)(cfg.n_q_heads + 2 * cfg.n_kv_heads) * cfg.head_dim;
-  wb += (uint64_t)cfg.n_layers * 2 * (2ull * cfg.hidden + qkv_rows * cfg.hidden +
-                                      (uint64_t)cfg.hidden * cfg.n_q_heads * cfg.head_dim +
-                                      (cfg.n_experts ? (uint64_t)cfg.n_experts * cfg.hidden
-                                                     : 3ull * cfg.ffn * cfg.hidden));
-  g.stats.weight_bytes = wb;
+  g.stats.weight_bytes = step_weight_bytes(cfg);
   g.stats.expert_bytes = cfg.n_experts ? 3ull * cfg.expert_ffn * cfg.hidden * 2 : 0;
   g.stats.kv_row_bytes = (uint64_t)cfg.n_layers * 2 * cfg.n_kv_heads * cfg.head_dim * 2;
   return MPK_OK;

@@ -16,7 +16,7 @@ static const KernelVariant* variant_at(int i) {
 
 // The kernel set of a batch size; null: none (the host admits no such batch).
 static const KernelVariant* pick_variant(uint32_t batch, bool moe, bool large_tasks, bool packed) {
-  const int nb = batch < kMfmaMinBatch && packed && !large_tasks ? 10 + (int)batch : batch == 1 ? (large_tasks && !moe ? 9 : 1) : batch < kMfmaMinBatch ? 2 : batch <= 4 ? 4 : batch <= 8 ? 8 : batch <= 16 ? 16 : 0;
+  const int nb = packed ? 10 + (int)batch : batch == 1 ? (large_tasks && !moe ? 9 : 1) : batch < kMfmaMinBatch ? 2 : batch <= 4 ? 4 : batch <= 8 ? 8 : batch <= 16 ? 16 : 0;
   for (int i = 0; i < kNumVariants; ++i)
     if (variant_at(i)->nb == nb && variant_at(i)->moe == moe) return variant_at(i);
   return nullptr;
@@ -302,9 +302,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
   if (hipGetDevice(&g->device) != hipSuccess) { set_error("hipGetDevice failed"); return fail(MPK_ERR_HIP); }
   HostGraph& h = g->h;
   // residency: dynamic LDS above half of a CU's 160 KB caps occupancy at one workgroup per CU
-  // "large": 3 MB or more of weights per worker and layer (8B shape: 1.6 MB, 70B shape: 6.8 MB)
-  const bool large_tasks = h.stats.weight_bytes / std::max(1u, cfg->n_layers) / std::max(1u, o.n_workers) >= (3u << 20);
-  g->kv = pick_variant(cfg->batch, cfg->n_experts != 0, large_tasks, h.packed_rows);
+  g->kv = pick_variant(cfg->batch, cfg->n_experts != 0, h.large_tasks, h.packed_rows);
   if (!g->kv) { set_error("no kernel set for batch %u", cfg->batch); return fail(MPK_ERR_INTERNAL); }
   hipError_t e = reserve_lds((const void*)g->kv->mega, h.lds_bytes);
   if (e == hipSuccess) e = reserve_lds((const void*)g->kv->op, h.lds_bytes);

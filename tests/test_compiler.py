@@ -558,3 +558,21 @@ def test_unmarked_residuals_are_read_only_by_wavefronts_that_have_seen_the_input
             continue
         loads = {i % 512 // 64 for i in range(int(f["outputs"]))}
         assert all(128 * w < f["inputs"] for w in loads), f
+
+
+@pytest.mark.parametrize("kw,workers,packs,larger", [
+    (dict(hidden=2048, n_q_heads=16, ffn=8192), 24, False, 8),     # 5 MB of weights a worker and layer: three weight buffers, no packing
+    (dict(hidden=2048, n_q_heads=16, ffn=4096), 24, True, 16),     # 2.8 MB: two rows to a row of a page, twice the rows in it
+    (dict(hidden=512, ffn=4096, vocab=4093, n_q_heads=8, n_kv_heads=8), 5, False, None),   # 3.2 MB, half of it the output head
+])
+def test_pages_are_sized_for_the_rows_the_kernel_set_packs(kw, workers, packs, larger):
+    """A page takes 16 rows of half a block, or as many times more as share a row of it; the tiles that find theirs
+    in a page are larger by that, in columns of a gate/up pair."""
+    ex, forms = _marks(G.small_variant("C1", **kw), fusion=31, transitive_reduction=1, n_workers=workers)
+    packed = forms["packed"][forms["inputs"] > 0]
+    assert (packed.max() > 1) == packs and packed.min() == 1
+    gateup = [oi for oi, op in enumerate(ex.ops) if op["kind"] == TG.K_GATEUP and oi in ex.col_begin]
+    assert bool(gateup) == (larger is not None)
+    for oi in gateup:
+        size = np.unique(np.diff(ex.col_begin[oi].astype(np.int64)))
+        assert larger <= size.max() - size.min() <= larger + 1
