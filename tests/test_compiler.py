@@ -576,3 +576,60 @@ def test_pages_are_sized_for_the_rows_the_kernel_set_packs(kw, workers, packs, l
     for oi in gateup:
         size = np.unique(np.diff(ex.col_begin[oi].astype(np.int64)))
         assert larger <= size.max() - size.min() <= larger + 1
+
+
+_DENSE = "0 4 5 13 5 15 5 5 15 5 15 1"   # embedding; QKV, attention, O, gate/up, down of two layers; head
+_EVENTS = "0 0 0 8 0 8 0 0 8 0 8 0"
+
+
+@pytest.mark.parametrize("kw,opts,want", [
+    (dict(), {}, _DENSE),
+    (dict(batch=2, hidden=2048, n_q_heads=16, n_kv_heads=2, max_seq=2624), {}, _DENSE),
+    (dict(qk_norm=True), dict(greedy_loop=1), _DENSE + " 0"),
+    (dict(batch=2), dict(serving=1, greedy_loop=1, kv_page_size=32, kv_pages=16), "0 " + _DENSE + " 0"),
+    # the router's task reads all of the expert tasks' and the combine's input: those may go by events
+    (dict(n_experts=16, top_k=4, ffn=0, expert_ffn=64), {}, "0 4 5 13 1 0 0 0 0 4 5 13 1 0 0 0 0 0"),
+    # operators in between that know no marks; an event that tasks of several kinds wait for
+    (dict(batch=2), dict(fusion=30), "0 0 4 5 9 0 4 9 0 4 5 9 0 4 9 0 0"),
+    (dict(batch=2), dict(fusion=29), "0 4 5 1 0 4 1 0 4 5 1 0 4 1 0 0"),
+    (dict(batch=2), dict(fusion=27), "0 4 5 13 1 0 12 5 5 15 1 0 12 1"),
+    (dict(batch=2), dict(fusion=15), "0 0 0 0 12 5 15 1 0 0 12 5 15 1"),
+    (dict(batch=2), dict(transitive_reduction=0), "0 4 5 9 0 8 0 0 8 0 12 1"),
+    # a residual that nothing vouches for
+    (dict(batch=2), dict(tiles_linear=2), "0 0 0 12 5 15 5 5 15 5 15 1"),
+    # never: matrix-core bodies, hybrid and per-operator launches, the loop kernel's graphs
+    (dict(batch=3), {}, _EVENTS), (dict(), dict(n_sched_wgs=1), _EVENTS), (dict(), dict(launch_mode=1), _EVENTS),
+    (dict(), dict(greedy_loop=2), _EVENTS + " 0"),
+])
+def test_which_operators_go_by_the_words_of_their_input(kw, opts, want):
+    """Marks of every operator in order (1 input, 2 residual, 4 output marked, 8 has a residual); all tasks of an
+    operator are alike."""
+    ex, forms = _marks(G.small_variant("C1", **kw), **{**dict(fusion=31, transitive_reduction=1), **opts})
+    marks = [np.unique(forms["marks"][ex.tasks["op"] == oi]) for oi in range(len(ex.ops))]
+    assert all(len(m) == 1 for m in marks)
+    assert " ".join(str(m[0]) for m in marks) == want
+
+
+@pytest.mark.parametrize("kw,opts", [
+    (dict(batch=2, max_seq=1024), {}), (dict(batch=2, max_seq=1024, n_q_heads=8, n_kv_heads=8), dict(n_workers=5)),
+    (dict(batch=2, max_seq=1024, n_kv_heads=1), dict(n_workers=37, attn_chunks=7)), (dict(max_seq=2624), dict(n_workers=1)),
+    (dict(batch=2, max_seq=1024, n_q_heads=3, n_kv_heads=3, head_dim=128), dict(transitive_reduction=0, n_workers=11, attn_chunks=6)),
+    (dict(batch=2, max_seq=1024), dict(tiles_linear=5, attn_chunks=4)),      # projection tiles that straddle heads
+])
+def test_attention_tasks_of_a_head_are_in_the_order_of_their_chunks(kw, opts):
+    """A marked sequence's last chunk merges and waits for the words of the others, wherever the lengths deal them: no
+    worker may have any of those behind it.  So a head's tasks come in order of (sequence, chunk), and every
+    worker's list in linearized order."""
+    ex, forms = _marks(G.small_variant("C1", **kw), **{**dict(fusion=31, transitive_reduction=1), **opts})
+    for w in range(len(ex.aot_off) - 1):
+        mine = ex.aot[ex.aot_off[w]:ex.aot_off[w + 1]].astype(np.int64)
+        assert (np.diff(mine) > 0).all()
+    for oi, op in enumerate(ex.ops):
+        if op["kind"] != TG.K_ATTN_PARTIAL:
+            continue
+        at = np.flatnonzero(ex.tasks["op"] == oi)
+        place = np.empty(len(at), np.int64)
+        place[ex.tasks["tile"][at]] = at
+        B, n_kv = int(op["tb"]), int(kw.get("n_kv_heads", 2))
+        per_head = place.reshape(B, n_kv, -1).transpose(1, 0, 2).reshape(n_kv, -1)   # [head][sequence, chunk]
+        assert (np.diff(per_head, axis=1) > 0).all()

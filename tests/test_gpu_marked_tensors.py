@@ -21,6 +21,8 @@ def _greedy(s, model, n, calls=None, **opts):
     dev = model.device
     model.reset_kv()
     g = M.compile_graph(s, model.weight_ptrs(), model.kv_ptrs(), **opts)
+    marked = bool((g.task_forms()["marks"] & M.binding.FORM_INPUT_MARKED).any())
+    assert marked == (opts.get("launch_mode", 0) == 0 and opts["greedy_loop"] != 2)   # (or a comparison says nothing)
     tok = torch.as_tensor(G.tokens(3, s).astype(np.int32), device=dev)
     pos = torch.as_tensor(np.array([(37 * b + 61) % (s.max_seq - n) for b in range(s.batch)], np.int32), device=dev)
     picked = torch.empty((n, s.batch), dtype=torch.int32, device=dev)
