@@ -309,7 +309,8 @@ typedef struct mpk_stats {
   uint64_t successor_bytes_linearized;   /* 8 B per event (first, last)                         */
   uint64_t weight_bytes;   /* bf16 weight bytes one step streams (embedding rows included)      */
   uint64_t kv_row_bytes;   /* K+V bytes read per cached position, summed over layers & kv heads */
-  uint64_t act_bytes;      /* fp32 activation buffers owned by the graph                        */
+  uint64_t act_bytes;      /* fp32 activation buffers owned by the graph: each activation once, and the
+                              marked ones (see mpk_task_form) in two more copies              */
   uint64_t expert_bytes;   /* mixture-of-experts: bf16 bytes of ONE expert of one layer (gate, up
                               and down matrices); weight_bytes then excludes the experts: a step
                               streams weight_bytes + expert_bytes x (distinct experts selected,

@@ -1081,7 +1081,8 @@ static void build_descs(const mpk_model_config& c, const mpk_kv_ptrs* kv, HostGr
 // every task is ahead-of-time.
 static void mark_tensors(HostGraph& g) {
   g.mark_flags.clear();
-  g.marked_tensor.assign(g.tensors.size(), 0);
+  g.mark_offset.assign(g.tensors.size(), SIZE_MAX);
+  g.mark_words = 0;
   if (g.opt.launch_mode != MPK_LAUNCH_MEGA || g.stats.n_jit_tasks) return;
   // Every launch of a graph has to use the two copies, or an odd number of steps between two that do leaves what the first
   // one wrote for the second to read: not where calls of several steps run the loop kernel.
@@ -1145,8 +1146,11 @@ static void mark_tensors(HostGraph& g) {
   }
   for (size_t i = 0; i < g.ops.size(); ++i) {
     if (!out[i]) continue;
-    g.marked_tensor[g.ops[i].out_tensor] = 1;
-    if (g.ops[i].side_out_tensor >= 0) g.marked_tensor[g.ops[i].side_out_tensor] = 1;
+    for (int t : {g.ops[i].out_tensor, g.ops[i].side_out_tensor}) {
+      if (t < 0 || g.tensors[t].offset == SIZE_MAX || g.mark_offset[t] != SIZE_MAX) continue;
+      g.mark_offset[t] = g.mark_words;
+      g.mark_words += ((size_t)g.tensors[t].rows * g.tensors[t].cols + 63) / 64 * 64;
+    }
   }
 }
 
@@ -1487,7 +1491,7 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
   g.stats.struct_size = sizeof(mpk_stats);
   g.stats.n_ops = (uint32_t)g.ops.size();
   g.stats.lds_bytes = g.lds_bytes;
-  g.stats.act_bytes = g.arena_floats * sizeof(float);
+  g.stats.act_bytes = (g.arena_floats + 2 * g.mark_words) * sizeof(float);
   g.stats.weight_bytes = step_weight_bytes(cfg);
   g.stats.expert_bytes = cfg.n_experts ? 3ull * cfg.expert_ffn * cfg.hidden * 2 : 0;
   g.stats.kv_row_bytes = (uint64_t)cfg.n_layers * 2 * cfg.n_kv_heads * cfg.head_dim * 2;

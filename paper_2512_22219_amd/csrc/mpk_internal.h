@@ -230,7 +230,8 @@ struct HostGraph {
                                  // until the runtime relocates them
   std::vector<uint16_t> mark_flags;   // parallel to tasks: TF_IN_MARKED / TF_IN2_MARKED / TF_OUT_MARKED of the marked
                                       // descriptors; empty: no task of the graph has any
-  std::vector<uint8_t> marked_tensor; // parallel to tensors
+  std::vector<size_t> mark_offset;    // parallel to tensors: first word in a copy of the marked ones, SIZE_MAX: not marked
+  size_t mark_words = 0;              // of one copy
   uint32_t n_real = 0, start_event = 0, terminal_event = 0;
   size_t arena_floats = 0;
   uint32_t lds_bytes = 0;

@@ -354,14 +354,9 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
   // ... and the descriptors of the launches that use marked tensors, one set per copy of those
   if (!h.mark_flags.empty()) {
     std::vector<std::pair<size_t, int>> starts;   // first word of a tensor in the arena, the tensor
-    std::vector<size_t> at(h.tensors.size(), 0);
-    for (size_t i = 0; i < h.tensors.size(); ++i) {
-      if (h.tensors[i].offset == SIZE_MAX) continue;
-      starts.emplace_back(h.tensors[i].offset, (int)i);
-      if (!h.marked_tensor[i]) continue;
-      at[i] = g->mark_words;
-      g->mark_words += ((size_t)h.tensors[i].rows * h.tensors[i].cols + 63) / 64 * 64;
-    }
+    for (size_t i = 0; i < h.tensors.size(); ++i)
+      if (h.tensors[i].offset != SIZE_MAX) starts.emplace_back(h.tensors[i].offset, (int)i);
+    g->mark_words = h.mark_words;
     std::sort(starts.begin(), starts.end());
     e = hipMalloc((void**)&g->d_marked, 2 * g->mark_words * sizeof(float));
     if (e != hipSuccess) { set_error("hipMalloc(%zu) for activations failed: %s", 2 * g->mark_words * sizeof(float), hipGetErrorString(e)); return fail(MPK_ERR_OOM); }
@@ -372,8 +367,8 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
         if (!p) return nullptr;
         const size_t off = (uintptr_t)p / sizeof(float) - 1;
         const auto it = std::prev(std::upper_bound(starts.begin(), starts.end(), std::make_pair(off, INT32_MAX)));
-        if (!h.marked_tensor[it->second]) return g->d_arena + off;
-        return g->d_marked + (size_t)copy * g->mark_words + at[it->second] + (off - it->first);
+        if (h.mark_offset[it->second] == SIZE_MAX) return g->d_arena + off;
+        return g->d_marked + (size_t)copy * g->mark_words + h.mark_offset[it->second] + (off - it->first);
       });
       for (size_t i = 0; i < d.size(); ++i) {
         d[i].flags |= h.mark_flags[i];

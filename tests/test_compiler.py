@@ -633,3 +633,13 @@ def test_attention_tasks_of_a_head_are_in_the_order_of_their_chunks(kw, opts):
         B, n_kv = int(op["tb"]), int(kw.get("n_kv_heads", 2))
         per_head = place.reshape(B, n_kv, -1).transpose(1, 0, 2).reshape(n_kv, -1)   # [head][sequence, chunk]
         assert (np.diff(per_head, axis=1) > 0).all()
+
+
+def test_activation_bytes_count_the_copies_of_marked_tensors():
+    """Whole lines of 64 floats: every tensor once, in a graph with marks the marked ones twice more.  Tiny model at batch 1,
+    one chunk a head: QKV, partials and merged attention, O, gate/up, down of two layers."""
+    s = G.small_variant("C1")
+    plain = host_graph(s, fusion=31, transitive_reduction=1, n_workers=256, launch_mode=1).stats()["act_bytes"]
+    marked = host_graph(s, fusion=31, transitive_reduction=1, n_workers=256).stats()["act_bytes"]
+    layer = sum(-(-n // 64) * 64 for n in (8 * 64, 4 * (64 + 2), 4 * 64, 256, 688, 256))
+    assert marked - plain == 2 * 4 * 2 * layer
