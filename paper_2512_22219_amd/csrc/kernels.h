@@ -1712,7 +1712,7 @@ __device__ __forceinline__ float mfma_inv_rms(const float* ssq, uint32_t bb, uin
 // LDS of a linear task (from the task area): job buffers (mfma_x_floats) | ssq [8][16] f32 | arrival flag.  A job takes up to 512 weight rows; a task of more (batch 3 and 4:
 // an output head of more than 512 rows a worker, few tiles given) is worked off in several, the input staged
 // again for each.
-// PACK: the packing of the input terms, that of the graph's batch size (mfma_pack).
+// PACK: the packing of the input terms, that of the graph's batch class: 3 up to 4 rows, 2 up to 8, 1 up to 16 (run_linear).
 template <int PACK, bool MEGA, class Svc = NoJit>
 __device__ __forceinline__ uint32_t linear_task_mfma(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev,
                                                      uint32_t* s_flag, const Svc& svc = Svc{}) {

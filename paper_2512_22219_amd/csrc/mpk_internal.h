@@ -61,9 +61,9 @@ enum TaskFlags : uint16_t {
   TF_OUT_MARKED = 32768, // ... and so does its output: see kUnsetWord
 };
 
-// Marked tensors.  A consumer that learns from an event counter that its input is complete pays four trips
-// to the coherence point in a row: the producer's stores have to be acknowledged before it may notify, the
-// notification travels, a poll sees it, and only then is the input loaded.  In an all-ahead-of-time step
+// Marked tensors.  A consumer that learns from an event counter that its input is complete pays five trips
+// to the coherence point in a row: the producer's stores, their acknowledgement before it may notify, the
+// notification, a poll that sees it, and only then the load of the input.  In an all-ahead-of-time step
 // an activation tensor therefore says for itself which of its elements have been written: before the step
 // every word of it is kUnsetWord, a NaN pattern that no producer stores (mark_clean), and a consumer loads its input
 // at once and loads again what it finds unset.  The producer neither waits for its stores nor notifies.
