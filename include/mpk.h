@@ -381,7 +381,9 @@ enum {
   MPK_FORM_INPUT_MARKED = 1,    /* waits on the words of its input, not on its dependent event   */
   MPK_FORM_RESIDUAL_MARKED = 2, /* ... and on those of its residual                               */
   MPK_FORM_OUTPUT_MARKED = 4,   /* its consumers do: it triggers no event                         */
-  MPK_FORM_RESIDUAL = 8         /* a linear task that adds a residual                             */
+  MPK_FORM_RESIDUAL = 8,        /* a linear task that adds a residual                             */
+  MPK_FORM_PAGE_NEXT = 16,      /* loads the first weight rows of its worker's next task into LDS */
+  MPK_FORM_PAGE_READY = 32      /* finds its own there                                            */
 };
 mpk_status mpk_graph_task_forms(const mpk_graph *g, mpk_task_form *buf, size_t cap, size_t *need);
 

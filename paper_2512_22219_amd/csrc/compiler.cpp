@@ -1319,6 +1319,8 @@ static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_comp
     for (uint32_t qi = g.aot_off[w] + 1; qi + 1 < g.aot_off[w + 1]; ++qi) {
       const HostOp *prev = lin_op(g.aot[qi - 1]), *cur = lin_op(g.aot[qi]), *next = lin_op(g.aot[qi + 1]);
       if (!prev || !cur || !next) continue;
+      // (there is one set of pages: T's own have to be used up before N's are requested, and T requests them first of all)
+      if (plan[g.aot[qi]] & TF_PAGE_READY) continue;
       if (prev->layer != cur->layer || cur->layer != next->layer || cur->layer < 0) continue;
       // T is short (fits its two register buffers: nothing of its own left to stream while it waits)
       const uint64_t cur_rows = (uint64_t)cur->cols * ((cur->flags & TF_GATEUP) ? 2u : 1u) / cur->tc;
@@ -1582,7 +1584,8 @@ void task_forms(const HostGraph& g, mpk_task_form* out) {
     out[i].marks = ((marks & TF_IN_MARKED) ? MPK_FORM_INPUT_MARKED : 0u) | ((marks & TF_IN2_MARKED) ? MPK_FORM_RESIDUAL_MARKED : 0u) |
                    ((marks & TF_OUT_MARKED) ? MPK_FORM_OUTPUT_MARKED : 0u);
     if (t.kind != TK_LINEAR) continue;
-    if (t.flags & TF_EPI_RESID) out[i].marks |= MPK_FORM_RESIDUAL;
+    out[i].marks |= ((t.flags & TF_EPI_RESID) ? MPK_FORM_RESIDUAL : 0u) | ((t.flags & TF_PAGE_NEXT) ? MPK_FORM_PAGE_NEXT : 0u) |
+                    ((t.flags & TF_PAGE_READY) ? MPK_FORM_PAGE_READY : 0u);
     out[i].inputs = t.K;
     out[i].outputs = (t.b1 - t.b0) * (t.c1 - t.c0);
     if (g.cfg.batch < kMfmaMinBatch) out[i].packed = g.packed_rows ? lin_pack(t.K, (t.c1 - t.c0) << ((t.flags & TF_GATEUP) ? 1 : 0)) : 1u;

@@ -605,7 +605,7 @@ def test_which_operators_go_by_the_words_of_their_input(kw, opts, want):
     """Marks of every operator in order (1 input, 2 residual, 4 output marked, 8 has a residual); all tasks of an
     operator are alike."""
     ex, forms = _marks(G.small_variant("C1", **kw), **{**dict(fusion=31, transitive_reduction=1), **opts})
-    marks = [np.unique(forms["marks"][ex.tasks["op"] == oi]) for oi in range(len(ex.ops))]
+    marks = [np.unique(forms["marks"][ex.tasks["op"] == oi] & 15) for oi in range(len(ex.ops))]
     assert all(len(m) == 1 for m in marks)
     assert " ".join(str(m[0]) for m in marks) == want
 
@@ -643,3 +643,18 @@ def test_activation_bytes_count_the_copies_of_marked_tensors():
     marked = host_graph(s, fusion=31, transitive_reduction=1, n_workers=256).stats()["act_bytes"]
     layer = sum(-(-n // 64) * 64 for n in (8 * 64, 4 * (64 + 2), 4 * 64, 256, 688, 256))
     assert marked - plain == 2 * 4 * 2 * layer
+
+
+PAGE_CHAINS = [(dict(hidden=2056, ffn=152), 5), (dict(hidden=2056, ffn=144, n_layers=3), 5), (dict(hidden=2600, ffn=320, qk_norm=True), 13),
+               (dict(hidden=256, ffn=688), 5)]
+
+
+@pytest.mark.parametrize("kw,workers", PAGE_CHAINS)
+def test_no_task_both_uses_its_pages_and_fills_them_for_the_next(kw, workers):
+    """Few workers: a gate/up task short enough to fill its successor's pages and long enough to have some itself."""
+    ex, forms = _marks(G.small_variant("C1", **kw), fusion=31, transitive_reduction=1, n_workers=workers)
+    nxt, ready = (forms["marks"] & M.binding.FORM_PAGE_NEXT) != 0, (forms["marks"] & M.binding.FORM_PAGE_READY) != 0
+    assert ready.any() and nxt.sum() == ready.sum() and not (nxt & ready).any()
+    for w in range(workers):   # ... and every page is filled by the task before
+        mine = ex.aot[ex.aot_off[w]:ex.aot_off[w + 1]]
+        assert np.array_equal(nxt[mine][:-1], ready[mine][1:])
