@@ -719,6 +719,17 @@ static void choose_partitions(const mpk_model_config& c, const mpk_compile_optio
       if (p.kind == MPK_OP_ATTN_PARTIAL && p.out_tensor == op.in_tensor) return true;
     return false;
   };
+  // How many pairs of a task and a tile of its residual's producer there are with `tc` column tiles.
+  auto residual_pairs = [&](HostOp op, uint32_t tc) {
+    op.tc = tc;
+    uint32_t n = 0;
+    for (const HostOp& p : g.ops) {
+      if (p.out_tensor != op.in2_tensor) continue;
+      for (uint32_t i = 0; i < tc; ++i)
+        n += col_tile_of(p, (col_tile_begin(op, i + 1) * op.unit - 1) / p.unit) - col_tile_of(p, col_tile_begin(op, i) * op.unit / p.unit) + 1;
+    }
+    return n;
+  };
   for (auto& op : g.ops) {
     uint32_t nu = op.cols / op.unit;
     switch (op.kind) {
@@ -748,7 +759,11 @@ static void choose_partitions(const mpk_model_config& c, const mpk_compile_optio
           const uint32_t attn_tasks = c.batch * c.n_kv_heads * std::max(1u, o.attn_chunks);
           if (attn_tasks < W) {
             const uint32_t rows = (nu + (W - attn_tasks) - 1) / (W - attn_tasks), pairs = (rows + 1) / 2;
-            if ((pairs + 7) / 8 * ((op.K + 4095u) / 4096u) <= 2u && op.tc > W - attn_tasks) {
+            // Without transitive reduction an O projection task depends on its residual's producers as well, and dummy tasks tell
+            // apart which: tiles that cut those of the producers across make more of them than the rule gains (us a step, 6 layers,
+            // 256 tiles as the producer / 192: 8B 708 / 721, 1B class 423 / 434; 256 / 128, 2B class at batch 2: 456 / 372).
+            const bool cuts = !o.transitive_reduction && (op.flags & TF_EPI_RESID) && residual_pairs(op, W - attn_tasks) > residual_pairs(op, op.tc);
+            if ((pairs + 7) / 8 * ((op.K + 4095u) / 4096u) <= 2u && op.tc > W - attn_tasks && !cuts) {
               op.tc = W - attn_tasks;
               // Where gate/up tasks find their first rows in LDS pages, their tiles are sized by who ran attention: the same
               // workers in every layer, the next operator starts where it would have.  Elsewhere it starts

@@ -658,3 +658,17 @@ def test_no_task_both_uses_its_pages_and_fills_them_for_the_next(kw, workers):
     for w in range(workers):   # ... and every page is filled by the task before
         mine = ex.aot[ex.aot_off[w]:ex.aot_off[w + 1]]
         assert np.array_equal(nxt[mine][:-1], ready[mine][1:])
+
+
+@pytest.mark.parametrize("kw,tr,tiles", [
+    (dict(hidden=4096, n_q_heads=32, n_kv_heads=8, head_dim=128), 1, 192),          # the workers without one of 64 attention tasks
+    (dict(hidden=4096, n_q_heads=32, n_kv_heads=8, head_dim=128), 0, 256),          # ... would cut the 256 tiles of the residual across
+    (dict(hidden=2048, n_q_heads=16, n_kv_heads=8, head_dim=128, batch=2), 1, 128),
+    (dict(hidden=2048, n_q_heads=16, n_kv_heads=8, head_dim=128, batch=2), 0, 128),   # two of them each
+    (dict(hidden=2048, n_q_heads=32, n_kv_heads=4, head_dim=128, ffn=0, n_experts=128, top_k=8, expert_ffn=768), 0, 224),   # 8 combine tasks
+])
+def test_o_projection_beside_attention_does_not_cut_its_residual_across(kw, tr, tiles):
+    """Without transitive reduction, more pairs of an O projection task and a residual tile are more dummy tasks in its way."""
+    ex, forms = _marks(G.small_variant("C1", max_seq=1088, **kw), fusion=31, transitive_reduction=tr)
+    attn = [oi for oi, op in enumerate(ex.ops) if op["kind"] == TG.K_ATTN_PARTIAL]
+    assert int(ex.ops[attn[1] + 1]["n_tasks"]) == tiles      # (behind layer 0's, whose residual is the embedding)
