@@ -706,14 +706,26 @@ static uint64_t step_weight_bytes(const mpk_model_config& c) {
          (uint64_t)c.n_layers * 2 * (2ull * c.hidden + qkv_rows * c.hidden + (uint64_t)c.hidden * c.n_q_heads * c.head_dim +
                                      (c.n_experts ? (uint64_t)c.n_experts * c.hidden : 3ull * c.ffn * c.hidden));
 }
+// Weight rows a task needs to be given pages.  Three half blocks a wavefront; of packed rows more than two, where O projections run
+// beside attention: those tasks have all their rows requested by the time the pages would help, and the roles that
+// pages fix cost more (6 or 8 layers, us a step without / with: 64 rows, two a row, 128 attention tasks 301 / 317; 96 rows, four
+// a row, 258 / 267; 70 and 86 rows, two a row, 342 / 329 and 406 / 378).  Elsewhere as many rows as others (the operators in
+// between leave time to fill pages: 64 rows, two a row, 439 / 420 with nothing but norms, residuals and gates fused).
+static uint32_t page_rows(const HostGraph& g, uint32_t pack) {
+  return pack > 1u && g.merges_attention ? 32u * pack + 1u : 48u;
+}
 static void choose_partitions(const mpk_model_config& c, const mpk_compile_options& o,
                               HostGraph& g) {
   const uint32_t W = o.n_workers;
   g.large_tasks = step_weight_bytes(c) / std::max(1u, c.n_layers) / std::max(1u, W) >= (3u << 20);
   // (no set packs rows and has a third weight buffer or experts; whatever is sized by packing asks here)
   const bool may_pack = c.batch < kMfmaMinBatch && !c.n_experts && !g.large_tasks;
+  for (const HostOp& op : g.ops) {
+    if (op.kind != MPK_OP_ATTN_PARTIAL) continue;
+    for (const HostOp& r : g.ops) g.merges_attention = g.merges_attention || (r.kind == MPK_OP_LINEAR && r.in_tensor == op.out_tensor);
+  }
   bool pages_likely = false;   // (page_plan looks more closely)
-  for (const auto& op : g.ops) pages_likely = pages_likely || (op.kind == MPK_OP_GATEUP && page_capable(c, o) && op.K <= 4096 && (uint64_t)op.cols * 2 >= 48ull * (may_pack ? lin_pack(op.K, op.cols * 2 / W) : 1u) * W);
+  for (const auto& op : g.ops) pages_likely = pages_likely || (op.kind == MPK_OP_GATEUP && page_capable(c, o) && op.K <= 4096 && (uint64_t)op.cols * 2 >= (uint64_t)page_rows(g, may_pack ? lin_pack(op.K, op.cols * 2 / W) : 1u) * W);
   auto after_attention = [&](const HostOp& op) {   // reads what attention tasks have merged
     for (const HostOp& p : g.ops)
       if (p.kind == MPK_OP_ATTN_PARTIAL && p.out_tensor == op.in_tensor) return true;
@@ -1318,8 +1330,7 @@ static size_t lin_task_floats_b1(const HostGraph& g, const HostOp& op) {
 // their worker's list (Section 5.3, pre-loading across tasks).  A pair (T, N) of consecutive linear
 // tasks of one worker qualifies when T comes right after another linear task (so the worker is not
 // one that just ran an attention task: it has the whole attention phase to wait through), T and N
-// both leave room for the pages in LDS, and N is long enough to gain (more than two half blocks
-// per wavefront).  Returns, per task of the linearized list, 0, TF_PAGE_NEXT or TF_PAGE_READY.
+// both leave room for the pages in LDS, and N is long enough to gain (page_rows).  Returns, per task of the linearized list, 0, TF_PAGE_NEXT or TF_PAGE_READY.
 static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_compile_options& o, const HostGraph& g) {
   std::vector<uint16_t> plan(g.tasks.size(), 0);
   if (!page_capable(c, o)) return plan;
@@ -1341,7 +1352,7 @@ static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_comp
       const uint64_t cur_rows = (uint64_t)cur->cols * ((cur->flags & TF_GATEUP) ? 2u : 1u) / cur->tc;
       const uint64_t next_rows = (uint64_t)next->cols * ((next->flags & TF_GATEUP) ? 2u : 1u) / next->tc;
       if (cur_rows * cur->K * 2 > 256 * 1024) continue;
-      if (next->K > 4096 || next_rows < 48 * (g.packed_rows ? lin_pack(next->K, (uint32_t)next_rows) : 1u) || (next->flags & TF_SPLITK) || next->seg_tiles) continue;
+      if (next->K > 4096 || next_rows < page_rows(g, g.packed_rows ? lin_pack(next->K, (uint32_t)next_rows) : 1u) || (next->flags & TF_SPLITK) || next->seg_tiles) continue;
       if (lin_task_floats_b1(g, *cur) > room || lin_task_floats_b1(g, *next) > room) continue;
       plan[g.aot[qi]] |= TF_PAGE_NEXT;
       plan[g.aot[qi + 1]] |= TF_PAGE_READY;

@@ -241,6 +241,7 @@ struct HostGraph {
   uint32_t lin_rows_max = 0;       // largest weight-row count of one linear task (gate/up pairs twice)
   bool large_tasks = false;        // 3 MB or more of weights per worker and layer (8B shape: 1.6 MB, 70B shape: 6.8 MB)
   bool packed_rows = false;        // some operator of a layer has tasks with packed weight rows (lin_pack), and the kernel set packs
+  bool merges_attention = false;   // attention tasks merge, O projections wait for them
   uint32_t lin_page_off = 0;       // float offset (in the task area of the LDS) of the pre-load pages, 0 = none
   std::vector<size_t> moe_meta_offset;   // per MoE layer: float offset of its meta-tensor in the arena
   std::vector<double> inv_freq;    // RoPE frequencies theta^(-2i/d), i < d/2

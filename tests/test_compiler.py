@@ -672,3 +672,19 @@ def test_o_projection_beside_attention_does_not_cut_its_residual_across(kw, tr, 
     ex, forms = _marks(G.small_variant("C1", max_seq=1088, **kw), fusion=31, transitive_reduction=tr)
     attn = [oi for oi, op in enumerate(ex.ops) if op["kind"] == TG.K_ATTN_PARTIAL]
     assert int(ex.ops[attn[1] + 1]["n_tasks"]) == tiles      # (behind layer 0's, whose residual is the embedding)
+
+
+@pytest.mark.parametrize("kw,fusion,pages", [
+    (dict(hidden=2048, ffn=8192, n_q_heads=32, n_kv_heads=8), 31, False),    # 64 rows a gate/up task, two a row: two half blocks
+    (dict(hidden=2048, ffn=8192, n_q_heads=32, n_kv_heads=8), 7, True),
+    (dict(hidden=1536, ffn=8960, n_q_heads=16, head_dim=128), 31, True),     # 70 rows
+    (dict(hidden=768, ffn=12288, n_q_heads=16, n_kv_heads=4), 31, False),    # 96 rows, four a row
+    (dict(hidden=768, ffn=12288, n_q_heads=16, n_kv_heads=4), 7, True),
+    (dict(hidden=4096, ffn=6144, n_q_heads=32, n_kv_heads=8), 31, True),     # 48 rows, one a row
+    (dict(hidden=4096, ffn=6016, n_q_heads=32, n_kv_heads=8), 31, False),    # 47
+])
+def test_rows_from_which_on_tasks_have_pages(kw, fusion, pages):
+    ex, forms = _marks(G.small_variant("C1", max_seq=1088, **kw), fusion=fusion, transitive_reduction=1)
+    gateup = [oi for oi, op in enumerate(ex.ops) if op["kind"] == TG.K_GATEUP]
+    for oi in gateup:
+        assert (forms["marks"][ex.tasks["op"] == oi] & M.binding.FORM_PAGE_READY).any() == pages
