@@ -390,7 +390,8 @@ mpk_status mpk_graph_task_forms(const mpk_graph *g, mpk_task_form *buf, size_t c
 /* Per-task timeline of the LAST decode step of a graph compiled with MPK_DEBUG_TRACE (the
  * counterpart of the paper's run-time overhead accounting, Section 6.5 "kernel-launch
  * reduction").  buf: host u64 [n_tasks][12] in linearized task order, ticks of the 100 MHz device
- * wall clock unless noted: 0 task picked up, 1 dependent event seen, 2 input staged (linear and
+ * wall clock unless noted: 0 task picked up, 1 dependent event seen (a task that goes by the words of its
+ * input, see mpk_task_form: its weights have been requested), 2 input staged (linear and
  * attention tasks), 3 body finished (first wavefront), 4 triggering event notified, 5 worker
  * index (not a time), 6 first wavefront's stores completed, 7 all wavefronts' stores completed,
  * 8 multiply phase finished (matrix-core linear tasks), 10 attention: this task's partial result
