@@ -85,8 +85,9 @@ struct mpk_graph {
   int device = -1;
   // device allocations
   TaskDesc* d_tasks = nullptr;
-  TaskDesc* d_tasks_marked[2] = {nullptr, nullptr};   // the same for launches that use marked tensors (kUnsetWord), even and odd steps
-  float* d_marked = nullptr;     // their two copies of the marked tensors, mark_words each
+  TaskDesc* d_tasks_marked[2] = {nullptr, nullptr};   // the same for launches that use marked tensors (kUnsetWord), even and odd
+                                 // steps, behind d_tasks
+  float* d_marked = nullptr;     // their two copies of the marked tensors, mark_words each, behind the rope table
   size_t mark_words = 0;
   EventDesc* d_events = nullptr;
   uint32_t* d_counters = nullptr;
@@ -140,7 +141,6 @@ struct mpk_graph {
 
 static void free_device(mpk_graph* g) {
   if (g->host_only) return;
-  (void)hipFree(g->d_tasks_marked[0]); (void)hipFree(g->d_tasks_marked[1]); (void)hipFree(g->d_marked);
   (void)hipFree(g->d_tasks); (void)hipFree(g->d_events); (void)hipFree(g->d_counters);
   (void)hipFree(g->d_aot_off); (void)hipFree(g->d_aot); (void)hipFree(g->d_op_list);
   (void)hipFree(g->d_err); (void)hipFree(g->d_arena);
@@ -318,13 +318,16 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     return fail(MPK_ERR_RESIDENCY);
   }
   // activation arena + relocation of the descriptors
-  const size_t rope_at = std::max<size_t>(h.arena_floats, 64);   // the rope table sits behind the activations
-  const size_t arena_bytes = (rope_at + 2 * (size_t)cfg->batch * cfg->head_dim) * sizeof(float);
+  // (the rope table sits behind the activations, the copies of the marked tensors behind it: one allocation, two fills)
+  const size_t rope_at = std::max<size_t>(h.arena_floats, 64);
+  g->rope_words = 2 * (size_t)cfg->batch * cfg->head_dim;
+  g->mark_words = h.mark_flags.empty() ? 0 : h.mark_words;
+  const size_t mark_at = (rope_at + g->rope_words + 63) / 64 * 64, arena_bytes = (mark_at + 2 * g->mark_words) * sizeof(float);
   e = hipMalloc((void**)&g->d_arena, arena_bytes);
   if (e != hipSuccess) { set_error("hipMalloc(%zu) for activations failed: %s", arena_bytes, hipGetErrorString(e)); return fail(MPK_ERR_OOM); }
   g->d_rope = g->d_arena + rope_at;
-  g->rope_words = 2 * (size_t)cfg->batch * cfg->head_dim;
-  if (hipMemset(g->d_arena, 0, arena_bytes) != hipSuccess || hipMemset(g->d_rope, 0xFF, g->rope_words * sizeof(float)) != hipSuccess) { set_error("hipMemset failed"); return fail(MPK_ERR_HIP); }
+  if (g->mark_words) g->d_marked = g->d_arena + mark_at;
+  if (hipMemset(g->d_arena, 0, rope_at * sizeof(float)) != hipSuccess || hipMemset(g->d_rope, 0xFF, arena_bytes - rope_at * sizeof(float)) != hipSuccess) { set_error("hipMemset failed"); return fail(MPK_ERR_HIP); }
   std::vector<TaskDesc> descs = h.descs;
   auto reloc = [&](const float* p) -> const float* {
     if (!p) return nullptr;
@@ -356,11 +359,8 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
     std::vector<std::pair<size_t, int>> starts;   // first word of a tensor in the arena, the tensor
     for (size_t i = 0; i < h.tensors.size(); ++i)
       if (h.tensors[i].offset != SIZE_MAX) starts.emplace_back(h.tensors[i].offset, (int)i);
-    g->mark_words = h.mark_words;
     std::sort(starts.begin(), starts.end());
-    e = hipMalloc((void**)&g->d_marked, 2 * g->mark_words * sizeof(float));
-    if (e != hipSuccess) { set_error("hipMalloc(%zu) for activations failed: %s", 2 * g->mark_words * sizeof(float), hipGetErrorString(e)); return fail(MPK_ERR_OOM); }
-    if (hipMemset(g->d_marked, 0xFF, 2 * g->mark_words * sizeof(float)) != hipSuccess) { set_error("hipMemset failed"); return fail(MPK_ERR_HIP); }
+    descs.reserve(3 * h.descs.size());
     for (int copy = 0; copy < 2; ++copy) {
       std::vector<TaskDesc> d = h.descs;
       relocate(d, [&](const float* p) -> const float* {
@@ -377,7 +377,7 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
         d[i].trig_event = -1;   // nobody waits for the events of marked outputs
       }
       name_counters(d);
-      if ((st = upload(&g->d_tasks_marked[copy], d)) != MPK_OK) return fail(st);
+      descs.insert(descs.end(), d.begin(), d.end());
     }
   }
   // per-operator task lists (baseline launch mode)
@@ -396,6 +396,8 @@ extern "C" mpk_status mpk_compile(const mpk_model_config* cfg, const mpk_weight_
   }
   std::vector<uint32_t> zeros(h.events.size(), 0), err(8, 0);
   if ((st = upload(&g->d_tasks, descs)) != MPK_OK) return fail(st);
+  if (g->mark_words)
+    for (int copy = 0; copy < 2; ++copy) g->d_tasks_marked[copy] = g->d_tasks + (copy + 1) * h.descs.size();
   if ((st = upload(&g->d_events, h.events)) != MPK_OK) return fail(st);
   if ((st = upload(&g->d_counters, zeros)) != MPK_OK) return fail(st);
   if ((st = upload(&g->d_aot_off, h.aot_off)) != MPK_OK) return fail(st);
