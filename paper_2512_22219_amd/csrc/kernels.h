@@ -266,7 +266,8 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 // pairs of inputs u * 512 + 64 w + i, u after u, and the lanes are added by wave_sum_dpp.  Sums of squares reach every
 // output of a projection, and a last bit of them decides which way appended bf16 rows round: a wider load must not
 // move them.  A load's lower 32 lanes hold an even u, the upper ones the next, lane l (of 32) the pairs of lanes
-// 2 l and 2 l + 1: lower lane l sums for lane 2 l, upper lane l for lane 2 l + 1, after an exchange of halves.
+// 2 l and 2 l + 1: lower lane l sums for lane 2 l, upper lane l for lane 2 l + 1, after an exchange of halves.  us a step,
+// four neighbouring inputs a thread / this: tiny model 41.6 / 42.1, 8B 2746 / 2755, 1B class 629 / 636.
 struct SumSq {
   float s = 0.f;
   __device__ __forceinline__ void add(const float4& v) {
@@ -293,7 +294,8 @@ struct SumSq {
   }
 };
 // Four sums at once, each as wave_sum_dpp adds it up: every lane of the wavefront's row r of 16 lanes gets that of value r
-// (sums of each row, then neighbouring rows of two values, and halves of two such pairs, put side by side by a swap and added).
+// (sums of each row, then neighbouring rows of two values, and halves of two such pairs, put side by side by a swap and added.
+// 22 vector operations; with the swaps first, which is another order, 10: 2B class at batch 2, four tokens 2110 us, now 2166).
 __device__ __forceinline__ float wave_sum4(float v0, float v1, float v2, float v3) {
   auto dpp = [](float x, auto ctrl) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));

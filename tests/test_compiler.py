@@ -534,7 +534,7 @@ def test_expert_shares_are_the_same_in_32_and_in_64_bits(n_active, tiles, n_task
 
 
 def _marks(shape, **opts):
-    """Per operator kind of the first layer (and the head): the set of its tasks' marks; and all (export, forms)."""
+    """Export and task forms of a graph for 256 workers."""
     g = host_graph(shape, **{**dict(n_workers=256), **opts})
     return g.export(), g.task_forms()
 
