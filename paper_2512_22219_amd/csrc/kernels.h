@@ -1277,8 +1277,8 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
 //     (Two terms leave x to 2^-18: logits near zero then miss the element-wise bound.)
 //   D: lane l holds batch column (l % 16), tile rows 4 (l / 16) .. + 3.
 // The input is staged in LDS as fp32, whole when it fits (4096 inputs up to batch 8, 2048 above;
-// longer inputs in chunks of that size), row stride padded by 128 bytes so that the lanes of a
-// fragment spread evenly over the banks; the wavefronts split it into the three terms as they go,
+// longer inputs in chunks of that size), the row stride padded (mfma_row_pad) so that the lanes of a
+// fragment spread over the banks; the wavefronts split it into the three terms as they go,
 // so no barrier separates the staging of one part from the multiplies of another.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -1367,6 +1367,74 @@ __device__ __forceinline__ void split8(const float4& p, const float4& q, u32x4* 
 __device__ __forceinline__ u32x4 select4(bool c, const u32x4& x, const u32x4& y) {
   return u32x4{c ? x.x : y.x, c ? x.y : y.y, c ? x.z : y.z, c ? x.w : y.w};
 }
+// `src` of the lane N before this one in its row of 16 lanes (N = 0: of this lane), in the lanes of the fours of a row that
+// BANKS names (bit k: lanes 4 k .. 4 k + 3); `old` in the others.
+template <int N, int BANKS>
+__device__ __forceinline__ uint32_t row_lanes(uint32_t old, uint32_t src) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)src, N ? 0x120 + N : 0xE4, 0xF, BANKS, false);
+}
+// The activation operands of a k-group's two multiplies (U = 0, 1), with PACK terms side by side in the columns, from the
+// group's 16 inputs that the multiplies want of this lane's row: at `src` those that this lane splits, and their gains if `norm`.
+// Every number is split once: the 16 / PACK-fold lanes that hold one row in different column groups share its 16 inputs and
+// hand the terms round.
+//   PACK 2: columns 0..7 (hi) split the first multiply's 8 inputs, columns 8..15 (mid) the second's
+//   PACK 3: column group q of four splits inputs 4 q .. 4 q + 3 of the 16
+// (Splitting all 16 in every lane and keeping one term was 128 vector instructions a k-group and wavefront, now 76 and
+// 54, and as many reads of the LDS more; two wavefronts share a SIMD, and a projection of 4096 inputs has 8 k-groups a wavefront
+// between its input and its last multiply.)
+// us a step before / after: 4B class at batch 4 794 / 746, 8B layers at batch 8 1037 / 1005, serving burst 8512 / 8170, odd
+// sizes at batch 5 494 / 463, mixture of experts at batch 1 860 / 837; the operands, and so the results, are the same bits.
+constexpr uint32_t mfma_split_at(int pack, uint32_t col) { return pack == 2 ? 8u * (col >> 3) : pack == 3 ? 4u * (col >> 2) : 0u; }
+template <int PACK>
+struct MfmaOperands {
+  u32x4 first[2], second[2], third[2];   // (second: PACK 1 and 2; third: PACK 1)
+  __device__ __forceinline__ void load(const float* src, const uint16_t* gain, bool norm) {
+    constexpr int N = PACK == 1 ? 2 : 1;   // runs of 8 (PACK 3: 4) inputs of this lane's own
+#pragma unroll
+    for (int U = 0; U < N; ++U) {
+      float4 x0 = *(const float4*)(src + 8 * U), x1 = x0;
+      if (PACK != 3) x1 = *(const float4*)(src + 8 * U + 4);
+      if (norm) {
+        u32x4 gg;
+        if (PACK != 3) {
+          gg = *(const u32x4*)(gain + 8 * U);
+        } else {
+          const u32x2 g2 = *(const u32x2*)gain;
+          gg = u32x4{g2.x, g2.y, 0u, 0u};
+        }
+        x0.x *= bf16_lo(gg.x); x0.y *= bf16_hi(gg.x); x0.z *= bf16_lo(gg.y); x0.w *= bf16_hi(gg.y);
+        if (PACK != 3) { x1.x *= bf16_lo(gg.z); x1.y *= bf16_hi(gg.z); x1.z *= bf16_lo(gg.w); x1.w *= bf16_hi(gg.w); }
+      }
+      if (PACK != 3) {
+        u32x4 h, m, l;
+        split8(x0, x1, &h, &m, &l);
+        if (PACK == 1) {
+          first[U] = h; second[U] = m; third[U] = l;
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            first[0][k] = row_lanes<8, 0xC>(h[k], m[k]);    // hi of its own half | mid of the other lane's
+            first[1][k] = row_lanes<8, 0x3>(m[k], h[k]);
+            second[0][k] = l[k];                            // (the second multiply's columns 8..15 are not results)
+            second[1][k] = row_lanes<8, 0xF>(l[k], l[k]);
+          }
+        }
+      } else {
+        uint32_t h[2], m[2], l[2];
+        split_hi_mid_lo(x0.x, x0.y, &h[0], &m[0], &l[0]);
+        split_hi_mid_lo(x0.z, x0.w, &h[1], &m[1], &l[1]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          // words k and 2 + k of a multiply come from column groups 2 U and 2 U + 1; columns 12..15 repeat lo
+          first[0][k] = row_lanes<4, 0x2>(row_lanes<0, 0x1>(row_lanes<8, 0xF>(l[k], l[k]), h[k]), m[k]);
+          first[0][2 + k] = row_lanes<0, 0x2>(row_lanes<12, 0x1>(row_lanes<4, 0xF>(l[k], l[k]), h[k]), m[k]);
+          first[1][k] = row_lanes<12, 0x2>(row_lanes<8, 0x1>(l[k], h[k]), m[k]);
+          first[1][2 + k] = row_lanes<8, 0x2>(row_lanes<4, 0x1>(row_lanes<12, 0xF>(l[k], l[k]), h[k]), m[k]);
+        }
+      }
+    }
+  }
+};
 
 // A pair of loads of 8 rows x 128 bytes (lane l: row l % 8 of rows 0..7 / 8..15, 16-byte block l / 8)
 // -> the two matrix operands of the pair (lane = row + 16 x input group), in place; the derivation
@@ -1406,7 +1474,7 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t K = G.K, nb = G.nb, nrt = G.nrt;
-  constexpr uint32_t Kc = mfma_kchunk(PACK == 1 ? 16u : PACK == 2 ? 8u : 4u), xstride = Kc + kMfmaXPad;   // inputs per chunk, floats between staged rows
+  constexpr uint32_t Kc = mfma_kchunk(PACK == 1 ? 16u : PACK == 2 ? 8u : 4u), xstride = Kc + mfma_row_pad(PACK);   // inputs per chunk, floats between staged rows
   static_assert(mfma_kchunk(1) == mfma_kchunk(4) && mfma_kchunk(5) == mfma_kchunk(8) && mfma_kchunk(9) == mfma_kchunk(16), "the chunk follows from the packing");
   // (Every quotient below is by a power of two, and a shift: the compiler does not know it of a variable, and a
   // division is some thirty instructions, several of them in every round.)
@@ -1554,9 +1622,11 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
       if ((uint32_t)lane == r) rowsum += sq;
     }
   };
-  // this lane's staged row and which term its column takes in the first multiply
+  // this lane's staged row, and its inputs of a k-group (operand U: input block 2 j + U)
   const uint32_t xrow = min(PACK == 1 ? frow : (PACK == 2 ? (frow & 7u) : (frow & 3u)), nb - 1u);
-  const float* xl = xs + (size_t)xrow * xstride + 2u * fk;   // (operand U of a k-group: input block 2 j + U)
+  const uint32_t xat = 2u * fk + mfma_split_at(PACK, frow);
+  const float* xl = xs + (size_t)xrow * xstride + xat;
+  const uint16_t* gx = gl + xat;
   f32x4 acc[4], acc_lo[4];   // (acc_lo: the lo term's products when PACK == 2)
   // one round slot: multiplies what buf holds for slot (c, i) -- fragment u of every slot group
   // against the three terms of that fragment's inputs, converted once per k-group -- and then
@@ -1566,37 +1636,24 @@ __device__ __forceinline__ uint32_t mfma_job_packed(const StepArgs& a, const Tas
     if (kg0 < hi) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) pair_to_operands(buf[FR * q], buf[FR * q + 1]);
-      static_for<0, (int)FR>([&](auto Uc) {
-        constexpr uint32_t U = (uint32_t)decltype(Uc)::value;
-        u32x4 p0, p1, p2;   // operands of the first, second, third multiply
-        static_for<0, 4>([&](auto Qc) {
-          constexpr uint32_t Q = (uint32_t)decltype(Qc)::value;
-          const uint32_t kg = kg0 + (Q >> sh);
-          const bool rowok = kgpr == 1u ? Q < nrtw : true;
-          if (kg < hi && rowok) {
-            if (Q == 0u || (Q >> sh) != ((Q - 1u) >> sh)) {   // first slot group of its k-group
-              const float* src = xl + kg * KG + U * 8u;
-              float4 x0 = *(const float4*)src, x1 = *(const float4*)(src + 4);
-              if (pro_norm) {
-                const u32x4 gg = *(const u32x4*)(gl + kg * KG + 2u * fk + U * 8u);
-                x0.x *= bf16_lo(gg.x); x0.y *= bf16_hi(gg.x); x0.z *= bf16_lo(gg.y); x0.w *= bf16_hi(gg.y);
-                x1.x *= bf16_lo(gg.z); x1.y *= bf16_hi(gg.z); x1.z *= bf16_lo(gg.w); x1.w *= bf16_hi(gg.w);
-              }
-              u32x4 h, m, l;
-              split8(x0, x1, &h, &m, &l);
-              if (PACK == 1) { p0 = h; p1 = m; p2 = l; }
-              if (PACK == 2) { p0 = select4(frow < 8u, h, m); p1 = l; }
-              if (PACK == 3) p0 = select4(frow < 4u, h, select4(frow < 8u, m, l));
-            }
+      MfmaOperands<PACK> op;
+      static_for<0, 4>([&](auto Qc) {
+        constexpr uint32_t Q = (uint32_t)decltype(Qc)::value;
+        const uint32_t kg = kg0 + (Q >> sh);
+        const bool rowok = kgpr == 1u ? Q < nrtw : true;
+        if (kg < hi && rowok) {
+          if (Q == 0u || (Q >> sh) != ((Q - 1u) >> sh)) op.load(xl + kg * KG, gx + kg * KG, pro_norm);   // first slot group of its k-group
+#pragma unroll
+          for (uint32_t U = 0; U < FR; ++U) {
             const bf16x8 av = __builtin_bit_cast(bf16x8, buf[FR * Q + U]);
-            acc[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, p0), acc[Q], 0, 0, 0);
-            if (PACK == 2) acc_lo[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, p1), acc_lo[Q], 0, 0, 0);
+            acc[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, op.first[U]), acc[Q], 0, 0, 0);
+            if (PACK == 2) acc_lo[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, op.second[U]), acc_lo[Q], 0, 0, 0);
             if (PACK == 1) {
-              acc[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, p1), acc[Q], 0, 0, 0);
-              acc[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, p2), acc[Q], 0, 0, 0);
+              acc[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, op.second[U]), acc[Q], 0, 0, 0);
+              acc[Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, op.third[U]), acc[Q], 0, 0, 0);
             }
           }
-        });
+        }
       });
     }
     request_round(buf, c2, i2);
