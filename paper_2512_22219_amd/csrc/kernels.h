@@ -555,6 +555,14 @@ __device__ __noinline__ void mark_report(uint32_t event) {
   }
 }
 
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
 // ------------------------------------------------------------------------------ linear tasks
 // T2/T6/T9/T11/T14: y[b][c] = sum_j W[c][j] x[b][j] for output columns [c0, c1), all batch rows
 // at once, with optional fused stages: RMSNorm of the input (TF_PRO_NORM), residual add
@@ -708,8 +716,34 @@ template <bool PACKED>
 __device__ __forceinline__ bool lin_full(const LinGeom<PACKED>& g, const LinHalf& B) {   // 4096 inputs in a row of memory, twice
   return B.seglen * g.pack() == kSegLen && B.n[0] == g.pack() && B.n[1] == g.pack();
 }
-// Requests a half block, stage by stage.
+// Stages of a half block that hold inputs: past the end of a short row (or of a long row's last segment) there are only
+// zeros to multiply by.  A projection of 256 inputs spent 0.6 of its 3.6 us on those, one of 2048 in tasks of a few rows 0.3 of 3.3.  us a
+// step with all stages / without: tiny model 41.9 / 36.9, 1B class 637 / 631, 2B class at batch 2, four tokens 2165 / 2113, mixture of
+// experts at batch 1 839 / 819.
 template <bool PACKED>
+__device__ __forceinline__ uint32_t lin_stages(const LinGeom<PACKED>& g, const LinHalf& B) {
+  return g.pack() > 1u ? (uint32_t)kRingStages : (B.seglen + 511u) / 512u;
+}
+// f(0) .. f(n - 1), and up to the next power of two that is at least LEAST.
+template <int LEAST, class F>
+__device__ __forceinline__ void lin_each_stage(uint32_t n, F&& f) {
+  static_for<0, LEAST>(f);
+  if constexpr (LEAST < kRingStages) {
+    if (n > (uint32_t)LEAST) {
+      static_for<LEAST, 2 * LEAST>(f);
+      if constexpr (2 * LEAST < kRingStages) {
+        if (n > 2u * LEAST) {
+          static_for<2 * LEAST, 4 * LEAST>(f);
+          if constexpr (4 * LEAST < kRingStages) {
+            if (n > 4u * LEAST) static_for<4 * LEAST, 8 * LEAST>(f);
+          }
+        }
+      }
+    }
+  }
+}
+// Requests a half block, stage by stage.
+template <int LEAST, bool PACKED>
 __device__ __forceinline__ void lin_request(const LinGeom<PACKED>& g, const LinHalf& B, HalfRing& ring, int lane) {
   if (lin_full(g, B)) {   // one base address per row, constant stage offsets
 #pragma unroll
@@ -717,10 +751,11 @@ __device__ __forceinline__ void lin_request(const LinGeom<PACKED>& g, const LinH
 #pragma unroll
       for (int i = 0; i < kHalfRows; ++i) ring.s[i][u] = ld_stream16(B.p[i] + lane * 8 + u * 512);
   } else {
-#pragma unroll
-    for (int u = 0; u < kRingStages; ++u)
+    lin_each_stage<LEAST>(lin_stages(g, B), [&](auto uc) {
+      constexpr int u = decltype(uc)::value;
 #pragma unroll
       for (int i = 0; i < kHalfRows; ++i) ring.s[i][u] = ld_stream16(lin_lane(g, B, i, u, lane));
+    });
   }
 }
 
@@ -740,21 +775,34 @@ __device__ __forceinline__ void lin_chain(int u, uint32_t pack, float (&acc)[kHa
       for (int b = 0; b < NB; ++b) acc[i][q][b] = goes_on ? acc[i][from][b] : 0.f;
   }
 }
-// Adds the half block's partial dot products to acc.
-template <int NB, int NG>   // NG: sums per half-block row, of 8 / NG stages each
-__device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ring, const float* xs, uint32_t Kp,
-                                            int lane, uint32_t pack, float (&acc)[kHalfRows][NG][NB]) {
-#pragma unroll
-  for (int u = 0; u < kRingStages; ++u) {
+// Adds the half block's partial dot products to acc; w(i, u): this lane's weights of stage u of half-block row i.
+template <int LEAST, int NB, int NG, class Weights>   // NG: sums per half-block row, of 8 / NG stages each
+__device__ __forceinline__ void lin_consume_from(const LinHalf& B, Weights w, const float* xs, uint32_t Kp,
+                                                 int lane, uint32_t pack, uint32_t stages, float (&acc)[kHalfRows][NG][NB]) {
+  lin_each_stage<LEAST>(stages, [&](auto uc) {
+    constexpr int u = decltype(uc)::value;
     lin_chain<NB, NG>(u, pack, acc);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const float4* xp = (const float4*)(xs + (size_t)b * Kp + B.seg * kSegLen + u * 512 + lane * 8);
       const float4 x0 = xp[0], x1 = xp[1];
 #pragma unroll
-      for (int i = 0; i < kHalfRows; ++i) acc[i][u * NG / kRingStages][b] = dot8(ring.s[i][u], x0, x1, acc[i][u * NG / kRingStages][b]);
+      for (int i = 0; i < kHalfRows; ++i) acc[i][u * NG / kRingStages][b] = dot8(w(i, u), x0, x1, acc[i][u * NG / kRingStages][b]);
+    }
+  });
+  if constexpr (NG > 1) {   // (a row's sum is that of the last stages)
+    if (stages <= 4u) {
+#pragma unroll
+      for (int i = 0; i < kHalfRows; ++i)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[i][NG - 1][b] = LEAST <= 2 && stages <= 2u ? acc[i][0][b] : acc[i][1][b];
     }
   }
+}
+template <int LEAST, int NB, int NG>
+__device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ring, const float* xs, uint32_t Kp,
+                                            int lane, uint32_t pack, uint32_t stages, float (&acc)[kHalfRows][NG][NB]) {
+  lin_consume_from<LEAST, NB, NG>(B, [&](int i, int u) -> const u32x4& { return ring.s[i][u]; }, xs, Kp, lane, pack, stages, acc);
 }
 
 // LDS pre-load pages (paper Section 5.3: data of a task that has not started yet is pre-loaded into
@@ -764,28 +812,17 @@ __device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ri
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 template <bool PACKED>
 __device__ __forceinline__ void lin_request_page(const LinGeom<PACKED>& g, const LinHalf& B, u32x4* page, int lane) {
-#pragma unroll
-  for (int u = 0; u < kRingStages; ++u) {
+  lin_each_stage<1>(lin_stages(g, B), [&](auto uc) {
+    constexpr int u = decltype(uc)::value;
 #pragma unroll
     for (int i = 0; i < kHalfRows; ++i)
       __builtin_amdgcn_global_load_lds(as_global((const u32x4*)lin_lane(g, B, i, u, lane)), (lds_ptr_t)(page + (i * kRingStages + u) * 64), 16, 0, 0);
-  }
+  });
 }
-template <int NB, int NG>
+template <int LEAST, int NB, int NG>
 __device__ __forceinline__ void lin_consume_page(const LinHalf& B, const u32x4* page, const float* xs, uint32_t Kp,
-                                                 int lane, uint32_t pack, float (&acc)[kHalfRows][NG][NB]) {
-#pragma unroll
-  for (int u = 0; u < kRingStages; ++u) {
-    lin_chain<NB, NG>(u, pack, acc);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const float4* xp = (const float4*)(xs + (size_t)b * Kp + B.seg * kSegLen + u * 512 + lane * 8);
-      const float4 x0 = xp[0], x1 = xp[1];
-#pragma unroll
-      for (int i = 0; i < kHalfRows; ++i)
-        acc[i][u * NG / kRingStages][b] = dot8(page[(i * kRingStages + u) * 64 + lane], x0, x1, acc[i][u * NG / kRingStages][b]);
-    }
-  }
+                                                 int lane, uint32_t pack, uint32_t stages, float (&acc)[kHalfRows][NG][NB]) {
+  lin_consume_from<LEAST, NB, NG>(B, [&](int i, int u) { return page[(i * kRingStages + u) * 64 + lane]; }, xs, Kp, lane, pack, stages, acc);
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() carries a release fence, for
@@ -913,6 +950,10 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   float* res_lds = outbuf + (size_t)rows_max * NB;   // [rows_max][NB]
   float* ssq = res_lds + (size_t)rows_max * NB;      // [8][NB]
   constexpr int NG = PACKED ? 4 : 1;
+  // How finely the stages of a short half block are left out.  Requests behind branches cannot be counted (see
+  // ld_stream16_ranged), and packed kernels of one row are better off with all of them (1B class at batch 1 639 us a step with
+  // requests left out, 628 without; multiplies left out one stage, two and four at a time 640, four only 628).
+  constexpr int kLeast = PACKED && NB == 1 ? 4 : 1, kLeastAsked = PACKED && NB == 1 ? kRingStages : 1;
   const auto g = lin_geom<PACKED>(t, wave);
   HalfRing h0, h1;   // local to the task: nothing is live around the task loop, so they stay in registers
   ring_clear(h0);
@@ -978,7 +1019,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // (the waits are builtins, one on each path: the compiler's own count of the loads in flight does not survive the
   // branches around the requests)
   if (preload && lin_valid(g, rq)) {
-    lin_request(g, lin_half(g, rq), h0, lane);
+    lin_request<kLeastAsked>(g, lin_half(g, rq), h0, lane);
     lin_advance(g, rq);
     asm volatile("; first half block requested" ::: "memory");
     if (in_marked) wait_vmem<2 * kRingStages>();
@@ -991,7 +1032,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   }
   const bool two = preload && lin_valid(g, rq);
   if (two) {
-    lin_request(g, lin_half(g, rq), h1, lane);
+    lin_request<kLeastAsked>(g, lin_half(g, rq), h1, lane);
     lin_advance(g, rq);
     asm volatile("; second half block requested" ::: "memory");
   }
@@ -1007,7 +1048,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     ring_clear(h2);
     three = preload && lin_valid(g, rq);
     if (three) {
-      lin_request(g, lin_half(g, rq), h2, lane);
+      lin_request<kLeastAsked>(g, lin_half(g, rq), h2, lane);
       lin_advance(g, rq);
       asm volatile("; third half block requested" ::: "memory");
     }
@@ -1036,17 +1077,17 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   trace_mark(a, t, 1);
   if (!preload) {   // pre-loading switched off: the first requests go out only now
     if (lin_valid(g, rq)) {
-      lin_request(g, lin_half(g, rq), h0, lane);
+      lin_request<kLeastAsked>(g, lin_half(g, rq), h0, lane);
       lin_advance(g, rq);
       asm volatile("; first half block requested after the event" ::: "memory");
     }
     if (lin_valid(g, rq)) {
-      lin_request(g, lin_half(g, rq), h1, lane);
+      lin_request<kLeastAsked>(g, lin_half(g, rq), h1, lane);
       lin_advance(g, rq);
       asm volatile("; second half block requested after the event" ::: "memory");
     }
     if (kThird && lin_valid(g, rq)) {
-      lin_request(g, lin_half(g, rq), h2, lane);
+      lin_request<kLeastAsked>(g, lin_half(g, rq), h2, lane);
       lin_advance(g, rq);
       asm volatile("; third half block requested after the event" ::: "memory");
     }
@@ -1159,31 +1200,31 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     LinCursor cs{g.r0, 0u};
     if (page_ready && lin_valid(g, cs)) {   // (requested a whole task ago: long since landed)
       const LinHalf B = lin_half(g, cs);
-      lin_consume_page<NB, NG>(B, page, xs, Kp, lane, g.pack(), acc);
+      lin_consume_page<kLeast, NB, NG>(B, page, xs, Kp, lane, g.pack(), lin_stages(g, B), acc);
       finish(B);
       lin_advance(g, cs);
     }
     while (lin_valid(g, cs)) {
       {
         const LinHalf B = lin_half(g, cs);
-        lin_consume<NB, NG>(B, h0, xs, Kp, lane, g.pack(), acc);
+        lin_consume<kLeast, NB, NG>(B, h0, xs, Kp, lane, g.pack(), lin_stages(g, B), acc);
         finish(B);
         lin_advance(g, cs);
       }
       if (lin_valid(g, rq)) {
-        lin_request(g, lin_half(g, rq), h0, lane);
+        lin_request<kLeastAsked>(g, lin_half(g, rq), h0, lane);
         lin_advance(g, rq);
         asm volatile("; first buffer requested again" ::: "memory");
       }
       if (!lin_valid(g, cs)) break;
       {
         const LinHalf B = lin_half(g, cs);
-        lin_consume<NB, NG>(B, h1, xs, Kp, lane, g.pack(), acc);
+        lin_consume<kLeast, NB, NG>(B, h1, xs, Kp, lane, g.pack(), lin_stages(g, B), acc);
         finish(B);
         lin_advance(g, cs);
       }
       if (lin_valid(g, rq)) {
-        lin_request(g, lin_half(g, rq), h1, lane);
+        lin_request<kLeastAsked>(g, lin_half(g, rq), h1, lane);
         lin_advance(g, rq);
         asm volatile("; second buffer requested again" ::: "memory");
       }
@@ -1191,12 +1232,12 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
         if (!lin_valid(g, cs)) break;
         {
           const LinHalf B = lin_half(g, cs);
-          lin_consume<NB, NG>(B, h2, xs, Kp, lane, g.pack(), acc);
+          lin_consume<kLeast, NB, NG>(B, h2, xs, Kp, lane, g.pack(), lin_stages(g, B), acc);
           finish(B);
           lin_advance(g, cs);
         }
         if (lin_valid(g, rq)) {
-          lin_request(g, lin_half(g, rq), h2, lane);
+          lin_request<kLeastAsked>(g, lin_half(g, rq), h2, lane);
           lin_advance(g, rq);
           asm volatile("; third buffer requested again" ::: "memory");
         }
@@ -1295,14 +1336,6 @@ __device__ __forceinline__ void split_hi_mid_lo(float x, float y, uint32_t* hi, 
   *hi = h;
   *mid = m;
   *lo = pack_bf16_rne(rx - bf16_lo(m), ry - bf16_hi(m));
-}
-
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
 }
 
 // Geometry of one matrix-core job: K inputs x nb staged rows x nrt 16-row weight tiles (nrt <= 32).
