@@ -447,7 +447,7 @@ __device__ __forceinline__ void rope_cs(const StepArgs& a, int32_t pos, uint32_t
 __device__ __forceinline__ void body_embed(const TaskDesc& t, const StepArgs& a) {
   for (uint32_t b = t.b0; b < t.b1; ++b) {
     int32_t tok = (int32_t)ld_relaxed((const uint32_t*)a.token_ids + b);   // may come from the previous step's sampling task
-    const int32_t pos = (a.flags & kServeBit) ? (int32_t)ld_relaxed((const uint32_t*)a.positions + b) : a.positions[b] + (int32_t)a.step;
+    const int32_t pos = (a.flags & kServeBit) ? (int32_t)ld_relaxed((const uint32_t*)a.positions + b) : as_global(a.positions)[b] + (int32_t)a.step;
     if (tok < 0 || (uint32_t)tok >= a.g->vocab) {
       if (threadIdx.x == 0) report(a, DE_BAD_TOKEN, b, (uint32_t)tok);
       tok = 0;
@@ -510,7 +510,8 @@ __device__ __forceinline__ float mark_clean(float v) {   // (no arithmetic gives
   return __float_as_uint(v) == kUnsetWord ? __uint_as_float(0x7FC00000u) : v;
 }
 __device__ __forceinline__ bool mark_unset(float v) { return __float_as_uint(v) == kUnsetWord; }
-__device__ __forceinline__ bool mark_unset(const float2& v) { return max(__float_as_uint(v.x), __float_as_uint(v.y)) == kUnsetWord; }
+__device__ __forceinline__ uint32_t mark_top(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ uint32_t mark_top(const float2& v) { return max(__float_as_uint(v.x), __float_as_uint(v.y)); }
 // Puts a word of the other copy back to unset (two words: p 8-byte aligned).
 __device__ __forceinline__ void mark_reset(float* p, int32_t twin) {
   if (twin) st_act_u32((uint32_t*)(p + (ptrdiff_t)twin * 64), kUnsetWord);
@@ -521,6 +522,12 @@ __device__ __forceinline__ void mark_reset2(float* p, int32_t twin) {
 }
 // Control word of the LDS: set by a wavefront that gives up waiting (the step is being aborted).
 constexpr uint32_t kLdsAbortAt = 8;
+// (its address space spelt out: a volatile access is a flat one otherwise, behind which the compiler waits for everything in flight)
+typedef volatile __attribute__((address_space(3))) uint32_t lds_word_t;
+__device__ __forceinline__ lds_word_t& abort_word() {
+  extern __shared__ __align__(16) float dyn_lds[];
+  return ((lds_word_t*)dyn_lds)[kLdsAbortAt];
+}
 struct MarkWait {
   uint32_t tries = 0;
   uint64_t t0 = 0;
@@ -534,16 +541,14 @@ __device__ __forceinline__ bool mark_wait(const StepArgs& a, bool unset, MarkWai
     const uint64_t now = wall_clock64();
     if (w.tries == 256u) w.t0 = now;
     if (now - w.t0 > a.g->timeout_ticks || __builtin_amdgcn_readfirstlane(ld_relaxed(a.g->err + 1)) != 0) {
-      extern __shared__ __align__(16) float dyn_lds[];
-      ((volatile uint32_t*)dyn_lds)[kLdsAbortAt] = 1u;
+      abort_word() = 1u;
       return false;
     }
   }
   return true;
 }
 __device__ __forceinline__ bool mark_aborted() {
-  extern __shared__ __align__(16) float dyn_lds[];
-  return __builtin_amdgcn_readfirstlane(((volatile uint32_t*)dyn_lds)[kLdsAbortAt]) != 0;
+  return __builtin_amdgcn_readfirstlane(abort_word()) != 0;
 }
 
 // A task has given up on its inputs: the watchdog's report, unless the step was being aborted already.
@@ -2233,7 +2238,7 @@ __device__ __forceinline__ void body_rope(const TaskDesc& t, const StepArgs& a) 
   const uint32_t d = a.g->head_dim, half = d / 2, nq = a.g->n_q, nkv = a.g->n_kv;
   const uint32_t s0 = t.c0 / d, s1 = t.c1 / d;
   for (uint32_t b = t.b0; b < t.b1; ++b) {
-    int32_t pos = a.positions[b] + (int32_t)a.step;
+    int32_t pos = as_global(a.positions)[b] + (int32_t)a.step;
     if (pos < 0 || (uint32_t)pos >= a.g->max_seq) {
       if (threadIdx.x == 0) report(a, DE_BAD_POSITION, b, (uint32_t)pos);
       continue;
@@ -2291,7 +2296,7 @@ __device__ __forceinline__ void body_rope(const TaskDesc& t, const StepArgs& a) 
 template <bool PAGED>
 __device__ __forceinline__ int32_t step_position(const StepArgs& a, uint32_t b) {
   if (PAGED && (a.flags & kServeBit)) return (int32_t)ld_relaxed((const uint32_t*)a.positions + b);
-  return a.positions[b] + (int32_t)a.step;
+  return as_global(a.positions)[b] + (int32_t)a.step;
 }
 
 // First row of chunk c of C of a sequence of len rows.  (A 64-bit division is a hundred instructions;
@@ -2307,14 +2312,15 @@ __device__ __forceinline__ uint32_t chunk_begin(const StepArgs& a, uint32_t c, u
 // goes, one at a time, to the sequence whose chunks are longest at that moment (lowest index on
 // ties).  A pure function of the positions, worked out by every wavefront for itself (lane b <
 // batch holds sequence b; batch <= 16).  Returns the sequence of task v, the task's chunk number
-// there, the sequence's chunk count and its first task.
+// there, the sequence's chunk count, its first task and its position.
 template <bool PAGED>
 __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_t v, uint32_t* seq, uint32_t* chunk,
-                                          uint32_t* chunks, uint32_t* first) {
+                                          uint32_t* chunks, uint32_t* first, int32_t* position) {
   const uint32_t B = a.g->batch, li = threadIdx.x & 15u;
   uint32_t w = 0;
+  int32_t pos = 0;
   if (li < B) {
-    const int32_t pos = step_position<PAGED>(a, li);
+    pos = step_position<PAGED>(a, li);
     w = (pos >= 0 && (uint32_t)pos < a.g->max_seq) ? (uint32_t)pos + 1u : 1u;   // (a bad position is reported by its tasks)
   }
   // within a row of 16 lanes by DPP moves (a lane shuffle is an LDS round trip, and the loop below is a
@@ -2349,6 +2355,7 @@ __device__ __forceinline__ void attn_deal(const StepArgs& a, uint32_t C, uint32_
   *first = (uint32_t)__builtin_amdgcn_readlane((int)start, bsel);
   *chunks = (uint32_t)__builtin_amdgcn_readlane((int)cnt, bsel);
   *chunk = v - *first;
+  *position = __builtin_amdgcn_readlane(pos, bsel);
 }
 
 // ------------------------------------------------------------------------------ attention on the matrix cores
@@ -2417,7 +2424,10 @@ __device__ __forceinline__ float row_ror(float v) {   // value of the lane N fur
 // consecutive chunk tasks: rows of Cs slots, ld floats apart, from slot `slot` of the row at `row` on.
 // A thread owns two adjacent output elements; all loads of up to 16 partials are in flight together
 // (the loads are what this costs: 3.3 us for 16 partials when they went out 8 at a time, 2 dwords
-// a partial, with an exp chain between).
+// a partial, with an exp chain between).  They must go out without a wait between them: where the compiler finds a flat
+// access nearby or a branch around each load it waits for everything, the task's own stores included.  Merge at batch 1,
+// from own partial to output, 8 partials 4.4 -> 2.4 us, 16 partials of head size 64 3.0 -> 2.0; us a step: 1B class 629 -> 617, 8B 2730
+// -> 2680, 2B class at batch 2, four tokens 2087 -> 2045, tiny model 36.0 -> 34.9.
 // MARKED: the partials of the others say for themselves whether they are there, and the calling task's own, the
 // last of the C, is in LDS (`own`: outputs [grp][d], `own_ml`: maximum and sum [grp][2]).
 template <int D, int GRP, bool MARKED = false>
@@ -2443,6 +2453,11 @@ __device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row
     } else
     for (uint32_t c0 = 0; c0 < C; c0 += kAtOnce) {
       float2 ml[kAtOnce], ov[kAtOnce];
+#pragma unroll
+      for (int k = 0; k < kAtOnce; ++k) {
+        ml[k] = make_float2(-INFINITY, 0.f);
+        ov[k] = make_float2(0.f, 0.f);
+      }
       const float* part1;
       uint32_t sl1;
       MarkWait mw;
@@ -2451,21 +2466,29 @@ __device__ __forceinline__ void attn_merge_partials(uint32_t C, const float* row
         part1 = part;
         sl1 = sl;
         unset = false;
+        auto load = [&](auto kc) {
+          constexpr int k = decltype(kc)::value;
+          const float* pp = part1 + j * (D + 2);
+          ml[k] = ld_act2(pp + D);
+          ov[k] = ld_act2(pp + e);
+          part1 += per;
+          if (++sl1 == Cs) { sl1 = 0; part1 += ld - (size_t)Cs * per; }
+        };
+        // n partials in ascending entries, eight, four, two and one at a time: a branch around each of them made the compiler
+        // wait for everything in flight between them (1.4 us to send off 7)
+        const uint32_t n = min(Cm - min(c0, Cm), (uint32_t)kAtOnce), r = n >= 8u ? n - 8u : n;
+        if (n >= 8u) static_for<0, 8>(load);
+        if (r >= 4u) static_for<8, 12>(load);
+        if (r & 10u) static_for<12, 14>(load);
+        if (r & 9u) static_for<14, 15>(load);
+        if (r & 8u) static_for<15, 16>(load);
+        if (MARKED) {   // (kUnsetWord is the largest word there is)
+          uint32_t top = 0;
 #pragma unroll
-        for (int k = 0; k < kAtOnce; ++k) {
-          ml[k] = make_float2(-INFINITY, 0.f);
-          ov[k] = make_float2(0.f, 0.f);
-          if (c0 + k < Cm) {
-            const float* pp = part1 + j * (D + 2);
-            ml[k] = ld_act2(pp + D);
-            ov[k] = ld_act2(pp + e);
-            part1 += per;
-            if (++sl1 == Cs) { sl1 = 0; part1 += ld - (size_t)Cs * per; }
-          }
+          for (int k = 0; k < kAtOnce; ++k) top = max(top, max(mark_top(ml[k]), mark_top(ov[k])));
+          asm("" : "+v"(top));   // (a vector register, also where every word is the same in all lanes)
+          unset = top == kUnsetWord;
         }
-        if (MARKED)
-#pragma unroll
-          for (int k = 0; k < kAtOnce; ++k) unset = unset || mark_unset(ml[k]) || mark_unset(ov[k]);
       } while (MARKED && mark_wait(a, unset, mw));
       part = part1;
       sl = sl1;
@@ -2617,7 +2640,9 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   if (PAGED && (wait_ev >= 0 || MARKED) && a.g->serve_event >= 0 && !wait_event(a, a.g->serve_event, s_flag)) return false;
   // sequence, chunk and chunk count the task works on, first task of that sequence
   uint32_t b = bs, c = u % Cs, C = Cs, v0 = bs * Cs;
-  if (t.flags & TF_ATTN_BALANCE) attn_deal<PAGED>(a, Cs, bs * Cs + c, &b, &c, &C, &v0);
+  int32_t pos;   // written by the host before the launch (or by the serving task)
+  if (t.flags & TF_ATTN_BALANCE) attn_deal<PAGED>(a, Cs, bs * Cs + c, &b, &c, &C, &v0, &pos);
+  else pos = (int32_t)uniform_u32((uint32_t)step_position<PAGED>(a, b));
   // a probability is 2^(s * kScale - m): one fused multiply-add and one v_exp_f32.  (The factor folded into
   // the query rounds every query element once more.)
   constexpr float kScale = (float)(1.4426950408889634074 / (D == 128 ? 11.313708498984760390 : 8.0));   // log2(e) / sqrt(d)
@@ -2633,7 +2658,6 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
   static_assert(grp * d + NW * NTERM * grp * WS + NW * grp * 2 + 2 * d + 8 + 16 == attn_lds_floats(D, GRP), "the host reserves this layout");
   uint32_t* pgs = flag + 16;                         // paged: the chunk's page numbers
   float* outp = t.out + (size_t)bs * t.ld_out + t.c0;
-  const int32_t pos = step_position<PAGED>(a, b);    // written by the host before the launch (or by the serving task)
   const bool bad_pos = pos < 0 || (uint32_t)pos >= a.g->max_seq;
   const uint32_t len = bad_pos ? 0u : (uint32_t)pos + 1;
   const uint32_t t0 = chunk_begin(a, c, len, C), t1 = chunk_begin(a, c + 1u, len, C);
@@ -2764,6 +2788,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     float u0 = 0.f, u1 = 0.f;
     float2 lo = make_float2(0.f, 0.f), hi = lo, rq = lo, r0 = lo, r1 = lo;
     MarkWait mw;
+    uint32_t top;
     do {
       if (has_q) {
         u0 = ld_act(qsrc + jq * d + eq);
@@ -2776,7 +2801,9 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
         r0 = ld_act2(angles + 2u * ek);
         r1 = ld_act2(angles + 2u * ek + 2u);
       }
-    } while (MARKED && mark_wait(a, mark_unset(u0) || mark_unset(u1) || mark_unset(lo) || mark_unset(hi) || mark_unset(rq) || mark_unset(r0) || mark_unset(r1), mw));
+      top = max(max(max(mark_top(u0), mark_top(u1)), max(mark_top(lo), mark_top(hi))), max(mark_top(rq), max(mark_top(r0), mark_top(r1))));
+      asm("" : "+v"(top));
+    } while (MARKED && mark_wait(a, top == kUnsetWord, mw));
     if (has_q) {
       if (qk_norm) {   // RMSNorm over the head: its `half` threads are one aligned group of lanes
         // (spelt out like the rotation below: left to the compiler, which square is rounded first depends on the code around it)
@@ -2817,7 +2844,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
       *(float2*)((threadIdx.x < d / 2 ? knew : vnew) + e) = make_float2(bf16_lo(w), bf16_hi(w));
     }
   }
-  __syncthreads();
+  lds_barrier();   // (published is LDS: nobody waits for the appended rows' stores here)
   trace_mark(a, t, 2);
   if (has_new && wave < grp) {   // score of the appended row for head `wave`
     float s = 0.f;
@@ -2964,7 +2991,7 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
     }
   }
   if (PAGED && bad_page) report(a, DE_BAD_PAGE, b, t0);   // (the rows came from page 0 instead: wrong, but in bounds)
-  __syncthreads();
+  lds_barrier();
   trace_mark(a, t, 10);
   // ---- the wavefronts' results and the appended row -> the task's partial result, two elements a thread
   const uint32_t nw = min(nblk, NW);
@@ -3008,8 +3035,6 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
       if (e == 0) st_act2(outp + j * (d + 2) + d, MARKED ? mark_clean(M) : M, MARKED ? mark_clean(l) : l);
     }
   }
-  if (MARKED)
-    for (uint32_t i = threadIdx.x; i < per / 2; i += kThreads) mark_reset2(outp + 2u * i, t.twin);
   trace_mark(a, t, 11);
   if constexpr (MARKED) {
     // No arrival counter: the sequence's last task in linearized order merges, and loads the others' partials
@@ -3019,6 +3044,8 @@ __device__ __forceinline__ bool body_attn_mfma(const TaskDesc& t, const StepArgs
       attn_merge_partials<D, GRP, true>(C, t.out + (size_t)(v0 / Cs) * t.ld_out + (size_t)g * Cs * per, v0 % Cs, Cs, t.ld_out,
                                         const_cast<float*>(t.in2) + (size_t)b * nq * d + (size_t)g * grp * d, a, t, qs, own_ml);
     }
+    // (behind the merge: its loads would come back behind the acknowledgement of these stores)
+    for (uint32_t i = threadIdx.x; i < per / 2; i += kThreads) mark_reset2(outp + 2u * i, t.twin);
   } else if (t.flags & TF_ATTN_MERGE) {
     // Arrival counter of (layer, sequence, KV head): the chunk task that arrives last sees all C
     // partials complete and merges them into the attention output.
@@ -3171,7 +3198,7 @@ __device__ __forceinline__ void body_argmax(const TaskDesc& t, const StepArgs& a
         st_act_u32((uint32_t*)const_cast<int32_t*>(a.token_ids) + b, mi);
         if (tokens_out) st_act_u32((uint32_t*)tokens_out + (size_t)a.step * B + b, mi);
         if ((uint32_t)a.step + 1u == a.n_steps && !(a.flags & kServeBit))   // (a serving launch: the serving task keeps the positions)
-          st_act_u32((uint32_t*)const_cast<int32_t*>(a.positions) + b, (uint32_t)(a.positions[b] + (int32_t)a.n_steps));
+          st_act_u32((uint32_t*)const_cast<int32_t*>(a.positions) + b, (uint32_t)(as_global(a.positions)[b] + (int32_t)a.n_steps));
       }
     }
     lds_barrier();
