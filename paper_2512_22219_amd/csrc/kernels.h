@@ -1951,26 +1951,21 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 // index), renormalised to sum one; ranks of a token's experts are in ascending expert index.
 // PER_LANE: experts a lane looks after, at least E / 64 (a loop over the eight that the largest E needs costs
 // its branches in every selection round).
+// A token's choice is a bit mask over the experts, built in scalar registers by the wavefront that makes it; behind the one
+// barrier a thread per expert counts bits in the tokens' masks, which gives everything the meta-tensor holds (its tokens, where
+// its list starts, its place among the active, the pairs) without a scan.  us a step at batch 1, 12 layers: lists by LDS atomics and
+// scans behind four barriers 793, masks 783 (batch 16, 6 layers: no difference).
 template <int PER_LANE>
 __device__ __forceinline__ void moe_route(const TaskDesc& t, const StepArgs& a, float* lds) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t E = t.p0, TK = t.p1, B = t.p2, P = B * TK;
-  uint32_t* sel = (uint32_t*)lds;          // [P] expert of pair p
-  float* wsel = lds + P;                   // [P] weight of pair p
-  uint32_t* cnt = (uint32_t*)(lds + 2 * P);   // [E]
-  uint32_t* off = cnt + E;                 // [E]
-  uint32_t* tokmask = off + E;             // [E] bit b: token b is routed to the expert (batch <= 16)
-  uint32_t* pairof = tokmask + E;          // [E][16] pair index of (expert, token)
+  uint64_t* masks = (uint64_t*)lds;                       // [B][PER_LANE] bit l of word i: expert l + 64 i (batch <= 16)
+  uint32_t* sel = (uint32_t*)(masks + B * PER_LANE);      // [P] expert of pair p
+  float* wsel = (float*)(sel + P);                        // [P] weight of pair p
   uint32_t* meta = (uint32_t*)t.out;
   constexpr int kPerLane = PER_LANE;
   const uint32_t nper = (E + 63u) / 64u;   // experts per lane actually present (uniform)
-  for (uint32_t p2 = threadIdx.x; p2 < P; p2 += kThreads) {   // a token whose router output is not finite selects nothing
-    sel[p2] = 0xFFFFFFFFu;
-    wsel[p2] = 0.f;
-  }
-  for (uint32_t e = threadIdx.x; e < E; e += kThreads) tokmask[e] = 0u;
-  lds_barrier();
   for (uint32_t tok = wave; tok < B; tok += kThreads / 64) {
     float pr[kPerLane];
     float m = -INFINITY;
@@ -1992,97 +1987,94 @@ __device__ __forceinline__ void moe_route(const TaskDesc& t, const StepArgs& a, 
       l += pr[i];
     }
     l = wave_sum_dpp(l);
+    // (left: what may still be chosen; an expert that is not there, or whose probability is not a number, never is)
+    float left[kPerLane];
+    uint64_t taken[kPerLane];
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i)
+    for (int i = 0; i < kPerLane; ++i) {
       if ((uint32_t)i < nper) pr[i] = pr[i] / l;
-    uint32_t taken = 0;   // bit i: this lane's expert lane + 64 i is selected
+      left[i] = (uint32_t)i < nper && (uint32_t)lane + 64u * i < E && pr[i] >= 0.f ? pr[i] : -1.f;
+      taken[i] = 0;
+    }
     for (uint32_t j = 0; j < TK; ++j) {
-      float best = -1.f;
-      uint32_t best_e = 0xFFFFFFFFu;
+      float best = left[0];
+#pragma unroll
+      for (int i = 1; i < kPerLane; ++i) best = fmaxf(best, left[i]);
+      best = wave_max_dpp(best);
+      if (best < 0.f) break;   // (a token whose router output is not finite selects nothing)
+      bool found = false;      // ties: the lowest expert
 #pragma unroll
       for (int i = 0; i < kPerLane; ++i) {
-        const uint32_t e = (uint32_t)lane + 64u * i;
-        if ((uint32_t)i < nper && e < E && !((taken >> i) & 1u) && pr[i] > best) { best = pr[i]; best_e = e; }   // ascending e: ties keep the lower
+        const uint64_t at = found ? 0ull : __ballot(left[i] == best);
+        if (at) {
+          const uint64_t bit = at & (0ull - at);
+          taken[i] |= bit;
+          left[i] = (bit >> lane) & 1ull ? -1.f : left[i];
+          found = true;
+        }
       }
-      const float wbest = wave_max_dpp(best);
-      const uint32_t we = wave_min_u32_dpp(best == wbest ? best_e : 0xFFFFFFFFu);
-      if (we != 0xFFFFFFFFu && (we & 63u) == (uint32_t)lane) taken |= 1u << (we >> 6);
     }
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) s += ((taken >> i) & 1u) ? pr[i] : 0.f;
+    for (int i = 0; i < kPerLane; ++i) s += ((taken[i] >> lane) & 1ull) ? pr[i] : 0.f;
     s = wave_sum_dpp(s);
     uint32_t before = 0;   // selected experts with a smaller index, so far
 #pragma unroll
     for (int i = 0; i < kPerLane; ++i) {
-      const bool mine = (taken >> i) & 1u;
-      const uint64_t mask = __ballot(mine);
-      if (mine) {
-        const uint32_t rank = before + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+      if ((taken[i] >> lane) & 1ull) {
+        const uint32_t rank = before + (uint32_t)__popcll(taken[i] & ((1ull << lane) - 1ull));
         sel[tok * TK + rank] = (uint32_t)lane + 64u * i;
         wsel[tok * TK + rank] = pr[i] / s;
       }
-      before += (uint32_t)__popcll(mask);
+      before += (uint32_t)__popcll(taken[i]);
+      if (lane == 0) masks[tok * kPerLane + i] = taken[i];
     }
-  }
-  lds_barrier();
-  // Per-expert token lists without serial scans: a pair thread sets its token's bit in the
-  // expert's mask and leaves its pair index in the expert's row of `pairof`; the expert's list
-  // is then its mask's bits in ascending order.
-  for (uint32_t p2 = threadIdx.x; p2 < P; p2 += kThreads) {
-    const uint32_t e = sel[p2], tok = p2 / TK;
-    if (e < E) {
-      atomicOr(&tokmask[e], 1u << tok);
-      pairof[e * 16u + tok] = p2;
-    }
-  }
-  lds_barrier();
-  // offsets and the active list: exclusive scans over the experts by wavefront 0, each lane
-  // owning kPerLane consecutive experts
-  if (wave == 0) {
-    uint32_t c[kPerLane], mine = 0, act = 0, mx = 0;
-#pragma unroll
-    for (int i = 0; i < kPerLane; ++i) {
-      const uint32_t e = (uint32_t)lane * kPerLane + i;
-      c[i] = e < E ? (uint32_t)__popc(tokmask[e]) : 0u;
-      mine += c[i];
-      act += c[i] ? 1u : 0u;
-      mx = max(mx, c[i]);
-    }
-    uint32_t run = mine, arun = act;   // inclusive scans across lanes
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t v = (uint32_t)__shfl_up((int)run, d, 64), w = (uint32_t)__shfl_up((int)arun, d, 64);
-      if (lane >= d) { run += v; arun += w; }
-    }
-    uint32_t o = run - mine, ai = arun - act;
-#pragma unroll
-    for (int i = 0; i < kPerLane; ++i) {
-      const uint32_t e = (uint32_t)lane * kPerLane + i;
-      if (e < E) {
-        cnt[e] = c[i];
-        off[e] = o;
-        if (c[i]) st_act_u32(meta + 2 + ai++, e);
-        o += c[i];
-      }
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, d, 64));
-    if (lane == 63) {
-      st_act_u32(meta, arun);
-      st_act_u32(meta + 1, mx);
+    if ((uint32_t)lane >= before && (uint32_t)lane < TK) {
+      sel[tok * TK + lane] = 0xFFFFFFFFu;
+      wsel[tok * TK + lane] = 0.f;
     }
   }
   lds_barrier();
   for (uint32_t e = threadIdx.x; e < E; e += kThreads) {
-    st_act_u32(meta + 2 + E + e, cnt[e]);
-    st_act_u32(meta + 2 + 2 * E + e, off[e]);
-    uint32_t o = off[e], m = tokmask[e];
-    while (m) {   // ascending token = ascending pair
-      const uint32_t tok = (uint32_t)__ffs((int)m) - 1u;
-      m &= m - 1u;
-      st_act_u32(meta + 2 + 3 * E + o++, pairof[e * 16u + tok]);
+    const uint32_t w = e >> 6;
+    const uint64_t bit = 1ull << (e & 63u), below = bit - 1ull;
+    uint32_t cnt = 0, off = 0, act = 0, of = 0;   // its tokens, all pairs of lower experts, active lower experts, bit b: token b
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) {
+      uint64_t any = 0;
+      const uint64_t low = (uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull);
+      for (uint32_t b = 0; b < B; ++b) {
+        const uint64_t mk = masks[b * kPerLane + i];
+        any |= mk;
+        off += (uint32_t)__popcll(mk & low);
+        if ((uint32_t)i == w && (mk & bit)) of |= 1u << b;
+      }
+      act += (uint32_t)__popcll(any & low);
+      if (i == kPerLane - 1 && e == E - 1u) st_act_u32(meta, act + (of ? 1u : 0u));
     }
+    cnt = (uint32_t)__popc(of);
+    st_act_u32(meta + 2 + E + e, cnt);
+    st_act_u32(meta + 2 + 2 * E + e, off);
+    if (cnt) st_act_u32(meta + 2 + act, e);
+    for (uint32_t o = off; of; of &= of - 1u) {   // ascending token = ascending pair
+      const uint32_t b = (uint32_t)__ffs((int)of) - 1u;
+      uint32_t rank = 0;
+#pragma unroll
+      for (int i = 0; i < kPerLane; ++i)
+        rank += (uint32_t)__popcll(masks[b * kPerLane + i] & ((uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull)));
+      st_act_u32(meta + 2 + 3 * E + o++, b * TK + rank);
+    }
+  }
+  if (wave == kThreads / 64u - 1u) {   // the largest count
+    uint32_t mx = 0;
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) {
+      uint32_t n = 0;
+      for (uint32_t b = 0; b < B; ++b) n += (uint32_t)(masks[b * kPerLane + i] >> lane) & 1u;
+      mx = max(mx, n);
+    }
+    mx = wave_reduce_dpp(mx, [](uint32_t x, uint32_t y) { return max(x, y); });
+    if (lane == 0) st_act_u32(meta + 1, mx);
   }
   for (uint32_t p2 = threadIdx.x; p2 < P; p2 += kThreads) {
     st_act_u32(meta + 2 + 3 * E + P + p2, __float_as_uint(wsel[p2]));
