@@ -587,6 +587,7 @@ static mpk_status build_ops(const mpk_model_config& c, const mpk_weight_ptrs* w,
       {
         HostOp& op = b.add(MPK_OP_EXPERT, l, "expert_gate_up", eh, 1, meta, gin);
         op.data_in = gin; op.data_in2 = meta_data; op.data_out = hbuf;
+        if (E <= kMoeOwnRouteExperts) op.data_aux = rl;
         op.w = lw.expert_wgu; op.K = H; op.flags |= TF_GATEUP;
         op.p0 = Fe; op.p1 = NT; op.p2 = 2 * Fe; op.p3 = E | (TK << 16);
         if (f & MPK_FUSE_NORM) { op.flags |= TF_PRO_NORM; op.w2 = lw.mlp_norm; op.f0 = c.rms_eps; }
@@ -1022,9 +1023,12 @@ static void build_descs(const mpk_model_config& c, const mpk_kv_ptrs* kv, HostGr
   const size_t kv_layer = g.opt.kv_page_size
                               ? (size_t)g.opt.kv_pages * c.n_kv_heads * g.opt.kv_page_size * c.head_dim
                               : (size_t)(g.opt.kv_batch ? g.opt.kv_batch : c.batch) * c.n_kv_heads * c.max_seq * c.head_dim;
-  std::map<int, int32_t> route_event;   // layer -> the event its routing task triggers
+  std::map<int, int32_t> route_event, router_event;   // layer -> the event its routing task triggers, the one it waits for
   for (const HostTask& rt : g.tasks)
-    if (rt.op != MPK_TASK_DUMMY_OP && g.ops[rt.op].kind == MPK_OP_ROUTER && rt.trig_event >= 0) route_event[g.ops[rt.op].layer] = rt.trig_event;
+    if (rt.op != MPK_TASK_DUMMY_OP && g.ops[rt.op].kind == MPK_OP_ROUTER) {
+      if (rt.trig_event >= 0) route_event[g.ops[rt.op].layer] = rt.trig_event;
+      if (rt.dep_event >= 0) router_event[g.ops[rt.op].layer] = rt.dep_event;
+    }
   for (size_t i = 0; i < g.tasks.size(); ++i) {
     const HostTask& ht = g.tasks[i];
     TaskDesc& t = g.descs[i];
@@ -1084,9 +1088,11 @@ static void build_descs(const mpk_model_config& c, const mpk_kv_ptrs* kv, HostGr
       t.ld_out = g.tensors[op.data_out].cols;
       // second-stage expert task: the event the layer's routing task triggers (+ 1), behind which
       // the meta-tensor may be read -- the task requests its first weights before its own event
-      if (op.kind == MPK_OP_EXPERT && !(op.flags & TF_GATEUP)) {
-        auto it = route_event.find(op.layer);
-        if (it != route_event.end()) t.aux1 = (void*)(uintptr_t)(it->second + 1);
+      // ... of the first stage: the event that the routing task waits for, behind which the router's output may be read
+      if (op.kind == MPK_OP_EXPERT && (!(op.flags & TF_GATEUP) || op.data_aux >= 0)) {
+        const auto& events = (op.flags & TF_GATEUP) ? router_event : route_event;
+        auto it = events.find(op.layer);
+        if (it != events.end()) t.aux1 = (void*)(uintptr_t)(it->second + 1);
       }
     }
     if (op.kind == MPK_OP_ROPE || op.kind == MPK_OP_ATTN_PARTIAL) {

@@ -1955,27 +1955,37 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 // barrier a thread per expert counts bits in the tokens' masks, which gives everything the meta-tensor holds (its tokens, where
 // its list starts, its place among the active, the pairs) without a scan.  us a step at batch 1, 12 layers: lists by LDS atomics and
 // scans behind four barriers 793, masks 783 (batch 16, 6 layers: no difference).
-template <int PER_LANE>
-__device__ __forceinline__ void moe_route(const TaskDesc& t, const StepArgs& a, float* lds) {
+// LOCAL: `meta` is an expert task's copy in LDS, of which it reads the words up to the end of the pair list and not [1].
+template <int PER_LANE, bool LOCAL>
+__device__ __forceinline__ void moe_route(const StepArgs& a, const float* in, uint32_t ld_in, uint32_t E, uint32_t TK, uint32_t B,
+                                          float* lds, uint32_t* meta) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t E = t.p0, TK = t.p1, B = t.p2, P = B * TK;
-  uint64_t* masks = (uint64_t*)lds;                       // [B][PER_LANE] bit l of word i: expert l + 64 i (batch <= 16)
-  uint32_t* sel = (uint32_t*)(masks + B * PER_LANE);      // [P] expert of pair p
+  const uint32_t P = B * TK, B4 = (B + 3u) & ~3u;
+  uint64_t* masks = (uint64_t*)lds;                       // [B4][PER_LANE] bit l of word i: expert l + 64 i (batch <= 16)
+  uint32_t* sel = (uint32_t*)(masks + B4 * PER_LANE);     // [P] expert of pair p
   float* wsel = (float*)(sel + P);                        // [P] weight of pair p
-  uint32_t* meta = (uint32_t*)t.out;
   constexpr int kPerLane = PER_LANE;
   const uint32_t nper = (E + 63u) / 64u;   // experts per lane actually present (uniform)
-  for (uint32_t tok = wave; tok < B; tok += kThreads / 64) {
+  auto put = [&](uint32_t at, uint32_t v) {
+    if constexpr (LOCAL) meta[at] = v;
+    else st_act_u32(meta + at, v);
+  };
+  for (uint32_t tok = wave; tok < B4; tok += kThreads / 64) {
+    if (tok >= B) {   // (nobody's: the counts below go by fours)
+      if (lane < kPerLane) masks[tok * kPerLane + lane] = 0;
+      continue;
+    }
     float pr[kPerLane];
     float m = -INFINITY;
 #pragma unroll
     for (int i = 0; i < kPerLane; ++i) {
       const uint32_t e = (uint32_t)lane + 64u * i;
       pr[i] = -INFINITY;
-      if ((uint32_t)i < nper && e < E) pr[i] = ld_act(t.in + (size_t)tok * t.ld_in + e);
-      m = fmaxf(m, pr[i]);
+      if ((uint32_t)i < nper && e < E) pr[i] = ld_act(in + (size_t)tok * ld_in + e);
     }
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) m = fmaxf(m, pr[i]);
     m = wave_max_dpp(m);
     float l = 0.f;
 #pragma unroll
@@ -1987,104 +1997,119 @@ __device__ __forceinline__ void moe_route(const TaskDesc& t, const StepArgs& a, 
       l += pr[i];
     }
     l = wave_sum_dpp(l);
-    // (left: what may still be chosen; an expert that is not there, or whose probability is not a number, never is)
-    float left[kPerLane];
+    // left: what may still be chosen, as a number that grows with the probability; 0: an expert that is not there, or whose
+    // probability is not a number, or that has been chosen.  (Of whole numbers the largest is found without a float maximum's
+    // quieting of its operands.)
+    uint32_t left[kPerLane];
     uint64_t taken[kPerLane];
 #pragma unroll
     for (int i = 0; i < kPerLane; ++i) {
       if ((uint32_t)i < nper) pr[i] = pr[i] / l;
-      left[i] = (uint32_t)i < nper && (uint32_t)lane + 64u * i < E && pr[i] >= 0.f ? pr[i] : -1.f;
+      left[i] = (uint32_t)i < nper && (uint32_t)lane + 64u * i < E && pr[i] >= 0.f ? __float_as_uint(pr[i]) + 1u : 0u;
       taken[i] = 0;
     }
     for (uint32_t j = 0; j < TK; ++j) {
-      float best = left[0];
+      uint32_t best = left[0];
 #pragma unroll
-      for (int i = 1; i < kPerLane; ++i) best = fmaxf(best, left[i]);
-      best = wave_max_dpp(best);
-      if (best < 0.f) break;   // (a token whose router output is not finite selects nothing)
+      for (int i = 1; i < kPerLane; ++i) best = max(best, left[i]);
+      best = wave_reduce_dpp(best, [](uint32_t x, uint32_t y) { return max(x, y); });
+      if (best == 0u) break;   // (a token whose router output is not finite selects nothing)
       bool found = false;      // ties: the lowest expert
 #pragma unroll
       for (int i = 0; i < kPerLane; ++i) {
         const uint64_t at = found ? 0ull : __ballot(left[i] == best);
         if (at) {
-          const uint64_t bit = at & (0ull - at);
-          taken[i] |= bit;
-          left[i] = (bit >> lane) & 1ull ? -1.f : left[i];
+          const int first = __builtin_ctzll(at);
+          taken[i] |= 1ull << first;
+          left[i] = lane == first ? 0u : left[i];
           found = true;
         }
       }
     }
-    float s = 0.f;
+    if constexpr (!LOCAL) {
+      float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) s += ((taken[i] >> lane) & 1ull) ? pr[i] : 0.f;
-    s = wave_sum_dpp(s);
-    uint32_t before = 0;   // selected experts with a smaller index, so far
+      for (int i = 0; i < kPerLane; ++i) s += ((taken[i] >> lane) & 1ull) ? pr[i] : 0.f;
+      s = wave_sum_dpp(s);
+      uint32_t before = 0;   // selected experts with a smaller index, so far
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) {
-      if ((taken[i] >> lane) & 1ull) {
-        const uint32_t rank = before + (uint32_t)__popcll(taken[i] & ((1ull << lane) - 1ull));
-        sel[tok * TK + rank] = (uint32_t)lane + 64u * i;
-        wsel[tok * TK + rank] = pr[i] / s;
+      for (int i = 0; i < kPerLane; ++i) {
+        if ((taken[i] >> lane) & 1ull) {
+          const uint32_t rank = before + (uint32_t)__popcll(taken[i] & ((1ull << lane) - 1ull));
+          sel[tok * TK + rank] = (uint32_t)lane + 64u * i;
+          wsel[tok * TK + rank] = pr[i] / s;
+        }
+        before += (uint32_t)__popcll(taken[i]);
       }
-      before += (uint32_t)__popcll(taken[i]);
+      if ((uint32_t)lane >= before && (uint32_t)lane < TK) {
+        sel[tok * TK + lane] = 0xFFFFFFFFu;
+        wsel[tok * TK + lane] = 0.f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i)
       if (lane == 0) masks[tok * kPerLane + i] = taken[i];
-    }
-    if ((uint32_t)lane >= before && (uint32_t)lane < TK) {
-      sel[tok * TK + lane] = 0xFFFFFFFFu;
-      wsel[tok * TK + lane] = 0.f;
-    }
   }
   lds_barrier();
   for (uint32_t e = threadIdx.x; e < E; e += kThreads) {
     const uint32_t w = e >> 6;
     const uint64_t bit = 1ull << (e & 63u), below = bit - 1ull;
-    uint32_t cnt = 0, off = 0, act = 0, of = 0;   // its tokens, all pairs of lower experts, active lower experts, bit b: token b
+    uint32_t off = 0, act = 0, of = 0;   // all pairs of lower experts, active lower experts, bit b: token b is its
+    uint64_t any[kPerLane] = {}, ranks = 0;   // (four bits a token: its rank there)
+    // (the masks of four tokens in flight: one after the other they are a chain of LDS round trips, 4 us at batch 16)
+    for (uint32_t b0 = 0; b0 < B4; b0 += 4u) {
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) {
-      uint64_t any = 0;
-      const uint64_t low = (uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull);
-      for (uint32_t b = 0; b < B; ++b) {
-        const uint64_t mk = masks[b * kPerLane + i];
-        any |= mk;
-        off += (uint32_t)__popcll(mk & low);
-        if ((uint32_t)i == w && (mk & bit)) of |= 1u << b;
+      for (uint32_t u = 0; u < 4u; ++u) {
+        uint32_t lower = 0;
+        bool has = false;
+#pragma unroll
+        for (int i = 0; i < kPerLane; ++i) {
+          const uint64_t mk = masks[(b0 + u) * kPerLane + i];
+          any[i] |= mk;
+          lower += (uint32_t)__popcll(mk & ((uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull)));
+          has = has || ((uint32_t)i == w && (mk & bit));
+        }
+        off += lower;
+        if (has) {
+          of |= 1u << (b0 + u);
+          ranks |= (uint64_t)lower << (4u * (b0 + u));   // (below TK <= 16)
+        }
       }
-      act += (uint32_t)__popcll(any & low);
-      if (i == kPerLane - 1 && e == E - 1u) st_act_u32(meta, act + (of ? 1u : 0u));
     }
-    cnt = (uint32_t)__popc(of);
-    st_act_u32(meta + 2 + E + e, cnt);
-    st_act_u32(meta + 2 + 2 * E + e, off);
-    if (cnt) st_act_u32(meta + 2 + act, e);
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) act += (uint32_t)__popcll(any[i] & ((uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull)));
+    const uint32_t cnt = (uint32_t)__popc(of);
+    if (e == E - 1u) put(0u, act + (of ? 1u : 0u));
+    put(2u + E + e, cnt);
+    put(2u + 2u * E + e, off);
+    if (cnt) put(2u + act, e);
     for (uint32_t o = off; of; of &= of - 1u) {   // ascending token = ascending pair
       const uint32_t b = (uint32_t)__ffs((int)of) - 1u;
-      uint32_t rank = 0;
-#pragma unroll
-      for (int i = 0; i < kPerLane; ++i)
-        rank += (uint32_t)__popcll(masks[b * kPerLane + i] & ((uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull)));
-      st_act_u32(meta + 2 + 3 * E + o++, b * TK + rank);
+      put(2u + 3u * E + o++, b * TK + (uint32_t)(ranks >> (4u * b) & 15u));
     }
   }
-  if (wave == kThreads / 64u - 1u) {   // the largest count
-    uint32_t mx = 0;
+  if constexpr (!LOCAL) {
+    if (wave == kThreads / 64u - 1u) {   // the largest count
+      uint32_t mx = 0;
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) {
-      uint32_t n = 0;
-      for (uint32_t b = 0; b < B; ++b) n += (uint32_t)(masks[b * kPerLane + i] >> lane) & 1u;
-      mx = max(mx, n);
+      for (int i = 0; i < kPerLane; ++i) {
+        uint32_t n = 0;
+        for (uint32_t b = 0; b < B; ++b) n += (uint32_t)(masks[b * kPerLane + i] >> lane) & 1u;
+        mx = max(mx, n);
+      }
+      mx = wave_reduce_dpp(mx, [](uint32_t x, uint32_t y) { return max(x, y); });
+      if (lane == 0) put(1u, mx);
     }
-    mx = wave_reduce_dpp(mx, [](uint32_t x, uint32_t y) { return max(x, y); });
-    if (lane == 0) st_act_u32(meta + 1, mx);
-  }
-  for (uint32_t p2 = threadIdx.x; p2 < P; p2 += kThreads) {
-    st_act_u32(meta + 2 + 3 * E + P + p2, __float_as_uint(wsel[p2]));
-    st_act_u32(meta + 2 + 3 * E + 2 * P + p2, sel[p2]);
+    for (uint32_t p2 = threadIdx.x; p2 < P; p2 += kThreads) {
+      put(2u + 3u * E + P + p2, __float_as_uint(wsel[p2]));
+      put(2u + 3u * E + 2u * P + p2, sel[p2]);
+    }
   }
 }
 
 __device__ __forceinline__ void body_moe_route(const TaskDesc& t, const StepArgs& a, float* lds) {
-  if (t.p0 <= 128u) moe_route<2>(t, a, lds);
-  else moe_route<(int)(kMoeMaxExperts / 64)>(t, a, lds);
+  if (t.p0 <= 128u) moe_route<2, false>(a, t.in, t.ld_in, t.p0, t.p1, t.p2, lds, (uint32_t*)t.out);
+  else moe_route<(int)(kMoeMaxExperts / 64), false>(a, t.in, t.ld_in, t.p0, t.p1, t.p2, lds, (uint32_t*)t.out);
 }
 
 // `ntile` 16-row tiles of one expert's weight matrix, starting at tile `tile0`, times the `ne`
@@ -2154,8 +2179,9 @@ __device__ __forceinline__ bool moe_expert_job(const TaskDesc& t, const StepArgs
 // Section 6.4); a task's share is worked off in jobs of at most 32 tiles that stay inside one expert.
 // wait_ev >= 0: the caller has NOT waited for the task's event yet (only for the routing task's,
 // so the meta-tensor is this step's); the first job does, behind its first weight requests.
+// own_route: there may be no meta-tensor yet: the routing is worked out here, from the router's output (kMoeOwnRouteExperts).
 template <int NB>
-__device__ __forceinline__ bool body_moe_expert(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev, uint32_t* s_flag) {
+__device__ __forceinline__ bool body_moe_expert(const TaskDesc& t, const StepArgs& a, float* lds, int32_t wait_ev, uint32_t* s_flag, bool own_route) {
   const uint32_t* meta = (const uint32_t*)t.in2;
   const uint32_t E = t.p3 & 0xFFFFu, TK = t.p3 >> 16, NT = t.p1, rows_per_expert = t.p2;
   const uint32_t tiles_per_expert = rows_per_expert / 16u;
@@ -2165,7 +2191,9 @@ __device__ __forceinline__ bool body_moe_expert(const TaskDesc& t, const StepArg
   // request could go out.
   const uint32_t P = a.g->batch * TK, MW = 2u + 3u * E + P;
   uint32_t* mlds = (uint32_t*)(lds + moe_x_floats(a.g->batch) + 8 * 16 + 32);   // behind the staged row lists
-  for (uint32_t i = threadIdx.x; i < MW; i += kThreads) mlds[i] = ld_relaxed(meta + i);
+  if (own_route) moe_route<2, true>(a, (const float*)t.aux0, E, E, TK, a.g->batch, lds, mlds);
+  else
+    for (uint32_t i = threadIdx.x; i < MW; i += kThreads) mlds[i] = ld_relaxed(meta + i);
   lds_barrier();
   const uint32_t n_active = min(__builtin_amdgcn_readfirstlane(mlds[0]), E);
   uint32_t u0, u1;   // this task's share of the tiles: equal in cost, see moe_task_share
@@ -3611,6 +3639,7 @@ __device__ __forceinline__ StepArgs published_args() {
 template <int NB, bool MEGA>
 __device__ __forceinline__ bool expert_task(const StepArgs& a, const TaskDesc& t, uint32_t task_index, bool skip_wait, float* lds, uint32_t* s_flag) {
   int32_t wait_ev = -1;
+  bool own_route = false;
   if (MEGA) {
     debug_jitter(a, task_index);
     wait_ev = (!skip_wait && t.dep_event >= 0 && ((const MPK_CONST EventDesc*)(a.events + t.dep_event))->required != 0) ? t.dep_event : -1;
@@ -3619,17 +3648,22 @@ __device__ __forceinline__ bool expert_task(const StepArgs& a, const TaskDesc& t
     // Cross-task pre-loading (Section 5.3) for the experts' second stage: which experts are active
     // is known since the routing task, long before the first stage has produced this task's
     // inputs.  Such a task (the compiler leaves the routing task's event number + 1 in aux1)
-    // waits for that event -- activated before the first stage could start, so this returns at
+    // waits for that event -- activated early in the first stage, so this returns at
     // once and only orders the reads of the meta-tensor -- finds its first job and requests that
     // job's first weights, and only then waits for its own event.
-    const bool second = wait_ev >= 0 && t.aux1 != nullptr && !(a.flags & kNoPreloadBit);
-    if (wait_ev >= 0 && !wait_event(a, second ? (int32_t)(uintptr_t)t.aux1 - 1 : wait_ev, s_flag)) return false;
-    if (!second) {
+    // A first-stage task with a number in aux1 (the event that the routing task waits for, + 1) waits for that one instead of its
+    // own and works the routing out by itself: see kMoeOwnRouteExperts.
+    const bool early = wait_ev >= 0 && t.aux1 != nullptr, first = t.flags & TF_GATEUP;
+    if (early && !wait_event(a, (int32_t)(uintptr_t)t.aux1 - 1, s_flag)) return false;
+    own_route = early && first;
+    if (own_route) wait_ev = -1;
+    if (wait_ev >= 0 && !(early && !(a.flags & kNoPreloadBit))) {
+      if (!wait_event(a, wait_ev, s_flag)) return false;
       wait_ev = -1;
-      trace_mark(a, t, 1);
     }
+    if (wait_ev < 0) trace_mark(a, t, 1);
   }
-  if (!body_moe_expert<NB>(t, a, lds, wait_ev, s_flag)) return false;
+  if (!body_moe_expert<NB>(t, a, lds, wait_ev, s_flag, own_route)) return false;
   if (MEGA) {
     trace_mark(a, t, 3);
     if (t.trig_event >= 0) signal_event(a, t);
