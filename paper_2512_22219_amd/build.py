@@ -18,6 +18,12 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-I" + os.path.join(os.path.dirname(_HERE), "include"),
          # packed fp32 instructions are not to be generated on this machine pool
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# Kernel sets are compiled for size.  Two compute units share 64 KB of instructions, and a layer of a mixture of experts walks
+# through more than that: its instruction cache misses 1300 times a layer at batch 1, 5400 at batch 16 (of some 3500 lines
+# that a dense layer is made of and that stay), each a trip to the L2 for a whole workgroup.  us a step, -O3 / -Os: mixture of
+# experts at batch 1 688 / 667, batch 16 1396 / 1378; dense sets, which fit, 0 to 2 % (tiny model 34.6 / 34.1, 8B 2690 / 2680, 8B layers at
+# batch 8 1002 / 997, 2B class at batch 2, four tokens 2039 / 2027).  Not the set of one packed row (1B class 619 both, shorter rows +0.6 %).
+_FOR_SPEED = (11,)
 
 
 def _n_variants() -> int:
@@ -41,7 +47,7 @@ def build(force: bool = True, jobs: int = 8) -> str:
     os.makedirs(_OBJ, exist_ok=True)
     work = [(SOURCES[0], os.path.join(_OBJ, "compiler.o"), []),
             (SOURCES[1], os.path.join(_OBJ, "runtime.o"), [])]
-    work += [(SOURCES[2], os.path.join(_OBJ, f"variant{i}.o"), [f"-DMPK_VARIANT_INDEX={i}"])
+    work += [(SOURCES[2], os.path.join(_OBJ, f"variant{i}.o"), [f"-DMPK_VARIANT_INDEX={i}"] + ([] if i in _FOR_SPEED else ["-Os"]))
              for i in range(_n_variants())]
     # the matrix-core sets with experts take longest: start them first
     work.sort(key=lambda j: 0 if j[1].endswith(("variant8.o", "variant9.o", "variant10.o")) else 1)
