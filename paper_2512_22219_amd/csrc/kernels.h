@@ -1994,6 +1994,7 @@ __device__ __forceinline__ void moe_route(const StepArgs& a, const float* in, ui
       const float lg = pr[i];
       pr[i] = 0.f;
       if ((uint32_t)i < nper && e < E) pr[i] = expf(lg - m);
+      asm("" : "+v"(pr[i]));   // (the same bits in every instance: an expert task and the routing task have to choose alike)
       l += pr[i];
     }
     l = wave_sum_dpp(l);

@@ -1,5 +1,6 @@
 """First-stage expert tasks that work the routing out by themselves (up to 128 experts) or read it from the meta-tensor, while
-the routing task is as late as it can be: every task delayed at random, and with nothing requested ahead of an event."""
+the routing task is as late as it can be: every task delayed at random, with nothing requested ahead of an event, and with NaN in
+whatever LDS nobody has written."""
 import hashlib
 
 import numpy as np
@@ -21,10 +22,11 @@ def _digest(s, **opts):
     return h.hexdigest()
 
 
-@pytest.mark.parametrize("batch,experts,top_k", [(1, 128, 8), (4, 5, 5), (5, 129, 2), (16, 65, 16)])
+@pytest.mark.parametrize("batch,experts,top_k", [(1, 128, 8), (4, 5, 5), (5, 129, 2), (16, 64, 16), (16, 65, 3)])
 def test_same_bits_however_late(batch, experts, top_k):
     s = G.small_variant("C1", batch=batch, hidden=272, ffn=0, n_experts=experts, top_k=top_k, expert_ffn=64, vocab=1003)
     want = _digest(s)
-    for opts in (dict(debug_flags=M.binding.DEBUG_JITTER), dict(no_preload=1), dict(no_preload=1, debug_flags=M.binding.DEBUG_JITTER),
+    late = M.binding.DEBUG_JITTER | M.binding.DEBUG_POISON
+    for opts in (dict(debug_flags=M.binding.DEBUG_JITTER), dict(debug_flags=late), dict(no_preload=1), dict(no_preload=1, debug_flags=late),
                  dict(launch_mode=M.binding.LAUNCH_PER_OP)):
         assert _digest(s, **opts) == want, opts
