@@ -1337,7 +1337,11 @@ static size_t lin_task_floats_b1(const HostGraph& g, const HostOp& op) {
 // tasks of one worker qualifies when T comes right after another linear task (so the worker is not
 // one that just ran an attention task: it has the whole attention phase to wait through), T and N
 // both leave room for the pages in LDS, and N is long enough to gain (page_rows).  Returns, per task of the linearized list, 0, TF_PAGE_NEXT or TF_PAGE_READY.
-static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_compile_options& o, const HostGraph& g) {
+// sized: the tiles have been sized for pages, those of the tasks marked there; no other task gets any (tiles of
+// other sizes can let more of them qualify).
+using TileMarks = std::vector<std::vector<uint8_t>>;   // [operator][tile], empty = no tile of the operator
+static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_compile_options& o, const HostGraph& g,
+                                       const TileMarks* sized = nullptr) {
   std::vector<uint16_t> plan(g.tasks.size(), 0);
   if (!page_capable(c, o)) return plan;
   const size_t room = (160 * 1024) / sizeof(float) - kLdsReduceFloats - kLdsCtrlFloats - kLinPagesFloats;
@@ -1360,6 +1364,11 @@ static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_comp
       if (cur_rows * cur->K * 2 > 256 * 1024) continue;
       if (next->K > 4096 || next_rows < page_rows(g, g.packed_rows ? lin_pack(next->K, (uint32_t)next_rows) : 1u) || (next->flags & TF_SPLITK) || next->seg_tiles) continue;
       if (lin_task_floats_b1(g, *cur) > room || lin_task_floats_b1(g, *next) > room) continue;
+      if (sized) {
+        const HostTask& n = g.tasks[g.aot[qi + 1]];
+        const std::vector<uint8_t>& marks = (*sized)[n.op];
+        if (n.tile >= marks.size() || !marks[n.tile]) continue;
+      }
       plan[g.aot[qi]] |= TF_PAGE_NEXT;
       plan[g.aot[qi + 1]] |= TF_PAGE_READY;
     }
@@ -1370,7 +1379,7 @@ static std::vector<uint16_t> page_plan(const mpk_model_config& c, const mpk_comp
 // Column tiles of the operators whose tasks are partly pre-loaded into LDS pages: a task with its
 // first kLinPageUnits weight rows already on the chip when its event fires gets that many more
 // rows than a task without, so that both have the same amount left to stream.
-static void apply_page_sizes(const std::vector<std::vector<uint8_t>>& ready, HostGraph& g) {
+static void apply_page_sizes(const TileMarks& ready, HostGraph& g) {
   for (size_t oi = 0; oi < g.ops.size() && oi < ready.size(); ++oi) {
     HostOp& op = g.ops[oi];
     if (ready[oi].empty() || ready[oi].size() != op.tc || !op.col_begin.empty()) continue;
@@ -1394,7 +1403,7 @@ static void apply_page_sizes(const std::vector<std::vector<uint8_t>>& ready, Hos
 
 struct SecondPass {
   const TileWorkers* tile_workers = nullptr;
-  const std::vector<std::vector<uint8_t>>* page_ready = nullptr;   // [operator][tile]
+  const TileMarks* page_ready = nullptr;
 };
 static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_weight_ptrs* w,
                                          const mpk_kv_ptrs* kv, const mpk_compile_options& opt_in,
@@ -1409,7 +1418,7 @@ mpk_status build_model_graph(const mpk_model_config& cfg, const mpk_weight_ptrs*
   for (int k = 0; k < 8; ++k) weighted = weighted || (opt_in.worker_weight_permille[k] != 0 && opt_in.worker_weight_permille[k] != opt_in.worker_weight_permille[0]);
   weighted = weighted && cfg.batch < kMfmaMinBatch;   // (a column more or less is nothing to a body of 16-row tiles, or a whole tile)
   // tiles that will find their first rows in the LDS pages
-  std::vector<std::vector<uint8_t>> ready(g.ops.size());
+  TileMarks ready(g.ops.size());
   bool paged = false;
   {
     const std::vector<uint16_t> plan = page_plan(cfg, g.opt, g);
@@ -1442,13 +1451,13 @@ mpk_status build_model_graph(const mpk_model_config& cfg, const mpk_weight_ptrs*
   sp.page_ready = &ready;
   st = build_model_graph_pass(cfg, w, kv, opt_in, sp, g2);
   if (st != MPK_OK) return st;
-  if (g2.tasks.size() != g.tasks.size()) { set_error("task list changed between the two compile passes"); return MPK_ERR_INTERNAL; }
-  for (size_t i = 0; i < g.tasks.size(); ++i)   // the assignment the sizes were computed for must be the one that came out
-    if (g.tasks[i].op != g2.tasks[i].op || g.tasks[i].tile != g2.tasks[i].tile || g.tasks[i].worker != g2.tasks[i].worker) {
-      set_error("worker assignment changed between the two compile passes");
-      return MPK_ERR_INTERNAL;
-    }
-  g = std::move(g2);
+  // The assignment that the sizes were computed for must be the one that came out.  Where tiles read parts of other
+  // tiles (attention heads cut across, few workers), other sizes can mean other dependencies, another order of the
+  // tasks and other workers: the graph of the first pass stays then, with even tiles and without pages.
+  bool same = g2.tasks.size() == g.tasks.size();
+  for (size_t i = 0; same && i < g.tasks.size(); ++i)
+    same = g.tasks[i].op == g2.tasks[i].op && g.tasks[i].tile == g2.tasks[i].tile && g.tasks[i].worker == g2.tasks[i].worker;
+  if (same) g = std::move(g2);
   return MPK_OK;
 }
 
@@ -1507,12 +1516,11 @@ static mpk_status build_model_graph_pass(const mpk_model_config& cfg, const mpk_
   size_t accept_lds = 0;
   g.lds_bytes = lds_requirement(cfg, g, C, &accept_lds);
   if (sp.page_ready) {   // (second pass: the tile sizes already account for the pages)
-    const std::vector<uint16_t> plan = page_plan(cfg, opt, g);
+    const std::vector<uint16_t> plan = page_plan(cfg, opt, g, sp.page_ready);
     bool any = false;
     for (size_t i = 0; i < g.tasks.size(); ++i) {
       g.descs[i].flags |= plan[i];
       any = any || plan[i];
-      if ((plan[i] & TF_PAGE_READY) && !(*sp.page_ready)[g.tasks[i].op][g.tasks[i].tile]) { set_error("page plan changed between the two compile passes"); return MPK_ERR_INTERNAL; }
     }
     if (any) {   // the pages sit at the top of the 160 KB
       g.lin_page_off = (uint32_t)((160 * 1024) / sizeof(float) - kLdsReduceFloats - kLdsCtrlFloats - kLinPagesFloats);

@@ -688,3 +688,23 @@ def test_rows_from_which_on_tasks_have_pages(kw, fusion, pages):
     gateup = [oi for oi, op in enumerate(ex.ops) if op["kind"] == TG.K_GATEUP]
     for oi in gateup:
         assert (forms["marks"][ex.tasks["op"] == oi] & M.binding.FORM_PAGE_READY).any() == pages
+
+
+RESIZED = [   # gate/up tiles larger by the rows they find in pages, and tiles of other operators that read parts of them
+    (dict(hidden=504, ffn=2024, n_kv_heads=4), dict(fusion=15, n_workers=32, attn_chunks=2, tiles_linear=7)),   # ... let tasks of other operators qualify
+    (dict(hidden=504, ffn=2024, n_kv_heads=4), dict(fusion=31, n_workers=32, attn_chunks=2, tiles_linear=7)),   # ... make other dependencies
+    (dict(hidden=1640, ffn=1760, n_q_heads=8, n_kv_heads=4, vocab=2958), dict(fusion=27, n_workers=8)),
+]
+
+
+@pytest.mark.parametrize("variant,opts", RESIZED)
+def test_pages_whose_tile_sizes_change_the_graph(variant, opts):
+    shape = G.small_variant("C1", **variant)
+    test_dependency_sets_bit_exact_and_structure("C1", variant, opts)
+    ex, forms = _marks(shape, **opts)
+    nxt, ready = (forms["marks"] & M.binding.FORM_PAGE_NEXT) != 0, (forms["marks"] & M.binding.FORM_PAGE_READY) != 0
+    for w in range(opts["n_workers"]):
+        mine = ex.aot[ex.aot_off[w]:ex.aot_off[w + 1]]
+        assert np.array_equal(nxt[mine][:-1], ready[mine][1:]) and not (nxt & ready).any()
+    # tiles are of even size where no task has pages
+    assert ready.any() == bool(ex.col_begin)
