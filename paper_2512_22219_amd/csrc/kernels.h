@@ -814,10 +814,12 @@ __device__ __forceinline__ void lin_consume(const LinHalf& B, const HalfRing& ri
 // shared-memory pages).  One page per wavefront holds one half block in the layout of a HalfRing:
 // [row 0..1][stage 0..7][lane] x 16 bytes.  The loads go from device memory straight into LDS (no
 // registers), so a page can be filled by one task and consumed by the worker's next one.
+// LEAST: that of the multiplies, which read every stage of the page that it makes them take (whatever the LDS holds in a stage
+// that nobody has filled may read as NaN, and 0 x NaN is NaN).
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
-template <bool PACKED>
+template <int LEAST, bool PACKED>
 __device__ __forceinline__ void lin_request_page(const LinGeom<PACKED>& g, const LinHalf& B, u32x4* page, int lane) {
-  lin_each_stage<1>(lin_stages(g, B), [&](auto uc) {
+  lin_each_stage<LEAST>(lin_stages(g, B), [&](auto uc) {
     constexpr int u = decltype(uc)::value;
 #pragma unroll
     for (int i = 0; i < kHalfRows; ++i)
@@ -1072,7 +1074,7 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
     const TaskDesc tn = ld_task(a, next_ti);
     const auto gn = lin_geom<PACKED>(tn, wave);
     const LinCursor cn{gn.r0, 0u};
-    if (lin_valid(gn, cn)) lin_request_page(gn, lin_half(gn, cn), page, lane);
+    if (lin_valid(gn, cn)) lin_request_page<kLeast>(gn, lin_half(gn, cn), page, lane);
   }
   // ---- dependent event: wavefront 0 polls, the others wait at the barrier
   if (wait_ev >= 0) {
