@@ -1227,7 +1227,7 @@ static uint32_t lds_requirement(const mpk_model_config& c, HostGraph& g, uint32_
           + 2 + 3 * (size_t)c.n_experts + (size_t)c.batch * c.top_k;   // | the task's copy of the meta-tensor
     }
     else if (op.kind == MPK_OP_ROUTER)
-      f = (size_t)c.batch * c.top_k * 2 + (size_t)c.n_experts * (3 + 16) + 64;   // pairs | per-expert counts, offsets, masks, pair table
+      f = moe_route_floats(c.batch, c.n_experts, c.top_k);
     else if (op.kind == MPK_OP_ATTN_PARTIAL) {
       const size_t pages = g.opt.kv_page_size ? c.max_seq / g.opt.kv_page_size : 0;   // paged cache: + the chunk's page numbers
       f = attn_lds_floats(c.head_dim, grp) + pages;

@@ -312,7 +312,7 @@ __device__ __forceinline__ float wave_sum4(float v0, float v1, float v2, float v
   const float b = swap_add(__builtin_amdgcn_permlane16_swap(row_sum(v2), row_sum(v3), false, false));
   return swap_add(__builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false));
 }
-// ... and the largest / smallest value of the wavefront the same way
+// ... and any other reduction (below: the largest value) the same way
 template <class Op>
 __device__ __forceinline__ uint32_t wave_reduce_dpp(uint32_t v, Op op) {
   auto dpp = [](uint32_t x, auto ctrl) {
@@ -330,9 +330,6 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
   return __uint_as_float(wave_reduce_dpp(__float_as_uint(v), [](uint32_t x, uint32_t y) {
     return __float_as_uint(fmaxf(__uint_as_float(x), __uint_as_float(y)));
   }));
-}
-__device__ __forceinline__ uint32_t wave_min_u32_dpp(uint32_t v) {
-  return wave_reduce_dpp(v, [](uint32_t x, uint32_t y) { return min(x, y); });
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -1959,14 +1956,15 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
 // scans behind four barriers 793, masks 783 (batch 16, 6 layers: no difference).
 // LOCAL: `meta` is an expert task's copy in LDS, of which it reads the words up to the end of the pair list and not [1].
 template <int PER_LANE, bool LOCAL>
-__device__ __forceinline__ void moe_route(const StepArgs& a, const float* in, uint32_t ld_in, uint32_t E, uint32_t TK, uint32_t B,
-                                          float* lds, uint32_t* meta) {
+__device__ __forceinline__ void moe_route(const float* in, uint32_t ld_in, uint32_t E, uint32_t TK, uint32_t B, float* lds, uint32_t* meta) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t P = B * TK, B4 = (B + 3u) & ~3u;
   uint64_t* masks = (uint64_t*)lds;                       // [B4][PER_LANE] bit l of word i: expert l + 64 i (batch <= 16)
-  uint32_t* sel = (uint32_t*)(masks + B4 * PER_LANE);     // [P] expert of pair p
+  uint32_t* lower_words = (uint32_t*)(masks + B4 * PER_LANE);   // [B4][PER_LANE] experts in the mask's lower words (PER_LANE > 2)
+  uint32_t* sel = lower_words + B4 * PER_LANE;            // [P] expert of pair p
   float* wsel = (float*)(sel + P);                        // [P] weight of pair p
+  uint32_t* wave_most = (uint32_t*)(wsel + P);            // [8] largest token count among a wavefront's experts
   constexpr int kPerLane = PER_LANE;
   const uint32_t nper = (E + 63u) / 64u;   // experts per lane actually present (uniform)
   auto put = [&](uint32_t at, uint32_t v) {
@@ -1975,7 +1973,10 @@ __device__ __forceinline__ void moe_route(const StepArgs& a, const float* in, ui
   };
   for (uint32_t tok = wave; tok < B4; tok += kThreads / 64) {
     if (tok >= B) {   // (nobody's: the counts below go by fours)
-      if (lane < kPerLane) masks[tok * kPerLane + lane] = 0;
+      if (lane < kPerLane) {
+        masks[tok * kPerLane + lane] = 0;
+        if constexpr (PER_LANE > 2) lower_words[tok * kPerLane + lane] = 0;
+      }
       continue;
     }
     float pr[kPerLane];
@@ -2017,15 +2018,34 @@ __device__ __forceinline__ void moe_route(const StepArgs& a, const float* in, ui
       for (int i = 1; i < kPerLane; ++i) best = max(best, left[i]);
       best = wave_reduce_dpp(best, [](uint32_t x, uint32_t y) { return max(x, y); });
       if (best == 0u) break;   // (a token whose router output is not finite selects nothing)
-      bool found = false;      // ties: the lowest expert
+      // ties: the lowest expert
+      if constexpr (PER_LANE == 2) {
+        bool found = false;
 #pragma unroll
-      for (int i = 0; i < kPerLane; ++i) {
-        const uint64_t at = found ? 0ull : __ballot(left[i] == best);
-        if (at) {
-          const int first = __builtin_ctzll(at);
-          taken[i] |= 1ull << first;
-          left[i] = lane == first ? 0u : left[i];
-          found = true;
+        for (int i = 0; i < kPerLane; ++i) {
+          const uint64_t at = found ? 0ull : __ballot(left[i] == best);
+          if (at) {
+            const int first = __builtin_ctzll(at);
+            taken[i] |= 1ull << first;
+            left[i] = lane == first ? 0u : left[i];
+            found = true;
+          }
+        }
+      } else {   // (no branches: eight of them a round made it 19.0 us a routing task at 512 experts and batch 16, now 16.7)
+        uint64_t at = 0;
+        int word = 0;
+#pragma unroll
+        for (int i = kPerLane - 1; i >= 0; --i) {
+          const uint64_t here = __ballot(left[i] == best);
+          at = here ? here : at;
+          word = here ? i : word;
+        }
+        const uint64_t one = at & (0ull - at);
+#pragma unroll
+        for (int i = 0; i < kPerLane; ++i) {
+          const uint64_t mine = i == word ? one : 0ull;
+          taken[i] |= mine;
+          left[i] = __builtin_amdgcn_inverse_ballot_w64(mine) ? 0u : left[i];
         }
       }
     }
@@ -2049,40 +2069,87 @@ __device__ __forceinline__ void moe_route(const StepArgs& a, const float* in, ui
         wsel[tok * TK + lane] = 0.f;
       }
     }
+    uint32_t lower = 0;
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i)
-      if (lane == 0) masks[tok * kPerLane + i] = taken[i];
+    for (int i = 0; i < kPerLane; ++i) {
+      if (lane == 0) {
+        masks[tok * kPerLane + i] = taken[i];
+        if constexpr (PER_LANE > 2) lower_words[tok * kPerLane + i] = lower;
+      }
+      lower += (uint32_t)__popcll(taken[i]);
+    }
   }
   lds_barrier();
-  for (uint32_t e = threadIdx.x; e < E; e += kThreads) {
-    const uint32_t w = e >> 6;
-    const uint64_t bit = 1ull << (e & 63u), below = bit - 1ull;
-    uint32_t off = 0, act = 0, of = 0;   // all pairs of lower experts, active lower experts, bit b: token b is its
-    uint64_t any[kPerLane] = {}, ranks = 0;   // (four bits a token: its rank there)
-    // (the masks of four tokens in flight: one after the other they are a chain of LDS round trips, 4 us at batch 16)
-    for (uint32_t b0 = 0; b0 < B4; b0 += 4u) {
+  static_assert(kMoeMaxExperts <= kThreads, "a thread per expert");
+  const uint32_t e = threadIdx.x;
+  const uint32_t w = wave;   // the word of the masks that has the expert's bit
+  uint32_t cnt = 0, act = 0;   // the expert's tokens, active lower experts
+  // Eight words a token are too many for every thread to read (128 reads at batch 16): a wavefront reads its own word of each,
+  // what lies below it was counted when the mask was made, and the lower words' active experts are counted by all lanes
+  // together: a lane ors a word of two tokens, then the lanes of a word or theirs.  us a step of 4 layers with 512 experts at
+  // batch 16: lists by LDS atomics and scans 1130, all words read by every thread 1141, this (and the selection above) 1101.
+  if constexpr (PER_LANE > 2) {
+    static_assert(PER_LANE == 8, "a lane per word of eight tokens");
+    uint32_t part[2] = {0, 0};
 #pragma unroll
-      for (uint32_t u = 0; u < 4u; ++u) {
-        uint32_t lower = 0;
-        bool has = false;
-#pragma unroll
-        for (int i = 0; i < kPerLane; ++i) {
-          const uint64_t mk = masks[(b0 + u) * kPerLane + i];
-          any[i] |= mk;
-          lower += (uint32_t)__popcll(mk & ((uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull)));
-          has = has || ((uint32_t)i == w && (mk & bit));
-        }
-        off += lower;
-        if (has) {
-          of |= 1u << (b0 + u);
-          ranks |= (uint64_t)lower << (4u * (b0 + u));   // (below TK <= 16)
-        }
+    for (uint32_t b = 0; b < 16u; b += 8u)
+      if (8u * b + (uint32_t)lane < 8u * B4) {
+        const uint64_t m = masks[8u * b + (uint32_t)lane];
+        part[0] |= (uint32_t)m;
+        part[1] |= (uint32_t)(m >> 32);
       }
+    uint32_t active = 0;   // lane i < 8: experts of word i
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t v = part[h];
+      v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);   // the lane 8 further in its row of 16
+      const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+      v = r[0] | r[1];
+      const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+      active += (uint32_t)__popc(q[0] | q[1]);
     }
 #pragma unroll
-    for (int i = 0; i < kPerLane; ++i) act += (uint32_t)__popcll(any[i] & ((uint32_t)i < w ? ~0ull : ((uint32_t)i == w ? below : 0ull)));
-    const uint32_t cnt = (uint32_t)__popc(of);
-    if (e == E - 1u) put(0u, act + (of ? 1u : 0u));
+    for (int i = 0; i < 7; ++i) act += (uint32_t)i < w ? (uint32_t)__builtin_amdgcn_readlane((int)active, i) : 0u;
+  }
+  if (e < E) {
+    const uint64_t bit = 1ull << lane, below = bit - 1ull;
+    uint32_t off = 0, of = 0;   // all pairs of lower experts, bit b: token b is its
+    uint64_t ranks = 0;                  // four bits a token: its rank there (below TK <= 16)
+    auto token = [&](uint32_t b, uint64_t own, uint32_t lower) {   // own: the token's word w; lower: its experts in lower words
+      lower += (uint32_t)__popcll(own & below);
+      off += lower;
+      if (own & bit) {
+        of |= 1u << b;
+        ranks |= (uint64_t)lower << (4u * b);
+      }
+    };
+    // (the masks of four tokens in flight: one after the other they are a chain of LDS round trips, 4 us at batch 16)
+    if constexpr (PER_LANE == 2) {
+      uint64_t any[2] = {};
+      for (uint32_t b0 = 0; b0 < B4; b0 += 4u) {
+#pragma unroll
+        for (uint32_t u = 0; u < 4u; ++u) {
+          const uint64_t m0 = masks[2u * (b0 + u)], m1 = masks[2u * (b0 + u) + 1u];
+          any[0] |= m0;
+          any[1] |= m1;
+          token(b0 + u, w ? m1 : m0, w ? (uint32_t)__popcll(m0) : 0u);
+        }
+      }
+      act = (uint32_t)__popcll((w ? any[1] : any[0]) & below) + (w ? (uint32_t)__popcll(any[0]) : 0u);
+    } else {
+      uint64_t any = 0;
+      for (uint32_t b0 = 0; b0 < B4; b0 += 4u) {
+#pragma unroll
+        for (uint32_t u = 0; u < 4u; ++u) {
+          const uint64_t own = masks[8u * (b0 + u) + w];
+          any |= own;
+          token(b0 + u, own, lower_words[8u * (b0 + u) + w]);
+        }
+      }
+      act += (uint32_t)__popcll(any & below);
+    }
+    cnt = (uint32_t)__popc(of);
+    if (e == E - 1u) put(0u, act + (cnt ? 1u : 0u));
     put(2u + E + e, cnt);
     put(2u + 2u * E + e, off);
     if (cnt) put(2u + act, e);
@@ -2092,27 +2159,25 @@ __device__ __forceinline__ void moe_route(const StepArgs& a, const float* in, ui
     }
   }
   if constexpr (!LOCAL) {
-    if (wave == kThreads / 64u - 1u) {   // the largest count
-      uint32_t mx = 0;
-#pragma unroll
-      for (int i = 0; i < kPerLane; ++i) {
-        uint32_t n = 0;
-        for (uint32_t b = 0; b < B; ++b) n += (uint32_t)(masks[b * kPerLane + i] >> lane) & 1u;
-        mx = max(mx, n);
-      }
-      mx = wave_reduce_dpp(mx, [](uint32_t x, uint32_t y) { return max(x, y); });
-      if (lane == 0) put(1u, mx);
-    }
+    const uint32_t most = wave_reduce_dpp(cnt, [](uint32_t x, uint32_t y) { return max(x, y); });
+    if (lane == 0) wave_most[wave] = most;
     for (uint32_t p2 = threadIdx.x; p2 < P; p2 += kThreads) {
       put(2u + 3u * E + P + p2, __float_as_uint(wsel[p2]));
       put(2u + 3u * E + 2u * P + p2, sel[p2]);
     }
+    lds_barrier();
+    if (threadIdx.x == 0) {
+      uint32_t mx = wave_most[0];
+#pragma unroll
+      for (int i = 1; i < (int)(kThreads / 64); ++i) mx = max(mx, wave_most[i]);
+      put(1u, mx);
+    }
   }
 }
 
-__device__ __forceinline__ void body_moe_route(const TaskDesc& t, const StepArgs& a, float* lds) {
-  if (t.p0 <= 128u) moe_route<2, false>(a, t.in, t.ld_in, t.p0, t.p1, t.p2, lds, (uint32_t*)t.out);
-  else moe_route<(int)(kMoeMaxExperts / 64), false>(a, t.in, t.ld_in, t.p0, t.p1, t.p2, lds, (uint32_t*)t.out);
+__device__ __forceinline__ void body_moe_route(const TaskDesc& t, float* lds) {
+  if (t.p0 <= 128u) moe_route<2, false>(t.in, t.ld_in, t.p0, t.p1, t.p2, lds, (uint32_t*)t.out);
+  else moe_route<(int)(kMoeMaxExperts / 64), false>(t.in, t.ld_in, t.p0, t.p1, t.p2, lds, (uint32_t*)t.out);
 }
 
 // `ntile` 16-row tiles of one expert's weight matrix, starting at tile `tile0`, times the `ne`
@@ -2194,7 +2259,7 @@ __device__ __forceinline__ bool body_moe_expert(const TaskDesc& t, const StepArg
   // request could go out.
   const uint32_t P = a.g->batch * TK, MW = 2u + 3u * E + P;
   uint32_t* mlds = (uint32_t*)(lds + moe_x_floats(a.g->batch) + 8 * 16 + 32);   // behind the staged row lists
-  if (own_route) moe_route<2, true>(a, (const float*)t.aux0, E, E, TK, a.g->batch, lds, mlds);
+  if (own_route) moe_route<2, true>((const float*)t.aux0, E, E, TK, a.g->batch, lds, mlds);
   else
     for (uint32_t i = threadIdx.x; i < MW; i += kThreads) mlds[i] = ld_relaxed(meta + i);
   lds_barrier();
@@ -3438,7 +3503,7 @@ __device__ __forceinline__ bool run_task(const TaskDesc& t, const StepArgs& a, f
     case TK_SWIGLU: body_swiglu(t); break;
     case TK_ARGMAX: body_argmax(t, a, lds); break;
     case TK_SERVE: body_serve(a); break;
-    case TK_MOE_ROUTE: if (MOE) body_moe_route(t, a, lds); break;
+    case TK_MOE_ROUTE: if (MOE) body_moe_route(t, lds); break;
     case TK_MOE_COMBINE: if (MOE) body_moe_combine(t, a); break;
     default: break;   // TK_DUMMY: no computation (normalization, Section 4.1)
   }

@@ -305,6 +305,11 @@ MPK_HOST_DEVICE inline void moe_task_share(uint32_t n_active, uint32_t tiles_per
 // for the routing task.
 constexpr uint32_t kMoeOwnRouteExperts = 128;
 constexpr uint32_t kMoeMaxExperts = 512, kMoeMaxPairs = 256, kMoeMaxTopK = 16;
+// LDS of the routing task: a mask over the experts per token (2 or 8 words of 64), the experts below each of its words,
+// expert and weight of every pair, the largest count of each wavefront.
+inline uint32_t moe_route_floats(uint32_t batch, uint32_t E, uint32_t top_k) {
+  return ((batch + 3u) & ~3u) * (E <= 128u ? 2u : kMoeMaxExperts / 64u) * 3u + 2u * batch * top_k + 8u;
+}
 
 constexpr uint32_t kMfmaMinBatch = 3;   // linear operators of this many rows and more run on the matrix cores
 constexpr uint32_t kMfmaJobRows = 512;  // weight rows of one matrix-core job

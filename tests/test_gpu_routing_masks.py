@@ -15,6 +15,10 @@ CASES = [   # batch, experts, chosen
     (16, 136, 3, "14e14eaadadcda6e"),
     (8, 512, 16, "a748fa4ae27ba8ac"),
     (3, 448, 2, "2387f5beede5f336"),
+    (16, 512, 16, "48fee2fc1cf4a5a0"),
+    (13, 300, 5, "8bff2920558640b0"),
+    (16, 129, 8, "07ca53b36a2cfc96"),
+    (1, 512, 1, "678a3b3668081847"),
 ]
 
 
