@@ -368,8 +368,8 @@ enum {
 mpk_status mpk_graph_export(const mpk_graph *g, void *buf, size_t cap, size_t *need);
 
 /* How the tasks are run, in linearized order, for tests and inspection: which tasks of a single-step launch learn from
- * the words of their input instead of an event that it is complete (and who writes for such readers), and, for
- * linear tasks, their inputs, outputs (rows x columns) and how many weight rows the vector body (batch 1 and 2) loads as
+ * the words of their input instead of an event that it is complete (and who writes for such readers), which expert tasks
+ * do not wait for the routing task, and, for linear tasks, their inputs, outputs (rows x columns) and how many weight rows the vector body (batch 1 and 2) loads as
  * one row of 4096 inputs (1: each by itself; 0: another body).  buf == NULL returns the element count in *need.
  * Works on host_only graphs; a generic task DAG's entries are all 0. */
 typedef struct mpk_task_form {
@@ -383,7 +383,9 @@ enum {
   MPK_FORM_OUTPUT_MARKED = 4,   /* its consumers do: it triggers no event                         */
   MPK_FORM_RESIDUAL = 8,        /* a linear task that adds a residual                             */
   MPK_FORM_PAGE_NEXT = 16,      /* loads the first weight rows of its worker's next task into LDS */
-  MPK_FORM_PAGE_READY = 32      /* finds its own there                                            */
+  MPK_FORM_PAGE_READY = 32,     /* finds its own there                                            */
+  MPK_FORM_OWN_ROUTING = 64     /* a first-stage expert task that waits for the router's output and works the routing
+                                   out by itself, instead of for the routing task and its meta-tensor */
 };
 mpk_status mpk_graph_task_forms(const mpk_graph *g, mpk_task_form *buf, size_t cap, size_t *need);
 

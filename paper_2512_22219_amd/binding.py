@@ -95,7 +95,7 @@ EXPORT_TASK = np.dtype([("op", "<u4"), ("tile", "<u4"), ("dep_event", "<i4"),
                         ("trig_event", "<i4"), ("worker", "<i4"), ("jit", "<u4")])
 TASK_FORM = np.dtype([("marks", "<u4"), ("packed", "<u4"), ("inputs", "<u4"), ("outputs", "<u4")])
 FORM_INPUT_MARKED, FORM_RESIDUAL_MARKED, FORM_OUTPUT_MARKED, FORM_RESIDUAL = 1, 2, 4, 8
-FORM_PAGE_NEXT, FORM_PAGE_READY = 16, 32
+FORM_PAGE_NEXT, FORM_PAGE_READY, FORM_OWN_ROUTING = 16, 32, 64
 EXPORT_EVENT = np.dtype([("required", "<u4"), ("first", "<u4"), ("last", "<u4"),
                          ("flags", "<u4")])
 

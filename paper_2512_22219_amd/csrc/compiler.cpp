@@ -1623,6 +1623,9 @@ void task_forms(const HostGraph& g, mpk_task_form* out) {
     const uint16_t marks = g.mark_flags.empty() ? 0 : g.mark_flags[i];
     out[i].marks = ((marks & TF_IN_MARKED) ? MPK_FORM_INPUT_MARKED : 0u) | ((marks & TF_IN2_MARKED) ? MPK_FORM_RESIDUAL_MARKED : 0u) |
                    ((marks & TF_OUT_MARKED) ? MPK_FORM_OUTPUT_MARKED : 0u);
+    // (as expert_task decides it: the hybrid launch hands out tasks whose event is active, the others do not wait)
+    if (t.kind == TK_MOE_EXPERT && (t.flags & TF_GATEUP) && t.aux1 && g.opt.launch_mode == MPK_LAUNCH_MEGA && !g.stats.n_jit_tasks)
+      out[i].marks |= MPK_FORM_OWN_ROUTING;
     if (t.kind != TK_LINEAR) continue;
     out[i].marks |= ((t.flags & TF_EPI_RESID) ? MPK_FORM_RESIDUAL : 0u) | ((t.flags & TF_PAGE_NEXT) ? MPK_FORM_PAGE_NEXT : 0u) |
                     ((t.flags & TF_PAGE_READY) ? MPK_FORM_PAGE_READY : 0u);

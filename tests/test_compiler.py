@@ -708,3 +708,30 @@ def test_pages_whose_tile_sizes_change_the_graph(variant, opts):
         assert np.array_equal(nxt[mine][:-1], ready[mine][1:]) and not (nxt & ready).any()
     # tiles are of even size where no task has pages
     assert ready.any() == bool(ex.col_begin)
+
+
+def own_routing(shape, **opts):
+    """Whether first-stage expert tasks work the routing out by themselves: the answers there are in a graph."""
+    ex, forms = _marks(shape, fusion=31, transitive_reduction=1, **opts)
+    own = (forms["marks"] & M.binding.FORM_OWN_ROUTING) != 0
+    kind = np.array([-1 if t["op"] == GU.DUMMY else ex.ops[t["op"]]["kind"] for t in ex.tasks])
+    first = np.zeros(len(own), bool)
+    stages = [oi for oi, op in enumerate(ex.ops) if op["kind"] == TG.K_EXPERT]
+    for oi in stages[::2]:
+        first |= ex.tasks["op"] == oi
+    assert not own[~first].any() and (kind[first] == TG.K_EXPERT).all() and first.any()
+    return set(own[first].tolist())
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3, 8, 16])
+def test_expert_tasks_that_work_the_routing_out_by_themselves(batch):
+    kw = dict(batch=batch, hidden=272, ffn=0, top_k=2, expert_ffn=64)
+    for experts in (2, 64, 127, 128, 129, 512):
+        s = G.small_variant("C1", n_experts=experts, **kw)
+        assert own_routing(s) == {experts <= 128}
+        assert own_routing(s, launch_mode=M.binding.LAUNCH_PER_OP) == {False}
+    s = G.small_variant("C1", n_experts=16, **kw)
+    assert own_routing(s, n_workers=24, tiles_moe=10) == {True}       # several tasks a worker
+    assert own_routing(s, n_workers=24, n_sched_wgs=1) == {False}     # hybrid launch: handed out when their event is active
+    assert own_routing(s, n_workers=24, n_sched_wgs=1, force_aot=1) == {True}
+    assert own_routing(s, greedy_loop=2) == own_routing(s, serving=1, greedy_loop=1, kv_page_size=32, kv_pages=64) == {True}

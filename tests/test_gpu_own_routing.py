@@ -9,6 +9,7 @@ import pytest
 import paper_2512_22219_amd as M
 from synth import gen as G
 from tests.gpu_util import GpuDecoder
+from tests.test_compiler import own_routing
 
 pytestmark = pytest.mark.gpu
 
@@ -25,6 +26,8 @@ def _digest(s, **opts):
 @pytest.mark.parametrize("batch,experts,top_k", [(1, 128, 8), (4, 5, 5), (5, 129, 2), (16, 64, 16), (16, 65, 3)])
 def test_same_bits_however_late(batch, experts, top_k):
     s = G.small_variant("C1", batch=batch, hidden=272, ffn=0, n_experts=experts, top_k=top_k, expert_ffn=64, vocab=1003)
+    assert own_routing(s) == ({True} if experts <= 128 else {False})   # (or the comparisons are of one way with itself)
+    assert own_routing(s, launch_mode=M.binding.LAUNCH_PER_OP) == {False}
     want = _digest(s)
     late = M.binding.DEBUG_JITTER | M.binding.DEBUG_POISON
     for opts in (dict(debug_flags=M.binding.DEBUG_JITTER), dict(debug_flags=late), dict(no_preload=1), dict(no_preload=1, debug_flags=late),
