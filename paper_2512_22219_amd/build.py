@@ -5,6 +5,7 @@ compiled once per set, in parallel, and the objects are linked with the host sid
 import os
 import re
 import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -18,39 +19,60 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-I" + os.path.join(os.path.dirname(_HERE), "include"),
          # packed fp32 instructions are not to be generated on this machine pool
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# Kernel sets are compiled for size.  Two compute units share 64 KB of instructions, and a layer of a mixture of experts walks
-# through more than that: its instruction cache misses 1300 times a layer at batch 1, 5400 at batch 16 (of some 3500 lines
-# that a dense layer is made of and that stay), each a trip to the L2 for a whole workgroup.  us a step, -O3 / -Os: mixture of
-# experts at batch 1 688 / 667, batch 16 1396 / 1378; dense sets, which fit, 0 to 2 % (tiny model 34.6 / 34.1, 8B 2690 / 2680, 8B layers at
-# batch 8 1002 / 997, 2B class at batch 2, four tokens 2039 / 2027).  Not the set of one packed row (1B class 619 both, shorter rows +0.6 %).
-_FOR_SPEED = (11,)
+_USAGE = "-Rpass-analysis=kernel-resource-usage"   # the compiler says what registers each kernel spills
 
 
-def _n_variants() -> int:
+def variants() -> list:
+    """The kernel sets, from their list in kernels.h: dicts with index, nb, moe, level, spills, hybrid_spills."""
     with open(os.path.join(_CSRC, "kernels.h")) as f:
-        return int(re.search(r"kNumVariants\s*=\s*(\d+)", f.read()).group(1))
+        text = f.read()
+    text = text[text.index("#define MPK_VARIANT_LIST"):text.index("#define MPK_COUNT_VARIANT")]
+    rows = re.findall(r"X\((\d+), (\d+), (true|false), (O3|Os), (\d+), (\d+)\)", text)
+    assert len(rows) == text.count(" X(") and [int(r[0]) for r in rows] == list(range(len(rows))), "MPK_VARIANT_LIST"
+    return [dict(index=int(i), nb=int(nb), moe=moe == "true", level="-" + level, spills=int(s), hybrid_spills=int(h))
+            for i, nb, moe, level, s, h in rows]
+
+
+def check_spills(variant: dict, remarks: str) -> None:
+    """Raises if a kernel of the set spills more vector registers than its entry in the list allows."""
+    found = re.findall(r"Function Name: (\S*mpk_\w+_kernel\S*) .*?VGPRs Spill: (\d+)", remarks, re.S)
+    if not found:
+        raise RuntimeError(f"kernel set {variant['index']}: the compiler names no kernel's registers")
+    for name, spilled in found:
+        hybrid = re.search(r"mega_kernelILi\d+ELb[01]ELb1E", name)
+        allowed = variant["hybrid_spills" if hybrid else "spills"]
+        if int(spilled) > allowed:
+            raise RuntimeError(f"kernel set {variant['index']}: {name} spills {spilled} vector registers, {allowed} allowed")
 
 
 def _compile(job):
-    src, obj, extra = job
-    subprocess.check_call(["hipcc", *FLAGS, *extra, "-c", src, "-o", obj],
-                          stderr=subprocess.DEVNULL if os.environ.get("MPK_BUILD_QUIET") else None)
+    src, obj, extra, variant = job
+    r = subprocess.run(["hipcc", *FLAGS, *extra, "-c", src, "-o", obj], stderr=subprocess.PIPE, text=True)
+    if not os.environ.get("MPK_BUILD_QUIET"):
+        said = r.stderr.splitlines() if r.returncode else [m for m in r.stderr.splitlines() if "warning:" in m]
+        sys.stderr.write("".join(m + "\n" for m in said))
+    r.check_returncode()
+    if variant is not None:
+        check_spills(variant, r.stderr)
     return obj
 
 
+def stale() -> bool:
+    """Is a source, or this file with its flags, newer than the library?"""
+    return not os.path.exists(LIB) or os.path.getmtime(LIB) < max(map(os.path.getmtime, SOURCES + HEADERS + [os.path.abspath(__file__)]))
+
+
 def build(force: bool = True, jobs: int = 8) -> str:
-    """Compile the library.  force=False rebuilds only when a source is newer than the library."""
-    if not force and os.path.exists(LIB):
-        newest = max(os.path.getmtime(p) for p in SOURCES + HEADERS)
-        if os.path.getmtime(LIB) >= newest:
-            return LIB
+    """Compile the library.  force=False rebuilds only when something that it is made from is newer."""
+    if not force and not stale():
+        return LIB
     os.makedirs(_OBJ, exist_ok=True)
-    work = [(SOURCES[0], os.path.join(_OBJ, "compiler.o"), []),
-            (SOURCES[1], os.path.join(_OBJ, "runtime.o"), [])]
-    work += [(SOURCES[2], os.path.join(_OBJ, f"variant{i}.o"), [f"-DMPK_VARIANT_INDEX={i}"] + ([] if i in _FOR_SPEED else ["-Os"]))
-             for i in range(_n_variants())]
+    work = [(SOURCES[0], os.path.join(_OBJ, "compiler.o"), [], None),
+            (SOURCES[1], os.path.join(_OBJ, "runtime.o"), [], None)]
+    work += [(SOURCES[2], os.path.join(_OBJ, f"variant{v['index']}.o"), [f"-DMPK_VARIANT_INDEX={v['index']}", v["level"], _USAGE], v)
+             for v in variants()]
     # the matrix-core sets with experts take longest: start them first
-    work.sort(key=lambda j: 0 if j[1].endswith(("variant8.o", "variant9.o", "variant10.o")) else 1)
+    work.sort(key=lambda j: 0 if j[3] and j[3]["moe"] and j[3]["nb"] in (4, 8, 16) else 1)
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(work)))) as pool:
         objs = list(pool.map(_compile, work))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB])

@@ -4183,12 +4183,29 @@ struct KernelVariant {
   void (*hybrid)(StepArgs);   // with scheduler workgroups
   void (*run_step)(StepArgs); // one step of a run of several, a launch per step
 };
-// index, batch class, mixture of experts
+// index, batch class, mixture of experts, optimisation level, vector registers that a kernel may spill, that its hybrid walk may
+// (build.py reads the last three).
+//
+// Level.  Kernel sets are compiled for size.  Two compute units share 64 KB of instructions, and a layer of a mixture of experts
+// walks through more than that: its instruction cache misses 1300 times a layer at batch 1, 5400 at batch 16 (of some 3500 lines
+// that a dense layer is made of and that stay), each a trip to the L2 for a whole workgroup.  us a step, -O3 / -Os: mixture of
+// experts at batch 1 688 / 667, batch 16 1396 / 1378; dense sets, which fit, 0 to 2 % (tiny model 34.6 / 34.1, 8B 2690 / 2680, 8B
+// layers at batch 8 1002 / 997, 2B class at batch 2, four tokens 2039 / 2027).  Not the set of one packed row (1B class 619 both,
+// shorter rows +0.6 %).
+//
+// Spills.  What the sets have, the same at both levels; the build fails above it.  A reload from scratch memory waits for every weight
+// load in flight, so the matrix-core bodies must have none; and a set of theirs that did (-Oz: 86 in the walk of batch 16 with
+// experts) gave NaN for experts of more than 8 rows, for a reason that reading its code has not shown.
 #define MPK_VARIANT_LIST(X) \
-  X(0, 1, false) X(1, 9, false) X(2, 2, false) X(3, 4, false) X(4, 8, false) X(5, 16, false) \
-  X(6, 1, true) X(7, 2, true) X(8, 4, true) X(9, 8, true) X(10, 16, true) X(11, 11, false) X(12, 12, false)
-constexpr int kNumVariants = 13;
-#define MPK_DECLARE_VARIANT(I, N, M) const KernelVariant* kernel_variant_##I();
+  X(0, 1, false, Os, 0, 0) X(1, 9, false, Os, 12, 40) X(2, 2, false, Os, 4, 34) \
+  X(3, 4, false, Os, 0, 0) X(4, 8, false, Os, 0, 0) X(5, 16, false, Os, 0, 0) \
+  X(6, 1, true, Os, 0, 0) X(7, 2, true, Os, 4, 34) \
+  X(8, 4, true, Os, 0, 0) X(9, 8, true, Os, 0, 0) X(10, 16, true, Os, 0, 0) \
+  X(11, 11, false, O3, 0, 0) X(12, 12, false, Os, 3, 34)
+#define MPK_COUNT_VARIANT(...) + 1
+constexpr int kNumVariants = 0 MPK_VARIANT_LIST(MPK_COUNT_VARIANT);
+#undef MPK_COUNT_VARIANT
+#define MPK_DECLARE_VARIANT(I, ...) const KernelVariant* kernel_variant_##I();
 MPK_VARIANT_LIST(MPK_DECLARE_VARIANT)
 #undef MPK_DECLARE_VARIANT
 

@@ -7,7 +7,7 @@
 
 namespace mpk {
 
-#define MPK_GET_VARIANT(I, N, M) kernel_variant_##I(),
+#define MPK_GET_VARIANT(I, ...) kernel_variant_##I(),
 static const KernelVariant* variant_at(int i) {
   static const KernelVariant* const table[kNumVariants] = {MPK_VARIANT_LIST(MPK_GET_VARIANT)};
   return table[i];

@@ -6,7 +6,7 @@
 namespace mpk {
 
 template <int I> struct VariantParams;
-#define MPK_PARAMS(I, N, M)                          \
+#define MPK_PARAMS(I, N, M, ...)                     \
   template <> struct VariantParams<I> {              \
     static constexpr int nb = N;                     \
     static constexpr bool moe = M;                   \
