@@ -994,6 +994,9 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // loads of a compute unit come back in the order they were issued, those of other wavefronts included: behind both
   // half blocks the input of a worker that is late anyway would be there 3 to 5 us after it could have
   // been, and a worker that is early by a fraction of a microsecond finds it on the second try.
+  // (As compiled every look waits for more than its input.  x_complete stands behind the join of several paths, where the compiler
+  // cannot count the loads in flight and waits for all of them, right behind the exact wait: the first look comes back
+  // with the whole first half block, and the second half block leaves a round trip later than it could.)
   bool x_ok = false;
   if (in_marked && preload) x_load(0u);
   // the residual slice of this tile (tile-local, small): its round trip overlaps the staging
@@ -1022,8 +1025,9 @@ __device__ __forceinline__ uint32_t linear_task(const TaskDesc& t, const StepArg
   // (every request site ends in an (empty) assembly statement of its own: otherwise the compiler
   // may merge the identical last loads of two sites into one whose destination is chosen at run
   // time, and a buffer addressed that way is moved from registers to scratch memory)
-  // (the waits are builtins, one on each path: the compiler's own count of the loads in flight does not survive the
-  // branches around the requests)
+  // (the exact waits are builtins, one on each path: the compiler's own count of the loads in flight does not survive the
+  // branches around the requests.  They are no condition of right results: a short row's half block is fewer loads than
+  // they count, and the compiler waits by itself for what it reads.)
   if (preload && lin_valid(g, rq)) {
     lin_request<kLeastAsked>(g, lin_half(g, rq), h0, lane);
     lin_advance(g, rq);

@@ -300,9 +300,10 @@ MPK_HOST_DEVICE inline void moe_task_share(uint32_t n_active, uint32_t tiles_per
 }
 // Up to this many experts every expert task of the first stage works the routing out from the router's output, for itself,
 // while the routing task leaves it in the meta-tensor for the second stage and the combine: a hop between operators less on the
-// path, and no copy of the meta-tensor.  us a step, meta-tensor / own routing: mixture of experts, batch 1, 12 layers 788 / 687,
-// batch 16, 6 layers 1437 / 1354.  More experts would need a second body, with eight experts a lane, in every expert kernel: they wait
-// for the routing task.
+// path, and no copy of the meta-tensor.  us a step, meta-tensor / own routing, all else the same: mixture of experts, batch 1, 12 layers
+// 705 / 666, batch 16, 6 layers 1385 / 1367.  More experts need a second body in every expert kernel, with eight experts a lane: they
+// wait for the routing task.  (With that body, 6 layers: 256 experts at batch 1 379 -> 358, batch 2 486 -> 458, batch 4 689 -> 667, 512
+// experts at batch 16, 4 layers, no difference; up to 128 experts 666 -> 666 and 1367 -> 1368.)
 constexpr uint32_t kMoeOwnRouteExperts = 128;
 constexpr uint32_t kMoeMaxExperts = 512, kMoeMaxPairs = 256, kMoeMaxTopK = 16;
 // LDS of the routing task: a mask over the experts per token (2 or 8 words of 64), the experts below each of its words,
@@ -317,8 +318,8 @@ constexpr uint32_t kMfmaJobRows = 512;  // weight rows of one matrix-core job
 // Matrix-core jobs (batch 3..16 and expert jobs) stage the input in LDS as fp32, a chunk of this
 // many inputs at a time; one definition for the host's LDS requirement and the kernels' layout.
 constexpr uint32_t mfma_kchunk(uint32_t nb) { return nb <= 8u ? 4096u : 2048u; }
-constexpr uint32_t kMfmaXPad = 32;   // floats reserved between staged rows beyond the chunk
-// ... and used: a read of 16 bytes a lane starts at 16 different multiples of 16 bytes in 16 neighbouring lanes (8 with two
+constexpr uint32_t kMfmaXPad = 32;   // floats reserved between staged rows beyond the chunk (the LDS that a graph is accepted by)
+// ... and used, 4 or 16 of them: a read of 16 bytes a lane starts at 16 different multiples of 16 bytes in 16 neighbouring lanes (8 with two
 // terms side by side, where no padding gives more; with 32 floats everywhere mixture of experts at batch 1 837 -> 862 us a step, 8B layers
 // at batch 16 1139 -> 1146).
 constexpr uint32_t mfma_row_pad(int pack) { return pack == 3 ? 16u : 4u; }
